@@ -7,12 +7,12 @@
 //   2. every genome's minimizers (the same k, w and hash as the reads) are
 //      extracted tile by tile;
 //   3. each minimizer's k-mer is inserted into a bucketed open-addressing
-//      table (4 slots of {k-mer, value} = one 64-byte line per bucket) and
-//      its occurrences are counted;
-//   4. k-mers occurring once keep their (genome, position) inline in the slot,
-//      so the common lookup costs one random 64-byte line; k-mers occurring
-//      several times point into an occurrence array; k-mers occurring more
-//      than max_occ times are marked as never seeding.
+//      table (4 slots of {k-mer, value} = one 64-byte line per bucket); k-mers
+//      occurring once keep their (genome, position) inline in the slot, so the
+//      common lookup costs one random 64-byte line;
+//   4. the minimizers whose k-mer was there already are listed and counted per
+//      slot: k-mers occurring several times point into an occurrence array,
+//      k-mers occurring more than max_occ times are marked as never seeding.
 // The table is sized for a load of at most 1/2 of its slots, so a lookup
 // nearly always ends in its first bucket.  Buckets come from a second,
 // salted hash of the k-mer (see bucket_of).
@@ -34,83 +34,119 @@ __global__ void k_genome_meta(const u64 *__restrict__ off, u64 n, const u64 *__r
     meta[g] = GenomeMeta{blk_off[g], (u32)len, taxon[g] | (has_n[g] ? 0x80000000u : 0u)};
 }
 
-__global__ void k_insert(const u64 *__restrict__ xs, u64 n, u64x2 *__restrict__ table, u64 nbuckets,
-                         u32 *__restrict__ cnt, unsigned long long *__restrict__ n_keys) {
-    u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    u64 x = xs[i];
-    u64 b = bucket_of(x, nbuckets);
-    for (;;) {
-        u64x2 *bk = table + b * 4;
-        for (int s = 0; s < 4; s++) {
-            unsigned long long *kp = (unsigned long long *)&bk[s].lo;
-            u64 cur = __hip_atomic_load(kp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (cur == SLOT_EMPTY_KEY) {
-                u64 old = atomicCAS(kp, (unsigned long long)SLOT_EMPTY_KEY, (unsigned long long)x);
-                if (old == SLOT_EMPTY_KEY) {
-                    atomicAdd(n_keys, 1ull);
-                    cur = x;
-                } else {
-                    cur = old;
+// Every minimizer claims its k-mer's slot: the thread that brings a k-mer first
+// writes its (genome, position) into the slot, later ones of the same k-mer go
+// on the duplicate list (slot and occurrence).  The list takes one atomic per
+// block of INS_ITEMS * INS_TPB minimizers and the number of distinct k-mers is
+// what is not on it: a counter that every first insertion adds to serialises
+// the whole kernel on one address (500 Mbp, 83M minimizers: 84.8 ms with that
+// counter, 7.3 ms without).  Bound by the random table lines: a read and a
+// compare-and-swap of one 64-byte bucket each.  The bucket's four keys are read
+// together; a key never changes once set, so only an empty slot needs the swap.
+constexpr int INS_TPB = 256, INS_ITEMS = 4;
+
+__global__ __launch_bounds__(INS_TPB) void k_insert(const u64 *__restrict__ xs, const u32 *__restrict__ gs,
+                                                    const u32 *__restrict__ ps, u64 n, u64x2 *table, u64 nbuckets,
+                                                    u64 *__restrict__ dup_slot, u64 *__restrict__ dup_occ,
+                                                    unsigned long long *__restrict__ n_dups) {
+    __shared__ u64 first;
+    u64 slot[INS_ITEMS];
+    u32 mine = 0;
+    const u64 base = (u64)blockIdx.x * (INS_TPB * INS_ITEMS) + threadIdx.x;
+#pragma unroll
+    for (int it = 0; it < INS_ITEMS; it++) {
+        const u64 i = base + (u64)it * INS_TPB;
+        slot[it] = ~0ull;
+        if (i >= n) continue;
+        const u64 x = xs[i];
+        u64 b = bucket_of(x, nbuckets);
+        for (bool placed = false; !placed;) {
+            u64x2 *bk = table + b * 4;
+            u64 key[4];
+#pragma unroll
+            for (int s = 0; s < 4; s++) key[s] = __hip_atomic_load(&bk[s].lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int s = 0; s < 4; s++) {
+                if (placed) continue;
+                u64 cur = key[s];
+                if (cur == SLOT_EMPTY_KEY) {
+                    cur = atomicCAS((unsigned long long *)&bk[s].lo, (unsigned long long)SLOT_EMPTY_KEY,
+                                    (unsigned long long)x);
+                    if (cur == SLOT_EMPTY_KEY) {
+                        bk[s].hi = ((u64)gs[i] << 32) | ps[i];
+                        placed = true;
+                    }
+                }
+                if (cur == x) {
+                    slot[it] = b * 4 + s;
+                    mine++;
+                    placed = true;
                 }
             }
-            if (cur == x) {
-                atomicAdd(&cnt[b * 4 + s], 1u);
-                return;
-            }
+            b = (b + 1 == nbuckets) ? 0 : b + 1;
         }
-        b = (b + 1 == nbuckets) ? 0 : b + 1;
+    }
+    u32 tot;
+    const u32 pre = block_exclusive_sum<INS_TPB, u32>(mine, &tot);
+    if (tot == 0) return;
+    if (threadIdx.x == 0) first = atomicAdd(n_dups, (unsigned long long)tot);
+    __syncthreads();
+    u64 o = first + pre;
+#pragma unroll
+    for (int it = 0; it < INS_ITEMS; it++) {
+        if (slot[it] == ~0ull) continue;
+        const u64 i = base + (u64)it * INS_TPB;
+        dup_slot[o] = slot[it];
+        dup_occ[o] = ((u64)gs[i] << 32) | ps[i];
+        o++;
     }
 }
 
-// Multi-occurrence sizes; marks k-mers above max_occ as never seeding.
-__global__ void k_slot_sizes(const u32 *__restrict__ cnt, u64 nslots, u32 max_occ, u64x2 *__restrict__ table,
-                             u32 *__restrict__ size, u32 *__restrict__ flags) {
-    u64 s = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= nslots) return;
-    u32 c = cnt[s];
+// The duplicates of a slot are numbered in the order of their atomics.
+__global__ void k_dup_rank(const u64 *__restrict__ dup_slot, u64 n_dups, u32 *__restrict__ cnt,
+                           u32 *__restrict__ rank) {
+    const u64 d = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+    if (d < n_dups) rank[d] = atomicAdd(&cnt[dup_slot[d]], 1u);
+}
+
+// Length of the occurrence list of each repeated k-mer, at its first duplicate
+// (0 at the others); a k-mer above max_occ gets none.
+__global__ void k_dup_sizes(const u64 *__restrict__ dup_slot, const u32 *__restrict__ rank, u64 n_dups,
+                            const u32 *__restrict__ cnt, u32 max_occ, u32 *__restrict__ size,
+                            u32 *__restrict__ flags) {
+    const u64 d = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+    if (d >= n_dups) return;
     u32 sz = 0;
-    if (c > 0) {
-        if (max_occ && c > max_occ) {
-            table[s].hi = SLOT_MULTI;  // count 0: never a seed
-        } else {
+    if (rank[d] == 0) {
+        const u32 c = cnt[dup_slot[d]] + 1;
+        if (!max_occ || c <= max_occ) {
             if (c > MAX_KEY_OCC) atomicOr(flags, ERR_KEY_OVERFLOW);
-            sz = c >= 2 ? c : 0;
+            sz = c;
         }
     }
-    size[s] = sz;
+    size[d] = sz;
 }
 
-__device__ inline u64 find_slot(const u64x2 *table, u64 nbuckets, u64 x) {
-    u64 b = bucket_of(x, nbuckets);
-    for (;;) {
-        for (int s = 0; s < 4; s++)
-            if (table[b * 4 + s].lo == x) return b * 4 + s;
-        b = (b + 1 == nbuckets) ? 0 : b + 1;
-    }
+// The first duplicate moves the slot's inline occurrence to the front of the
+// k-mer's list and points the slot at the list (count 0 marks a k-mer above
+// max_occ: never a seed).
+__global__ void k_dup_heads(const u64 *__restrict__ dup_slot, const u32 *__restrict__ rank,
+                            const u64 *__restrict__ start, u64 n_dups, u64x2 *__restrict__ table,
+                            u64 *__restrict__ occ) {
+    const u64 d = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+    if (d >= n_dups || rank[d] != 0) return;
+    const u64 st = start[d], sz = start[d + 1] - st, s = dup_slot[d];
+    if (sz) occ[st] = table[s].hi;
+    table[s].hi = sz ? SLOT_MULTI | (sz << 40) | st : SLOT_MULTI;
 }
 
-__global__ void k_fill(const u64 *__restrict__ xs, const u32 *__restrict__ gs, const u32 *__restrict__ ps, u64 n,
-                       u64x2 *__restrict__ table, u64 nbuckets, u32 *__restrict__ cnt, const u64 *__restrict__ start,
-                       u64 *__restrict__ occ) {
-    u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    u64 s = find_slot(table, nbuckets, xs[i]);
-    u64 gp = ((u64)gs[i] << 32) | ps[i];
-    u64 sz = start[s + 1] - start[s];
-    if (sz > 0) {
-        u32 k = atomicSub(&cnt[s], 1u) - 1u;
-        occ[start[s] + k] = gp;
-    } else if (table[s].hi != SLOT_MULTI) {
-        table[s].hi = gp;  // the only occurrence, stored inline
-    }
-}
-
-__global__ void k_finalize(u64x2 *__restrict__ table, u64 nslots, const u64 *__restrict__ start) {
-    u64 s = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= nslots) return;
-    u64 sz = start[s + 1] - start[s];
-    if (sz >= 2) table[s].hi = SLOT_MULTI | (sz << 40) | start[s];
+__global__ void k_dup_place(const u64 *__restrict__ dup_slot, const u64 *__restrict__ dup_occ,
+                            const u32 *__restrict__ rank, u64 n_dups, const u64x2 *__restrict__ table,
+                            u64 *__restrict__ occ) {
+    const u64 d = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+    if (d >= n_dups) return;
+    const u64 v = table[dup_slot[d]].hi;
+    if (slot_count(v)) occ[slot_start(v) + 1 + rank[d]] = dup_occ[d];
 }
 
 void build_index(mt_index &ix, const mt_index_params &p, const mt_seqs &g, const uint32_t *taxon, uint32_t n_taxa,
@@ -173,36 +209,44 @@ void build_index(mt_index &ix, const mt_index_params &p, const mt_seqs &g, const
     u64 nslots = nbuckets * 4;
     ix.table.alloc(nslots);
     MT_HIP(hipMemsetAsync(ix.table.p, 0xFF, nslots * sizeof(u64x2), s));
-    DBuf<u32> cnt(nslots);
-    MT_HIP(hipMemsetAsync(cnt.p, 0, nslots * sizeof(u32), s));
-    DBuf<unsigned long long> nkeys(1);
-    MT_HIP(hipMemsetAsync(nkeys.p, 0, sizeof(u64), s));
+    DBuf<u64> dup_slot(n_min), dup_occ(n_min);
+    DBuf<unsigned long long> ndups(1);
+    MT_HIP(hipMemsetAsync(ndups.p, 0, sizeof(u64), s));
     if (n_min) {
-        k_insert<<<grid_for(n_min, 256), 256, 0, s>>>(ex.p, n_min, ix.table.p, nbuckets, cnt.p, nkeys.p);
+        k_insert<<<grid_for(n_min, INS_TPB * INS_ITEMS), INS_TPB, 0, s>>>(ex.p, eg.p, ep.p, n_min, ix.table.p,
+                                                                          nbuckets, dup_slot.p, dup_occ.p, ndups.p);
         MT_HIP(hipGetLastError());
     }
+    u64 nd = 0;
+    read_back(s, ndups.p, &nd, sizeof(u64));
+    ix.n_keys = n_min - nd;
     tm.mark("index_insert");
-    DBuf<u32> size(nslots);
-    k_slot_sizes<<<grid_for(nslots, 256), 256, 0, s>>>(cnt.p, nslots, p.max_occ, ix.table.p, size.p, flags.p);
-    MT_HIP(hipGetLastError());
-    DBuf<u64> start(nslots + 1);
-    scan_u32(size.p, start.p, nslots, s);
+    // the occurrence lists of the k-mers that several minimizers brought; the
+    // work is that of the duplicates, not of the table
     u64 n_multi = 0;
-    read_back(s, start.p + nslots, &n_multi, sizeof(u64));
-    read_back(s, nkeys.p, &ix.n_keys, sizeof(u64));
-    u32 f1 = 0;
-    read_back(s, flags.p, &f1, sizeof(u32));
-    check_flags(f1);
-    ix.n_multi_occ = n_multi;
-    tm.mark("index_sizes");
-    ix.occ.alloc(n_multi);
-    if (n_min) {
-        k_fill<<<grid_for(n_min, 256), 256, 0, s>>>(ex.p, eg.p, ep.p, n_min, ix.table.p, nbuckets, cnt.p, start.p,
-                                                    ix.occ.p);
+    if (nd) {
+        DBuf<u32> cnt(nslots), rank(nd), size(nd);
+        DBuf<u64> start(nd + 1);
+        MT_HIP(hipMemsetAsync(cnt.p, 0, nslots * sizeof(u32), s));
+        k_dup_rank<<<grid_for(nd, 256), 256, 0, s>>>(dup_slot.p, nd, cnt.p, rank.p);
         MT_HIP(hipGetLastError());
+        k_dup_sizes<<<grid_for(nd, 256), 256, 0, s>>>(dup_slot.p, rank.p, nd, cnt.p, p.max_occ, size.p, flags.p);
+        MT_HIP(hipGetLastError());
+        scan_u32(size.p, start.p, nd, s);
+        u32 f1 = 0;
+        MT_HIP(hipMemcpyAsync(&f1, flags.p, sizeof(u32), hipMemcpyDeviceToHost, s));
+        read_back(s, start.p + nd, &n_multi, sizeof(u64));
+        check_flags(f1);
+        tm.mark("index_sizes");
+        ix.occ.alloc(n_multi);
+        k_dup_heads<<<grid_for(nd, 256), 256, 0, s>>>(dup_slot.p, rank.p, start.p, nd, ix.table.p, ix.occ.p);
+        MT_HIP(hipGetLastError());
+        k_dup_place<<<grid_for(nd, 256), 256, 0, s>>>(dup_slot.p, dup_occ.p, rank.p, nd, ix.table.p, ix.occ.p);
+        MT_HIP(hipGetLastError());
+    } else {
+        ix.occ.alloc(0);
     }
-    k_finalize<<<grid_for(nslots, 256), 256, 0, s>>>(ix.table.p, nslots, start.p);
-    MT_HIP(hipGetLastError());
+    ix.n_multi_occ = n_multi;
     tm.mark("index_fill");
     MT_HIP(hipStreamSynchronize(s));
     tm.finish();

@@ -1,0 +1,62 @@
+"""The index build on databases around its block sizes: minimizers whose k-mer
+is in the table already go on a duplicate list (one reservation per block of
+1,024 minimizers), from which the occurrence lists are built.  The counts the
+index reports against numpy's over the oracle's occurrences, and every
+occurrence through the seed hits of reads cut from the genomes themselves.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mt():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2311_02029_amd as mt_
+    return mt_
+
+
+def _genomes(kind):
+    rng = np.random.default_rng(77)
+    if kind == "no minimizers":
+        return [b"ACGTACGT", b"NNNNNNNNNNNNNNNNNNNNNNNNNNNNNN"]
+    if kind == "no duplicates":
+        return [synth.ACGT[synth.random_codes(rng, 5000)].tobytes() for _ in range(3)]
+    if kind == "one block":  # fewer than 1,024 minimizers, half of them duplicates
+        g = synth.ACGT[synth.random_codes(rng, 2400)].tobytes()
+        return [g, g]
+    if kind == "many copies":  # 40 copies over several blocks, one of them reversed in order
+        a, b = (synth.ACGT[synth.random_codes(rng, 3000)].tobytes() for _ in range(2))
+        return [a + b] * 39 + [b + a]
+    if kind == "one k-mer":  # homopolymers: a single k-mer, thousands of occurrences
+        return [b"A" * 4000, b"A" * 3000 + b"C" * 2000]
+    gen = synth.make_strain_genomes(rng, 3, 20_000, 4)
+    return [gen.ascii().get(i) for i in range(gen.n)]
+
+
+@pytest.mark.parametrize("max_occ", [0, 1, 3, 39])
+@pytest.mark.parametrize("kind", ["no minimizers", "no duplicates", "one block", "many copies", "one k-mer", "strains"])
+def test_index_lists_every_occurrence(mt, kind, max_occ):
+    ga = synth.SeqSet.from_list(_genomes(kind))
+    k, w = 15, 8
+    ix, oix = mt.Index(ga, k, w, max_occ), oracle.Index(ga, k, w, max_occ)
+    x = oix.occurrences()[0] if max_occ == 0 else oracle.Index(ga, k, w).occurrences()[0]
+    keys, counts = np.unique(x, return_counts=True)
+    info = ix.info()
+    assert info["n_minimizers"] == len(x) and info["n_keys"] == len(keys)
+    listed = (counts >= 2) & ((counts <= max_occ) if max_occ else True)
+    assert info["n_multi_occ"] == int(counts[listed].sum())
+    reads = synth.SeqSet.from_list([ga.get(g)[a:a + 120] for g in range(ga.n)
+                                    for a in range(0, max(1, len(ga.get(g)) - 100), 90)])
+    hits = ix.containment(mt.to_device(reads)).cpu().numpy().view(np.uint64)
+    assert np.array_equal(hits, oix.containment(reads))
+    got = ix.classify(mt.to_device(reads), min_hits=1, top_n=0, e_value=3).to_host()
+    ref = oix.classify(reads, 1, 0, 0, 3)
+    for f in ("cand_offsets", "genome", "diag", "hits", "approx"):
+        assert np.array_equal(got[f], ref[f]), f
