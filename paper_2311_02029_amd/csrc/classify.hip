@@ -20,7 +20,7 @@ namespace mt {
 // ------------------------------------------------------------------ setup --
 
 __global__ void k_read_setup(const u64 *__restrict__ off, u64 n, u32 e_mode, u32 e_value, u16 *__restrict__ read_E,
-                             u32 *__restrict__ flags, u32 *__restrict__ max_E) {
+                             u32 *__restrict__ flags) {
     u64 r = (u64)blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= n) return;
     u64 m = off[r + 1] - off[r];
@@ -31,9 +31,7 @@ __global__ void k_read_setup(const u64 *__restrict__ off, u64 n, u32 e_mode, u32
     if (m > 65535) f |= ERR_READ_TOO_LONG;
     if (E > 65534) f |= ERR_E_TOO_LARGE;
     if (f) atomicOr(flags, f);
-    u32 e = E > 65535 ? 65535u : (u32)E;
-    read_E[r] = (u16)e;
-    atomicMax(max_E, e);
+    read_E[r] = (u16)(E > 65535 ? 65535u : E);
 }
 
 // ----------------------------------------------------------------- lookup --
@@ -506,13 +504,10 @@ void launch_reduce_slots(const mt_result &res, const mt_index &ix, const u64 *sl
 void ReadBatch::prepare(const mt_seqs &reads, u32 e_mode, u32 e_value, hipStream_t s) {
     n = reads.n;
     flags.alloc(1);
-    maxE.alloc(1);
     MT_HIP(hipMemsetAsync(flags.p, 0, sizeof(u32), s));
-    MT_HIP(hipMemsetAsync(maxE.p, 0, sizeof(u32), s));
     read_E.alloc(n);
     if (n) {
-        k_read_setup<<<grid_for(n, 256), 256, 0, s>>>(reads.offsets, n, e_mode, e_value, read_E.p, flags.p,
-                                                      maxE.p);
+        k_read_setup<<<grid_for(n, 256), 256, 0, s>>>(reads.offsets, n, e_mode, e_value, read_E.p, flags.p);
         MT_HIP(hipGetLastError());
     }
     pack_sequences(reads, 65535, ERR_READ_TOO_LONG, "read longer than 65535 bases", planes, flags.p, nullptr, s);
@@ -533,8 +528,7 @@ void validate_query(const mt_query_params &q) {
 struct StagedCands {
     DBuf<u64> stage_key, read_hs;
     DBuf<u32> stage_hits, ncand;
-    u64 H = 0;      // seed hits (bounds every candidate count)
-    u32 max_E = 0;  // largest E of the reads
+    u64 H = 0;  // seed hits (bounds every candidate count)
 };
 
 static void stage_seed_count(const mt_index &ix, const mt_query_params &q, const mt_seqs &reads, ReadBatch &rb,
@@ -547,13 +541,11 @@ static void stage_seed_count(const mt_index &ix, const mt_query_params &q, const
     const int tile = reads.n && reads.total / reads.n > 512 ? 1024 : 256;
     minimizer_plan(reads, rb.planes, ix.k, ix.w, tile, mp, s);
     tm.mark("seed_count");
-    u32 hf[2];
+    u32 hf = 0;
     u64 n_min = 0;
-    MT_HIP(hipMemcpyAsync(&hf[0], rb.flags.p, sizeof(u32), hipMemcpyDeviceToHost, s));
-    MT_HIP(hipMemcpyAsync(&hf[1], rb.maxE.p, sizeof(u32), hipMemcpyDeviceToHost, s));
+    MT_HIP(hipMemcpyAsync(&hf, rb.flags.p, sizeof(u32), hipMemcpyDeviceToHost, s));
     read_back(s, mp.min_off.p + mp.tiles_cap, &n_min, sizeof(u64));
-    check_flags(hf[0]);
-    sc.max_E = hf[1];
+    check_flags(hf);
     DBuf<u64> min_x(n_min), min_val(n_min);
     DBuf<u32> min_seq(n_min), min_pos(n_min), min_nocc(n_min);
     minimizer_emit(reads, rb.planes, ix.k, ix.w, mp, min_x.p, min_seq.p, min_pos.p, s);
@@ -607,7 +599,7 @@ static void stage_seed_count(const mt_index &ix, const mt_query_params &q, const
 // Filter the candidates of res (pair_read indexes `reads`, whose planes are
 // in rb) and reduce them per result read with read_E.
 static void stage_filter_reduce(const mt_index &ix, const mt_query_params &q, const mt_seqs &reads,
-                                const ReadBatch &rb, const u32 *pair_read, u64 cap, u32 max_E, const u16 *read_E,
+                                const ReadBatch &rb, const u32 *pair_read, u64 cap, const u16 *read_E,
                                 mt_result &res, Timer &tm, hipStream_t s) {
     const u64 n = res.n_reads;
     FilterArgs fa{};
@@ -631,7 +623,7 @@ static void stage_filter_reduce(const mt_index &ix, const mt_query_params &q, co
     fa.accept = res.accept.p;
     fa.flags = rb.flags.p;
     if (q.filter == MT_FILTER_OBSTACLE) {
-        launch_filter(fa, cap, max_E, s, &tm);
+        launch_filter(fa, cap, q.e_mode == MT_E_FIXED ? (int)q.e_value : -1, s, &tm);
     } else {
         launch_filter_simple(fa, cap, q.filter, s);
         tm.mark("filter");
@@ -665,7 +657,7 @@ void classify_per_stage(const mt_index &ix, const mt_query_params &q, const mt_s
         MT_HIP(hipGetLastError());
     }
     tm.mark("compact");
-    stage_filter_reduce(ix, q, reads, rb, pair_read.p, cap, sc.max_E, rb.read_E.p, res, tm, s);
+    stage_filter_reduce(ix, q, reads, rb, pair_read.p, cap, rb.read_E.p, res, tm, s);
 }
 
 // ------------------------------------------------------------ both strands --
@@ -906,7 +898,7 @@ static void classify_both_strands(const mt_index &ix, const mt_query_params &q, 
         MT_HIP(hipGetLastError());
     }
     tm.mark("compact");
-    stage_filter_reduce(ix, q, two, rb, pair_read.p, cap, sc.max_E, res.read_E.p, res, tm, s);
+    stage_filter_reduce(ix, q, two, rb, pair_read.p, cap, res.read_E.p, res, tm, s);
     u32 f = 0;
     read_back(s, rb.flags.p, &f, sizeof f);
     check_flags(f);
@@ -1125,7 +1117,7 @@ extern "C" int mt_filter_pairs_kind(const mt_index *index, const mt_seqs *reads,
         fa.accept = accept_out;
         fa.flags = rb.flags.p;
         if (kind == MT_FILTER_OBSTACLE)
-            mt::launch_filter(fa, n_pairs, 0, s);
+            mt::launch_filter(fa, n_pairs, -1, s);
         else
             mt::launch_filter_simple(fa, n_pairs, kind, s);
         mt::u32 f = 0;

@@ -41,7 +41,6 @@ namespace mt {
 struct ReadBatch {
     u64 n = 0;
     DBuf<u32> flags;   // validation flags
-    DBuf<u32> maxE;    // largest E of the batch
     DBuf<u16> read_E;  // E per read
     PackedSeqs planes; // read bit planes
     void prepare(const mt_seqs &reads, u32 e_mode, u32 e_value, hipStream_t s);
@@ -72,8 +71,9 @@ struct FilterArgs {
 
 // Filters pairs [0, n) (n = *n_dev if set, else n_host; n_cap bounds it):
 // pairs are bucketed by their E (one synchronization to size the buckets),
-// then each bucket runs the kernel shaped for it.
-void launch_filter(const FilterArgs &a, u64 n_cap, u32 max_E, hipStream_t s, Timer *tm = nullptr);
+// then each bucket runs the kernel shaped for it.  fixed_E: the E of every
+// pair when the caller knows it, else -1; pairs of one short E need no buckets.
+void launch_filter(const FilterArgs &a, u64 n_cap, int fixed_E, hipStream_t s, Timer *tm = nullptr);
 // Pairs [0, count) through the Hamming (MT_FILTER_HAMMING), base-counting
 // (MT_FILTER_BASE_COUNT), q-gram (MT_FILTER_QGRAM) or shifted Hamming (MT_FILTER_SHD)
 // filter; count = *n_dev if set, else n_host, at most n.

@@ -74,39 +74,104 @@ __device__ inline u8 pair_class(const FilterArgs &a, u64 p) {
     return CLS_GENERAL;
 }
 
-// Counting and placing pairs use one atomic per wavefront and class: the
-// lanes of a class are ranked by ballot, and their lowest lane adds them all.
-__global__ void k_pair_class(FilterArgs a, u64 n_cap, u32 *__restrict__ count, u8 *__restrict__ cls) {
-    const u64 p = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-    const u64 np = a.n_dev ? *a.n_dev : a.n_host;
-    const bool active = p < np && p < n_cap;
-    const int lane = threadIdx.x & 63;
-    u8 c = 0xFF;
-    if (active) {
-        c = pair_class(a, p);
-        cls[p] = c;
-    }
-    for (int k = 0; k < N_CLASSES; k++) {
-        const u64 m = __ballot(c == k);
-        if (m && lane == __builtin_ctzll(m)) atomicAdd(&count[k], (u32)__builtin_popcountll(m));
-    }
+// Bucketing without shared counters: block b of both passes takes the same
+// contiguous range of pairs; the first pass leaves the block's count of every
+// class, k_pair_offsets turns the counts (class-major) into places, and the
+// second pass fills them.  With global cursors, one atomic per wavefront and
+// class on a handful of words, each pass took 180 us for 1M pairs, waiting on
+// those words; now each takes 8 us (2M pairs of mixed classes).
+constexpr int CL_TPB = 256, CL_MAX_BLOCKS = 1024;
+
+struct PairRange {
+    u64 lo, hi;
+};
+__device__ inline PairRange block_range(u64 n) {
+    const u64 per = ((n + gridDim.x - 1) / gridDim.x + CL_TPB - 1) / CL_TPB * CL_TPB;
+    const u64 lo = min((u64)blockIdx.x * per, n);
+    return PairRange{lo, min(lo + per, n)};
 }
 
-__global__ void k_pair_scatter(FilterArgs a, u64 n_cap, const u8 *__restrict__ cls, const u32 *__restrict__ base,
-                               u32 *__restrict__ cursor, u32 *__restrict__ idx) {
-    const u64 p = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-    const u64 np = a.n_dev ? *a.n_dev : a.n_host;
-    const bool active = p < np && p < n_cap;
+// Pairs to filter: the device count when there is one (bounded by the
+// launch's capacity), else the host count.
+__device__ inline u64 pair_count(const FilterArgs &a, u64 n_cap) {
+    const u64 n = a.n_dev ? *a.n_dev : a.n_host;
+    return n < n_cap ? n : n_cap;
+}
+
+__global__ __launch_bounds__(CL_TPB) void k_pair_class(FilterArgs a, u64 n_cap, u32 *__restrict__ blk_count,
+                                                       u8 *__restrict__ cls) {
+    __shared__ u32 cnt[N_CLASSES];
+    if (threadIdx.x < N_CLASSES) cnt[threadIdx.x] = 0;
+    __syncthreads();
+    const PairRange range = block_range(pair_count(a, n_cap));
     const int lane = threadIdx.x & 63;
-    const u8 c = active ? cls[p] : (u8)0xFF;
-    for (int k = 0; k < N_CLASSES; k++) {
-        const u64 m = __ballot(c == k);
-        if (!m) continue;
-        const int leader = __builtin_ctzll(m);
-        u32 first = 0;
-        if (lane == leader) first = atomicAdd(&cursor[k], (u32)__builtin_popcountll(m));
-        first = __shfl(first, leader, 64);
-        if (c == k) idx[base[k] + first + __builtin_popcountll(m & ((1ull << lane) - 1))] = (u32)p;
+    u32 mine = 0;  // lane k of a wavefront counts class k
+    for (u64 p0 = range.lo; p0 < range.hi; p0 += CL_TPB) {
+        const u64 p = p0 + threadIdx.x;
+        u8 c = 0xFF;
+        if (p < range.hi) {
+            c = pair_class(a, p);
+            cls[p] = c;
+        }
+#pragma unroll
+        for (int k = 0; k < N_CLASSES; k++) {
+            const u64 m = __ballot(c == k);
+            if (lane == k) mine += (u32)__popcll(m);
+        }
+    }
+    if (lane < N_CLASSES && mine) atomicAdd(&cnt[lane], mine);
+    __syncthreads();
+    if (threadIdx.x < N_CLASSES) blk_count[(u64)threadIdx.x * gridDim.x + blockIdx.x] = cnt[threadIdx.x];
+}
+
+// One block: exclusive offsets of the N_CLASSES * nb counts in class-major
+// order, and every class's total.
+constexpr int OFF_TPB = 1024, OFF_ITEMS = (N_CLASSES * CL_MAX_BLOCKS + OFF_TPB - 1) / OFF_TPB;
+__global__ __launch_bounds__(OFF_TPB) void k_pair_offsets(u32 *__restrict__ blk_count, u32 nb,
+                                                          u32 *__restrict__ total) {
+    __shared__ u32 begin[N_CLASSES + 1];
+    const u32 n = N_CLASSES * nb, i0 = threadIdx.x * OFF_ITEMS;
+    u32 v[OFF_ITEMS], t = 0;
+#pragma unroll
+    for (int i = 0; i < OFF_ITEMS; i++) {
+        v[i] = i0 + i < n ? blk_count[i0 + i] : 0;
+        t += v[i];
+    }
+    u32 all;
+    u32 run = block_exclusive_sum<OFF_TPB, u32>(t, &all);
+#pragma unroll
+    for (int i = 0; i < OFF_ITEMS; i++) {
+        if (i0 + i < n) {
+            blk_count[i0 + i] = run;
+            if ((i0 + i) % nb == 0) begin[(i0 + i) / nb] = run;
+        }
+        run += v[i];
+    }
+    if (threadIdx.x == 0) begin[N_CLASSES] = all;
+    __syncthreads();
+    if (threadIdx.x < N_CLASSES) total[threadIdx.x] = begin[threadIdx.x + 1] - begin[threadIdx.x];
+}
+
+__global__ __launch_bounds__(CL_TPB) void k_pair_scatter(FilterArgs a, u64 n_cap, const u8 *__restrict__ cls,
+                                                         const u32 *__restrict__ blk_off, u32 *__restrict__ idx) {
+    __shared__ u32 cursor[N_CLASSES];
+    if (threadIdx.x < N_CLASSES) cursor[threadIdx.x] = blk_off[(u64)threadIdx.x * gridDim.x + blockIdx.x];
+    __syncthreads();
+    const PairRange range = block_range(pair_count(a, n_cap));
+    const int lane = threadIdx.x & 63;
+    for (u64 p0 = range.lo; p0 < range.hi; p0 += CL_TPB) {
+        const u64 p = p0 + threadIdx.x;
+        const u8 c = p < range.hi ? cls[p] : (u8)0xFF;
+#pragma unroll
+        for (int k = 0; k < N_CLASSES; k++) {
+            const u64 m = __ballot(c == k);
+            if (!m) continue;
+            const int leader = __builtin_ctzll(m);
+            u32 first = 0;
+            if (lane == leader) first = atomicAdd(&cursor[k], (u32)__builtin_popcountll(m));
+            first = __shfl(first, leader, 64);
+            if (c == k) idx[first + __builtin_popcountll(m & ((1ull << lane) - 1))] = (u32)p;
+        }
     }
 }
 
@@ -149,14 +214,15 @@ __device__ inline int walk_in_registers(const PairView &v, int E, int lane) {
     return c < E + 1 ? c : E + 1;
 }
 
-// G lanes per pair over the bucket idx[0, n).// G lanes per pair over the bucket idx[0, n).
+// G lanes per pair over the bucket idx[0, n), or over pairs [0, n) when idx is
+// null (n then also bounded by the pairs there are).
 template <int G>
 __global__ __launch_bounds__(256) void k_filter(FilterArgs a, const u32 *__restrict__ idx, u64 n) {
     u64 tid = (u64)blockIdx.x * blockDim.x + threadIdx.x;
     u64 t = tid / G;
     int lane = (int)(tid % G);
-    if (t >= n) return;
-    u64 p = idx[t];
+    if (t >= (idx ? n : pair_count(a, n))) return;
+    u64 p = idx ? idx[t] : t;
     u32 r, g, err;
     int E;
     bool ok;
@@ -344,7 +410,7 @@ __global__ __launch_bounds__(512) void k_filter_long(FilterArgs a, const u32 *__
     u64x2 *L = (u64x2 *)(lds + (size_t)wid * tile * LDS_BLOCK_BYTES);
     u64 *NB = (u64 *)(lds + (size_t)wid * tile * LDS_BLOCK_BYTES + (size_t)tile * 16);
     for (u64 t = (u64)blockIdx.x * wpb + wid; t < n; t += (u64)gridDim.x * wpb) {
-        const u64 p = idx[t];
+        const u64 p = idx ? idx[t] : t;
         u32 r, g, err;
         int E;
         bool ok;
@@ -457,33 +523,32 @@ static void launch_bucket(const FilterArgs &a, const u32 *idx, u64 cnt, int buck
 
 // Buckets the pairs (one synchronization for the bucket sizes); idx / counts
 // receive the bucketed pair indices and the per-bucket counts and offsets.
+// When one bucket holds every pair there is nothing to place: idx stays empty
+// (its pointer null) and the bucket is pairs [0, count).
 static void bucket_pairs(const FilterArgs &a, u64 n_cap, DBuf<u32> &idx, u32 hc[N_CLASSES], u32 hb[N_CLASSES],
                          hipStream_t s) {
-    DBuf<u32> count(N_CLASSES), cursor(N_CLASSES), base(N_CLASSES);
+    const unsigned nb = (unsigned)std::min<u64>(grid_for(n_cap, CL_TPB), CL_MAX_BLOCKS);
+    DBuf<u32> blk(N_CLASSES * (u64)nb), total(N_CLASSES);
     DBuf<u8> cls(n_cap);
-    idx.alloc(n_cap);
-    MT_HIP(hipMemsetAsync(count.p, 0, N_CLASSES * sizeof(u32), s));
-    MT_HIP(hipMemsetAsync(cursor.p, 0, N_CLASSES * sizeof(u32), s));
-    k_pair_class<<<grid_for(n_cap, 256), 256, 0, s>>>(a, n_cap, count.p, cls.p);
+    k_pair_class<<<nb, CL_TPB, 0, s>>>(a, n_cap, blk.p, cls.p);
     MT_HIP(hipGetLastError());
-    read_back(s, count.p, hc, N_CLASSES * sizeof(u32));
+    k_pair_offsets<<<1, OFF_TPB, 0, s>>>(blk.p, nb, total.p);
+    MT_HIP(hipGetLastError());
+    read_back(s, total.p, hc, N_CLASSES * sizeof(u32));
     u32 acc = 0;
+    int populated = 0;
     for (int c = 0; c < N_CLASSES; c++) {
         hb[c] = acc;
         acc += hc[c];
+        populated += hc[c] != 0;
     }
-    if (acc == 0) return;
-    MT_HIP(hipMemcpyAsync(base.p, hb, N_CLASSES * sizeof(u32), hipMemcpyHostToDevice, s));
-    k_pair_scatter<<<grid_for(n_cap, 256), 256, 0, s>>>(a, n_cap, cls.p, base.p, cursor.p, idx.p);
+    if (populated <= 1) {
+        for (int c = 0; c < N_CLASSES; c++) hb[c] = 0;
+        return;
+    }
+    idx.alloc(n_cap);
+    k_pair_scatter<<<nb, CL_TPB, 0, s>>>(a, n_cap, cls.p, blk.p, idx.p);
     MT_HIP(hipGetLastError());
-    MT_HIP(hipStreamSynchronize(s));  // hb lives on this host stack frame
-}
-
-// Pairs to filter: the device count when there is one (bounded by the
-// launch's capacity), else the host count.
-__device__ inline u64 pair_count(const FilterArgs &a, u64 n_cap) {
-    const u64 n = a.n_dev ? *a.n_dev : a.n_host;
-    return n < n_cap ? n : n_cap;
 }
 
 // Table 1's single-row and base-frequency filters on explicit pairs, one
@@ -713,15 +778,23 @@ static const char *const BUCKET_MARKS[N_CLASSES] = {"filter E<=7",     "filter E
                                                     "filter long<=96", "filter long<=192", "filter long<=384",
                                                     "filter long<=768", "filter general"};
 
-void launch_filter(const FilterArgs &a, u64 n_cap, u32 /*max_E*/, hipStream_t s, Timer *tm) {
+void launch_filter(const FilterArgs &a, u64 n_cap, int fixed_E, hipStream_t s, Timer *tm) {
     if (n_cap == 0) return;
+    if (fixed_E >= 0 && fixed_E <= 31) {
+        // one class, known without looking at the pairs: no bucketing and no
+        // synchronization (pairs out of range are reported by every kernel)
+        const int c = fixed_E <= 7 ? 0 : fixed_E <= 15 ? 1 : 2;
+        launch_bucket(a, nullptr, n_cap, c, current_variant(c), s);
+        if (tm) tm->mark(BUCKET_MARKS[c]);
+        return;
+    }
     DBuf<u32> idx;
     u32 hc[N_CLASSES], hb[N_CLASSES];
     bucket_pairs(a, n_cap, idx, hc, hb, s);
     if (tm) tm->mark("filter buckets");
     for (int c = 0; c < N_CLASSES; c++) {
         if (hc[c] == 0) continue;
-        launch_bucket(a, idx.p + hb[c], hc[c], c, current_variant(c), s);
+        launch_bucket(a, idx.p ? idx.p + hb[c] : nullptr, hc[c], c, current_variant(c), s);
         if (tm) tm->mark(BUCKET_MARKS[c]);
     }
 }
@@ -744,11 +817,11 @@ void autotune_filter(const FilterArgs &a, u64 n_pairs, u32 reps, hipStream_t s) 
             float ms_v[6] = {0, 0, 0, 0, 0, 0};
             for (int v = 0; v < BUCKETS[c].n_variants; v++) {
                 if (!variant_ok(c, v)) continue;
-                launch_bucket(a, idx.p + hb[c], hc[c], c, v, s);
+                launch_bucket(a, idx.p ? idx.p + hb[c] : nullptr, hc[c], c, v, s);
                 float mn = 0;
                 for (u32 r = 0; r < (reps ? reps : 1); r++) {
                     MT_HIP(hipEventRecord(e0, s));
-                    launch_bucket(a, idx.p + hb[c], hc[c], c, v, s);
+                    launch_bucket(a, idx.p ? idx.p + hb[c] : nullptr, hc[c], c, v, s);
                     MT_HIP(hipEventRecord(e1, s));
                     MT_HIP(hipEventSynchronize(e1));
                     float ms = 0;

@@ -283,6 +283,7 @@ void scan_u32_ws(const u32 *in, u64 *out, u64 n, u64 *ws, u64 ws_words, hipStrea
     MT_HIP(hipGetLastError());
 }
 
+// One thread per segment.
 __global__ void k_segment_map(const u64 *__restrict__ off, u64 n, u32 *__restrict__ map, u64 cap) {
     u64 sidx = (u64)blockIdx.x * blockDim.x + threadIdx.x;
     if (sidx >= n) return;
@@ -290,10 +291,15 @@ __global__ void k_segment_map(const u64 *__restrict__ off, u64 n, u32 *__restric
     for (u64 b = off[sidx]; b < e; b++) map[b] = (u32)sidx;
 }
 
-// The same map with one thread per block, which finds its segment by bisection
-// over the offsets: a few long segments (genomes) would leave one thread per
-// segment writing them serially (200 genomes of 39k blocks: 4.3 ms against
-// 0.04 ms).
+// One wavefront per segment.
+__global__ void k_segment_map_wave(const u64 *__restrict__ off, u64 n, u32 *__restrict__ map, u64 cap) {
+    const u64 sidx = ((u64)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    if (sidx >= n) return;
+    const u64 e = off[sidx + 1] < cap ? off[sidx + 1] : cap;
+    for (u64 b = off[sidx] + (threadIdx.x & 63); b < e; b += 64) map[b] = (u32)sidx;
+}
+
+// One thread per block, which finds its segment by bisection over the offsets.
 __global__ void k_segment_search(const u64 *__restrict__ off, u64 n, u32 *__restrict__ map, u64 cap) {
     const u64 b = (u64)blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= cap || b >= off[n]) return;
@@ -306,12 +312,18 @@ __global__ void k_segment_search(const u64 *__restrict__ off, u64 n, u32 *__rest
     map[b] = (u32)lo;
 }
 
+// The writers are serial within a segment, so a few long segments (genomes)
+// take the search, whose log2 n steps hit the cache (200 genomes of 39k blocks:
+// 0.04 ms, one thread each 4.3 ms).  Among many segments a wavefront each pays
+// from about 16 blocks on (100k reads of 86 blocks: 59 us with a thread each,
+// 43 us; the search 150 us); shorter ones (reads of 150 bases: 3 blocks)
+// would leave most of its lanes idle.
 void segment_map(const u64 *off, u64 n, u32 *map, u64 cap, hipStream_t s) {
     if (n == 0) return;
-    // from 16 blocks a segment on (reads of a kilobase) the search is the
-    // shorter chain: it takes log2 n cached loads, the writer one store a block
-    if (cap / n >= 16)
+    if (n <= 4096)
         k_segment_search<<<grid_for(cap, 256), 256, 0, s>>>(off, n, map, cap);
+    else if (cap / n >= 16)
+        k_segment_map_wave<<<grid_for(n * 64, 256), 256, 0, s>>>(off, n, map, cap);
     else
         k_segment_map<<<grid_for(n, 256), 256, 0, s>>>(off, n, map, cap);
     MT_HIP(hipGetLastError());

@@ -1,0 +1,98 @@
+"""The filter over explicit pairs at the edges of its kernels: read lengths
+around the 32- and 64-base words, E around the buckets' bounds, windows that
+leave either genome end, N on both sides, pair counts around the bucketing's
+blocks, one bucket or several.  Every pair against the oracle.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mt():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2311_02029_amd as mt_
+    return mt_
+
+
+LENGTHS = [0, 1, 5, 6, 7, 31, 32, 33, 63, 64, 65, 100, 127, 128, 129, 150, 191, 192, 193, 255, 256, 257, 300, 700]
+ALL_E = [0, 1, 3, 7, 8, 15, 16, 31]
+
+
+@pytest.fixture(scope="module")
+def case(mt):
+    """Reads of every length from a genome without N, one with N and a short
+    one, with errors; each at its place, shifted, off both genome ends and at
+    a wrong place, under every E."""
+    rng = np.random.default_rng(91)
+    clean = synth.ACGT[synth.random_codes(rng, 3000)]
+    dirty = synth.ACGT[synth.random_codes(rng, 3000)].copy()
+    dirty[rng.random(3000) < 0.01] = ord("N")
+    genomes = [clean, dirty, clean[:40], np.frombuffer(b"A" * 400, np.uint8)]
+    ga = synth.SeqSet.from_list([g.tobytes() for g in genomes])
+    reads, pr, pg, pd, pe = [], [], [], [], []
+    for m in LENGTHS:
+        for g, start in ((0, 0), (0, 1500), (0, 3000 - m), (1, 700), (2, 0), (3, 100)):
+            L = len(genomes[g])
+            body = genomes[g][max(0, min(start, L - m)):][:m].copy()
+            if len(body) < m:
+                body = np.concatenate([body, synth.ACGT[rng.integers(0, 4, m - len(body))]])
+            hit = rng.random(m) < rng.choice([0.0, 0.02, 0.1])
+            body[hit] = synth.ACGT[rng.integers(0, 4, int(hit.sum()))]
+            if rng.random() < 0.3 and m:
+                body[rng.integers(0, m)] = ord("N")
+            if rng.random() < 0.5 and m > 20:  # an indel
+                i = int(rng.integers(5, m - 5))
+                body = np.concatenate([body[:i], body[i + 1:], synth.ACGT[rng.integers(0, 4, 1)]])
+            reads.append(body.tobytes())
+            for E in ALL_E:
+                for gg, d in ((g, start), (g, start - 3), (g, start + 20), (0, -E - m), (0, -m // 2), (0, 2990),
+                              (0, 3000 + E), (2, -5), (0, int(rng.integers(0, 2500)))):
+                    pr.append(len(reads) - 1)
+                    pg.append(gg)
+                    pd.append(d)
+                    pe.append(E)
+    rs = synth.SeqSet.from_list(reads)
+    arr = (np.array(pr, np.uint32), np.array(pg, np.uint32), np.array(pd, np.int64), np.array(pe, np.uint16))
+    oix = oracle.Index(ga, 15, 10)
+    return dict(ga=ga, ix=mt.Index(ga, 15, 10), rs=rs, dr=mt.to_device(rs), pairs=arr,
+                want=[oix.filter_pairs(rs, *arr, kind=kind) for kind in range(5)])
+
+
+def _run(mt, case, sel, kind=0):
+    import torch
+    pr, pg, pd, pe = (a[sel] for a in case["pairs"])
+    ap, ac = case["ix"].filter_pairs(case["dr"], torch.from_numpy(pr.view(np.int32)).cuda(),
+                                     torch.from_numpy(pg.view(np.int32)).cuda(), torch.from_numpy(pd).cuda(),
+                                     torch.from_numpy(pe.view(np.int16)).cuda(), kind=kind)
+    return ap.cpu().numpy().view(np.uint16), ac.cpu().numpy()
+
+
+@pytest.mark.parametrize("kind", range(5))
+def test_every_pair_under_every_filter(mt, case, kind):
+    sel = np.arange(len(case["pairs"][0]))
+    ap, ac = _run(mt, case, sel, kind)
+    bad = np.flatnonzero(ap != case["want"][kind][0])
+    assert len(bad) == 0, [tuple(int(a[i]) for a in case["pairs"]) for i in bad[:5]]
+    assert np.array_equal(ac, case["want"][kind][1])
+
+
+@pytest.mark.parametrize("E", ALL_E)
+def test_one_bucket(mt, case, E):
+    sel = np.flatnonzero(case["pairs"][3] == E)
+    np.random.default_rng(E).shuffle(sel)
+    ap, ac = _run(mt, case, sel)
+    assert np.array_equal(ap, case["want"][0][0][sel]) and np.array_equal(ac, case["want"][0][1][sel])
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 255, 256, 257, 512, 262_143, 262_144, 262_145, 600_001])
+def test_pair_counts_around_blocks(mt, case, n):
+    sel = np.random.default_rng(n).integers(0, len(case["pairs"][0]), n)
+    ap, ac = _run(mt, case, sel)
+    assert np.array_equal(ap, case["want"][0][0][sel]) and np.array_equal(ac, case["want"][0][1][sel])
