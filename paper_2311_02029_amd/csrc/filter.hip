@@ -3,9 +3,9 @@
 //
 // Pairs are bucketed by their threshold E, and long pairs by the LDS they
 // need, so that each bucket gets the kernel shaped for it (uneven batching):
-//   E <= 7   groups of G lanes per pair, one band row per lane (G = 16, 32 or 64)
-//   E <= 15  G = 32 or 64
-//   E <= 31  G = 64: one pair per wavefront
+//   E <= 31  one lane per pair, the rows as the bits of one or two words; or
+//            groups of G lanes per pair, one band row per lane (G = 16, 32 or 64
+//            for E <= 7, 32 or 64 for E <= 15, 64 above)
 //   E > 31   long reads, four bins by the 64-base blocks of read plus
 //            reference window they stage in LDS (<= 96, 192, 384, 768): one
 //            pair per wavefront, each lane owning a contiguous strip of the
@@ -14,7 +14,7 @@
 //            wavefronts per block;
 //            or the rows-in-lanes kernel reading the window from global memory
 //   larger   the rows-in-lanes kernel.
-// The variant of each bucket (G, W, layout) is chosen by the autotuner
+// The variant of each bucket (lane or G, W, layout) is chosen by the autotuner
 // (mt_autotune) or set by mt_tune_set; every variant gives the same result.
 #include <mutex>
 #include <string>
@@ -80,7 +80,7 @@ __device__ inline u8 pair_class(const FilterArgs &a, u64 p) {
 // second pass fills them.  With global cursors, one atomic per wavefront and
 // class on a handful of words, each pass took 180 us for 1M pairs, waiting on
 // those words; now each takes 8 us (2M pairs of mixed classes).
-constexpr int CL_TPB = 256, CL_MAX_BLOCKS = 1024;
+constexpr int CL_TPB = 256, CL_MAX_BLOCKS = 512;
 
 struct PairRange {
     u64 lo, hi;
@@ -455,6 +455,225 @@ __global__ __launch_bounds__(512) void k_filter_long(FilterArgs a, const u32 *__
     }
 }
 
+// One lane per pair, E <= 31.  The walk is a serial chain of a few steps, each
+// over the 2E+1 rows; here a lane takes a pair's whole step with the rows as
+// the bits of R 32-bit words.  Column t of all rows at once: the window's planes
+// from column j, shifted by t, against the read's base t (a mask of ones or
+// zeros per plane), two three-input bit operations a word.  A row stays alive
+// while its columns match, so after NC columns (few rows match that far by
+// chance: rows / 4^NC) either no row is alive and the longest run is the number
+// of columns that left one, or the few survivors' runs are measured 64 columns
+// at a time.  Bound by VALU issue: rows in lanes (k_filter) spends a group of
+// 16 to 64 lanes on a step of the same length.
+// 1M pairs of 150 bases at E = 7, half of them wrong places: 298 us with 16
+// lanes a pair, 79 us here.
+//
+// The pair's read and window planes are staged in LDS: every step reads them at
+// places of its own per lane, which the vector cache serves one line at a time.
+// A wavefront's 64 pairs share LANE_DW dwords (a pair of 150 bases takes 24 to
+// 28, with the N planes 42); longer pairs go in several batches, and one that
+// does not fit at all (reads past 20 kbp) takes the whole wavefront.
+constexpr int LANE_TPB = 256, LANE_DW = 2552, LANE_PAD = 8;  // 40 KB a block: four blocks a CU
+
+template <int R, int NC, bool kN>
+__device__ inline int lane_walk(const u32 *Q, int nbr, const u32 *W, int nbw, int wofs, int m, int E) {
+    const u32 *ql_ = Q, *qh_ = Q + 2 * nbr, *qn_ = Q + 4 * nbr;
+    const u32 *wl_ = W, *wh_ = W + 2 * nbw, *wn_ = W + 4 * nbw;
+    const int rows = 2 * E + 1;
+    u32 mask[R];
+#pragma unroll
+    for (int i = 0; i < R; i++) mask[i] = rows >= 32 * (i + 1) ? ~0u : rows > 32 * i ? (1u << (rows - 32 * i)) - 1u : 0u;
+    int j = 0, c = 0;
+    for (;;) {
+        const int kq = j >> 5;
+        const u32 sq = (u32)j & 31u;
+        const u32 ql = __builtin_amdgcn_alignbit(ql_[kq + 1], ql_[kq], sq);
+        const u32 qh = __builtin_amdgcn_alignbit(qh_[kq + 1], qh_[kq], sq);
+        const u32 qn = kN ? __builtin_amdgcn_alignbit(qn_[kq + 1], qn_[kq], sq) : 0u;
+        const int pw = wofs + j, kw = pw >> 5;
+        const u32 sw = (u32)pw & 31u;
+        u32 xl[R + 1], xh[R + 1], xn[R + 1];
+#pragma unroll
+        for (int i = 0; i <= R; i++) {
+            xl[i] = __builtin_amdgcn_alignbit(wl_[kw + i + 1], wl_[kw + i], sw);
+            xh[i] = __builtin_amdgcn_alignbit(wh_[kw + i + 1], wh_[kw + i], sw);
+            xn[i] = kN ? __builtin_amdgcn_alignbit(wn_[kw + i + 1], wn_[kw + i], sw) : 0u;
+        }
+        u32 alive[R], any = 0;
+        int best = 0;
+#pragma unroll
+        for (int i = 0; i < R; i++) alive[i] = mask[i];
+#pragma unroll
+        for (int t = 0; t < NC; t++) {
+            const u32 a = (u32)((int)(ql << (31 - t)) >> 31), b = (u32)((int)(qh << (31 - t)) >> 31);
+            const u32 n = kN ? (u32)((int)(qn << (31 - t)) >> 31) : 0u;
+            any = 0;
+#pragma unroll
+            for (int i = 0; i < R; i++) {
+                // truth table 0x90 takes (x, y, z) to x & ~(y ^ z)
+                const u32 wl = t ? __builtin_amdgcn_alignbit(xl[i + 1], xl[i], t) : xl[i];
+                const u32 wh = t ? __builtin_amdgcn_alignbit(xh[i + 1], xh[i], t) : xh[i];
+                u32 v = __builtin_amdgcn_bitop3_b32(alive[i], wl, a, 0x90);
+                v = __builtin_amdgcn_bitop3_b32(v, wh, b, 0x90);
+                if constexpr (kN) v &= ~((t ? __builtin_amdgcn_alignbit(xn[i + 1], xn[i], t) : xn[i]) | n);
+                alive[i] = v;
+                any |= v;
+            }
+            best += any != 0;
+        }
+        if (any) {
+            u64 al = alive[0];
+            if (R > 1) al |= (u64)alive[R - 1] << 32;
+            while (al) {
+                const int row = (int)__builtin_ctzll(al);
+                al &= al - 1;
+                int run = NC;
+                while (j + run < m) {
+                    const int cq = j + run, cw = pw + row + run;
+                    const int k = cq >> 5, kk = cw >> 5;
+                    const u32 s = (u32)cq & 31u, ss = (u32)cw & 31u;
+                    const u32 q1 = ql_[k + 1], h1 = qh_[k + 1], w1 = wl_[kk + 1], v1 = wh_[kk + 1];
+                    u32 m0 = (__builtin_amdgcn_alignbit(q1, ql_[k], s) ^ __builtin_amdgcn_alignbit(w1, wl_[kk], ss)) |
+                             (__builtin_amdgcn_alignbit(h1, qh_[k], s) ^ __builtin_amdgcn_alignbit(v1, wh_[kk], ss));
+                    u32 m1 = (__builtin_amdgcn_alignbit(ql_[k + 2], q1, s) ^
+                              __builtin_amdgcn_alignbit(wl_[kk + 2], w1, ss)) |
+                             (__builtin_amdgcn_alignbit(qh_[k + 2], h1, s) ^
+                              __builtin_amdgcn_alignbit(wh_[kk + 2], v1, ss));
+                    if constexpr (kN) {
+                        m0 |= __builtin_amdgcn_alignbit(qn_[k + 1], qn_[k], s) |
+                              __builtin_amdgcn_alignbit(wn_[kk + 1], wn_[kk], ss);
+                        m1 |= __builtin_amdgcn_alignbit(qn_[k + 2], qn_[k + 1], s) |
+                              __builtin_amdgcn_alignbit(wn_[kk + 2], wn_[kk + 1], ss);
+                    }
+                    if (m0 | m1) {
+                        run += m0 ? (int)__builtin_ctz(m0) : 32 + (int)__builtin_ctz(m1);
+                        break;
+                    }
+                    run += 64;
+                }
+                best = max(best, run);
+            }
+        }
+        j += min(best, m - j);  // columns past the read's end count for nothing
+        if (j >= m) break;
+        c += 1;
+        if (c > E) break;
+        j += 1;
+    }
+    return c;
+}
+
+// Stages the lane's pair (nbr read blocks from rb, nbw window blocks from b0 of
+// its genome) at S and walks it.
+template <int R, int NC, bool kN>
+__device__ inline int lane_pair(const FilterArgs &a, u32 *S, u64 rb, int nbr, const GenomeMeta &gm, i64 b0, int nbw,
+                                int wofs, int m, int E) {
+    u64 *q = (u64 *)S;
+    for (int b = 0; b < nbr; b++) {
+        const u64x2 x = a.read_lohi[rb + b];
+        q[b] = x.lo;
+        q[nbr + b] = x.hi;
+        if (kN) q[2 * nbr + b] = a.read_nb[rb + b];
+    }
+    u64 *w = q + (kN ? 3 : 2) * nbr;
+    const u64x2 *rl = a.ref_lohi + gm.blk;
+    const u64 *rn = a.ref_nb + gm.blk;
+    for (int b = 0; b < nbw; b++) {
+        if constexpr (kN) {
+            const Bits64 x = ref_block(rl, rn, (i64)gm.len, meta_has_n(gm), b0 + b);
+            w[b] = x.lo;
+            w[nbw + b] = x.hi;
+            w[2 * nbw + b] = x.nb;
+        } else {  // the whole window lies inside a genome without N
+            const u64x2 x = rl[b0 + b];
+            w[b] = x.lo;
+            w[nbw + b] = x.hi;
+        }
+    }
+    return lane_walk<R, NC, kN>(S, nbr, (const u32 *)w, nbw, wofs, m, E);
+}
+
+template <int R, int NC>
+__global__ __launch_bounds__(LANE_TPB) void k_filter_lane(FilterArgs a, const u32 *__restrict__ idx, u64 n) {
+    __shared__ __align__(16) u32 lds[LANE_TPB / 64][LANE_DW + LANE_PAD];
+    const u64 np = idx ? n : pair_count(a, n);
+    const u64 t = (u64)blockIdx.x * LANE_TPB + threadIdx.x;
+    if (t - (threadIdx.x & 63) >= np) return;  // the whole wavefront is past the end
+    const int lane = threadIdx.x & 63;
+    u32 *S = lds[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)];
+    const bool in = t < np;
+    const u64 p = !in ? 0 : idx ? idx[t] : t;
+    u32 r = 0, g = 0, err = 0;
+    int E = 0, m = 0, nbr = 0, nbw = 0, wofs = 0;
+    bool ok = false, with_n = false;
+    u64 rb = 0;
+    i64 diag = 0, b0 = 0;
+    GenomeMeta gm{};
+    if (in) {
+        pair_fields(a, p, r, g, E, ok, err);
+        if (ok) {
+            m = read_len(a, r);
+            rb = a.read_blk[r];
+            diag = a.pair_diag[p];
+            gm = a.meta[g];
+            b0 = (diag - E) >> 6;  // floor: the window starts left of the genome for some
+            wofs = (int)(diag - E - 64 * b0);
+            nbr = (m + 63) / 64;
+            nbw = (wofs + 2 * E + m + 63) / 64;
+            with_n = meta_has_n(gm) || diag - E < 0 || diag + m + E > (i64)gm.len;
+            for (int w = 0; w < nbr && !with_n; w++) {
+                const int left = m - 64 * w;
+                with_n = (a.read_nb[rb + w] & (left >= 64 ? ~0ull : (1ull << left) - 1)) != 0;
+            }
+        }
+    }
+    int c = 0;
+    const u64 any_n = __ballot(with_n);
+    const int need = (any_n ? 6 : 4) * (nbr + nbw);
+    u64 todo = __ballot(ok && m > 0 && need <= LANE_DW);
+    u64 big = __ballot(ok && need > LANE_DW);
+    while (todo) {
+        int end = ((todo >> lane) & 1) ? need : 0;  // inclusive prefix sum of the lanes left
+        const int mine = end;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(end, o, 64);
+            if (lane >= o) end += y;
+        }
+        const bool now = mine && end <= LANE_DW;
+        if (now) {
+            if (any_n)
+                c = lane_pair<R, NC, true>(a, S + (end - mine), rb, nbr, gm, b0, nbw, wofs, m, E);
+            else
+                c = lane_pair<R, NC, false>(a, S + (end - mine), rb, nbr, gm, b0, nbw, wofs, m, E);
+        }
+        todo &= ~__ballot(now);
+        lds_wave_sync();
+    }
+    while (big) {
+        const int l = __builtin_ctzll(big);
+        big &= big - 1;
+        const u32 wr = __shfl(r, l, 64), wg = __shfl(g, l, 64);
+        const GenomeMeta wm = a.meta[wg];
+        PairView v;
+        v.qlohi = a.read_lohi + a.read_blk[wr];
+        v.qnb = a.read_nb + a.read_blk[wr];
+        v.m = read_len(a, wr);
+        v.rlohi = a.ref_lohi + wm.blk;
+        v.rnb = a.ref_nb + wm.blk;
+        v.L = (i64)wm.len;
+        v.has_n = meta_has_n(wm);
+        v.diag = __shfl(diag, l, 64);
+        const int wc = obstacle_walk<64>(v, __shfl(E, l, 64), lane);
+        if (lane == l) c = wc;
+    }
+    if (!in) return;
+    if (!ok) atomicOr(a.flags, err);
+    const int ap = min(c, E + 1);
+    a.approx[p] = ok ? (u16)ap : (u16)0xFFFF;
+    a.accept[p] = ok && ap <= E;
+}
+
 // ------------------------------------------------------------- variants --
 
 namespace {
@@ -468,9 +687,9 @@ struct BucketDesc {
 // Variant v of a long bin: v < 4 -> strips in LDS with 1 << v wavefronts per
 // block (if its LDS fits a workgroup), v == 4 -> rows in lanes from global memory.
 const BucketDesc BUCKETS[N_CLASSES] = {
-    {"E<=7", 3, {"g16", "g32", "g64"}},
-    {"E<=15", 2, {"g32", "g64"}},
-    {"E<=31", 1, {"g64"}},
+    {"E<=7", 4, {"g16", "g32", "g64", "lane"}},
+    {"E<=15", 3, {"g32", "g64", "lane"}},
+    {"E<=31", 2, {"g64", "lane"}},
     {"long<=96", 5, {"lds_w1", "lds_w2", "lds_w4", "lds_w8", "global"}},
     {"long<=192", 5, {"lds_w1", "lds_w2", "lds_w4", "lds_w8", "global"}},
     {"long<=384", 5, {"lds_w1", "lds_w2", "lds_w4", "lds_w8", "global"}},
@@ -478,12 +697,12 @@ const BucketDesc BUCKETS[N_CLASSES] = {
     {"general", 1, {"global"}},
 };
 
-// Defaults: the narrowest groups for short E, the most wavefronts per block
-// whose LDS fits 64 KB for the long bins.
-const int DEFAULT_VARIANT[N_CLASSES] = {0, 0, 0, 3, 3, 2, 1, 0};
+// Defaults: a lane per pair for short E, the most wavefronts per block whose LDS
+// fits 64 KB for the long bins.
+const int DEFAULT_VARIANT[N_CLASSES] = {3, 2, 1, 3, 3, 2, 1, 0};
 
 std::mutex g_tune_mu;
-int g_variant[N_CLASSES] = {0, 0, 0, 3, 3, 2, 1, 0};
+int g_variant[N_CLASSES] = {3, 2, 1, 3, 3, 2, 1, 0};
 float g_tune_ms[N_CLASSES][6];
 u64 g_tune_pairs[N_CLASSES];
 
@@ -504,7 +723,11 @@ int current_variant(int bucket) {
 // Launches the pairs idx[0, cnt) of one bucket with one of its variants.
 static void launch_bucket(const FilterArgs &a, const u32 *idx, u64 cnt, int bucket, int v, hipStream_t s) {
     if (cnt == 0) return;
-    if (bucket == 0 || bucket == 1) {
+    if (bucket < CLS_LONG && v == BUCKETS[bucket].n_variants - 1) {
+        const unsigned blocks = grid_for(cnt, LANE_TPB);
+        if (bucket < 2) k_filter_lane<1, 6><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
+        else k_filter_lane<2, 7><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
+    } else if (bucket == 0 || bucket == 1) {
         const int g = std::string(BUCKETS[bucket].variants[v]) == "g16" ? 16
                       : std::string(BUCKETS[bucket].variants[v]) == "g32" ? 32 : 64;
         if (g == 16) k_filter<16><<<grid_for(cnt * 16, 256), 256, 0, s>>>(a, idx, cnt);
