@@ -61,6 +61,61 @@ __device__ inline u32 base_code(u32 c) {
     return acgt ? two : (u == 'N' ? 4u : 5u);
 }
 
+// Four ASCII bases at once: byte i of *code has base i's code in its low two
+// bits (0 for N), and byte i of *diff is zero iff the byte is A, C, G or T in
+// either case: the letter of the code, looked up in a four-byte table, against
+// the upper-cased byte.
+__device__ inline void base_codes4(u32 v, u32 *code, u32 *diff) {
+    *code = (v >> 1) ^ (v >> 2);
+    *diff = __builtin_amdgcn_perm(0u, 0x54474341u, *code & 0x03030303u) ^ (v & 0xDFDFDFDFu);
+}
+
+// Bit i of the result: byte i of the four words is nonzero / the byte of the
+// four words is N in either case (bit 4 j + t: byte t of word j).
+__device__ inline u32 nonzero_bytes16(const u32 (&d)[4]) {
+    u32 r = 0;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        const u32 t = ((((d[j] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | d[j]) >> 7) & 0x01010101u;
+        r |= __builtin_amdgcn_udot4(t, 0x08040201u, 0u, false) << (4 * j);
+    }
+    return r;
+}
+__device__ inline u32 n_bytes16(const u32 (&v)[4]) {
+    u32 d[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) d[j] = (v[j] & 0xDFDFDFDFu) ^ 0x4E4E4E4Eu;
+    return ~nonzero_bytes16(d) & 0xFFFFu;
+}
+
+// Plane bits of 16 ASCII bases: bit i of lo / hi is bit 0 / 1 of base i's code;
+// returns whether every byte is A, C, G or T (else *other has the bits of the
+// bytes that are not).  Each plane takes four byte dot products with powers of two.
+__device__ inline void plane_bits16(const u32 (&v)[4], u32 *lo, u32 *hi, u32 *other) {
+    u32 x[4], d[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) base_codes4(v[j], &x[j], &d[j]);
+    u32 l0 = __builtin_amdgcn_udot4(x[0] & 0x01010101u, 0x08040201u, 0u, false);
+    u32 l1 = __builtin_amdgcn_udot4(x[2] & 0x01010101u, 0x08040201u, 0u, false);
+    u32 h0 = __builtin_amdgcn_udot4(x[0] & 0x02020202u, 0x08040201u, 0u, false);  // twice the bits
+    u32 h1 = __builtin_amdgcn_udot4(x[2] & 0x02020202u, 0x08040201u, 0u, false);
+    l0 = __builtin_amdgcn_udot4(x[1] & 0x01010101u, 0x80402010u, l0, false);
+    l1 = __builtin_amdgcn_udot4(x[3] & 0x01010101u, 0x80402010u, l1, false);
+    h0 = __builtin_amdgcn_udot4(x[1] & 0x02020202u, 0x80402010u, h0, false);
+    h1 = __builtin_amdgcn_udot4(x[3] & 0x02020202u, 0x80402010u, h1, false);
+    *lo = l0 | (l1 << 8);
+    *hi = (h0 | (h1 << 8)) >> 1;
+    *other = (d[0] | d[1] | d[2] | d[3]) ? nonzero_bytes16(d) : 0u;
+}
+
+// 16 bytes from any address.
+typedef u32 u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+__device__ inline void load16(const u8 *p, u32 (&v)[4]) {
+    const u32x4_any x = *(const u32x4_any *)p;
+#pragma unroll
+    for (int j = 0; j < 4; j++) v[j] = x[j];
+}
+
 // splitmix64 finalizer (Steele, Lea and Flood 2014), a bijection on 64-bit words.
 __host__ __device__ inline u64 mix64(u64 z) {
     z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
