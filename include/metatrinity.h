@@ -416,7 +416,8 @@ int mt_result_times(const mt_result *res, uint64_t *submit_ns, uint64_t *done_ns
  * rows of Table 1's pigeonhole filters).  Filter pairs are bucketed by E
  * (<= 7, <= 15, <= 31) and, for larger E, by the 64-base blocks of read and
  * reference window they stage in LDS (<= 96, 192, 384, 768); each bucket has
- * variants: one lane or a group of lanes per pair for small E, the LDS tile
+ * variants: for small E one lane per pair (the first variant, under the name
+ * of the narrowest group of lanes) or a wider group; for large E the LDS tile
  * with 1/2/4/8 wavefronts per block or a rows-in-lanes layout reading global
  * memory for large E.  Every variant gives bit-identical results; the choice
  * is process-wide and applies to mt_classify (per-stage form and the fused

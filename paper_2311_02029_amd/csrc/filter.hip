@@ -4,8 +4,8 @@
 // Pairs are bucketed by their threshold E, and long pairs by the LDS they
 // need, so that each bucket gets the kernel shaped for it (uneven batching):
 //   E <= 31  one lane per pair, the rows as the bits of one or two words; or
-//            groups of G lanes per pair, one band row per lane (G = 16, 32 or 64
-//            for E <= 7, 32 or 64 for E <= 15, 64 above)
+//            groups of G lanes per pair, one band row per lane (G = 32 or 64 for
+//            E <= 7, 64 for E <= 15)
 //   E > 31   long reads, four bins by the 64-base blocks of read plus
 //            reference window they stage in LDS (<= 96, 192, 384, 768): one
 //            pair per wavefront, each lane owning a contiguous strip of the
@@ -684,12 +684,14 @@ struct BucketDesc {
     const char *variants[6];
 };
 
+// Variant 0 of a short bucket is one lane per pair; it keeps the name of the
+// narrowest group, which it replaces, so that saved selections go on loading.
 // Variant v of a long bin: v < 4 -> strips in LDS with 1 << v wavefronts per
 // block (if its LDS fits a workgroup), v == 4 -> rows in lanes from global memory.
 const BucketDesc BUCKETS[N_CLASSES] = {
-    {"E<=7", 4, {"g16", "g32", "g64", "lane"}},
-    {"E<=15", 3, {"g32", "g64", "lane"}},
-    {"E<=31", 2, {"g64", "lane"}},
+    {"E<=7", 3, {"g16", "g32", "g64"}},
+    {"E<=15", 2, {"g32", "g64"}},
+    {"E<=31", 1, {"g64"}},
     {"long<=96", 5, {"lds_w1", "lds_w2", "lds_w4", "lds_w8", "global"}},
     {"long<=192", 5, {"lds_w1", "lds_w2", "lds_w4", "lds_w8", "global"}},
     {"long<=384", 5, {"lds_w1", "lds_w2", "lds_w4", "lds_w8", "global"}},
@@ -699,10 +701,10 @@ const BucketDesc BUCKETS[N_CLASSES] = {
 
 // Defaults: a lane per pair for short E, the most wavefronts per block whose LDS
 // fits 64 KB for the long bins.
-const int DEFAULT_VARIANT[N_CLASSES] = {3, 2, 1, 3, 3, 2, 1, 0};
+const int DEFAULT_VARIANT[N_CLASSES] = {0, 0, 0, 3, 3, 2, 1, 0};
 
 std::mutex g_tune_mu;
-int g_variant[N_CLASSES] = {3, 2, 1, 3, 3, 2, 1, 0};
+int g_variant[N_CLASSES] = {0, 0, 0, 3, 3, 2, 1, 0};
 float g_tune_ms[N_CLASSES][6];
 u64 g_tune_pairs[N_CLASSES];
 
@@ -723,16 +725,12 @@ int current_variant(int bucket) {
 // Launches the pairs idx[0, cnt) of one bucket with one of its variants.
 static void launch_bucket(const FilterArgs &a, const u32 *idx, u64 cnt, int bucket, int v, hipStream_t s) {
     if (cnt == 0) return;
-    if (bucket < CLS_LONG && v == BUCKETS[bucket].n_variants - 1) {
+    if (bucket < CLS_LONG && v == 0) {
         const unsigned blocks = grid_for(cnt, LANE_TPB);
         if (bucket < 2) k_filter_lane<1, 6><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
         else k_filter_lane<2, 7><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
-    } else if (bucket == 0 || bucket == 1) {
-        const int g = std::string(BUCKETS[bucket].variants[v]) == "g16" ? 16
-                      : std::string(BUCKETS[bucket].variants[v]) == "g32" ? 32 : 64;
-        if (g == 16) k_filter<16><<<grid_for(cnt * 16, 256), 256, 0, s>>>(a, idx, cnt);
-        else if (g == 32) k_filter<32><<<grid_for(cnt * 32, 256), 256, 0, s>>>(a, idx, cnt);
-        else k_filter<64><<<grid_for(cnt * 64, 256), 256, 0, s>>>(a, idx, cnt);
+    } else if (bucket == 0 && v == 1) {
+        k_filter<32><<<grid_for(cnt * 32, 256), 256, 0, s>>>(a, idx, cnt);
     } else if (bucket >= CLS_LONG && bucket < CLS_LONG + LONG_BINS && v < 4) {
         const int tile = LONG_CAP[bucket - CLS_LONG], wpb = 1 << v;
         u64 blocks = (cnt + wpb - 1) / wpb;
