@@ -447,8 +447,10 @@ __global__ __launch_bounds__(RED_TPB) void k_reduce(const u64 *__restrict__ cand
                                                     u32 n_taxa, u8 *__restrict__ read_accepted,
                                                     unsigned long long *__restrict__ uniq,
                                                     unsigned long long *__restrict__ multi,
-                                                    unsigned long long *__restrict__ unmapped) {
+                                                    unsigned long long *__restrict__ unmapped,
+                                                    const u32 *__restrict__ gate) {
     __shared__ u32 cnt[2 * RED_LDS_TAXA + 1];
+    if (gate && *gate) return;
     const u64 stride = (u64)gridDim.x * RED_TPB;
     if (n_taxa > RED_LDS_TAXA) {
         const GlobalCounts out{uniq, multi, unmapped};
@@ -469,6 +471,17 @@ __global__ __launch_bounds__(RED_TPB) void k_reduce(const u64 *__restrict__ cand
         unsigned long long *dst = i < n_taxa ? &uniq[i] : i < 2 * n_taxa ? &multi[i - n_taxa] : unmapped;
         atomicAdd(dst, (unsigned long long)v);
     }
+}
+
+void launch_reduce(mt_result &res, const mt_index &ix, const u16 *read_E, const u32 *gate, hipStream_t s) {
+    const u64 n = res.n_reads;
+    if (n == 0) return;
+    const unsigned blocks = (unsigned)std::min<u64>(grid_for(n, RED_TPB), (u64)count_blocks() / 2);
+    k_reduce<<<blocks, RED_TPB, 0, s>>>(res.cand_off.p, n, res.genome.p, res.approx.p, read_E, ix.taxon.p, ix.n_taxa,
+                                        res.read_accepted.p, (unsigned long long *)res.uniq.p,
+                                        (unsigned long long *)res.multi.p, (unsigned long long *)res.unmapped.p,
+                                        gate);
+    MT_HIP(hipGetLastError());
 }
 
 // The taxon step per request slot of a served batch: reads [slot_off[s],
@@ -601,14 +614,13 @@ static void stage_seed_count(const mt_index &ix, const mt_query_params &q, const
 static void stage_filter_reduce(const mt_index &ix, const mt_query_params &q, const mt_seqs &reads,
                                 const ReadBatch &rb, const u32 *pair_read, u64 cap, const u16 *read_E,
                                 mt_result &res, Timer &tm, hipStream_t s) {
-    const u64 n = res.n_reads;
     FilterArgs fa{};
     fa.pair_read = pair_read;
     fa.pair_genome = res.genome.p;
     fa.pair_diag = res.diag.p;
     fa.pair_E = nullptr;
     fa.read_E = rb.read_E.p;
-    fa.n_dev = res.cand_off.p + n;
+    fa.n_dev = res.cand_off.p + res.n_reads;
     fa.n_host = cap;
     fa.n_reads = reads.n;
     fa.read_off = reads.offsets;
@@ -628,15 +640,7 @@ static void stage_filter_reduce(const mt_index &ix, const mt_query_params &q, co
         launch_filter_simple(fa, cap, q.filter, s);
         tm.mark("filter");
     }
-    // reduce
-    if (n) {
-        const unsigned blocks = std::min<u64>(grid_for(n, RED_TPB), (u64)count_blocks() / 2);
-        k_reduce<<<blocks, RED_TPB, 0, s>>>(res.cand_off.p, n, res.genome.p, res.approx.p, read_E, ix.taxon.p,
-                                            ix.n_taxa, res.read_accepted.p, (unsigned long long *)res.uniq.p,
-                                            (unsigned long long *)res.multi.p,
-                                            (unsigned long long *)res.unmapped.p);
-        MT_HIP(hipGetLastError());
-    }
+    launch_reduce(res, ix, read_E, nullptr, s);
     tm.mark("reduce");
 }
 
@@ -644,6 +648,7 @@ void classify_per_stage(const mt_index &ix, const mt_query_params &q, const mt_s
                         mt_result &res, Timer &tm, hipStream_t s) {
     const u64 n = reads.n;
     StagedCands sc;
+    zero_counters(res, s);
     stage_seed_count(ix, q, reads, rb, sc, tm, s);
     // candidates
     u64 cap = q.top_n ? std::min<u64>(sc.H, n * (u64)q.top_n) : sc.H;
@@ -823,8 +828,7 @@ static void both_strands_fused(const mt_index &ix, const mt_query_params &q, con
     scan_u32(nmerged.p, res.cand_off.p, n, s);
     u64 total = 0;
     read_back(s, res.cand_off.p + n, &total, sizeof total);
-    res.alloc_cands(total);
-    res.strand.alloc(total);
+    res.alloc_cands(total, true);
     if (n) {
         k_strand_merge_done<<<grid_for(n, 256), 256, 0, s>>>(
             r2.cand_off.p, n, r2.genome.p, r2.diag.p, r2.hits.p, r2.approx.p, r2.accept.p, r2.read_E.p,
@@ -832,12 +836,7 @@ static void both_strands_fused(const mt_index &ix, const mt_query_params &q, con
             res.read_E.p);
         MT_HIP(hipGetLastError());
         tm.mark("merge");
-        const unsigned blocks = std::min<u64>(grid_for(n, RED_TPB), (u64)count_blocks() / 2);
-        k_reduce<<<blocks, RED_TPB, 0, s>>>(res.cand_off.p, n, res.genome.p, res.approx.p, res.read_E.p,
-                                            ix.taxon.p, ix.n_taxa, res.read_accepted.p,
-                                            (unsigned long long *)res.uniq.p, (unsigned long long *)res.multi.p,
-                                            (unsigned long long *)res.unmapped.p);
-        MT_HIP(hipGetLastError());
+        launch_reduce(res, ix, res.read_E.p, nullptr, s);
         tm.mark("reduce");
     }
     res.n_cands = total;
@@ -851,6 +850,7 @@ static void classify_both_strands(const mt_index &ix, const mt_query_params &q, 
                                   ReadBatch &rb, mt_result &res, Timer &tm, hipStream_t s) {
     const u64 n = reads.n;
     MT_REQUIRE(n < (1ull << 31), "at most 2^31 - 1 reads per call on both strands");
+    zero_counters(res, s);
     DBuf<u64> off2(2 * n + 1);
     DBuf<u8> seq2(2 * reads.total);
     {
@@ -887,8 +887,7 @@ static void classify_both_strands(const mt_index &ix, const mt_query_params &q, 
         MT_HIP(hipGetLastError());
     }
     const u64 cap = q.top_n ? std::min<u64>(sc.H, n * (u64)q.top_n) : sc.H;
-    res.alloc_cands(cap);
-    res.strand.alloc(cap);
+    res.alloc_cands(cap, true);
     scan_u32(nmerged.p, res.cand_off.p, n, s);
     DBuf<u32> pair_read(cap);
     if (n) {
@@ -906,29 +905,55 @@ static void classify_both_strands(const mt_index &ix, const mt_query_params &q, 
 }
 
 void mt_result_init(mt_result &res, u64 n, u32 n_taxa, hipStream_t s) {
-    res.n_reads = n;
-    res.n_taxa = n_taxa;
-    res.cand_off.alloc(n + 1);
-    res.read_accepted.alloc(n);
-    res.read_E.alloc(n);
-    res.uniq.alloc(n_taxa);
-    res.multi.alloc(n_taxa);
-    res.unmapped.alloc(1);
-    MT_HIP(hipMemsetAsync(res.uniq.p, 0, (n_taxa ? n_taxa : 1) * sizeof(u64), s));
-    MT_HIP(hipMemsetAsync(res.multi.p, 0, (n_taxa ? n_taxa : 1) * sizeof(u64), s));
-    MT_HIP(hipMemsetAsync(res.unmapped.p, 0, sizeof(u64), s));
+    res.alloc_reads(n, n_taxa);
     if (n == 0) MT_HIP(hipMemsetAsync(res.cand_off.p, 0, sizeof(u64), s));
+}
+
+void zero_counters(mt_result &res, hipStream_t s) {
+    MT_HIP(hipMemsetAsync(res.uniq.p, 0, res.n_counters() * sizeof(u64), s));
+}
+
+// Takes n elements off a block being laid out (or only measured, p null); every
+// array starts on a 64-byte line.
+template <class T>
+static void place(Arr<T> &a, u8 *p, u64 &at, u64 n) {
+    a.p = p ? (T *)(p + at) : nullptr;
+    at += (n * sizeof(T) + 63) / 64 * 64;
 }
 
 }  // namespace mt
 
-void mt_result::alloc_cands(mt::u64 c) {
+void mt_result::alloc_reads(mt::u64 n, mt::u32 taxa) {
+    n_reads = n;
+    n_taxa = taxa;
+    for (int pass = 0; pass < 2; pass++) {
+        mt::u64 at = 0;
+        mt::Arr<mt::u64> counters;
+        mt::place(counters, reads_block.p, at, n_counters());
+        mt::place(cand_off, reads_block.p, at, n + 1);
+        mt::place(read_E, reads_block.p, at, n);
+        mt::place(read_accepted, reads_block.p, at, n);
+        uniq.p = counters.p;
+        multi.p = uniq.p + taxa;
+        unmapped.p = multi.p + taxa;
+        if (pass == 0) reads_block.alloc(at);
+    }
+}
+
+void mt_result::alloc_cands(mt::u64 c, bool strands) {
     cap = c;
-    genome.alloc(c);
-    diag.alloc(c);
-    hits.alloc(c);
-    approx.alloc(c);
-    accept.alloc(c);
+    cands_block.release();
+    for (int pass = 0; pass < 2; pass++) {
+        mt::u64 at = 0;
+        mt::place(diag, cands_block.p, at, c);
+        mt::place(genome, cands_block.p, at, c);
+        mt::place(hits, cands_block.p, at, c);
+        mt::place(approx, cands_block.p, at, c);
+        mt::place(accept, cands_block.p, at, c);
+        strand.p = nullptr;
+        if (strands) mt::place(strand, cands_block.p, at, c);
+        if (pass == 0) cands_block.alloc(at);
+    }
 }
 
 // ---------------------------------------------------------------------- ABI --

@@ -3,21 +3,34 @@
 
 #include "index.hpp"
 
+namespace mt {
+// One of a result's arrays, inside one of its two blocks.
+template <class T>
+struct Arr {
+    T *p = nullptr;
+};
+}  // namespace mt
+
 struct mt_result {
     mt::u64 n_reads = 0, n_cands = 0, cap = 0;
     mt::u32 n_taxa = 0;
-    mt::DBuf<mt::u64> cand_off;       // n_reads + 1
-    mt::DBuf<mt::u8> read_accepted;   // n_reads
-    mt::DBuf<mt::u16> read_E;         // n_reads
-    mt::DBuf<mt::u32> genome;         // candidates (capacity cap)
-    mt::DBuf<mt::i64> diag;
-    mt::DBuf<mt::u32> hits;
-    mt::DBuf<mt::u16> approx;
-    mt::DBuf<mt::u8> accept;
-    mt::DBuf<mt::u8> strand;          // both-strand results only (else empty)
-    mt::DBuf<mt::u64> uniq, multi;    // n_taxa
-    mt::DBuf<mt::u64> unmapped;       // 1
-    void alloc_cands(mt::u64 c);
+    // One block holds the arrays whose sizes the reads and the index give, one the
+    // candidate arrays (capacity cap): two allocations a result, and the counters
+    // (uniq, multi, unmapped, back to back) are cleared at once.
+    mt::DBuf<mt::u8> reads_block, cands_block;
+    mt::Arr<mt::u64> uniq, multi;       // n_taxa
+    mt::Arr<mt::u64> unmapped;          // 1
+    mt::Arr<mt::u64> cand_off;          // n_reads + 1
+    mt::Arr<mt::u16> read_E;            // n_reads
+    mt::Arr<mt::u8> read_accepted;      // n_reads
+    mt::Arr<mt::i64> diag;              // candidates
+    mt::Arr<mt::u32> genome, hits;
+    mt::Arr<mt::u16> approx;
+    mt::Arr<mt::u8> accept;
+    mt::Arr<mt::u8> strand;             // both-strand results only (else null)
+    void alloc_reads(mt::u64 n, mt::u32 taxa);
+    void alloc_cands(mt::u64 c, bool strands = false);
+    mt::u64 n_counters() const { return 2 * (mt::u64)n_taxa + 1; }  // at uniq.p
     // Served results live in host memory (the DBufs above stay empty).
     bool on_host = false;
     struct Host {
@@ -67,6 +80,13 @@ struct FilterArgs {
     u16 *approx;
     u8 *accept;
     u32 *flags;
+    // the fused form: reads as ASCII instead of planes (read_off into seq, its
+    // bytes seq_total), whether each has an N, and its offsets check (nonzero:
+    // nothing is filtered)
+    const u8 *seq;
+    u64 seq_total;
+    const u8 *read_n;
+    const u32 *gate;
 };
 
 // Filters pairs [0, n) (n = *n_dev if set, else n_host; n_cap bounds it):
@@ -74,6 +94,8 @@ struct FilterArgs {
 // then each bucket runs the kernel shaped for it.  fixed_E: the E of every
 // pair when the caller knows it, else -1; pairs of one short E need no buckets.
 void launch_filter(const FilterArgs &a, u64 n_cap, int fixed_E, hipStream_t s, Timer *tm = nullptr);
+// Pairs [0, *n_dev) of the fused form (at most cap), every E at most max_E <= 31.
+void launch_filter_fused(const FilterArgs &a, u64 cap, int max_E, hipStream_t s);
 // Pairs [0, count) through the Hamming (MT_FILTER_HAMMING), base-counting
 // (MT_FILTER_BASE_COUNT), q-gram (MT_FILTER_QGRAM) or shifted Hamming (MT_FILTER_SHD)
 // filter; count = *n_dev if set, else n_host, at most n.
@@ -87,13 +109,15 @@ void tune_set(int bucket, int variant);
 void tune_reset();
 
 void validate_query(const mt_query_params &q);
+// Allocates the per-read and per-taxon arrays; the forms below clear the counters.
 void mt_result_init(mt_result &res, u64 n, u32 n_taxa, hipStream_t s);
+void zero_counters(mt_result &res, hipStream_t s);
 void classify_per_stage(const mt_index &ix, const mt_query_params &q, const mt_seqs &reads, ReadBatch &rb,
                         mt_result &res, Timer &tm, hipStream_t s);
 // Fused form.  Checks the call's flags and sets res.n_cands before it
 // returns; graph = launch the sequence as one captured HIP graph.
-// Containment search: adds every genome's seed hits over `reads` to hits
-// (device, n_genomes).  containment runs reads of up to 256 bases in one
+// Containment search: every genome's seed hits over `reads` (device, n_genomes;
+// containment_per_stage adds to hits).  containment runs reads of up to 256 bases in one
 // fused kernel and the rest through containment_per_stage.
 void containment(const mt_index &ix, const mt_seqs &reads, u64 *hits, hipStream_t s);
 void containment_per_stage(const mt_index &ix, const mt_seqs &reads, u64 *hits, hipStream_t s);
@@ -104,6 +128,9 @@ void classify_staged(const mt_index &ix, const mt_query_params &q, const mt_seqs
                      mt_result &res, Timer &tm, hipStream_t s);
 void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs &reads, ReadBatch &rb,
                     mt_result &res, Timer &tm, hipStream_t s, bool graph);
+// The taxon step: read_accepted and the taxon counts of res from its filtered
+// candidates; gate (nullable): nonzero skips it.
+void launch_reduce(mt_result &res, const mt_index &ix, const u16 *read_E, const u32 *gate, hipStream_t s);
 // The taxon step of a batch that holds several requests: reads
 // [slot_off[s], slot_off[s+1]) add into counts[s] = {unique[n_taxa],
 // multi[n_taxa], unmapped} (device arrays; slot_off and counts on the device).

@@ -175,7 +175,6 @@ extern "C" int mt_containment(const mt_index *index, const mt_seqs *reads, uint6
     return guarded("mt_containment", [&] {
         MT_REQUIRE(reads->n == 0 || (reads->seq && reads->offsets), "null read arrays");
         CallScope scope(s);
-        if (index->n_genomes) MT_HIP(hipMemsetAsync(hits, 0, index->n_genomes * sizeof(uint64_t), s));
         containment(*index, *reads, hits, s);
     });
 }

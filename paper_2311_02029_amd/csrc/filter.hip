@@ -563,17 +563,49 @@ __device__ inline int lane_walk(const u32 *Q, int nbr, const u32 *W, int nbw, in
     return c;
 }
 
-// Stages the lane's pair (nbr read blocks from rb, nbw window blocks from b0 of
-// its genome) at S and walks it.
-template <int R, int NC, bool kN>
+// One 64-base block of a read's planes from its ASCII (cnt bases from byte at).
+__device__ inline Bits64 ascii_block(const FilterArgs &a, u64 at, int cnt) {
+    u32 lo[4], hi[4], nb[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        u32 v[4] = {0, 0, 0, 0};
+        const int c = min(16, cnt - 16 * i);
+        lo[i] = hi[i] = 0;
+        nb[i] = 0xFFFFu;
+        if (c > 0) {
+            if (at + 16 * i + 16 <= a.seq_total) {
+                load16(a.seq + at + 16 * i, v);
+            } else {
+#pragma unroll
+                for (int t = 0; t < 16; t++)
+                    if (t < c) v[t >> 2] |= (u32)a.seq[at + 16 * i + t] << (8 * (t & 3));
+            }
+            plane_bits16(v, &lo[i], &hi[i], &nb[i]);
+        }
+    }
+    return Bits64{lo[0] | lo[1] << 16 | (u64)(lo[2] | lo[3] << 16) << 32,
+                  hi[0] | hi[1] << 16 | (u64)(hi[2] | hi[3] << 16) << 32,
+                  nb[0] | nb[1] << 16 | (u64)(nb[2] | nb[3] << 16) << 32};
+}
+
+// Stages the lane's pair (nbr read blocks, from block rb of the planes or byte
+// rb of the ASCII; nbw window blocks from b0 of its genome) at S and walks it.
+template <int R, int NC, bool kN, bool kAscii>
 __device__ inline int lane_pair(const FilterArgs &a, u32 *S, u64 rb, int nbr, const GenomeMeta &gm, i64 b0, int nbw,
                                 int wofs, int m, int E) {
     u64 *q = (u64 *)S;
     for (int b = 0; b < nbr; b++) {
-        const u64x2 x = a.read_lohi[rb + b];
-        q[b] = x.lo;
-        q[nbr + b] = x.hi;
-        if (kN) q[2 * nbr + b] = a.read_nb[rb + b];
+        if constexpr (kAscii) {
+            const Bits64 x = ascii_block(a, rb + 64 * (u64)b, m - 64 * b);
+            q[b] = x.lo;
+            q[nbr + b] = x.hi;
+            if (kN) q[2 * nbr + b] = x.nb;
+        } else {
+            const u64x2 x = a.read_lohi[rb + b];
+            q[b] = x.lo;
+            q[nbr + b] = x.hi;
+            if (kN) q[2 * nbr + b] = a.read_nb[rb + b];
+        }
     }
     u64 *w = q + (kN ? 3 : 2) * nbr;
     const u64x2 *rl = a.ref_lohi + gm.blk;
@@ -593,9 +625,12 @@ __device__ inline int lane_pair(const FilterArgs &a, u32 *S, u64 rb, int nbr, co
     return lane_walk<R, NC, kN>(S, nbr, (const u32 *)w, nbw, wofs, m, E);
 }
 
-template <int R, int NC>
+// kAscii: the fused form's pairs, reads of at most 320 bases as ASCII (no pair
+// is too long for the LDS).
+template <int R, int NC, bool kAscii>
 __global__ __launch_bounds__(LANE_TPB) void k_filter_lane(FilterArgs a, const u32 *__restrict__ idx, u64 n) {
     __shared__ __align__(16) u32 lds[LANE_TPB / 64][LANE_DW + LANE_PAD];
+    if (kAscii && *a.gate) return;
     const u64 np = idx ? n : pair_count(a, n);
     const u64 t = (u64)blockIdx.x * LANE_TPB + threadIdx.x;
     if (t - (threadIdx.x & 63) >= np) return;  // the whole wavefront is past the end
@@ -613,7 +648,7 @@ __global__ __launch_bounds__(LANE_TPB) void k_filter_lane(FilterArgs a, const u3
         pair_fields(a, p, r, g, E, ok, err);
         if (ok) {
             m = read_len(a, r);
-            rb = a.read_blk[r];
+            rb = kAscii ? a.read_off[r] : a.read_blk[r];
             diag = a.pair_diag[p];
             gm = a.meta[g];
             b0 = (diag - E) >> 6;  // floor: the window starts left of the genome for some
@@ -621,9 +656,13 @@ __global__ __launch_bounds__(LANE_TPB) void k_filter_lane(FilterArgs a, const u3
             nbr = (m + 63) / 64;
             nbw = (wofs + 2 * E + m + 63) / 64;
             with_n = meta_has_n(gm) || diag - E < 0 || diag + m + E > (i64)gm.len;
-            for (int w = 0; w < nbr && !with_n; w++) {
-                const int left = m - 64 * w;
-                with_n = (a.read_nb[rb + w] & (left >= 64 ? ~0ull : (1ull << left) - 1)) != 0;
+            if constexpr (kAscii) {
+                with_n |= a.read_n[r] != 0;
+            } else {
+                for (int w = 0; w < nbr && !with_n; w++) {
+                    const int left = m - 64 * w;
+                    with_n = (a.read_nb[rb + w] & (left >= 64 ? ~0ull : (1ull << left) - 1)) != 0;
+                }
             }
         }
     }
@@ -643,14 +682,14 @@ __global__ __launch_bounds__(LANE_TPB) void k_filter_lane(FilterArgs a, const u3
         const bool now = mine && end <= LANE_DW;
         if (now) {
             if (any_n)
-                c = lane_pair<R, NC, true>(a, S + (end - mine), rb, nbr, gm, b0, nbw, wofs, m, E);
+                c = lane_pair<R, NC, true, kAscii>(a, S + (end - mine), rb, nbr, gm, b0, nbw, wofs, m, E);
             else
-                c = lane_pair<R, NC, false>(a, S + (end - mine), rb, nbr, gm, b0, nbw, wofs, m, E);
+                c = lane_pair<R, NC, false, kAscii>(a, S + (end - mine), rb, nbr, gm, b0, nbw, wofs, m, E);
         }
         todo &= ~__ballot(now);
         lds_wave_sync();
     }
-    while (big) {
+    while (!kAscii && big) {
         const int l = __builtin_ctzll(big);
         big &= big - 1;
         const u32 wr = __shfl(r, l, 64), wg = __shfl(g, l, 64);
@@ -727,8 +766,8 @@ static void launch_bucket(const FilterArgs &a, const u32 *idx, u64 cnt, int buck
     if (cnt == 0) return;
     if (bucket < CLS_LONG && v == 0) {
         const unsigned blocks = grid_for(cnt, LANE_TPB);
-        if (bucket < 2) k_filter_lane<1, 6><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
-        else k_filter_lane<2, 7><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
+        if (bucket < 2) k_filter_lane<1, 6, false><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
+        else k_filter_lane<2, 7, false><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
     } else if (bucket == 0 && v == 1) {
         k_filter<32><<<grid_for(cnt * 32, 256), 256, 0, s>>>(a, idx, cnt);
     } else if (bucket >= CLS_LONG && bucket < CLS_LONG + LONG_BINS && v < 4) {
@@ -1018,6 +1057,14 @@ void launch_filter(const FilterArgs &a, u64 n_cap, int fixed_E, hipStream_t s, T
         launch_bucket(a, idx.p ? idx.p + hb[c] : nullptr, hc[c], c, current_variant(c), s);
         if (tm) tm->mark(BUCKET_MARKS[c]);
     }
+}
+
+void launch_filter_fused(const FilterArgs &a, u64 cap, int max_E, hipStream_t s) {
+    if (cap == 0) return;
+    const unsigned blocks = grid_for(cap, LANE_TPB);
+    if (max_E <= 15) k_filter_lane<1, 6, true><<<blocks, LANE_TPB, 0, s>>>(a, nullptr, cap);
+    else k_filter_lane<2, 7, true><<<blocks, LANE_TPB, 0, s>>>(a, nullptr, cap);
+    MT_HIP(hipGetLastError());
 }
 
 // Times every variant of every bucket that holds pairs (best of `reps`

@@ -1,114 +1,75 @@
-// Fused seed-count + filter path for short reads (Fig. 1 steps 2b-2d and 3a
-// in one kernel).  One wavefront owns one read at a time:
-//   1. its bytes (requested while the previous read was counted) become
-//      lo / hi / N bit planes with ballots, kept in a per-read LDS slot, and a
-//      big-endian 2-bit stream in LDS;
-//   2. lane i hashes the k-mer at position i (per 64-position round) into a
-//      per-wave LDS tile;
-//   3. lane s scans window s for its smallest valid (hash, position); picks
-//      are marked in LDS and compacted with ballot + popcount;
-//   4. each minimizer lane probes one 64-byte table bucket (all four slots
-//      loaded at once); a read's hits are counted in registers, one ballot
-//      per distinct (genome, diagonal), when they fit one lane each, and in a
-//      per-read LDS hash table otherwise;
-//   5. locations with >= min_hits become candidates, and each candidate's
-//      rank in (hits desc, genome, diagonal) order picks the top_n;
-//   6. the kept candidates join a per-wave queue; a full queue is filtered by
-//      groups of G lanes (G = 16, 32 or 64 by E), one band row d per lane:
-//      the row's mismatch words are built from 64-base reference fetches,
-//      parked in LDS, and the obstacle walk advances by ctz of the row bits
-//      plus a max over the group;
-//   7. a read whose candidates are all filtered gets its accept flag and its
-//      per-taxon unique / multi count.
-// Reads beyond the kernel's limits (longer than 256 bases, E above 31, more
-// than 256 seed hits, or more than 8 candidates when every candidate is kept)
-// are queued and finished by the per-stage kernels, so every read gets the
-// same result as in per-stage mode; top_n above 8 runs per stage throughout.
-#include <cstddef>
-#include <type_traits>
+// Fused seeding for short reads (Fig. 1 steps 2b-2c in one kernel), then the
+// filter and the taxon step over its candidates (2d, 3a).
+//   k_seed_lane   one lane per read (lane.hpp): 2-bit stream, k-mers and window
+//                 minima base by base, then one table probe per minimizer; the
+//                 read's locations are counted in a short per-lane list, and the
+//                 ones with >= min_hits hits ranked in (hits desc, genome,
+//                 diagonal) order and cut to the top_n;
+//   k_seed_wave   one wavefront per read: the reads whose lane met a tie of
+//                 minimizer keys or more locations than its list holds, small
+//                 read sets (which would leave most of the chip idle with 64
+//                 reads a wavefront) and minimizer windows without a lane instance;
+//   k_compact_seeds   candidates to their places in the result;
+//   k_filter_lane     the obstacle walk, one lane per pair (filter.hip);
+//   k_reduce          accept flag and taxon counts per read (classify.hip).
+// The launches follow one another without the host.  Reads beyond the kernels'
+// limits (longer than 320 bases, or 256 in k_seed_wave; E above 31; more than
+// 256 seed hits; more than 8 candidates when every candidate is kept) are queued
+// and finished by the per-stage kernels, so every read gets the same result as
+// in per-stage mode; top_n above 8 runs per stage throughout.
+#include <algorithm>
 
 #include "classify.hpp"
+#include "lane.hpp"
 
 namespace mt {
 
 constexpr int F_WPB = 4;         // wavefronts per block
-constexpr int F_MAX_M = 256;     // longest read the fused kernel takes
+constexpr int F_MAX_M = 256;     // longest read of k_seed_wave
 constexpr int F_HIT_CAP = 256;   // seed hits per read (distinct locations fit the table)
 constexpr int F_TSLOTS = 256;    // per-read LDS hash table of locations
-constexpr int F_MAX_E = 31;      // 2E + 1 rows fit one wavefront
-constexpr int F_MAX_TOPN = 8;  // staged candidates per read (top_n = 0 keeps up to this many)
-constexpr int F_QCAP = 4;        // queued (read, candidate) pairs per wave: one per 16-lane group
-constexpr int F_PCAP = 8;        // reads per wave waiting for their filter results
+constexpr int F_MAX_E = 31;      // 2E + 1 rows fit two words of the filter
+constexpr int F_MAX_TOPN = 8;    // staged candidates per read (top_n = 0 keeps up to this many)
 constexpr int F_WORDS = F_MAX_M / 16 + 2;  // 2-bit stream words (16 bases per word) + padding
 
-enum : u32 { ST_READS, ST_BASES, ST_MINS, ST_WBLOCKS, ST_CANDS, ST_UNMAPPED, ST_OCC, ST_COUNT };
+// Fewest reads for k_seed_lane: 64 reads a wavefront fill the chip late, and a
+// lane's chain of k-mers and probes has a latency of its own of about 80 us.
+// 32k reads of 150 bases: 88 us in lanes, 63 with a wavefront each; 64k: 101
+// against 119.
+constexpr u64 LANE_MIN_READS = 48 * 1024;
 
-struct FusedArgs {
+enum : u32 { ST_READS, ST_BASES, ST_MINS, ST_WBLOCKS, ST_CANDS, ST_OCC, ST_COUNT };
+
+struct SeedArgs {
     const u8 *seq;
     const u64 *off;
-    u64 n;
+    u64 n, total;
     u32 k, w, min_hits, top_n, e_mode, e_value;
     u32 ncap;  // staging slots per read: top_n, or F_MAX_TOPN when top_n = 0 (keep all)
     const u64x2 *table;
     u64 nbuckets;
     const u64 *occ;
-    const GenomeMeta *meta;
-    const u64x2 *ref_lohi;
-    const u64 *ref_nb;
-    // staging: top_n slots per read
-    u32 *st_genome;
-    i64 *st_diag;
+    // staging: rank-major, slot (rank, read) at rank * n + read
+    u64 *st_key;
     u32 *st_hits;
-    u16 *st_approx;
-    u8 *st_accept;
     u32 *ncand;
-    u8 *read_accepted;
     u16 *read_E;
-    unsigned long long *uniq, *multi, *unmapped;
-    u32 *fb_list;
-    u32 *fb_count;
+    u8 *read_n;  // 1 if the read has an N
+    u32 *slow_list, *slow_count;  // reads for k_seed_wave
+    u32 *fb_list, *fb_count;      // reads for the per-stage kernels
     u32 *flags;
     const u32 *gate;  // offsets check result: nonzero skips the whole launch
     u64 *stats_part;  // ST_COUNT work counts per block
 };
-static_assert(std::is_standard_layout<FusedArgs>::value, "FusedArgs fields are read by offset");
 
-// A field of the launch's arguments read from the kernel-argument segment
-// where it is used rather than held in scalar registers throughout: the
-// fields used once per read or per pair would otherwise crowd out the
-// registers the loop needs, and spilled scalar registers cost a vector
-// instruction at every use.  FusedArgs is the kernel's only argument, so it
-// starts the segment.
-//
-// The segment's address exists only in the kernel itself: a function compiled
-// apart from the kernel reads it as zero (and then faults), so this helper and
-// every function that uses it are forced inline.
-template <class T>
-__device__ __attribute__((always_inline)) inline T karg_field(size_t off) {
-    const __attribute__((address_space(4))) char *base =
-        (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
-    return *(volatile const __attribute__((address_space(4))) T *)(base + off);
+// E of a read of m bases; ERR_E_TOO_LARGE in *flags when it passes the limit.
+__device__ inline int read_threshold(const SeedArgs &a, int m, u32 *flags) {
+    const u64 E = a.e_mode == MT_E_FIXED           ? a.e_value
+                  : a.e_mode == MT_E_CEIL_PERMILLE ? ((u64)m * a.e_value + 999) / 1000
+                                                   : ((u64)m * a.e_value) / 1000;
+    if (E > 65534) *flags |= ERR_E_TOO_LARGE;
+    return E > 65535 ? 65535 : (int)E;
 }
-#define KA(field) karg_field<decltype(FusedArgs::field)>(offsetof(FusedArgs, field))
-
-// A read whose candidates wait in the filter queue (per-wave LDS).
-struct PendRead {
-    u64 plane[12];   // lo[0..3], hi[0..3], nb[0..3] of the read
-    u64 r;
-    u32 nc, left;    // candidates, candidates not yet filtered
-    u16 E, m;
-    u16 apx[F_MAX_TOPN];
-    u32 tax[F_MAX_TOPN];
-};
-
-// One queued (read, candidate) pair.
-struct QEntry {
-    u64 key;   // (genome, diagonal)
-    u32 out;   // staging slot: read * top_n + candidate index
-    u32 hits;
-    u8 pend;   // PendRead slot
-    u8 cidx;   // candidate index within the read
-};
 
 __device__ inline void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -127,6 +88,183 @@ __device__ inline u64 readlane64(u64 v, int l) {
 // Number of set bits of m below this lane.
 __device__ inline u32 lanes_below(u64 m, int lane) {
     return (u32)__popcll(lane ? m & ((~0ull) >> (64 - lane)) : 0ull);
+}
+
+// Appends r to a list for the lanes with `add` set, one atomic per wavefront.
+__device__ inline void list_append(bool add, u64 r, int lane, u32 *list, u32 *count) {
+    const u64 m = ballot64(add);
+    if (!m) return;
+    const int leader = __builtin_ctzll(m);
+    u32 first = 0;
+    if (lane == leader) first = atomicAdd(count, (u32)__popcll(m));
+    first = __shfl(first, leader, 64);
+    if (add) list[first + lanes_below(m, lane)] = (u32)r;
+}
+
+__device__ inline u32 wave_sum(u32 v) {
+#pragma unroll
+    for (int o = 32; o; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// One lane per read.  MAXD: locations a lane's list holds; MAXM: longest read.  The list is searched
+// from its front for every hit; the first location, usually the only one, stays
+// in registers.
+// Bound by the random table lines of the probes: 1M reads of 150 bases on 500 Mbp
+// take 0.65 ms (20.8M probes, 32 G/s; the per-stage lookup, which does nothing
+// else, reaches 36 G/s), 10M on 4 Gbp of strains 13.4 ms with 52M occurrence
+// lists (208M probes, 16 G/s; the lookup alone reaches 19 G/s on that table of
+// 24 GB).  k_seed_wave takes 1.57 and 18.6 ms on the same reads.
+template <int W, int MAXD, int MAXM>
+__global__ __launch_bounds__(LN_TPB) void k_seed_lane(SeedArgs a) {
+    __shared__ LaneReads<MAXM> sh_reads[LN_TPB / 64];
+    __shared__ u64 sh_key[LN_TPB / 64][MAXD][64];
+    __shared__ u16 sh_cnt[LN_TPB / 64][MAXD][64];
+    __shared__ u32 sh_stats[ST_COUNT];
+    if (*a.gate) return;  // malformed offsets: nothing may be read through them
+    if (threadIdx.x < ST_COUNT) sh_stats[threadIdx.x] = 0;
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    LaneReads<MAXM> &L = sh_reads[wid];
+    u64 *keys = &sh_key[wid][0][lane];
+    u16 *cnts = &sh_cnt[wid][0][lane];
+    const u32 k = a.k, T = a.min_hits ? a.min_hits : 1u, N = a.ncap;
+    const u64 r = (u64)blockIdx.x * LN_TPB + threadIdx.x;
+    const bool in = r < a.n;
+    u64 beg = 0;
+    int m = 0, E = 0;
+    u32 wflags = 0;
+    bool fall = false, slow = false;
+    if (in) {
+        beg = a.off[r];
+        m = (int)(a.off[r + 1] - beg);
+        E = read_threshold(a, m, &wflags);
+        a.read_E[r] = (u16)E;
+        fall = m > LN_MAX_M || E > F_MAX_E;
+        slow = !fall && m > MAXM;
+    }
+    const bool take = in && !fall && !slow;
+    if (!take) m = 0;
+    const int max_m = wave_max(m);
+    const LaneRead rd = lane_decode(a.seq, beg, m, a.total, lane, max_m, L);
+    if (rd.bad) wflags |= ERR_BAD_BYTE;  // the call fails; its codes are in range all the same
+    const bool mixed = ballot64(rd.has_n || m != max_m) != 0;
+    const bool sure = mixed ? lane_minimizers<W, true>(L, lane, m, max_m, k)
+                            : lane_minimizers<W, false>(L, lane, m, max_m, k);
+    slow |= take && !sure;
+
+    // one probe per minimizer; every occurrence is a hit on its location
+    int H = 0, nd = 0, nmin = 0, nocc = 0;
+    bool many = false;
+    u64 key0 = ~0ull;
+    u32 cnt0 = 0;
+    auto hit = [&](u64 key) {
+        if (key == key0) {
+            cnt0++;
+            return;
+        }
+        if (nd == 0) {
+            key0 = key;
+            cnt0 = 1;
+            nd = 1;
+            return;
+        }
+        int e = 1;
+        while (e < nd && keys[e * 64] != key) e++;
+        if (e < nd) {
+            cnts[e * 64] += 1;
+        } else if (nd < MAXD) {
+            keys[e * 64] = key;
+            cnts[e * 64] = 1;
+            nd++;
+        } else {
+            many = true;
+        }
+    };
+    if (take && !slow) {
+        PickIter<MAXM> it(L, lane, max_m - (int)k + 1);
+        // the next minimizer's bucket is requested before this one's is looked at
+        Probe cur, nxt;
+        int pn = it.next(L, lane);
+        if (pn >= 0) nxt.request(a.table, a.nbuckets, lane_kmer(L, lane, pn, k));
+        while (pn >= 0) {
+            const int p = pn;
+            cur = nxt;
+            pn = it.next(L, lane);
+            if (pn >= 0) nxt.request(a.table, a.nbuckets, lane_kmer(L, lane, pn, k));
+            const u64 v = cur.find(a.table, a.nbuckets);
+            nmin++;
+            if (v == SLOT_NONE) continue;
+            const u32 c = slot_count(v);  // 0 for a k-mer above max_occ
+            H += (int)min(c, (u32)F_HIT_CAP + 1u);
+            if (H > F_HIT_CAP) {
+                fall = true;
+                break;
+            }
+            if (!(v & SLOT_MULTI)) {
+                hit(cand_key((u32)(v >> 32), (i64)(u32)v - p));
+            } else {  // four occurrences in flight at a time
+                const u64 st = slot_start(v);
+                nocc += (int)c;
+                for (u32 u0 = 0; u0 < c; u0 += 4) {
+                    u64 gp[4];
+#pragma unroll
+                    for (int t = 0; t < 4; t++) gp[t] = u0 + t < c ? a.occ[st + u0 + t] : 0ull;
+#pragma unroll
+                    for (int t = 0; t < 4; t++)
+                        if (u0 + t < c) hit(cand_key((u32)(gp[t] >> 32), (i64)(u32)gp[t] - p));
+                }
+            }
+            if (many) break;
+        }
+    }
+    if (many) slow = true;
+
+    // the locations with >= min_hits hits, each to its rank
+    int nc = 0;
+    if (take && !slow && !fall && nd) {
+        keys[0] = key0;
+        cnts[0] = (u16)cnt0;
+        u32 C = 0;
+        for (int e = 0; e < nd; e++) C += cnts[e * 64] >= T;
+        if (a.top_n == 0 && C > N) {
+            fall = true;  // keep-all with more candidates than staging slots
+        } else {
+            nc = (int)min(C, N);
+            for (int e = 0; e < nd; e++) {
+                const u32 he = cnts[e * 64];
+                if (he < T) continue;
+                const u64 ke = keys[e * 64];
+                u32 rank = 0;
+                for (int b = 0; b < nd; b++) {
+                    const u32 hb = cnts[b * 64];
+                    rank += hb > he || (hb == he && keys[b * 64] < ke);
+                }
+                if (rank < N) {
+                    a.st_key[(u64)rank * a.n + r] = ke;
+                    a.st_hits[(u64)rank * a.n + r] = he;
+                }
+            }
+        }
+    }
+    if (in) {
+        a.ncand[r] = (u32)nc;
+        a.read_n[r] = rd.has_n;
+    }
+    list_append(in && slow && !fall, r, lane, a.slow_list, a.slow_count);
+    list_append(in && fall, r, lane, a.fb_list, a.fb_count);
+    if (wflags) atomicOr(a.flags, wflags);
+    // work counts: one record per block, summed by k_fused_summary
+    const bool done = take && !slow && !fall;
+    const u32 st[ST_COUNT] = {done, done ? (u32)m : 0u, done ? (u32)nmin : 0u,
+                              (u32)nc * (u32)((m + 2 * E + 63) / 64), (u32)nc, done ? (u32)nocc : 0u};
+#pragma unroll
+    for (u32 i = 0; i < ST_COUNT; i++) {
+        const u32 t = wave_sum(st[i]);
+        if (lane == 0) atomicAdd(&sh_stats[i], t);
+    }
+    __syncthreads();
+    if (threadIdx.x < ST_COUNT) a.stats_part[(u64)blockIdx.x * ST_COUNT + threadIdx.x] = sh_stats[threadIdx.x];
 }
 
 // Slot of a location key in the per-read LDS table.
@@ -210,151 +348,6 @@ __device__ inline int window_argmin_any(const u64 *hh, int ws, int win) {
     }
 }
 
-// Filters the first qn queued pairs, one pair per group of G lanes (lane_g <
-// 2E+1 owns band row d = lane_g - E): the row's mismatch words over the read
-// come from the read planes (LDS) and 64-base reference fetches, then the
-// obstacle walk runs on registers.  Results go to the staging slot and to the
-// pair's pending read.
-// Obstacle-free run from column j of a row kept in LDS as four words (all
-// ones past them; the row's bits past the read's end are set, so the run
-// stops by the end).
-__device__ inline int lds_run(const u64 *row, int j) {
-    int w = j >> 6;
-    const u32 s = (u32)j & 63u;
-    int run = 0;
-    for (;;) {
-        const u64 lo = w < 4 ? row[w < 3 ? w : 3] : ~0ull;
-        const u64 hi = w + 1 < 4 ? row[w + 1 < 3 ? w + 1 : 3] : ~0ull;
-        const u64 v = funnel(lo, hi, s);
-        if (v) return run + (int)__builtin_ctzll(v);
-        run += 64;
-        w += 1;
-    }
-}
-
-template <int G>
-__device__ __attribute__((always_inline)) inline void filter_batch(const FusedArgs &a, const QEntry *q, int qn, PendRead *pend, int lane,
-                                    u64 *rowbuf) {
-    const int gi = lane / G, lane_g = lane % G;
-    if (gi >= qn) return;
-    const QEntry e = q[gi];
-    PendRead &pr = pend[e.pend];
-    const int E = pr.E, m = pr.m;
-    const u32 g = key_genome(e.key);
-    const i64 diag = key_diag(e.key);
-    const GenomeMeta gm = KA(meta)[g];
-    u64 row[4] = {~0ull, ~0ull, ~0ull, ~0ull};
-    if (lane_g < 2 * E + 1) {
-        // four 64-base fetches per row (building the row from the five blocks it
-        // spans, each fetched once, needs more live registers than this kernel
-        // has to spare: it spilled four times as many)
-        const i64 base = diag + (lane_g - E);
-        const u64x2 *rl = KA(ref_lohi) + gm.blk;
-        const u64 *rn = KA(ref_nb) + gm.blk;
-        const i64 L = (i64)gm.len;
-        const bool hn = meta_has_n(gm);
-        const Bits64 w0 = fetch_ref(rl, rn, L, hn, base);
-        const Bits64 w1 = fetch_ref(rl, rn, L, hn, base + 64);
-        const Bits64 w2 = fetch_ref(rl, rn, L, hn, base + 128);
-        const Bits64 w3 = fetch_ref(rl, rn, L, hn, base + 192);
-        row[0] = (pr.plane[0] ^ w0.lo) | (pr.plane[4] ^ w0.hi) | pr.plane[8] | w0.nb;
-        row[1] = (pr.plane[1] ^ w1.lo) | (pr.plane[5] ^ w1.hi) | pr.plane[9] | w1.nb;
-        row[2] = (pr.plane[2] ^ w2.lo) | (pr.plane[6] ^ w2.hi) | pr.plane[10] | w2.nb;
-        row[3] = (pr.plane[3] ^ w3.lo) | (pr.plane[7] ^ w3.hi) | pr.plane[11] | w3.nb;
-    }
-    // the row goes to this lane's four words of the per-read LDS table (empty
-    // while candidates are filtered: 64 lanes x 4 words fill its 256 slots)
-    // and is walked from there, which keeps registers free; the table is
-    // emptied again afterwards
-    u64 *myrow = rowbuf + 4 * lane;
-    myrow[0] = row[0];
-    myrow[1] = row[1];
-    myrow[2] = row[2];
-    myrow[3] = row[3];
-    int j = 0, c = 0;
-    for (;;) {
-        int run = group_max<G>(lds_run(myrow, j));
-        j += run;
-        if (j >= m) break;
-        c += 1;
-        if (c > E) break;
-        j += 1;
-    }
-    myrow[0] = myrow[1] = myrow[2] = myrow[3] = ~0ull;
-    const int ap = c < E + 1 ? c : E + 1;
-    if (lane_g == 0) {
-        KA(st_genome)[e.out] = g;
-        KA(st_diag)[e.out] = diag;
-        KA(st_hits)[e.out] = e.hits;
-        KA(st_approx)[e.out] = (u16)ap;
-        KA(st_accept)[e.out] = ap <= E;
-        pr.apx[e.cidx] = (u16)ap;
-        pr.tax[e.cidx] = meta_taxon(gm);
-    }
-}
-
-// Read accept flag and per-taxon counts of a read whose candidates are all
-// filtered: the distinct taxa of its accepted candidates with the smallest
-// count; one taxon is unique, several are multi-mapped.
-__device__ __attribute__((always_inline)) inline void finalize_read(const FusedArgs &a, const PendRead &pr, u64 *wst) {
-    const int nc = (int)pr.nc, E = pr.E;
-    int best = 0x7fffffff;
-    for (int c = 0; c < nc; c++)
-        if (pr.apx[c] <= E && pr.apx[c] < best) best = pr.apx[c];
-    if (best == 0x7fffffff) {
-        KA(read_accepted)[pr.r] = 0;
-        atomicAdd(&wst[ST_UNMAPPED], 1ull);  // the block adds its count once at the end
-        return;
-    }
-    KA(read_accepted)[pr.r] = 1;
-    int nt = 0;
-    u32 first = 0;
-    for (int c = 0; c < nc; c++) {
-        if (pr.apx[c] != best) continue;
-        bool seen = false;
-        for (int b = 0; b < c; b++) seen |= pr.apx[b] == best && pr.tax[b] == pr.tax[c];
-        if (seen) continue;
-        if (nt == 0) first = pr.tax[c];
-        nt++;
-    }
-    if (nt == 1) {
-        atomicAdd(&KA(uniq)[first], 1ull);
-        return;
-    }
-    for (int c = 0; c < nc; c++) {
-        if (pr.apx[c] != best) continue;
-        bool seen = false;
-        for (int b = 0; b < c; b++) seen |= pr.apx[b] == best && pr.tax[b] == pr.tax[c];
-        if (!seen) atomicAdd(&KA(multi)[pr.tax[c]], 1ull);
-    }
-}
-
-// Runs the queued filter batch (group size by the queue's class), then
-// finalizes every pending read whose last candidate it filtered.  Returns the
-// new set of used pending slots.
-template <int MAXG>
-__device__ __attribute__((always_inline)) inline u32 flush_queue(const FusedArgs &a, QEntry *q, int &qn, int qG, PendRead *pend, u32 used,
-                                  int lane, u64 *wst, u64 *rowbuf) {
-    if (qn > 0) {
-        if (MAXG == 16 || qG == 16)
-            filter_batch<16>(a, q, qn, pend, lane, rowbuf);
-        else if (MAXG == 32 || qG == 32)
-            filter_batch<32>(a, q, qn, pend, lane, rowbuf);
-        else
-            filter_batch<64>(a, q, qn, pend, lane, rowbuf);
-        wave_sync();
-        if (lane == 0)
-            for (int i = 0; i < qn; i++) pend[q[i].pend].left -= 1;
-        wave_sync();
-        qn = 0;
-    }
-    bool done = lane < F_PCAP && ((used >> lane) & 1u) && pend[lane].left == 0;
-    if (done) finalize_read(a, pend[lane], wst);
-    u32 fin = (u32)ballot64(done);
-    wave_sync();
-    return used & ~fin;
-}
-
 // The bytes of one read, one per lane for each 64-base round (reads longer
 // than the kernel takes are not loaded).
 struct ReadBytes {
@@ -363,7 +356,7 @@ struct ReadBytes {
     u32 b[4];
 };
 
-__device__ inline void issue_read_bytes(const FusedArgs &a, u64 r, int lane, ReadBytes &rb) {
+__device__ inline void issue_read_bytes(const SeedArgs &a, u64 r, int lane, ReadBytes &rb) {
     rb.beg = a.off[r];
     rb.m = (int)(a.off[r + 1] - rb.beg);
 #pragma unroll
@@ -373,27 +366,45 @@ __device__ inline void issue_read_bytes(const FusedArgs &a, u64 r, int lane, Rea
     }
 }
 
-// Five wavefronts per SIMD (96 registers, a few spilled; the LDS of 4-wave
-// blocks also allows five): the kernel waits on memory as much as it issues.
-//
-// MAXG: the widest filter group the launch needs (16 when every read's E is at
-// most 7, 32 when at most 15, 64 in general); narrower instances hold fewer
-// copies of the filter, which leaves the register allocator more room.
-// REP: the index is repetitive (many k-mers occur in several genomes, as in a
-// database of near-identical strains), so reads whose probes find several
-// occurrences are also counted in registers; without it those reads use the
-// per-read LDS table, and the instance spends no registers on that path.
-template <int MAXG, bool REP>
-__global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_fused(FusedArgs a) {
+static void launch_seed_lane(const SeedArgs &a, bool rep, unsigned blocks, hipStream_t s) {
+    const bool ok = with_window(a.w, [&](auto w) {
+        constexpr int W = decltype(w)::value;
+        // Reads that are short on average take the instance whose LDS holds half
+        // as many wavefronts again (1M reads of 150 bases: 0.67 against 0.75 ms); its
+        // longer reads go to k_seed_wave.
+        const bool brief = a.total / a.n <= 160;
+        if (rep) {
+            if (brief) k_seed_lane<W, 12, LN_SHORT_M><<<blocks, LN_TPB, 0, s>>>(a);
+            else k_seed_lane<W, 12, LN_MAX_M><<<blocks, LN_TPB, 0, s>>>(a);
+        } else {
+            if (brief) k_seed_lane<W, 6, LN_SHORT_M><<<blocks, LN_TPB, 0, s>>>(a);
+            else k_seed_lane<W, 6, LN_MAX_M><<<blocks, LN_TPB, 0, s>>>(a);
+        }
+    });
+    if (!ok) throw Error(MT_EINTERNAL, "no lane kernel for this minimizer window");
+    MT_HIP(hipGetLastError());
+}
+
+// One wavefront per read: reads list[0, *list_n), or all of them when list is null.
+//   1. the read's bytes, one per lane and requested while the previous read was
+//      counted, become an N plane (ballots) and a big-endian 2-bit stream in LDS;
+//   2. lane i hashes the k-mer at position i (per 64-position round);
+//   3. lane s scans window s for its smallest valid (hash, position); picks are
+//      marked in LDS and compacted with ballot + popcount;
+//   4. each minimizer lane probes one table bucket; a read's hits are counted in
+//      registers, one ballot per distinct location, when they fit one lane each,
+//      and in a per-read LDS hash table otherwise;
+//   5. the locations with >= min_hits hits are ranked and staged.
+// blk0: first record of stats_part.
+__global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_seed_wave(
+    SeedArgs a, const u32 *__restrict__ list, const u32 *__restrict__ list_n, u32 blk0) {
     __shared__ u64 sh_h[F_WPB][F_MAX_M];     // k-mer hashes (~0 when invalid); later candidate keys
     __shared__ u64 sh_tkey[F_WPB][F_TSLOTS]; // per-read hash table of (genome, diagonal) keys
     __shared__ u32 sh_tcnt[F_WPB][F_TSLOTS]; // ... and their seed-hit counts
     __shared__ u16 sh_pos[F_WPB][F_MAX_M];   // minimizer positions; later candidate hit counts
     __shared__ u8 sh_pick[F_WPB][F_MAX_M];   // window picks
     __shared__ u32 sh_st[F_WPB][F_WORDS];    // big-endian 2-bit stream of the read
-    __shared__ u32 sh_sel[F_WPB][F_MAX_TOPN];
-    __shared__ QEntry sh_q[F_WPB][F_QCAP];
-    __shared__ PendRead sh_pend[F_WPB][F_PCAP];
+    __shared__ u64 sh_nb[F_WPB][4];          // N plane (1 past the end)
     __shared__ u64 sh_stats[F_WPB][ST_COUNT];
     __shared__ u8 sh_tlist[F_WPB][F_TSLOTS];  // slots of the per-read table in use
     __shared__ u32 sh_tn[F_WPB];             // ... and their number
@@ -409,13 +420,11 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
     u16 *mpos = sh_pos[wid];
     u8 *pick = sh_pick[wid];
     u32 *stream = sh_st[wid];
-    u32 *sel = sh_sel[wid];
-    QEntry *queue = sh_q[wid];
-    PendRead *pend = sh_pend[wid];
+    u64 *nbp = sh_nb[wid];
     u64 *wst = sh_stats[wid];
     u8 *tlist = sh_tlist[wid];
     u32 *tn = &sh_tn[wid];
-    if (lane < ST_COUNT) wst[lane] = 0;
+    if (lane < (int)ST_COUNT) wst[lane] = 0;
     if (lane == 0) *tn = 0;
     // the table starts empty and every read leaves it empty
     for (int t = lane; t < F_TSLOTS; t += 64) {
@@ -427,66 +436,62 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
     const u64 kmask = (1ull << k) - 1;
     const u64 stride = (u64)gridDim.x * F_WPB;
     u32 wflags = 0;
-    int qn = 0, qG = 16;  // queued pairs and their group size
-    u32 used = 0;         // pending-read slots in use
-
-    u64 r = (u64)blockIdx.x * F_WPB + wid;
+    const u64 n = list ? *list_n : a.n;
+    u64 i = (u64)blockIdx.x * F_WPB + wid;
+    u64 r = 0;
     ReadBytes cur;
-    if (r < a.n) issue_read_bytes(a, r, lane, cur);
-    for (; r < a.n; r += stride) {
-        const u64 rn = r + stride;
+    if (i < n) {
+        r = list ? list[i] : i;
+        issue_read_bytes(a, r, lane, cur);
+    }
+    for (u64 rn = 0; i < n; i += stride, r = rn) {
+        const bool more = i + stride < n;
+        rn = !more ? 0 : list ? list[i + stride] : i + stride;  // the next read
         const int m = cur.m;
-        u64 Ewide = KA(e_mode) == MT_E_FIXED ? KA(e_value)
-                    : KA(e_mode) == MT_E_CEIL_PERMILLE ? ((u64)m * KA(e_value) + 999) / 1000
-                                                     : ((u64)m * KA(e_value)) / 1000;
-        if (Ewide > 65534) wflags |= ERR_E_TOO_LARGE;
-        const int E = Ewide > 65535 ? 65535 : (int)Ewide;
-        if (lane == 0) KA(read_E)[r] = (u16)E;
-        if (m > F_MAX_M || E > F_MAX_E) {  // (2E + 1 <= MAXG here: the launch picks MAXG from the largest E)
+        const int E = read_threshold(a, m, &wflags);
+        if (lane == 0) a.read_E[r] = (u16)E;
+        if (m > F_MAX_M || E > F_MAX_E) {
             if (lane == 0) {
-                KA(fb_list)[atomicAdd(KA(fb_count), 1u)] = (u32)r;
-                KA(ncand)[r] = 0;  // until the per-stage kernels fill it in
+                a.fb_list[atomicAdd(a.fb_count, 1u)] = (u32)r;
+                a.ncand[r] = 0;  // until the per-stage kernels fill it in
+                a.read_n[r] = 0;
             }
-            if (rn < a.n) issue_read_bytes(a, rn, lane, cur);
+            if (more) issue_read_bytes(a, rn, lane, cur);
             continue;
         }
 
-        // 1. bit planes of the read (bases past m are N), written straight into
-        // a free pending-read slot, and the read's big-endian 2-bit stream
-        const int slot = __builtin_ctz(~used);
-        PendRead &pr = pend[slot];
+        // 1. N plane of the read (bases past m are N) and its big-endian 2-bit stream
         if (lane < F_WORDS) stream[lane] = 0;
-        bool bad = false;
+        bool bad = false, has_n = false;
         // the next read's offsets, its start in even lanes and its end in odd
         // ones: requested before the planes are built and read after them, so
         // the planes hide the load (a wave-uniform load would be waited for at
         // once, to move it to scalar registers)
         u64 noff = 0;
-        if (rn < a.n) noff = a.off[rn + (u64)(lane & 1)];
+        if (more) noff = a.off[rn + (u64)(lane & 1)];
         wave_sync();
 #pragma unroll
         for (int q = 0; q < 4; q++) {
             int i = 64 * q + lane;
             u32 c = i < m ? base_code(cur.b[q]) : 4u;
             bad |= c == 5;
-            u64 lo = ballot64(c < 4 && (c & 1u));
-            u64 hi = ballot64(c < 4 && (c & 2u));
-            u64 nb = ballot64(c >= 4);
-            if (lane == 0) {
-                pr.plane[q] = lo;
-                pr.plane[4 + q] = hi;
-                pr.plane[8 + q] = nb;
-            }
+            const u64 nb = ballot64(c >= 4);
+            if (lane == 0) nbp[q] = nb;
+            has_n |= i < m && c == 4;
             if (c < 4 && c > 0) atomicOr(&stream[i >> 4], c << (30 - 2 * (i & 15)));
         }
         // (the next read's bytes are requested after the probes)
         const u64 nbeg = readlane64(noff, 0), nend = readlane64(noff, 1);
         if (ballot64(bad)) {
             wflags |= ERR_BAD_BYTE;
-            if (lane == 0) KA(ncand)[r] = 0;  // the call fails; its compaction still runs
-            if (rn < a.n) issue_read_bytes(a, rn, lane, cur);
+            if (lane == 0) {  // the call fails; its compaction still runs
+                a.ncand[r] = 0;
+                a.read_n[r] = 0;
+            }
+            if (more) issue_read_bytes(a, rn, lane, cur);
             continue;
         }
+        has_n = ballot64(has_n) != 0;
         wave_sync();
 
         // 2. k-mer hashes (~0 for k-mers with an N)
@@ -495,7 +500,7 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
         for (int q = 0; q < 4; q++) {
             int i = 64 * q + lane;
             if (i < nk) {
-                u64 nb = funnel(pr.plane[8 + q], q < 3 ? pr.plane[9 + q] : ~0ull, (u32)lane);
+                u64 nb = funnel(nbp[q], q < 3 ? nbp[q + 1] : ~0ull, (u32)lane);
                 hh[i] = (nb & kmask) == 0 ? mix64(stream_kmer(stream, i, k)) : ~0ull;
             }
             pick[i] = 0;
@@ -559,7 +564,7 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
                 hm = sm;
                 H = __popcll(sm);
                 inreg = true;
-            } else if (REP && t0 == 0 && nmin <= 64 && ballot64(cnt > 15u) == 0) {
+            } else if (t0 == 0 && nmin <= 64 && ballot64(cnt > 15u) == 0) {
                 // exclusive prefix sum of cnt over the lanes, bit by bit
                 u32 off = 0, tot = 0;
 #pragma unroll
@@ -584,7 +589,7 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
                         tkey[lane] = ~0ull;
                         tcnt[lane] = 0;
                     }
-                    if (f & 0x10000u) gv = KA(occ)[gv];
+                    if (f & 0x10000u) gv = a.occ[gv];
                     key = has ? cand_key((u32)(gv >> 32), (i64)(u32)gv - (i64)(f & 0xffffu)) : 0ull;
                     hm = ballot64(has);
                     H = (int)tot;
@@ -593,7 +598,7 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
                 }
             }
             if (inreg) {
-                const bool mine = REP ? (bool)((hm >> lane) & 1u) : single;
+                const bool mine = (hm >> lane) & 1u;
                 for (u64 rem = hm; rem;) {
                     const int ld = __builtin_amdgcn_readfirstlane(__builtin_ctzll(rem));
                     const u64 kl = readlane64(key, ld);
@@ -627,7 +632,7 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
                     for (u32 u0 = 0; u0 < cnt; u0 += 4) {
                         u64 gp[4];
 #pragma unroll
-                        for (int t = 0; t < 4; t++) gp[t] = u0 + t < cnt ? KA(occ)[st + u0 + t] : 0ull;
+                        for (int t = 0; t < 4; t++) gp[t] = u0 + t < cnt ? a.occ[st + u0 + t] : 0ull;
 #pragma unroll
                         for (int t = 0; t < 4; t++)
                             if (u0 + t < cnt) table_add(tkey, tcnt, tlist, tn, cand_key((u32)(gp[t] >> 32), (i64)(u32)gp[t] - p));
@@ -638,7 +643,7 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
         }
         // the next read's bytes arrive while this one is counted and filtered
         ReadBytes nxt;
-        if (rn < a.n) {
+        if (more) {
             nxt.beg = nbeg;
             nxt.m = (int)(nend - nbeg);
 #pragma unroll
@@ -655,8 +660,9 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
             }
             if (lane == 0) {
                 *tn = 0;
-                KA(fb_list)[atomicAdd(KA(fb_count), 1u)] = (u32)r;
-                KA(ncand)[r] = 0;
+                a.fb_list[atomicAdd(a.fb_count, 1u)] = (u32)r;
+                a.ncand[r] = 0;
+                a.read_n[r] = has_n;
             }
             cur = nxt;
             wave_sync();
@@ -691,8 +697,9 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
         if (a.top_n == 0 && C > (int)N) {
             // keep-all with more candidates than staging slots: per-stage finish
             if (lane == 0) {
-                KA(fb_list)[atomicAdd(KA(fb_count), 1u)] = (u32)r;
-                KA(ncand)[r] = 0;
+                a.fb_list[atomicAdd(a.fb_count, 1u)] = (u32)r;
+                a.ncand[r] = 0;
+                a.read_n[r] = has_n;
             }
             cur = nxt;
             wave_sync();
@@ -710,48 +717,15 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
                     u32 hb = ccnt[b];
                     rank += hb > hc || (hb == hc && hh[b] < kc);
                 }
-                if (rank < nc) sel[rank] = (u32)cidx;
+                if (rank < nc) {
+                    a.st_key[(u64)rank * a.n + r] = kc;
+                    a.st_hits[(u64)rank * a.n + r] = hc;
+                }
             }
         }
-        wave_sync();
-
-        // 6. queue the kept candidates for batched filtering
-        if (lane == 0) KA(ncand)[r] = (u32)nc;
-        if (nc == 0) {
-            if (lane == 0) {
-                KA(read_accepted)[r] = 0;
-                atomicAdd(&wst[ST_UNMAPPED], 1ull);
-            }
-        } else {
-            const int rows = 2 * E + 1;
-            const int G = (MAXG == 16 || rows <= 16) ? 16 : (MAXG == 32 || rows <= 32) ? 32 : 64;
-            used |= 1u << slot;
-            if (lane == 0) {
-                pr.r = r;
-                pr.nc = (u32)nc;
-                pr.left = (u32)nc;
-                pr.E = (u16)E;
-                pr.m = (u16)m;
-            }
-            wave_sync();
-            // one flush site: the queue is flushed when it is full or holds
-            // pairs of another group size; the candidates that fit are queued
-            // together, one lane each
-            for (int c0 = 0; c0 < nc;) {
-                if (qn > 0 && (qn == 64 / qG || qG != G))
-                    used = flush_queue<MAXG>(a, queue, qn, qG, pend, used, lane, wst, tkey);
-                qG = G;
-                const int room = 64 / G - qn;
-                const int take = nc - c0 < room ? nc - c0 : room;
-                if (lane < take) {
-                    const int c = c0 + lane;
-                    const u32 si = sel[c];
-                    queue[qn + lane] = QEntry{hh[si], (u32)(r * N + (u64)c), ccnt[si], (u8)slot, (u8)c};
-                }
-                qn += take;
-                c0 += take;
-                wave_sync();
-            }
+        if (lane == 0) {
+            a.ncand[r] = (u32)nc;
+            a.read_n[r] = has_n;
         }
         if (lane == 0) {  // work counts, kept in LDS to spare registers
             wst[ST_READS] += 1;
@@ -764,25 +738,19 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
         cur = nxt;
         wave_sync();
     }
-    used = flush_queue<MAXG>(a, queue, qn, qG, pend, used, lane, wst, tkey);
-    if (lane == 0) {
-        if (used) wflags |= ERR_INTERNAL;  // every queued read is finalized by now
-        if (wflags) atomicOr(KA(flags), wflags);
-    }
+    if (lane == 0 && wflags) atomicOr(a.flags, wflags);
     // work counts: one record per block, summed by k_fused_summary
     __syncthreads();
     if (threadIdx.x < ST_COUNT) {
         u64 t = 0;
         for (int w = 0; w < F_WPB; w++) t += sh_stats[w][threadIdx.x];
-        KA(stats_part)[(u64)blockIdx.x * ST_COUNT + threadIdx.x] = t;
-        // unmapped reads: one global atomic per block instead of one per read
-        if (threadIdx.x == ST_UNMAPPED && t) atomicAdd(KA(unmapped), (unsigned long long)t);
+        a.stats_part[(u64)(blk0 + blockIdx.x) * ST_COUNT + threadIdx.x] = t;
     }
 }
 
 // Control words of one fused call: [0] offsets check, [1] run flags,
-// [2] fallback count.
-constexpr int CTL_GATE = 0, CTL_FLAGS = 1, CTL_FB = 2, CTL_WORDS = 4;
+// [2] reads for the per-stage kernels, [3] reads for k_seed_wave.
+constexpr int CTL_GATE = 0, CTL_FLAGS = 1, CTL_FB = 2, CTL_SLOW = 3, CTL_WORDS = 4;
 
 // Host-visible summary of one fused call, read back with a single copy.
 struct FusedSummary {
@@ -791,8 +759,11 @@ struct FusedSummary {
     u64 stats[ST_COUNT];
 };
 
-__global__ void k_fused_init(u32 *__restrict__ ctl) {
-    if (threadIdx.x < CTL_WORDS) ctl[threadIdx.x] = 0;
+// Clears the control words and n counters.
+__global__ void k_fused_init(u32 *__restrict__ ctl, u64 *__restrict__ counters, u64 n) {
+    const u64 t = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < CTL_WORDS) ctl[t] = 0;
+    for (u64 i = t; i < n; i += (u64)gridDim.x * blockDim.x) counters[i] = 0;
 }
 
 // Block s < ST_COUNT sums work count s over the kernel's blocks; block 0
@@ -824,15 +795,48 @@ __global__ __launch_bounds__(SUM_TPB) void k_fused_summary(const u32 *__restrict
     }
 }
 
-// Offsets check for the fused path (it reads the ASCII bytes directly).
+// Offsets check for the fused path (it reads the ASCII bytes directly): the
+// error flags of read r.
+__device__ inline u32 check_read(const u64 *__restrict__ off, u64 r, u64 n, u64 total) {
+    const u64 a = off[r], b = off[r + 1];
+    if (b < a || b > total || (r == 0 && a != 0) || (r == n - 1 && b != total)) return ERR_OFFSETS;
+    return b - a > 65535 ? (u32)ERR_READ_TOO_LONG : 0u;
+}
+
 __global__ void k_check_reads(const u64 *__restrict__ off, u64 n, u64 total, u32 *__restrict__ flags) {
-    u64 s = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    u64 a = off[s], b = off[s + 1];
-    u32 f = 0;
-    if (b < a || b > total || (s == 0 && a != 0) || (s == n - 1 && b != total)) f |= ERR_OFFSETS;
-    else if (b - a > 65535) f |= ERR_READ_TOO_LONG;
+    const u64 r = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= n) return;
+    const u32 f = check_read(off, r, n, total);
     if (f) atomicOr(flags, f);
+}
+
+// k_fused_init and k_check_reads in one launch, by one block: for small read sets,
+// where a launch costs more than the block's few rounds.
+constexpr int BEGIN_TPB = 1024;
+constexpr u64 BEGIN_MAX = 16 * BEGIN_TPB;  // reads and counters
+__global__ __launch_bounds__(BEGIN_TPB) void k_fused_begin(const u64 *__restrict__ off, u64 n, u64 total,
+                                                           u32 *__restrict__ ctl, u64 *__restrict__ counters,
+                                                           u64 n_counters) {
+    __shared__ u32 gate;
+    if (threadIdx.x == 0) gate = 0;
+    __syncthreads();
+    u32 f = 0;
+    for (u64 r = threadIdx.x; r < n; r += BEGIN_TPB) f |= check_read(off, r, n, total);
+    for (u64 i = threadIdx.x; i < n_counters; i += BEGIN_TPB) counters[i] = 0;
+    if (f) atomicOr(&gate, f);
+    __syncthreads();
+    if (threadIdx.x < CTL_WORDS) ctl[threadIdx.x] = threadIdx.x == CTL_GATE ? gate : 0;
+}
+
+static void enqueue_begin(const u64 *off, u64 n, u64 total, u32 *ctl, u64 *counters, u64 n_counters, hipStream_t s) {
+    if (n <= BEGIN_MAX && n_counters <= BEGIN_MAX) {
+        k_fused_begin<<<1, BEGIN_TPB, 0, s>>>(off, n, total, ctl, counters, n_counters);
+    } else {
+        const unsigned blocks = (unsigned)std::min<u64>(grid_for(n_counters, 1024), 1024);
+        k_fused_init<<<blocks, 1024, 0, s>>>(ctl, counters, n_counters);
+        k_check_reads<<<grid_for(n, 256), 256, 0, s>>>(off, n, total, ctl + CTL_GATE);
+    }
+    MT_HIP(hipGetLastError());
 }
 
 // Subset of reads (the fallback list) gathered into a contiguous batch.
@@ -850,41 +854,45 @@ __global__ void k_subset_copy(const u8 *__restrict__ seq, const u64 *__restrict_
     for (u64 t = threadIdx.x; t < len; t += blockDim.x) sub_seq[dst + t] = seq[src + t];
 }
 
-__global__ void k_subset_scatter(const u32 *__restrict__ list, u64 n, u32 stride, const u64 *__restrict__ sub_off,
-                                 const u8 *__restrict__ sub_acc, const u32 *__restrict__ sg,
-                                 const i64 *__restrict__ sd, const u32 *__restrict__ sh,
-                                 const u16 *__restrict__ sa, const u8 *__restrict__ sc, u32 *__restrict__ ncand,
-                                 u8 *__restrict__ read_accepted, u32 *__restrict__ st_genome,
-                                 i64 *__restrict__ st_diag, u32 *__restrict__ st_hits, u16 *__restrict__ st_approx,
-                                 u8 *__restrict__ st_accept) {
-    u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+// Counts and accept flags of the per-stage finished reads.
+__global__ void k_subset_counts(const u32 *__restrict__ list, u64 n, const u64 *__restrict__ sub_off,
+                                const u8 *__restrict__ sub_acc, u32 *__restrict__ ncand,
+                                u8 *__restrict__ read_accepted) {
+    const u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    u64 r = list[i];
-    u64 b = sub_off[i], e = sub_off[i + 1];
-    ncand[r] = (u32)(e - b);
-    read_accepted[r] = sub_acc[i];
-    for (u64 c = b; c < e && c - b < stride; c++) {  // the rest (keep-all) is placed by k_subset_place
-        u64 o = r * stride + (c - b);
-        st_genome[o] = sg[c];
-        st_diag[o] = sd[c];
-        st_hits[o] = sh[c];
-        st_approx[o] = sa[c];
-        st_accept[o] = sc[c];
+    ncand[list[i]] = (u32)(sub_off[i + 1] - sub_off[i]);
+    read_accepted[list[i]] = sub_acc[i];
+}
+
+// Filtered candidates of the fused reads from their places without the
+// per-stage finished reads (which had none) to those with them.
+__global__ void k_move_cands(const u64 *__restrict__ from, const u64 *__restrict__ to, u64 n,
+                             const u32 *__restrict__ sg, const i64 *__restrict__ sd, const u32 *__restrict__ sh,
+                             const u16 *__restrict__ sa, const u8 *__restrict__ sc, u32 *__restrict__ genome,
+                             i64 *__restrict__ diag, u32 *__restrict__ hits, u16 *__restrict__ approx,
+                             u8 *__restrict__ accept) {
+    const u64 r = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= n) return;
+    const u64 o = to[r];
+    for (u64 c = from[r], e = from[r + 1], d = o; c < e; c++, d++) {
+        genome[d] = sg[c];
+        diag[d] = sd[c];
+        hits[d] = sh[c];
+        approx[d] = sa[c];
+        accept[d] = sc[c];
     }
 }
 
-// Candidates of the per-stage finished reads straight into the final arrays
-// (keep-all reads may have more candidates than staging slots).
+// Candidates of the per-stage finished reads.
 __global__ void k_subset_place(const u32 *__restrict__ list, u64 n, const u64 *__restrict__ sub_off,
                                const u32 *__restrict__ sg, const i64 *__restrict__ sd, const u32 *__restrict__ sh,
                                const u16 *__restrict__ sa, const u8 *__restrict__ sc,
-                               const u64 *__restrict__ cand_off, u64 cap, u32 *__restrict__ genome,
+                               const u64 *__restrict__ cand_off, u32 *__restrict__ genome,
                                i64 *__restrict__ diag, u32 *__restrict__ hits, u16 *__restrict__ approx,
                                u8 *__restrict__ accept) {
     u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const u64 r = list[i], b = sub_off[i], e = sub_off[i + 1], o = cand_off[r];
-    if (o + (e - b) > cap) return;  // never past the candidate capacity
+    const u64 b = sub_off[i], e = sub_off[i + 1], o = cand_off[list[i]];
     for (u64 c = b; c < e; c++) {
         genome[o + c - b] = sg[c];
         diag[o + c - b] = sd[c];
@@ -894,29 +902,28 @@ __global__ void k_subset_place(const u32 *__restrict__ list, u64 n, const u64 *_
     }
 }
 
-__global__ void k_add_u64(unsigned long long *__restrict__ dst, const u64 *__restrict__ src, u64 n) {
+__global__ void k_add_u64(unsigned long long *__restrict__ dst, const u64 *__restrict__ src, u64 n, u64 less) {
     u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] += src[i];
+    if (i < n) dst[i] += src[i] - less;
 }
 
-__global__ void k_compact_staged(const u32 *__restrict__ gate, const u64 *__restrict__ cand_off, u64 n, u32 top_n,
-                                 u64 cap,
-                                 const u32 *__restrict__ st_genome, const i64 *__restrict__ st_diag,
-                                 const u32 *__restrict__ st_hits, const u16 *__restrict__ st_approx,
-                                 const u8 *__restrict__ st_accept, u32 *__restrict__ genome, i64 *__restrict__ diag,
-                                 u32 *__restrict__ hits, u16 *__restrict__ approx, u8 *__restrict__ accept) {
-    u64 r = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+// Staged candidates to their places (cap: room in the result's arrays).
+__global__ void k_compact_seeds(const u32 *__restrict__ gate, const u64 *__restrict__ cand_off, u64 n, u32 N, u64 cap,
+                                const u64 *__restrict__ st_key, const u32 *__restrict__ st_hits,
+                                u32 *__restrict__ genome, i64 *__restrict__ diag, u32 *__restrict__ hits,
+                                u32 *__restrict__ pair_read) {
+    const u64 r = (u64)blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= n || *gate) return;
-    u64 o = cand_off[r], c = cand_off[r + 1] - o;
-    if (c > top_n) c = top_n;
+    const u64 o = cand_off[r];
+    u64 c = cand_off[r + 1] - o;
+    if (c > N) c = N;
     if (o > cap || c > cap - o) return;  // never past the candidate capacity
     for (u64 i = 0; i < c; i++) {
-        u64 s = r * top_n + i;
-        genome[o + i] = st_genome[s];
-        diag[o + i] = st_diag[s];
-        hits[o + i] = st_hits[s];
-        approx[o + i] = st_approx[s];
-        accept[o + i] = st_accept[s];
+        const u64 key = st_key[i * n + r];
+        genome[o + i] = key_genome(key);
+        diag[o + i] = key_diag(key);
+        hits[o + i] = st_hits[i * n + r];
+        pair_read[o + i] = (u32)r;
     }
 }
 
@@ -924,55 +931,65 @@ __global__ void k_compact_staged(const u32 *__restrict__ gate, const u64 *__rest
 // synchronization and no memset, so the sequence can also be captured and
 // replayed as one HIP graph.
 struct FusedLaunch {
-    FusedArgs a;
+    SeedArgs a;
+    const mt_index *ix;
     u32 *ctl;
-    u64 n;
-    u32 N;
-    unsigned blocks;
-    u64 total;
+    u32 *pair_read;
+    unsigned lane_blocks, wave_blocks;  // lane_blocks 0: every read in k_seed_wave
     mt_result *res;
     FusedSummary *sum;
-    bool rep;  // repetitive index: the kernel instance with register counting of repeated k-mers
+    bool rep;  // repetitive index: room for more locations per read in the lane kernel
 };
 
 static void enqueue_fused(const FusedLaunch &L, Timer *tm, hipStream_t s) {
-    const FusedArgs &a = L.a;
-    k_fused_init<<<1, 64, 0, s>>>(L.ctl);
-    k_check_reads<<<grid_for(L.n, 256), 256, 0, s>>>(a.off, L.n, L.total, L.ctl + CTL_GATE);
+    const SeedArgs &a = L.a;
+    mt_result &res = *L.res;
+    enqueue_begin(a.off, a.n, a.total, L.ctl, res.uniq.p, res.n_counters(), s);
     if (tm) tm->mark("check");
-    // the widest filter group any read can need: E is fixed, or grows with the
-    // length, which is at most F_MAX_M in the kernel (longer reads take the
-    // per-stage path), so every fused read's 2E + 1 rows fit the instance's
-    // widest group
-    u64 maxE = a.e_mode == MT_E_FIXED           ? a.e_value
-               : a.e_mode == MT_E_CEIL_PERMILLE ? ((u64)F_MAX_M * a.e_value + 999) / 1000
-                                                : ((u64)F_MAX_M * a.e_value) / 1000;
-    if (maxE > (u64)F_MAX_E) maxE = F_MAX_E;
-    if (L.rep) {
-        if (maxE <= 7)
-            k_fused<16, true><<<L.blocks, 64 * F_WPB, 0, s>>>(a);
-        else if (maxE <= 15)
-            k_fused<32, true><<<L.blocks, 64 * F_WPB, 0, s>>>(a);
-        else
-            k_fused<64, true><<<L.blocks, 64 * F_WPB, 0, s>>>(a);
+    if (L.lane_blocks) {
+        launch_seed_lane(a, L.rep, L.lane_blocks, s);
+        k_seed_wave<<<L.wave_blocks, 64 * F_WPB, 0, s>>>(a, a.slow_list, a.slow_count, L.lane_blocks);
     } else {
-        if (maxE <= 7)
-            k_fused<16, false><<<L.blocks, 64 * F_WPB, 0, s>>>(a);
-        else if (maxE <= 15)
-            k_fused<32, false><<<L.blocks, 64 * F_WPB, 0, s>>>(a);
-        else
-            k_fused<64, false><<<L.blocks, 64 * F_WPB, 0, s>>>(a);
+        k_seed_wave<<<L.wave_blocks, 64 * F_WPB, 0, s>>>(a, nullptr, nullptr, 0);
     }
+    MT_HIP(hipGetLastError());
     if (tm) tm->mark("fused");
-    scan_u32(a.ncand, L.res->cand_off.p, L.n, s);
-    k_compact_staged<<<grid_for(L.n, 256), 256, 0, s>>>(L.ctl + CTL_GATE, L.res->cand_off.p, L.n, L.N, L.res->cap,
-                                                        a.st_genome,
-                                                        a.st_diag, a.st_hits, a.st_approx, a.st_accept,
-                                                        L.res->genome.p, L.res->diag.p, L.res->hits.p,
-                                                        L.res->approx.p, L.res->accept.p);
-    k_fused_summary<<<ST_COUNT, SUM_TPB, 0, s>>>(L.ctl, L.res->cand_off.p + L.n, a.stats_part, L.blocks, L.sum);
+    scan_u32(a.ncand, res.cand_off.p, a.n, s);
+    k_compact_seeds<<<grid_for(a.n, 256), 256, 0, s>>>(a.gate, res.cand_off.p, a.n, a.ncap, res.cap, a.st_key,
+                                                       a.st_hits, res.genome.p, res.diag.p, res.hits.p, L.pair_read);
     MT_HIP(hipGetLastError());
     if (tm) tm->mark("compact");
+    FilterArgs fa{};
+    fa.pair_read = L.pair_read;
+    fa.pair_genome = res.genome.p;
+    fa.pair_diag = res.diag.p;
+    fa.read_E = a.read_E;
+    fa.n_dev = res.cand_off.p + a.n;
+    fa.n_host = res.cap;
+    fa.n_reads = a.n;
+    fa.read_off = a.off;
+    fa.n_genomes = L.ix->n_genomes;
+    fa.meta = L.ix->meta.p;
+    fa.ref_lohi = L.ix->ref.lohi.p;
+    fa.ref_nb = L.ix->ref.nb.p;
+    fa.approx = res.approx.p;
+    fa.accept = res.accept.p;
+    fa.flags = a.flags;
+    fa.seq = a.seq;
+    fa.seq_total = a.total;
+    fa.read_n = a.read_n;
+    fa.gate = a.gate;
+    // the largest E a fused read can have: E is fixed, or grows with the length
+    const u64 maxE = a.e_mode == MT_E_FIXED           ? a.e_value
+                     : a.e_mode == MT_E_CEIL_PERMILLE ? ((u64)LN_MAX_M * a.e_value + 999) / 1000
+                                                      : ((u64)LN_MAX_M * a.e_value) / 1000;
+    launch_filter_fused(fa, res.cap, (int)std::min<u64>(maxE, F_MAX_E), s);
+    if (tm) tm->mark("filter");
+    launch_reduce(res, *L.ix, a.read_E, a.gate, s);
+    k_fused_summary<<<ST_COUNT, SUM_TPB, 0, s>>>(L.ctl, res.cand_off.p + a.n, a.stats_part,
+                                                 L.lane_blocks + L.wave_blocks, L.sum);
+    MT_HIP(hipGetLastError());
+    if (tm) tm->mark("reduce");
 }
 
 // One executable graph per host thread, updated in place when a new capture
@@ -1040,6 +1057,7 @@ void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs 
     }
     rb.n = n;
     if (n == 0) {
+        zero_counters(res, s);
         res.n_cands = 0;
         return;
     }
@@ -1047,23 +1065,25 @@ void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs 
     int dev = 0, cus = 0;
     MT_HIP(hipGetDevice(&dev));
     MT_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    u64 blocks = (n + F_WPB - 1) / F_WPB;
-    const u64 cap = (u64)cus * 64;  // many short blocks: resident blocks finish together
-    if (blocks > cap) blocks = cap;
+    const bool lanes = n >= LANE_MIN_READS && ix.w >= (u32)LN_MIN_W && ix.w <= (u32)LN_MAX_W;
+    const u64 lane_blocks = lanes ? grid_for(n, LN_TPB) : 0;
+    // k_seed_wave: many short blocks, so that resident blocks finish together; a
+    // list of slow reads, whose length only the device knows, takes fewer
+    u64 wave_blocks = std::min<u64>((n + F_WPB - 1) / F_WPB, (u64)cus * (lanes ? 8 : 64));
 
-    DBuf<u32> st_genome(n * N), st_hits(n * N), ncand(n), fb_list(n), ctl(CTL_WORDS);
-    DBuf<i64> st_diag(n * N);
-    DBuf<u16> st_approx(n * N);
-    DBuf<u8> st_accept(n * N);
-    DBuf<u64> stats_part(blocks * ST_COUNT);
+    DBuf<u64> st_key(n * N);
+    DBuf<u32> st_hits(n * N), ncand(n), fb_list(n), slow_list(lanes ? n : 0), ctl(CTL_WORDS), pair_read(n * N);
+    DBuf<u8> read_n(n);
+    DBuf<u64> stats_part((lane_blocks + wave_blocks) * ST_COUNT);
     DBuf<FusedSummary> sum(1);
     res.alloc_cands(n * N);
 
     FusedLaunch L{};
-    FusedArgs &a = L.a;
+    SeedArgs &a = L.a;
     a.seq = (const u8 *)reads.seq;
     a.off = reads.offsets;
     a.n = n;
+    a.total = reads.total;
     a.k = ix.k;
     a.w = ix.w;
     a.min_hits = q.min_hits;
@@ -1074,30 +1094,23 @@ void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs 
     a.table = ix.table.p;
     a.nbuckets = ix.nbuckets;
     a.occ = ix.occ.p;
-    a.meta = ix.meta.p;
-    a.ref_lohi = ix.ref.lohi.p;
-    a.ref_nb = ix.ref.nb.p;
-    a.st_genome = st_genome.p;
-    a.st_diag = st_diag.p;
+    a.st_key = st_key.p;
     a.st_hits = st_hits.p;
-    a.st_approx = st_approx.p;
-    a.st_accept = st_accept.p;
     a.ncand = ncand.p;
-    a.read_accepted = res.read_accepted.p;
     a.read_E = res.read_E.p;
-    a.uniq = (unsigned long long *)res.uniq.p;
-    a.multi = (unsigned long long *)res.multi.p;
-    a.unmapped = (unsigned long long *)res.unmapped.p;
+    a.read_n = read_n.p;
+    a.slow_list = slow_list.p;
+    a.slow_count = ctl.p + CTL_SLOW;
     a.fb_list = fb_list.p;
     a.fb_count = ctl.p + CTL_FB;
     a.flags = ctl.p + CTL_FLAGS;
     a.gate = ctl.p + CTL_GATE;
     a.stats_part = stats_part.p;
+    L.ix = &ix;
     L.ctl = ctl.p;
-    L.n = n;
-    L.N = N;
-    L.blocks = (unsigned)blocks;
-    L.total = reads.total;
+    L.pair_read = pair_read.p;
+    L.lane_blocks = (unsigned)lane_blocks;
+    L.wave_blocks = (unsigned)wave_blocks;
     L.res = &res;
     L.sum = sum.p;
     // repetitive: at least one occurrence in eight belongs to a k-mer found in
@@ -1121,7 +1134,7 @@ void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs 
     ls.fused_cands += h.stats[ST_CANDS];
     ls.fused_occ += h.stats[ST_OCC];
     ls.n_minimizers += h.stats[ST_MINS];
-    // Every read's count is at most N (k_fused writes one count per read), so
+    // Every read's count is at most N (the seed kernels write one per read), so
     // the total fits the staged capacity; a result never claims more
     // candidates than its arrays hold.
     if (h.n_cands > res.cap) throw Error(MT_EINTERNAL, "fused candidate count exceeds the staged capacity");
@@ -1129,9 +1142,8 @@ void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs 
     const u32 nfb = h.nfb;
     if (nfb == 0) return;
 
-    // Reads past the fused kernel's limits: finish them per stage on a
-    // gathered subset, scatter the results into the staging slots, and
-    // compact again.
+    // Reads past the fused kernels' limits: finish them per stage on a
+    // gathered subset, and make room for their candidates among the others'.
     DBuf<u64> sub_len(nfb), sub_off(nfb + 1);
     k_subset_lengths<<<grid_for(nfb, 256), 256, 0, s>>>(reads.offsets, fb_list.p, nfb, sub_len.p);
     MT_HIP(hipGetLastError());
@@ -1150,34 +1162,37 @@ void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs 
     u32 f2 = 0;
     read_back(s, srb.flags.p, &f2, sizeof f2);
     check_flags(f2);
-    k_subset_scatter<<<grid_for(nfb, 256), 256, 0, s>>>(fb_list.p, nfb, N, tmp.cand_off.p, tmp.read_accepted.p,
-                                                        tmp.genome.p, tmp.diag.p, tmp.hits.p, tmp.approx.p,
-                                                        tmp.accept.p, ncand.p, res.read_accepted.p, st_genome.p,
-                                                        st_diag.p, st_hits.p, st_approx.p, st_accept.p);
+    k_subset_counts<<<grid_for(nfb, 256), 256, 0, s>>>(fb_list.p, nfb, tmp.cand_off.p, tmp.read_accepted.p, ncand.p,
+                                                       res.read_accepted.p);
     MT_HIP(hipGetLastError());
     if (ix.n_taxa) {
-        k_add_u64<<<grid_for(ix.n_taxa, 256), 256, 0, s>>>((unsigned long long *)res.uniq.p, tmp.uniq.p, ix.n_taxa);
+        k_add_u64<<<grid_for(ix.n_taxa, 256), 256, 0, s>>>((unsigned long long *)res.uniq.p, tmp.uniq.p, ix.n_taxa, 0);
         k_add_u64<<<grid_for(ix.n_taxa, 256), 256, 0, s>>>((unsigned long long *)res.multi.p, tmp.multi.p,
-                                                           ix.n_taxa);
+                                                           ix.n_taxa, 0);
     }
-    k_add_u64<<<1, 64, 0, s>>>((unsigned long long *)res.unmapped.p, tmp.unmapped.p, 1);
+    // these reads counted as unmapped while they had no candidates
+    k_add_u64<<<1, 64, 0, s>>>((unsigned long long *)res.unmapped.p, tmp.unmapped.p, 1, nfb);
+    MT_HIP(hipGetLastError());
+    DBuf<u64> old_off(n + 1);
+    MT_HIP(hipMemcpyAsync(old_off.p, res.cand_off.p, (n + 1) * sizeof(u64), hipMemcpyDeviceToDevice, s));
+    const DBuf<u8> old_cands(std::move(res.cands_block));
+    const auto old_genome = res.genome, old_hits = res.hits;
+    const auto old_diag = res.diag;
+    const auto old_approx = res.approx;
+    const auto old_accept = res.accept;
     scan_u32(ncand.p, res.cand_off.p, n, s);
     u64 total = 0;
     read_back(s, res.cand_off.p + n, &total, sizeof total);
-    if (total > res.cap) res.alloc_cands(total);  // keep-all reads with many candidates
-    k_compact_staged<<<grid_for(n, 256), 256, 0, s>>>(ctl.p + CTL_GATE, res.cand_off.p, n, N, res.cap, st_genome.p,
-                                                      st_diag.p, st_hits.p, st_approx.p, st_accept.p, res.genome.p,
-                                                      res.diag.p, res.hits.p, res.approx.p, res.accept.p);
+    res.alloc_cands(total);
+    k_move_cands<<<grid_for(n, 256), 256, 0, s>>>(old_off.p, res.cand_off.p, n, old_genome.p, old_diag.p, old_hits.p,
+                                                  old_approx.p, old_accept.p, res.genome.p, res.diag.p, res.hits.p,
+                                                  res.approx.p, res.accept.p);
     MT_HIP(hipGetLastError());
-    if (q.top_n == 0) {
-        // the finished reads' full lists, after the compaction (which copied
-        // at most N staged entries of theirs)
-        k_subset_place<<<grid_for(nfb, 256), 256, 0, s>>>(fb_list.p, nfb, tmp.cand_off.p, tmp.genome.p, tmp.diag.p,
-                                                          tmp.hits.p, tmp.approx.p, tmp.accept.p, res.cand_off.p,
-                                                          res.cap, res.genome.p, res.diag.p, res.hits.p,
-                                                          res.approx.p, res.accept.p);
-        MT_HIP(hipGetLastError());
-    }
+    k_subset_place<<<grid_for(nfb, 256), 256, 0, s>>>(fb_list.p, nfb, tmp.cand_off.p, tmp.genome.p, tmp.diag.p,
+                                                      tmp.hits.p, tmp.approx.p, tmp.accept.p, res.cand_off.p,
+                                                      res.genome.p, res.diag.p, res.hits.p, res.approx.p,
+                                                      res.accept.p);
+    MT_HIP(hipGetLastError());
     res.n_cands = total;
     tm.mark("fallback");
 }
@@ -1358,12 +1373,13 @@ __global__ __launch_bounds__(64 * F_WPB) void k_contain_fused(ContainArgs a) {
 
 void containment(const mt_index &ix, const mt_seqs &reads, u64 *hits, hipStream_t s) {
     const u64 n = reads.n;
-    if (n == 0 || ix.n_genomes == 0) return;
+    if (ix.n_genomes == 0) return;
+    if (n == 0) {
+        MT_HIP(hipMemsetAsync(hits, 0, ix.n_genomes * sizeof(u64), s));
+        return;
+    }
     DBuf<u32> ctl(CTL_WORDS), fb_list(n);
-    k_fused_init<<<1, 64, 0, s>>>(ctl.p);
-    MT_HIP(hipGetLastError());
-    k_check_reads<<<grid_for(n, 256), 256, 0, s>>>(reads.offsets, n, reads.total, ctl.p + CTL_GATE);
-    MT_HIP(hipGetLastError());
+    enqueue_begin(reads.offsets, n, reads.total, ctl.p, hits, ix.n_genomes, s);
     int dev = 0, cus = 0;
     MT_HIP(hipGetDevice(&dev));
     MT_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
