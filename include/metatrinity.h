@@ -154,6 +154,11 @@ int mt_index_get_info(const mt_index *index, mt_index_info *info);
 int mt_classify(const mt_index *index, const mt_query_params *params,
                 const mt_seqs *reads, void *stream, mt_result **out);
 
+/* The arrays of a device result lie in two blocks, readable from the first array
+ * of the block to the end of its last: the per-read and per-taxon arrays, and the
+ * per-candidate arrays (with the strands), so that a short result can be copied to
+ * the host in two pieces. */
+
 /* Per-read outputs (device arrays of n_reads entries, cand_offsets n_reads+1):
  * cand_offsets  CSR into the candidate arrays;
  * read_accepted 1 if at least one candidate of the read is accepted;
