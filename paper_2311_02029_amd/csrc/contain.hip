@@ -2,7 +2,7 @@
 // count of every reference genome over a whole read set, on the index that
 // stage 2 uses, and the subset-database selection by the normalised cutoff.
 //
-// Reads of up to 256 bases run in one fused kernel (fused.hip).  Longer reads
+// Reads of up to 320 bases run in one fused kernel (fused.hip).  Longer reads
 // take the per-stage chain here: bases packed to bit planes, minimizer tiles,
 // then one kernel that probes the table for every read minimizer and adds one
 // hit to the genome of each occurrence.  Integer atomics on per-block LDS

@@ -1199,33 +1199,106 @@ void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs 
 
 // ------------------------------------------------------ containment search --
 
-// Containment search (Fig. 1 steps 1a-1c) for reads of up to F_MAX_M bases,
-// one wavefront per read: its N plane by ballot and its 2-bit stream in LDS,
-// k-mer hashes and window minima as in k_fused (steps 1-3), then one table
-// probe per minimizer lane adding one hit to the genome of every occurrence.
+// Containment search (Fig. 1 steps 1a-1c): minimizers as in the classification,
+// then one table probe each, adding one hit to the genome of every occurrence.
 // Up to CF_LDS_GENOMES genomes a block counts in LDS and adds its nonzero
 // counters to the global ones when it ends; with more genomes the hits go to
-// the global counters directly.  Longer reads are listed for the per-stage
-// chain.
+// the global counters directly.  k_contain_lane takes a lane per read,
+// k_contain_wave a wavefront (k_seed_lane and k_seed_wave divide the reads the
+// same way); reads beyond both are listed for the per-stage chain.
 struct ContainArgs {
     const u8 *seq;
     const u64 *off;
-    u64 n;
+    u64 n, total;
     u32 k, w;
     const u64x2 *table;
     u64 nbuckets;
     const u64 *occ;
     u64 n_genomes;
     unsigned long long *hits;
-    u32 *fb_list;
-    u32 *fb_count;
+    u32 *slow_list, *slow_count;  // reads for k_contain_wave
+    u32 *fb_list, *fb_count;
     u32 *flags;
     const u32 *gate;  // offsets check result: nonzero skips the whole launch
 };
 
 constexpr u64 CF_LDS_GENOMES = 2048;  // 64-bit counters, at most 16 KB per block
 
-__global__ __launch_bounds__(64 * F_WPB) void k_contain_fused(ContainArgs a) {
+// One hit per occurrence of a probed k-mer (v: its slot value).
+__device__ inline void count_genomes(const u64 *__restrict__ occ, u64 v, unsigned long long *dst) {
+    if (v == SLOT_NONE) return;
+    if (!(v & SLOT_MULTI)) {
+        atomicAdd(&dst[v >> 32], 1ull);
+        return;
+    }
+    const u32 c = slot_count(v);  // 0 for a k-mer above max_occ
+    const u64 st = slot_start(v);
+    for (u32 u = 0; u < c; u++) atomicAdd(&dst[occ[st + u] >> 32], 1ull);
+}
+
+// One lane per read, grid-stride so that a block's counters are flushed once.
+// Bound by the probes' random table lines: 1M reads of 150 bases on 500 Mbp,
+// 0.60 ms (k_contain_wave on the same reads 1.09 ms).
+template <int W, int MAXM>
+__global__ __launch_bounds__(LN_TPB) void k_contain_lane(ContainArgs a) {
+    __shared__ LaneReads<MAXM> sh_reads[LN_TPB / 64];
+    extern __shared__ unsigned long long cnt[];  // one counter per genome when they fit (sized at launch)
+    if (*a.gate) return;  // malformed offsets: the whole grid leaves
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    LaneReads<MAXM> &L = sh_reads[wid];
+    const bool in_lds = a.n_genomes <= CF_LDS_GENOMES;  // uniform over the grid
+    unsigned long long *dst = in_lds ? cnt : a.hits;
+    if (in_lds)
+        for (u64 g = threadIdx.x; g < a.n_genomes; g += LN_TPB) cnt[g] = 0;
+    __syncthreads();
+    const u32 k = a.k;
+    u32 wflags = 0;
+    for (u64 r0 = (u64)blockIdx.x * LN_TPB + 64 * wid; r0 < a.n; r0 += (u64)gridDim.x * LN_TPB) {
+        const u64 r = r0 + lane;
+        const bool in = r < a.n;
+        u64 beg = 0;
+        int m = 0;
+        if (in) {
+            beg = a.off[r];
+            m = (int)(a.off[r + 1] - beg);
+        }
+        const bool fall = m > LN_MAX_M;
+        bool slow = !fall && m > MAXM;
+        const bool take = in && !fall && !slow;
+        if (!take) m = 0;
+        const int max_m = wave_max(m);
+        const LaneRead rd = lane_decode(a.seq, beg, m, a.total, lane, max_m, L);
+        if (rd.bad) wflags |= ERR_BAD_BYTE;  // the call fails; its codes are in range all the same
+        const bool mixed = ballot64(rd.has_n || m != max_m) != 0;
+        const bool sure = mixed ? lane_minimizers<W, true>(L, lane, m, max_m, k)
+                                : lane_minimizers<W, false>(L, lane, m, max_m, k);
+        slow |= take && !sure;
+        if (take && !slow) {
+            PickIter<MAXM> it(L, lane, max_m - (int)k + 1);
+            Probe cur, nxt;
+            int pn = it.next(L, lane);
+            if (pn >= 0) nxt.request(a.table, a.nbuckets, lane_kmer(L, lane, pn, k));
+            while (pn >= 0) {
+                cur = nxt;
+                pn = it.next(L, lane);
+                if (pn >= 0) nxt.request(a.table, a.nbuckets, lane_kmer(L, lane, pn, k));
+                count_genomes(a.occ, cur.find(a.table, a.nbuckets), dst);
+            }
+        }
+        list_append(in && slow, r, lane, a.slow_list, a.slow_count);
+        list_append(in && fall, r, lane, a.fb_list, a.fb_count);
+    }
+    if (wflags) atomicOr(a.flags, wflags);
+    if (in_lds) {
+        __syncthreads();
+        for (u64 g = threadIdx.x; g < a.n_genomes; g += LN_TPB)
+            if (cnt[g]) atomicAdd(&a.hits[g], cnt[g]);
+    }
+}
+
+// One wavefront per read: reads list[0, *list_n), or all of them when list is null.
+__global__ __launch_bounds__(64 * F_WPB) void k_contain_wave(ContainArgs a, const u32 *__restrict__ list,
+                                                             const u32 *__restrict__ list_n) {
     __shared__ u64 sh_h[F_WPB][F_MAX_M];
     __shared__ u16 sh_pos[F_WPB][F_MAX_M];
     __shared__ u8 sh_pick[F_WPB][F_MAX_M];
@@ -1248,12 +1321,14 @@ __global__ __launch_bounds__(64 * F_WPB) void k_contain_fused(ContainArgs a) {
     const u64 kmask = (1ull << k) - 1;
     u32 wflags = 0;
     const u64 stride = (u64)gridDim.x * F_WPB;
-    u64 r = (u64)blockIdx.x * F_WPB + wid;
+    const u64 n = list ? *list_n : a.n;
+    u64 i = (u64)blockIdx.x * F_WPB + wid;
+    u64 r = i >= n ? 0 : list ? list[i] : i;
     // the read in hand: its length and its bytes, one per lane per 64-base
     // round (the next read's are requested while this one is probed)
     int m = 0;
     u32 b[4];
-    if (r < a.n) {
+    if (i < n) {
         const u64 beg = a.off[r];
         m = (int)(a.off[r + 1] - beg);
 #pragma unroll
@@ -1262,13 +1337,14 @@ __global__ __launch_bounds__(64 * F_WPB) void k_contain_fused(ContainArgs a) {
             b[q] = (m <= F_MAX_M && i < m) ? (u32)a.seq[beg + i] : (u32)'N';
         }
     }
-    for (; r < a.n; r += stride) {
-        const u64 rn = r + stride;
+    for (u64 rn = 0; i < n; i += stride, r = rn) {
+        const bool more = i + stride < n;
+        rn = !more ? 0 : list ? list[i + stride] : i + stride;  // the next read
         // the next read's offsets, its start in even lanes and its end in odd
         // ones (read after the minimizers; a wave-uniform load would be waited
         // for at once)
         u64 noff = 0;
-        if (rn < a.n) noff = a.off[rn + (u64)(lane & 1)];
+        if (more) noff = a.off[rn + (u64)(lane & 1)];
         if (m > F_MAX_M) {
             if (lane == 0) a.fb_list[atomicAdd(a.fb_count, 1u)] = (u32)r;
             const u64 nbeg = readlane64(noff, 0);
@@ -1276,7 +1352,7 @@ __global__ __launch_bounds__(64 * F_WPB) void k_contain_fused(ContainArgs a) {
 #pragma unroll
             for (int q = 0; q < 4; q++) {
                 const int i = 64 * q + lane;
-                b[q] = (rn < a.n && m <= F_MAX_M && i < m) ? (u32)a.seq[nbeg + i] : (u32)'N';
+                b[q] = (more && m <= F_MAX_M && i < m) ? (u32)a.seq[nbeg + i] : (u32)'N';
             }
             continue;
         }
@@ -1343,23 +1419,16 @@ __global__ __launch_bounds__(64 * F_WPB) void k_contain_fused(ContainArgs a) {
 #pragma unroll
             for (int q = 0; q < 4; q++) {
                 const int i = 64 * q + lane;
-                b[q] = (rn < a.n && nm <= F_MAX_M && i < nm) ? (u32)a.seq[nbeg + i] : (u32)'N';
+                b[q] = (more && nm <= F_MAX_M && i < nm) ? (u32)a.seq[nbeg + i] : (u32)'N';
             }
-            m = rn < a.n ? nm : 0;
+            m = more ? nm : 0;
         }
         // 4. one probe per minimizer; one hit per occurrence to its genome
         for (int t0 = 0; t0 < nmin; t0 += 64) {
             const int j = t0 + lane;
             if (j >= nmin) continue;
             const u64 v = table_lookup(a.table, a.nbuckets, stream_kmer(stream, mpos[j], k));
-            if (v == SLOT_NONE) continue;
-            if (!(v & SLOT_MULTI)) {
-                atomicAdd(&dst[v >> 32], 1ull);
-                continue;
-            }
-            const u32 c = slot_count(v);  // 0 for a k-mer above max_occ
-            const u64 st = slot_start(v);
-            for (u32 u = 0; u < c; u++) atomicAdd(&dst[a.occ[st + u] >> 32], 1ull);
+            count_genomes(a.occ, v, dst);
         }
         wave_sync();  // the next read reuses the wavefront's LDS
     }
@@ -1378,7 +1447,8 @@ void containment(const mt_index &ix, const mt_seqs &reads, u64 *hits, hipStream_
         MT_HIP(hipMemsetAsync(hits, 0, ix.n_genomes * sizeof(u64), s));
         return;
     }
-    DBuf<u32> ctl(CTL_WORDS), fb_list(n);
+    const bool lanes = n >= LANE_MIN_READS && ix.w >= (u32)LN_MIN_W && ix.w <= (u32)LN_MAX_W;
+    DBuf<u32> ctl(CTL_WORDS), fb_list(n), slow_list(lanes ? n : 0);
     enqueue_begin(reads.offsets, n, reads.total, ctl.p, hits, ix.n_genomes, s);
     int dev = 0, cus = 0;
     MT_HIP(hipGetDevice(&dev));
@@ -1386,12 +1456,23 @@ void containment(const mt_index &ix, const mt_seqs &reads, u64 *hits, hipStream_
     // the genome counters take only the LDS the index needs, so more blocks fit
     // a CU (eight wavefronts per SIMD for a few hundred genomes); enough blocks
     // to fill them
-    const u64 blocks = std::min<u64>(grid_for(n, F_WPB), (u64)std::max(cus, 1) * 32);
     const size_t lds = ix.n_genomes <= CF_LDS_GENOMES ? ix.n_genomes * sizeof(unsigned long long) : 0;
-    ContainArgs a{(const u8 *)reads.seq, reads.offsets, n, ix.k, ix.w, ix.table.p, ix.nbuckets, ix.occ.p,
-                  ix.n_genomes, (unsigned long long *)hits, fb_list.p, ctl.p + CTL_FB, ctl.p + CTL_FLAGS,
-                  ctl.p + CTL_GATE};
-    k_contain_fused<<<(unsigned)blocks, 64 * F_WPB, lds, s>>>(a);
+    const ContainArgs a{(const u8 *)reads.seq, reads.offsets, n, reads.total, ix.k, ix.w, ix.table.p, ix.nbuckets,
+                        ix.occ.p, ix.n_genomes, (unsigned long long *)hits, slow_list.p, ctl.p + CTL_SLOW, fb_list.p,
+                        ctl.p + CTL_FB, ctl.p + CTL_FLAGS, ctl.p + CTL_GATE};
+    const u64 wave_blocks = std::min<u64>(grid_for(n, F_WPB), (u64)std::max(cus, 1) * (lanes ? 8 : 32));
+    if (lanes) {
+        const unsigned blocks = (unsigned)std::min<u64>(grid_for(n, LN_TPB), (u64)std::max(cus, 1) * 16);
+        with_window(ix.w, [&](auto w) {
+            constexpr int W = decltype(w)::value;
+            if (reads.total / n <= 160) k_contain_lane<W, LN_SHORT_M><<<blocks, LN_TPB, lds, s>>>(a);
+            else k_contain_lane<W, LN_MAX_M><<<blocks, LN_TPB, lds, s>>>(a);
+        });
+        MT_HIP(hipGetLastError());
+        k_contain_wave<<<(unsigned)wave_blocks, 64 * F_WPB, lds, s>>>(a, a.slow_list, a.slow_count);
+    } else {
+        k_contain_wave<<<(unsigned)wave_blocks, 64 * F_WPB, lds, s>>>(a, nullptr, nullptr);
+    }
     MT_HIP(hipGetLastError());
     u32 h[CTL_WORDS];
     read_back(s, ctl.p, h, sizeof h);
