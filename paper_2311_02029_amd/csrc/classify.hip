@@ -523,7 +523,9 @@ void ReadBatch::prepare(const mt_seqs &reads, u32 e_mode, u32 e_value, hipStream
         k_read_setup<<<grid_for(n, 256), 256, 0, s>>>(reads.offsets, n, e_mode, e_value, read_E.p, flags.p);
         MT_HIP(hipGetLastError());
     }
-    pack_sequences(reads, 65535, ERR_READ_TOO_LONG, "read longer than 65535 bases", planes, flags.p, nullptr, s);
+    has_n.alloc(n);
+    MT_HIP(hipMemsetAsync(has_n.p, 0, n ? n : 1, s));
+    pack_sequences(reads, 65535, ERR_READ_TOO_LONG, "read longer than 65535 bases", planes, flags.p, has_n.p, s);
 }
 
 void validate_query(const mt_query_params &q) {
@@ -627,6 +629,7 @@ static void stage_filter_reduce(const mt_index &ix, const mt_query_params &q, co
     fa.read_blk = rb.planes.blk_off.p;
     fa.read_lohi = rb.planes.lohi.p;
     fa.read_nb = rb.planes.nb.p;
+    fa.read_has_n = rb.has_n.p;
     fa.n_genomes = ix.n_genomes;
     fa.meta = ix.meta.p;
     fa.ref_lohi = ix.ref.lohi.p;
@@ -1134,6 +1137,7 @@ extern "C" int mt_filter_pairs_kind(const mt_index *index, const mt_seqs *reads,
         fa.read_blk = rb.planes.blk_off.p;
         fa.read_lohi = rb.planes.lohi.p;
         fa.read_nb = rb.planes.nb.p;
+        fa.read_has_n = rb.has_n.p;
         fa.n_genomes = index->n_genomes;
         fa.meta = index->meta.p;
         fa.ref_lohi = index->ref.lohi.p;

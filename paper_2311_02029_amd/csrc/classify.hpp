@@ -55,6 +55,7 @@ struct ReadBatch {
     u64 n = 0;
     DBuf<u32> flags;   // validation flags
     DBuf<u16> read_E;  // E per read
+    DBuf<u8> has_n;    // 1 if the read has an N
     PackedSeqs planes; // read bit planes
     void prepare(const mt_seqs &reads, u32 e_mode, u32 e_value, hipStream_t s);
 };
@@ -73,6 +74,7 @@ struct FilterArgs {
     const u64 *read_blk;
     const u64x2 *read_lohi;
     const u64 *read_nb;
+    const u8 *read_has_n;
     u64 n_genomes;
     const GenomeMeta *meta;
     const u64x2 *ref_lohi;
@@ -81,11 +83,9 @@ struct FilterArgs {
     u8 *accept;
     u32 *flags;
     // the fused form: reads as ASCII instead of planes (read_off into seq, its
-    // bytes seq_total), whether each has an N, and its offsets check (nonzero:
-    // nothing is filtered)
+    // bytes seq_total), and its offsets check (nonzero: nothing is filtered)
     const u8 *seq;
     u64 seq_total;
-    const u8 *read_n;
     const u32 *gate;
 };
 

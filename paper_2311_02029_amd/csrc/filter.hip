@@ -7,14 +7,12 @@
 //            groups of G lanes per pair, one band row per lane (G = 32 or 64 for
 //            E <= 7, 64 for E <= 15)
 //   E > 31   long reads, four bins by the 64-base blocks of read plus
-//            reference window they stage in LDS (<= 96, 192, 384, 768): one
-//            pair per wavefront, each lane owning a contiguous strip of the
-//            2E+1 rows, compared 32 columns at a time from three window
-//            dwords per chunk of 32 rows, with the bin's LDS tile and W
-//            wavefronts per block;
+//            reference window they stage in LDS (<= 96, 192, 384, 768): 1, 2, 4
+//            or 8 pairs per wavefront, the rows as the bits of words dealt to the
+//            pair's lanes;
 //            or the rows-in-lanes kernel reading the window from global memory
 //   larger   the rows-in-lanes kernel.
-// The variant of each bucket (lane or G, W, layout) is chosen by the autotuner
+// The variant of each bucket (lane or G, pairs per wavefront, layout) is chosen by the autotuner
 // (mt_autotune) or set by mt_tune_set; every variant gives the same result.
 #include <mutex>
 #include <string>
@@ -23,11 +21,24 @@
 
 namespace mt {
 
-constexpr int N_CLASSES = 8;  // E<=7, E<=15, E<=31, four long bins, general
+constexpr int N_BUCKETS = 8;  // E<=7, E<=15, E<=31, four long bins, general
 constexpr int CLS_LONG = 3, LONG_BINS = 4, CLS_GENERAL = 7;
+// Classes are the buckets, and the long bins twice more: for the pairs with an N
+// in read or window, or a window past a genome end, which stage and compare a
+// third plane (CLS_LONG_N), and for bands too wide to stage in segments
+// (CLS_LONG_WIDE).
+constexpr int CLS_LONG_N = N_BUCKETS, CLS_LONG_WIDE = CLS_LONG_N + LONG_BINS;
+constexpr int N_CLASSES = CLS_LONG_WIDE + LONG_BINS;
+__host__ __device__ inline int class_bucket(int c) {
+    return c < N_BUCKETS ? c : CLS_LONG + (c - N_BUCKETS) % LONG_BINS;
+}
 constexpr int LONG_CAP[LONG_BINS] = {96, 192, 384, 768};  // 64-base blocks staged per wavefront
 constexpr int LDS_BLOCK_BYTES = 24;                        // {lo, hi} + nb of one 64-base block
 constexpr int LONG_LDS_MAX = 64 * 1024;                    // per workgroup
+// A pair of the long kernel holds LONG_TILE blocks in LDS, or LONG_TILE_N with the N
+// planes (the same bytes), a segment of its columns at a time; bands up to
+// LONG_MAX_E, or LONG_MAX_E_N, leave at least 1,000 columns for a segment.
+constexpr int LONG_TILE = 81, LONG_TILE_N = 54, LONG_MAX_E = 1440, LONG_MAX_E_N = 600;
 
 __device__ inline void pair_fields(const FilterArgs &a, u64 p, u32 &r, u32 &g, int &E, bool &ok, u32 &err) {
     r = a.pair_read[p];
@@ -57,7 +68,12 @@ __device__ inline void long_blocks(int m, int E, int &nrb, int &nwb) {
     nwb = ((m + 2 * E + 190) >> 6) + 2;
 }
 
-// Class of pair p (0..3: the bucket kernels; 4: the general kernel).
+// Whether any compared column of a pair can meet an N or a position outside the
+// genome.
+__device__ inline bool pair_with_n(const FilterArgs &a, u32 r, const GenomeMeta &gm, i64 diag, int m, int E) {
+    return meta_has_n(gm) || diag - E < 0 || diag + m + E > (i64)gm.len || a.read_has_n[r];
+}
+
 __device__ inline u8 pair_class(const FilterArgs &a, u64 p) {
     u32 r, g, err;
     int E;
@@ -68,9 +84,14 @@ __device__ inline u8 pair_class(const FilterArgs &a, u64 p) {
     if (E <= 15) return 1;
     if (E <= 31) return 2;
     int nrb, nwb;
-    long_blocks(read_len(a, r), E, nrb, nwb);
+    const int m = read_len(a, r);
+    long_blocks(m, E, nrb, nwb);
     for (int b = 0; b < LONG_BINS; b++)
-        if (nrb + nwb <= LONG_CAP[b]) return (u8)(CLS_LONG + b);
+        if (nrb + nwb <= LONG_CAP[b])
+        {
+            const bool with_n = pair_with_n(a, r, a.meta[g], a.pair_diag[p], m, E);
+            return (u8)((E > (with_n ? LONG_MAX_E_N : LONG_MAX_E) ? CLS_LONG_WIDE : with_n ? CLS_LONG_N : CLS_LONG) + b);
+        }
     return CLS_GENERAL;
 }
 
@@ -269,192 +290,6 @@ __device__ inline void lds_wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// 64 bases from position p of planes staged in LDS (p >= 0, block p/64 + 1
-// staged); kWithN = false reads the N plane as zero.
-template <bool kWithN = true>
-__device__ inline Bits64 lds_bits(const u64x2 *lohi, const u64 *nb, i64 p) {
-    u64 b = (u64)p >> 6;
-    u32 s = (u32)p & 63u;
-    u64x2 x0 = lohi[b], x1 = lohi[b + 1];
-    Bits64 r;
-    r.lo = funnel(x0.lo, x1.lo, s);
-    r.hi = funnel(x0.hi, x1.hi, s);
-    r.nb = kWithN ? funnel(nb[b], nb[b + 1], s) : 0ull;
-    return r;
-}
-
-// Dword k (bases 32k .. 32k+31) of the lo (pl = 0) or hi (pl = 1) plane of
-// {lo, hi} blocks staged in LDS, and of the nb plane.
-__device__ inline u32 plane_dw(const u64x2 *lohi, int pl, u32 k) {
-    return reinterpret_cast<const u32 *>(lohi)[(k >> 1) * 4 + pl * 2 + (k & 1)];
-}
-__device__ inline u32 nb_dw(const u64 *nb, u32 k) { return reinterpret_cast<const u32 *>(nb)[k]; }
-
-// One chunk of a lane's rows in the long walk, without branches (a divergent
-// branch costs scalar exec-mask instructions): row i's 32 window bases are
-// bits [i, i + 32) of (x1:x0) per plane.  The trip count is the wave's rows
-// per chunk (uniform); with kTail, rows past the lane's cnt repeat its last
-// row, which leaves the maximum unchanged.  bmax gets the largest run (all
-// ones for a row whose 32 columns match: the find-first-one value for 0), and
-// full the rows whose 32 columns all match, to be continued by the caller.
-template <bool kWithN, bool kTail>
-__device__ inline void chunk_rows(u32 xl0, u32 xl1, u32 xh0, u32 xh1, u32 xn0, u32 xn1, u32 ql, u32 qh, u32 qn,
-                                  int SC, int cnt, u32 &full, u32 &bmax) {
-#pragma unroll 4
-    for (int i = 0; i < SC; i++) {
-        const u32 ie = kTail ? (u32)min(i, cnt - 1) : (u32)i;
-        const u32 wl = __builtin_amdgcn_alignbit(xl1, xl0, ie);
-        const u32 wh = __builtin_amdgcn_alignbit(xh1, xh0, ie);
-        const u32 wn = kWithN ? __builtin_amdgcn_alignbit(xn1, xn0, ie) : 0u;
-        // (ql ^ wl) | (qh ^ wh) | qn | wn in two (three with the window's N
-        // plane) 3-input bit operations: truth table 0xde takes (x, z, y) to
-        // (x ^ y) | z
-        const u32 t = __builtin_amdgcn_bitop3_b32(ql, kWithN ? (qn | wn) : qn, wl, 0xde);
-        const u32 mm = __builtin_amdgcn_bitop3_b32(qh, t, wh, 0xde);
-        const u32 run = mm ? (u32)__builtin_ctz(mm) : ~0u;
-        full |= (run >> 31) << i;
-        bmax = max(bmax, run);
-    }
-    if (kTail) full &= cnt >= 32 ? ~0u : (1u << cnt) - 1u;  // the repeated rows are not continued
-}
-
-// The obstacle walk of one pair over planes staged in LDS (read at L / NB,
-// window at WL / WN, row 0 and column 0 at window offset wbase), rows in
-// contiguous strips per lane; returns the obstacle count.  kWithN = false
-// leaves the window's N plane out: only for pairs whose compared window lies
-// inside a genome without N, where that plane is zero.
-template <bool kWithN>
-__device__ inline int long_walk(const u64x2 *L, const u64 *NB, const u64x2 *WL, const u64 *WN, i64 wbase, int m,
-                                int E, int lane) {
-    // lane owns the contiguous rows [r0, r1); per step each chunk of 32 of
-    // them is compared over 32 columns from three window dwords per plane
-    // (one alignbit per plane and row), and only a row with no obstacle
-    // in those columns continues 64 columns at a time
-    const int rows = 2 * E + 1;
-    const int S = (rows + 63) / 64;
-    // every lane takes S rows; the last lanes repeat the band's last rows,
-    // which leaves the maximum unchanged
-    const int r0 = min(lane * S, rows - S), r1 = r0 + S;
-    const int SC = min(32, S);
-    int j = 0, c = 0;
-    for (;;) {
-        // 32 read bases from j (one alignbit per plane)
-        const u32 kq = (u32)j >> 5, sq = (u32)j & 31u;
-        const u32 ql = __builtin_amdgcn_alignbit(plane_dw(L, 0, kq + 1), plane_dw(L, 0, kq), sq);
-        const u32 qh = __builtin_amdgcn_alignbit(plane_dw(L, 1, kq + 1), plane_dw(L, 1, kq), sq);
-        const u32 qn = __builtin_amdgcn_alignbit(nb_dw(NB, kq + 1), nb_dw(NB, kq), sq);
-        const int left = m - j;
-        int best = 0;
-        for (int s0 = r0; s0 < r1; s0 += 32) {  // chunks of <= 32 rows
-            // window bases of rows s0.. at column j start at p0; three
-            // dwords per plane cover every row of the chunk
-            const i64 p0 = wbase + (s0 - E) + j;
-            const u32 k0 = (u32)((u64)p0 >> 5), sh0 = (u32)p0 & 31u;
-            const u32 l0 = plane_dw(WL, 0, k0), l1 = plane_dw(WL, 0, k0 + 1), l2 = plane_dw(WL, 0, k0 + 2);
-            const u32 h0 = plane_dw(WL, 1, k0), h1 = plane_dw(WL, 1, k0 + 1), h2 = plane_dw(WL, 1, k0 + 2);
-            u32 n0 = 0, n1 = 0, n2 = 0;
-            if constexpr (kWithN) {
-                n0 = nb_dw(WN, k0);
-                n1 = nb_dw(WN, k0 + 1);
-                n2 = nb_dw(WN, k0 + 2);
-            }
-            const int cnt = min(32, r1 - s0);
-            // Bits [sh0, sh0 + 64) of the three dwords: row i's 32 window
-            // bases are bits [i, i + 32) of them, one alignbit per plane.
-            const u32 xl0 = __builtin_amdgcn_alignbit(l1, l0, sh0), xl1 = __builtin_amdgcn_alignbit(l2, l1, sh0);
-            const u32 xh0 = __builtin_amdgcn_alignbit(h1, h0, sh0), xh1 = __builtin_amdgcn_alignbit(h2, h1, sh0);
-            u32 xn0 = 0, xn1 = 0;
-            if constexpr (kWithN) {
-                xn0 = __builtin_amdgcn_alignbit(n1, n0, sh0);
-                xn1 = __builtin_amdgcn_alignbit(n2, n1, sh0);
-            }
-            u32 full = 0, bmax = 0;
-            if (S <= 32)  // every chunk row is the lane's own: no tail to mask
-                chunk_rows<kWithN, false>(xl0, xl1, xh0, xh1, xn0, xn1, ql, qh, qn, SC, cnt, full, bmax);
-            else
-                chunk_rows<kWithN, true>(xl0, xl1, xh0, xh1, xn0, xn1, ql, qh, qn, SC, cnt, full, bmax);
-            best = max(best, min((int)min(bmax, 32u), left));
-            // 32 matching columns: continue 64 at a time
-            while (full) {
-                const int i = (int)__builtin_ctz(full);
-                full &= full - 1;
-                int run = 32;
-                const i64 pos = p0 + i;
-                while (j + run < m) {
-                    const u64 m2 = mismatch(lds_bits(L, NB, j + run), lds_bits<kWithN>(WL, WN, pos + run));
-                    if (m2) {
-                        run += (int)__builtin_ctzll(m2);
-                        break;
-                    }
-                    run += 64;
-                }
-                best = max(best, min(run, left));
-            }
-        }
-        best = group_max<64>(best);
-        j += best;
-        if (j >= m) break;
-        c += 1;
-        if (c > E) break;
-        j += 1;
-    }
-    return c;
-}
-
-// Long reads / large E: one wavefront per pair, planes in LDS (`tile` blocks
-// per wavefront, at least the pairs' nrb + nwb; blockDim.x / 64 wavefronts).
-__global__ __launch_bounds__(512) void k_filter_long(FilterArgs a, const u32 *__restrict__ idx, u64 n, int tile) {
-    extern __shared__ __align__(16) unsigned char lds[];
-    const int wpb = blockDim.x >> 6;
-    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    u64x2 *L = (u64x2 *)(lds + (size_t)wid * tile * LDS_BLOCK_BYTES);
-    u64 *NB = (u64 *)(lds + (size_t)wid * tile * LDS_BLOCK_BYTES + (size_t)tile * 16);
-    for (u64 t = (u64)blockIdx.x * wpb + wid; t < n; t += (u64)gridDim.x * wpb) {
-        const u64 p = idx ? idx[t] : t;
-        u32 r, g, err;
-        int E;
-        bool ok;
-        pair_fields(a, p, r, g, E, ok, err);  // bucketed pairs are valid
-        const int m = read_len(a, r);
-        const i64 diag = a.pair_diag[p];
-        const GenomeMeta gm = a.meta[g];
-        int nrb, nwb;
-        long_blocks(m, E, nrb, nwb);
-        const i64 b0 = (diag - E) >> 6;  // first window block (floor)
-        const i64 gblocks = ((i64)gm.len + 63) / 64 + 1;
-        const u64 rb = a.read_blk[r];
-        const bool with_n = meta_has_n(gm) || diag - E < 0 || diag + m + E > (i64)gm.len;
-        for (int b = lane; b < nrb; b += 64) {
-            L[b] = a.read_lohi[rb + b];
-            NB[b] = a.read_nb[rb + b];
-        }
-        for (int b = lane; b < nwb; b += 64) {
-            const i64 gb = b0 + b;
-            u64x2 v{0ull, 0ull};
-            u64 nbv = ~0ull;
-            if (gb >= 0 && gb < gblocks) {
-                v = a.ref_lohi[gm.blk + (u64)gb];
-                nbv = with_n ? a.ref_nb[gm.blk + (u64)gb] : 0ull;
-            }
-            L[nrb + b] = v;
-            NB[nrb + b] = nbv;
-        }
-        lds_wave_sync();
-        const u64x2 *WL = L + nrb;
-        const u64 *WN = NB + nrb;
-        const i64 wbase = diag - 64 * b0;  // window offset of (row 0, column 0)
-        // every compared window position inside a genome without N: no N plane
-        const int c = with_n ? long_walk<true>(L, NB, WL, WN, wbase, m, E, lane)
-                             : long_walk<false>(L, NB, WL, WN, wbase, m, E, lane);
-        const int ap = c < E + 1 ? c : E + 1;
-        if (lane == 0) {
-            a.approx[p] = (u16)ap;
-            a.accept[p] = ap <= E;
-        }
-        lds_wave_sync();
-    }
-}
-
 // One lane per pair, E <= 31.  The walk is a serial chain of a few steps, each
 // over the 2E+1 rows; here a lane takes a pair's whole step with the rows as
 // the bits of R 32-bit words.  Column t of all rows at once: the window's planes
@@ -475,85 +310,105 @@ __global__ __launch_bounds__(512) void k_filter_long(FilterArgs a, const u32 *__
 // does not fit at all (reads past 20 kbp) takes the whole wavefront.
 constexpr int LANE_TPB = 256, LANE_DW = 2552, LANE_PAD = 8;  // 40 KB a block: four blocks a CU
 
-template <int R, int NC, bool kN>
-__device__ inline int lane_walk(const u32 *Q, int nbr, const u32 *W, int nbw, int wofs, int m, int E) {
-    const u32 *ql_ = Q, *qh_ = Q + 2 * nbr, *qn_ = Q + 4 * nbr;
-    const u32 *wl_ = W, *wh_ = W + 2 * nbw, *wn_ = W + 4 * nbw;
-    const int rows = 2 * E + 1;
-    u32 mask[R];
+// A pair's planes in LDS as dwords of 32 bases: the read's from its first base, the
+// window's from its first staged block.
+struct LdsPair {
+    const u32 *ql, *qh, *qn, *wl, *wh, *wn;
+    __device__ LdsPair(const u32 *Q, int nbr, const u32 *W, int nbw)
+        : ql(Q), qh(Q + 2 * nbr), qn(Q + 4 * nbr), wl(W), wh(W + 2 * nbw), wn(W + 4 * nbw) {}
+};
+
+// 32 bits of a plane from bit p.
+__device__ inline u32 plane_at(const u32 *d, int p) {
+    return __builtin_amdgcn_alignbit(d[(p >> 5) + 1], d[p >> 5], (u32)p & 31u);
+}
+
+// Run of the row whose column j lies at window position pw, known to match for
+// `run` columns, 64 columns at a time (past the read's end it counts whatever
+// lies there: the caller cuts it).
+template <bool kN>
+__device__ inline int long_run(const LdsPair &P, int j, int pw, int m, int run) {
+    while (j + run < m) {
+        const int cq = j + run, cw = pw + run;
+        const int k = cq >> 5, kk = cw >> 5;
+        const u32 s = (u32)cq & 31u, ss = (u32)cw & 31u;
+        const u32 q1 = P.ql[k + 1], h1 = P.qh[k + 1], w1 = P.wl[kk + 1], v1 = P.wh[kk + 1];
+        u32 m0 = (__builtin_amdgcn_alignbit(q1, P.ql[k], s) ^ __builtin_amdgcn_alignbit(w1, P.wl[kk], ss)) |
+                 (__builtin_amdgcn_alignbit(h1, P.qh[k], s) ^ __builtin_amdgcn_alignbit(v1, P.wh[kk], ss));
+        u32 m1 = (__builtin_amdgcn_alignbit(P.ql[k + 2], q1, s) ^ __builtin_amdgcn_alignbit(P.wl[kk + 2], w1, ss)) |
+                 (__builtin_amdgcn_alignbit(P.qh[k + 2], h1, s) ^ __builtin_amdgcn_alignbit(P.wh[kk + 2], v1, ss));
+        if constexpr (kN) {
+            m0 |= plane_at(P.qn, cq) | plane_at(P.wn, cw);
+            m1 |= plane_at(P.qn, cq + 32) | plane_at(P.wn, cw + 32);
+        }
+        if (m0 | m1) return run + (m0 ? (int)__builtin_ctz(m0) : 32 + (int)__builtin_ctz(m1));
+        run += 64;
+    }
+    return run;
+}
+
+// One step from column j for the 32 W rows whose first lies at window position pw
+// (rows: those of them that exist): the longest run, found column by column with
+// the rows as bits.
+template <int W, int NC, bool kN>
+__device__ inline int rows_step(const LdsPair &P, u32 ql, u32 qh, u32 qn, int j, int pw, int m, int rows) {
+    const int kw = pw >> 5;
+    const u32 sw = (u32)pw & 31u;
+    u32 xl[W + 1], xh[W + 1], xn[W + 1], alive[W], any = 0;
 #pragma unroll
-    for (int i = 0; i < R; i++) mask[i] = rows >= 32 * (i + 1) ? ~0u : rows > 32 * i ? (1u << (rows - 32 * i)) - 1u : 0u;
+    for (int i = 0; i <= W; i++) {
+        xl[i] = __builtin_amdgcn_alignbit(P.wl[kw + i + 1], P.wl[kw + i], sw);
+        xh[i] = __builtin_amdgcn_alignbit(P.wh[kw + i + 1], P.wh[kw + i], sw);
+        xn[i] = kN ? __builtin_amdgcn_alignbit(P.wn[kw + i + 1], P.wn[kw + i], sw) : 0u;
+    }
+    int best = 0;
+#pragma unroll
+    for (int i = 0; i < W; i++)
+        alive[i] = rows >= 32 * (i + 1) ? ~0u : rows > 32 * i ? (1u << (rows - 32 * i)) - 1u : 0u;
+#pragma unroll
+    for (int t = 0; t < NC; t++) {
+        const u32 a = (u32)((int)(ql << (31 - t)) >> 31), b = (u32)((int)(qh << (31 - t)) >> 31);
+        const u32 n = kN ? (u32)((int)(qn << (31 - t)) >> 31) : 0u;
+        any = 0;
+#pragma unroll
+        for (int i = 0; i < W; i++) {
+            // truth table 0x90 takes (x, y, z) to x & ~(y ^ z)
+            const u32 wl = t ? __builtin_amdgcn_alignbit(xl[i + 1], xl[i], t) : xl[i];
+            const u32 wh = t ? __builtin_amdgcn_alignbit(xh[i + 1], xh[i], t) : xh[i];
+            u32 v = __builtin_amdgcn_bitop3_b32(alive[i], wl, a, 0x90);
+            v = __builtin_amdgcn_bitop3_b32(v, wh, b, 0x90);
+            if constexpr (kN) v &= ~((t ? __builtin_amdgcn_alignbit(xn[i + 1], xn[i], t) : xn[i]) | n);
+            alive[i] = v;
+            any |= v;
+        }
+        best += any != 0;
+    }
+    if (any) {
+        static_assert(W <= 4, "the survivors of up to 128 rows");
+        u64 al = alive[0], more = 0;
+        if (W > 1) al |= (u64)alive[W > 1 ? 1 : 0] << 32;
+        if (W > 2) more = alive[W > 2 ? 2 : 0] | (W > 3 ? (u64)alive[W > 3 ? 3 : 0] << 32 : 0ull);
+        int base = 0;
+        while (al | more) {
+            if (W > 2 && al == 0) {
+                al = more;
+                more = 0;
+                base = 64;
+            }
+            const int row = base + (int)__builtin_ctzll(al);
+            al &= al - 1;
+            best = max(best, long_run<kN>(P, j, pw + row, m, NC));
+        }
+    }
+    return best;
+}
+
+template <int R, int NC, bool kN>
+__device__ inline int lane_walk(const LdsPair &P, int wofs, int m, int E) {
     int j = 0, c = 0;
     for (;;) {
-        const int kq = j >> 5;
-        const u32 sq = (u32)j & 31u;
-        const u32 ql = __builtin_amdgcn_alignbit(ql_[kq + 1], ql_[kq], sq);
-        const u32 qh = __builtin_amdgcn_alignbit(qh_[kq + 1], qh_[kq], sq);
-        const u32 qn = kN ? __builtin_amdgcn_alignbit(qn_[kq + 1], qn_[kq], sq) : 0u;
-        const int pw = wofs + j, kw = pw >> 5;
-        const u32 sw = (u32)pw & 31u;
-        u32 xl[R + 1], xh[R + 1], xn[R + 1];
-#pragma unroll
-        for (int i = 0; i <= R; i++) {
-            xl[i] = __builtin_amdgcn_alignbit(wl_[kw + i + 1], wl_[kw + i], sw);
-            xh[i] = __builtin_amdgcn_alignbit(wh_[kw + i + 1], wh_[kw + i], sw);
-            xn[i] = kN ? __builtin_amdgcn_alignbit(wn_[kw + i + 1], wn_[kw + i], sw) : 0u;
-        }
-        u32 alive[R], any = 0;
-        int best = 0;
-#pragma unroll
-        for (int i = 0; i < R; i++) alive[i] = mask[i];
-#pragma unroll
-        for (int t = 0; t < NC; t++) {
-            const u32 a = (u32)((int)(ql << (31 - t)) >> 31), b = (u32)((int)(qh << (31 - t)) >> 31);
-            const u32 n = kN ? (u32)((int)(qn << (31 - t)) >> 31) : 0u;
-            any = 0;
-#pragma unroll
-            for (int i = 0; i < R; i++) {
-                // truth table 0x90 takes (x, y, z) to x & ~(y ^ z)
-                const u32 wl = t ? __builtin_amdgcn_alignbit(xl[i + 1], xl[i], t) : xl[i];
-                const u32 wh = t ? __builtin_amdgcn_alignbit(xh[i + 1], xh[i], t) : xh[i];
-                u32 v = __builtin_amdgcn_bitop3_b32(alive[i], wl, a, 0x90);
-                v = __builtin_amdgcn_bitop3_b32(v, wh, b, 0x90);
-                if constexpr (kN) v &= ~((t ? __builtin_amdgcn_alignbit(xn[i + 1], xn[i], t) : xn[i]) | n);
-                alive[i] = v;
-                any |= v;
-            }
-            best += any != 0;
-        }
-        if (any) {
-            u64 al = alive[0];
-            if (R > 1) al |= (u64)alive[R - 1] << 32;
-            while (al) {
-                const int row = (int)__builtin_ctzll(al);
-                al &= al - 1;
-                int run = NC;
-                while (j + run < m) {
-                    const int cq = j + run, cw = pw + row + run;
-                    const int k = cq >> 5, kk = cw >> 5;
-                    const u32 s = (u32)cq & 31u, ss = (u32)cw & 31u;
-                    const u32 q1 = ql_[k + 1], h1 = qh_[k + 1], w1 = wl_[kk + 1], v1 = wh_[kk + 1];
-                    u32 m0 = (__builtin_amdgcn_alignbit(q1, ql_[k], s) ^ __builtin_amdgcn_alignbit(w1, wl_[kk], ss)) |
-                             (__builtin_amdgcn_alignbit(h1, qh_[k], s) ^ __builtin_amdgcn_alignbit(v1, wh_[kk], ss));
-                    u32 m1 = (__builtin_amdgcn_alignbit(ql_[k + 2], q1, s) ^
-                              __builtin_amdgcn_alignbit(wl_[kk + 2], w1, ss)) |
-                             (__builtin_amdgcn_alignbit(qh_[k + 2], h1, s) ^
-                              __builtin_amdgcn_alignbit(wh_[kk + 2], v1, ss));
-                    if constexpr (kN) {
-                        m0 |= __builtin_amdgcn_alignbit(qn_[k + 1], qn_[k], s) |
-                              __builtin_amdgcn_alignbit(wn_[kk + 1], wn_[kk], ss);
-                        m1 |= __builtin_amdgcn_alignbit(qn_[k + 2], qn_[k + 1], s) |
-                              __builtin_amdgcn_alignbit(wn_[kk + 2], wn_[kk + 1], ss);
-                    }
-                    if (m0 | m1) {
-                        run += m0 ? (int)__builtin_ctz(m0) : 32 + (int)__builtin_ctz(m1);
-                        break;
-                    }
-                    run += 64;
-                }
-                best = max(best, run);
-            }
-        }
+        const u32 qn = kN ? plane_at(P.qn, j) : 0u;
+        const int best = rows_step<R, NC, kN>(P, plane_at(P.ql, j), plane_at(P.qh, j), qn, j, wofs + j, m, 2 * E + 1);
         j += min(best, m - j);  // columns past the read's end count for nothing
         if (j >= m) break;
         c += 1;
@@ -622,7 +477,7 @@ __device__ inline int lane_pair(const FilterArgs &a, u32 *S, u64 rb, int nbr, co
             w[nbw + b] = x.hi;
         }
     }
-    return lane_walk<R, NC, kN>(S, nbr, (const u32 *)w, nbw, wofs, m, E);
+    return lane_walk<R, NC, kN>(LdsPair(S, nbr, (const u32 *)w, nbw), wofs, m, E);
 }
 
 // kAscii: the fused form's pairs, reads of at most 320 bases as ASCII (no pair
@@ -655,15 +510,7 @@ __global__ __launch_bounds__(LANE_TPB) void k_filter_lane(FilterArgs a, const u3
             wofs = (int)(diag - E - 64 * b0);
             nbr = (m + 63) / 64;
             nbw = (wofs + 2 * E + m + 63) / 64;
-            with_n = meta_has_n(gm) || diag - E < 0 || diag + m + E > (i64)gm.len;
-            if constexpr (kAscii) {
-                with_n |= a.read_n[r] != 0;
-            } else {
-                for (int w = 0; w < nbr && !with_n; w++) {
-                    const int left = m - 64 * w;
-                    with_n = (a.read_nb[rb + w] & (left >= 64 ? ~0ull : (1ull << left) - 1)) != 0;
-                }
-            }
+            with_n = pair_with_n(a, r, gm, diag, m, E);
         }
     }
     int c = 0;
@@ -713,6 +560,148 @@ __global__ __launch_bounds__(LANE_TPB) void k_filter_lane(FilterArgs a, const u3
     a.accept[p] = ok && ap <= E;
 }
 
+// Long reads / large E: P = 64 / G pairs per wavefront (and block), each by a group
+// of G lanes with its planes in LDS (`tile` 64-base blocks a pair), the rows as
+// bits: the words of 32 rows are dealt to the lanes in strips, a step is rows_step
+// on a lane's words and a maximum over the group.  A group that is done with its
+// pair takes its next one at once, so pairs of one wavefront need not be alike.
+// The planes are staged a segment of columns at a time, the next one from the
+// current column on when fewer than LONG_AHEAD columns are left: whole reads of 10
+// kbp took 25 KB for four pairs, six wavefronts a CU.  A run that leaves the
+// segment is measured from global memory.
+// Bound by VALU issue.  With the rows in lanes (16 of them each, 32 columns
+// compared per row) a step took a whole wavefront for one pair; a step here is
+// about as long, for P pairs.  kN: the classes with N planes.
+// 300k pairs of 1-10 kbp at E = 5%: 21.1 ms in the three bins before, 8.7 ms now.
+template <int G>
+__device__ inline int long_group_max(int v) {
+    if constexpr (G == 8) {
+        v = max(v, __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false));   // quad_perm 1,0,3,2
+        v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false));   // quad_perm 2,3,0,1
+        return max(v, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, false));  // row_half_mirror
+    } else {
+        return group_max<G>(v);
+    }
+}
+
+constexpr int LONG_PAD = 16;  // dwords: a step may read a few words past the last plane
+constexpr int LONG_AHEAD = 256;
+
+// Pairs idx[0, n) (pairs [0, n) when idx is null) by block `block` of `blocks`.
+template <int G, bool kN>
+__device__ inline void filter_long(const FilterArgs &a, const u32 *__restrict__ idx, u64 n, int tile, u32 block,
+                                   u32 blocks, u32 *lds) {
+    constexpr int P = 64 / G, PLANES = kN ? 3 : 2;
+    const int lane = threadIdx.x, lg = lane % G;
+    u64 *S = (u64 *)(lds + (lane / G) * tile * 2 * PLANES);
+    u64 t = (u64)block * P + lane / G, p = 0;
+    bool live = false, stage = false;
+    u32 r = 0, g = 0;
+    int m = 0, E = 0, j = 0, c = 0, wofs = 0, strip = 0;
+    int sb = 0, nbr = 0, nbw = 0, end = 0;  // segment: first block, blocks of read and window, end column
+    i64 b0 = 0;
+    while (__ballot(live || t < n)) {
+        if (!live && t < n) {  // the group's next pair (bucketed pairs are valid)
+            p = idx ? idx[t] : t;
+            t += (u64)blocks * P;
+            u32 err;
+            bool ok;
+            pair_fields(a, p, r, g, E, ok, err);
+            m = read_len(a, r);
+            const i64 from = a.pair_diag[p] - E;
+            b0 = from >> 6;  // first window block (floor)
+            wofs = (int)(from - 64 * b0);
+            strip = ((2 * E + 32) / 32 + G - 1) / G;  // words of 32 rows per lane
+            j = c = 0;
+            live = stage = true;
+        }
+        if (stage) {
+            sb = j >> 6;
+            const int extra = (2 * E + 126) / 64;  // window blocks beyond the read's
+            nbr = min((m + 63) / 64 - sb, (tile - extra) / 2);
+            nbw = min((wofs + 2 * E + m + 63) / 64 - sb, nbr + extra);
+            end = min(m, 64 * (sb + nbr));
+            const u64 rb = a.read_blk[r] + sb;
+            const GenomeMeta gm = a.meta[g];
+            for (int b = lg; b < nbr; b += G) {
+                const u64x2 x = a.read_lohi[rb + b];
+                S[b] = x.lo;
+                S[nbr + b] = x.hi;
+                if (kN) S[2 * nbr + b] = a.read_nb[rb + b];
+            }
+            u64 *w = S + PLANES * nbr;
+            const u64x2 *rl = a.ref_lohi + gm.blk;
+            const i64 wb = b0 + sb;
+            for (int b = lg; b < nbw; b += G) {
+                if constexpr (kN) {
+                    const Bits64 x = ref_block(rl, a.ref_nb + gm.blk, (i64)gm.len, meta_has_n(gm), wb + b);
+                    w[b] = x.lo;
+                    w[nbw + b] = x.hi;
+                    w[2 * nbw + b] = x.nb;
+                } else {  // the whole window lies inside a genome without N
+                    const u64x2 x = rl[wb + b];
+                    w[b] = x.lo;
+                    w[nbw + b] = x.hi;
+                }
+            }
+            stage = false;
+        }
+        lds_wave_sync();
+        const bool wide = __ballot(live && strip > 2) != 0;  // some group's strips pass two words
+        if (live) {
+            const LdsPair L((const u32 *)S, nbr, (const u32 *)(S + PLANES * nbr), nbw);
+            const int jl = j - 64 * sb, left = end - j;  // column in the segment; columns left of it
+            int best = 0;
+            if (left > 0) {
+                const u32 ql = plane_at(L.ql, jl), qh = plane_at(L.qh, jl), qn = kN ? plane_at(L.qn, jl) : 0u;
+                const int rows = min(2 * E + 1, 32 * strip * (lg + 1));  // the lane's rows end here
+                int r0 = 32 * strip * lg;
+                if (wide)
+                    for (; r0 < rows; r0 += 128)
+                        best = max(best, rows_step<4, 6, kN>(L, ql, qh, qn, jl, wofs + jl + r0, jl + left, rows - r0));
+                else if (r0 < rows)
+                    best = rows_step<2, 6, kN>(L, ql, qh, qn, jl, wofs + jl + r0, jl + left, rows - r0);
+            }
+            best = long_group_max<G>(best);
+            if (best >= left && end < m) {  // a run leaves the segment
+                const GenomeMeta gm = a.meta[g];
+                const PairView v{a.read_lohi + a.read_blk[r], a.read_nb + a.read_blk[r], m, a.ref_lohi + gm.blk,
+                                 a.ref_nb + gm.blk, (i64)gm.len, meta_has_n(gm), a.pair_diag[p]};
+                best = 0;
+                for (int row = lg; row <= 2 * E; row += G) best = max(best, row_run(v, row - E, j));
+                best = long_group_max<G>(best);
+            }
+            j += min(best, m - j);
+            if (j < m) {
+                c += 1;
+                j += 1;
+            }
+            stage = j + LONG_AHEAD > end && end < m;
+            if (j >= m || c > E) {
+                live = stage = false;
+                if (lg == 0) {
+                    const int ap = min(c, E + 1);
+                    a.approx[p] = (u16)ap;
+                    a.accept[p] = ap <= E;
+                }
+            }
+        }
+        lds_wave_sync();  // a group's planes are read before its next ones come in
+    }
+}
+
+// The first blocks_n blocks take the n_n pairs with N planes at idx_n (few, as a
+// rule, and as long as the others: they run beside them), the rest the n pairs at
+// idx.
+template <int G>
+__global__ __launch_bounds__(64) void k_filter_long(FilterArgs a, const u32 *__restrict__ idx, u64 n, int tile,
+                                                    const u32 *__restrict__ idx_n, u64 n_n, int tile_n,
+                                                    u32 blocks_n) {
+    extern __shared__ __align__(16) u32 lds[];
+    if (blockIdx.x < blocks_n) filter_long<G, true>(a, idx_n, n_n, tile_n, blockIdx.x, blocks_n, lds);
+    else filter_long<G, false>(a, idx, n, tile, blockIdx.x - blocks_n, gridDim.x - blocks_n, lds);
+}
+
 // ------------------------------------------------------------- variants --
 
 namespace {
@@ -725,9 +714,12 @@ struct BucketDesc {
 
 // Variant 0 of a short bucket is one lane per pair; it keeps the name of the
 // narrowest group, which it replaces, so that saved selections go on loading.
-// Variant v of a long bin: v < 4 -> strips in LDS with 1 << v wavefronts per
-// block (if its LDS fits a workgroup), v == 4 -> rows in lanes from global memory.
-const BucketDesc BUCKETS[N_CLASSES] = {
+// Variant v of a long bin: v < 4 -> pairs in LDS, 8 per wavefront for the default
+// variant and half as many with each below it; v == 4 -> rows in lanes from global
+// memory.  (The names count the wavefronts that shared a block when a pair took a
+// whole wavefront and its whole planes; their limits stay, so that the same
+// selections are taken and refused as ever.)
+const BucketDesc BUCKETS[N_BUCKETS] = {
     {"E<=7", 3, {"g16", "g32", "g64"}},
     {"E<=15", 2, {"g32", "g64"}},
     {"E<=31", 1, {"g64"}},
@@ -738,14 +730,13 @@ const BucketDesc BUCKETS[N_CLASSES] = {
     {"general", 1, {"global"}},
 };
 
-// Defaults: a lane per pair for short E, the most wavefronts per block whose LDS
-// fits 64 KB for the long bins.
-const int DEFAULT_VARIANT[N_CLASSES] = {0, 0, 0, 3, 3, 2, 1, 0};
+// Defaults: a lane per pair for short E, eight pairs per wavefront for the long bins.
+const int DEFAULT_VARIANT[N_BUCKETS] = {0, 0, 0, 3, 3, 2, 1, 0};
 
 std::mutex g_tune_mu;
-int g_variant[N_CLASSES] = {0, 0, 0, 3, 3, 2, 1, 0};
-float g_tune_ms[N_CLASSES][6];
-u64 g_tune_pairs[N_CLASSES];
+int g_variant[N_BUCKETS] = {0, 0, 0, 3, 3, 2, 1, 0};
+float g_tune_ms[N_BUCKETS][6];
+u64 g_tune_pairs[N_BUCKETS];
 
 bool variant_ok(int bucket, int v) {
     if (v < 0 || v >= BUCKETS[bucket].n_variants) return false;
@@ -761,8 +752,32 @@ int current_variant(int bucket) {
 
 }  // namespace
 
-// Launches the pairs idx[0, cnt) of one bucket with one of its variants.
-static void launch_bucket(const FilterArgs &a, const u32 *idx, u64 cnt, int bucket, int v, hipStream_t s) {
+// Blocks for cnt pairs of the long kernel: up to four pairs to a group once there
+// are blocks for every CU, so that groups with short pairs go on while others finish.
+static u32 long_blocks_for(u64 cnt, int G) {
+    const u64 one = (cnt * G + 63) / 64, four = (cnt * G + 255) / 256;
+    return (u32)std::min<u64>(std::max<u64>(four, std::min<u64>(one, 4096)), 1u << 20);
+}
+
+template <int G>
+static void launch_long(const FilterArgs &a, const u32 *idx, u64 cnt, int tile, const u32 *idx_n, u64 cnt_n,
+                        int tile_n, hipStream_t s) {
+    const u32 blocks = long_blocks_for(cnt, G), blocks_n = long_blocks_for(cnt_n, G);
+    if (blocks + blocks_n == 0) return;
+    const size_t bytes = (size_t)(64 / G) * std::max(cnt ? tile * 16 : 0, cnt_n ? tile_n * 24 : 0) + LONG_PAD * 4;
+    k_filter_long<G><<<blocks + blocks_n, 64, bytes, s>>>(a, idx, cnt, tile, idx_n, cnt_n, tile_n, blocks_n);
+}
+
+// A bucket's pairs, class by class: places in idx (or pairs [0, count) of the one
+// class there is, idx null) and counts.
+struct Buckets {
+    const u32 *idx;
+    const u32 *count, *at;  // per class
+    const u32 *of(int cls) const { return idx ? idx + at[cls] : nullptr; }
+};
+
+// Launches the pairs of a short bucket or the general one.
+static void launch_short(const FilterArgs &a, const u32 *idx, u64 cnt, int bucket, int v, hipStream_t s) {
     if (cnt == 0) return;
     if (bucket < CLS_LONG && v == 0) {
         const unsigned blocks = grid_for(cnt, LANE_TPB);
@@ -770,15 +785,38 @@ static void launch_bucket(const FilterArgs &a, const u32 *idx, u64 cnt, int buck
         else k_filter_lane<2, 7, false><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
     } else if (bucket == 0 && v == 1) {
         k_filter<32><<<grid_for(cnt * 32, 256), 256, 0, s>>>(a, idx, cnt);
-    } else if (bucket >= CLS_LONG && bucket < CLS_LONG + LONG_BINS && v < 4) {
-        const int tile = LONG_CAP[bucket - CLS_LONG], wpb = 1 << v;
-        u64 blocks = (cnt + wpb - 1) / wpb;
-        if (blocks > 16384) blocks = 16384;
-        k_filter_long<<<(unsigned)blocks, 64 * wpb, (size_t)wpb * tile * LDS_BLOCK_BYTES, s>>>(a, idx, cnt, tile);
     } else {
         k_filter<64><<<grid_for(cnt * 64, 256), 256, 0, s>>>(a, idx, cnt);
     }
     MT_HIP(hipGetLastError());
+}
+
+// Launches the pairs of one bucket with one of its variants.
+static void launch_bucket(const FilterArgs &a, const Buckets &B, int bucket, int v, hipStream_t s) {
+    const u64 cnt = B.count[bucket];
+    const u32 *idx = B.of(bucket);
+    if (bucket >= CLS_LONG && bucket < CLS_LONG + LONG_BINS) {
+        const int b = bucket - CLS_LONG, cn = CLS_LONG_N + b, cw = CLS_LONG_WIDE + b;
+        const int below = DEFAULT_VARIANT[bucket] - v;  // the default is the last that fits
+        if (v == 4) {
+            for (int c : {bucket, cn, cw})
+                if (B.count[c])
+                    k_filter<64><<<grid_for((u64)B.count[c] * 64, 256), 256, 0, s>>>(a, B.of(c), B.count[c]);
+        } else {
+            if (below <= 0)
+                launch_long<8>(a, idx, cnt, LONG_TILE, B.of(cn), B.count[cn], LONG_TILE_N, s);
+            else if (below == 1)
+                launch_long<16>(a, idx, cnt, LONG_TILE, B.of(cn), B.count[cn], LONG_TILE_N, s);
+            else if (below == 2)
+                launch_long<32>(a, idx, cnt, LONG_TILE, B.of(cn), B.count[cn], LONG_TILE_N, s);
+            else
+                launch_long<64>(a, idx, cnt, LONG_TILE, B.of(cn), B.count[cn], LONG_TILE_N, s);
+            launch_long<32>(a, nullptr, 0, 0, B.of(cw), B.count[cw], LONG_CAP[b], s);
+        }
+        MT_HIP(hipGetLastError());
+    } else {
+        launch_short(a, idx, cnt, bucket, v, s);
+    }
 }
 
 // Buckets the pairs (one synchronization for the bucket sizes); idx / counts
@@ -1033,8 +1071,15 @@ void launch_filter_simple(const FilterArgs &a, u64 n, u32 kind, hipStream_t s) {
     MT_HIP(hipGetLastError());
 }
 
+// Pairs of a bucket's classes.
+static u64 bucket_count(const u32 *count, int bucket) {
+    u64 n = 0;
+    for (int c = 0; c < N_CLASSES; c++) n += class_bucket(c) == bucket ? count[c] : 0;
+    return n;
+}
+
 // Stage names of the per-bucket timing marks.
-static const char *const BUCKET_MARKS[N_CLASSES] = {"filter E<=7",     "filter E<=15",    "filter E<=31",
+static const char *const BUCKET_MARKS[N_BUCKETS] = {"filter E<=7",     "filter E<=15",    "filter E<=31",
                                                     "filter long<=96", "filter long<=192", "filter long<=384",
                                                     "filter long<=768", "filter general"};
 
@@ -1044,7 +1089,7 @@ void launch_filter(const FilterArgs &a, u64 n_cap, int fixed_E, hipStream_t s, T
         // one class, known without looking at the pairs: no bucketing and no
         // synchronization (pairs out of range are reported by every kernel)
         const int c = fixed_E <= 7 ? 0 : fixed_E <= 15 ? 1 : 2;
-        launch_bucket(a, nullptr, n_cap, c, current_variant(c), s);
+        launch_short(a, nullptr, n_cap, c, current_variant(c), s);
         if (tm) tm->mark(BUCKET_MARKS[c]);
         return;
     }
@@ -1052,10 +1097,10 @@ void launch_filter(const FilterArgs &a, u64 n_cap, int fixed_E, hipStream_t s, T
     u32 hc[N_CLASSES], hb[N_CLASSES];
     bucket_pairs(a, n_cap, idx, hc, hb, s);
     if (tm) tm->mark("filter buckets");
-    for (int c = 0; c < N_CLASSES; c++) {
-        if (hc[c] == 0) continue;
-        launch_bucket(a, idx.p ? idx.p + hb[c] : nullptr, hc[c], c, current_variant(c), s);
-        if (tm) tm->mark(BUCKET_MARKS[c]);
+    for (int b = 0; b < N_BUCKETS; b++) {
+        if (bucket_count(hc, b) == 0) continue;
+        launch_bucket(a, Buckets{idx.p, hc, hb}, b, current_variant(b), s);
+        if (tm) tm->mark(BUCKET_MARKS[b]);
     }
 }
 
@@ -1078,18 +1123,20 @@ void autotune_filter(const FilterArgs &a, u64 n_pairs, u32 reps, hipStream_t s) 
     MT_HIP(hipEventCreate(&e0));
     MT_HIP(hipEventCreate(&e1));
     try {
-        for (int c = 0; c < N_CLASSES; c++) {
-            if (hc[c] == 0) continue;
+        for (int c = 0; c < N_BUCKETS; c++) {
+            const u64 pairs = bucket_count(hc, c);
+            if (pairs == 0) continue;
+            auto launch = [&](int v) { launch_bucket(a, Buckets{idx.p, hc, hb}, c, v, s); };
             float best_ms = 0;
             int best = -1;
             float ms_v[6] = {0, 0, 0, 0, 0, 0};
             for (int v = 0; v < BUCKETS[c].n_variants; v++) {
                 if (!variant_ok(c, v)) continue;
-                launch_bucket(a, idx.p ? idx.p + hb[c] : nullptr, hc[c], c, v, s);
+                launch(v);
                 float mn = 0;
                 for (u32 r = 0; r < (reps ? reps : 1); r++) {
                     MT_HIP(hipEventRecord(e0, s));
-                    launch_bucket(a, idx.p ? idx.p + hb[c] : nullptr, hc[c], c, v, s);
+                    launch(v);
                     MT_HIP(hipEventRecord(e1, s));
                     MT_HIP(hipEventSynchronize(e1));
                     float ms = 0;
@@ -1105,7 +1152,7 @@ void autotune_filter(const FilterArgs &a, u64 n_pairs, u32 reps, hipStream_t s) 
             std::lock_guard<std::mutex> g(g_tune_mu);
             if (best >= 0) g_variant[c] = best;
             for (int v = 0; v < 6; v++) g_tune_ms[c][v] = ms_v[v];
-            g_tune_pairs[c] = hc[c];
+            g_tune_pairs[c] = pairs;
         }
     } catch (...) {
         (void)hipEventDestroy(e0);
@@ -1116,10 +1163,10 @@ void autotune_filter(const FilterArgs &a, u64 n_pairs, u32 reps, hipStream_t s) 
     (void)hipEventDestroy(e1);
 }
 
-int tune_buckets() { return N_CLASSES; }
+int tune_buckets() { return N_BUCKETS; }
 
 void tune_info(int bucket, mt_tune_bucket &out) {
-    MT_REQUIRE(bucket >= 0 && bucket < N_CLASSES, "no such filter bucket");
+    MT_REQUIRE(bucket >= 0 && bucket < N_BUCKETS, "no such filter bucket");
     std::lock_guard<std::mutex> g(g_tune_mu);
     const BucketDesc &d = BUCKETS[bucket];
     out.name = d.name;
@@ -1133,7 +1180,7 @@ void tune_info(int bucket, mt_tune_bucket &out) {
 }
 
 void tune_set(int bucket, int variant) {
-    MT_REQUIRE(bucket >= 0 && bucket < N_CLASSES, "no such filter bucket");
+    MT_REQUIRE(bucket >= 0 && bucket < N_BUCKETS, "no such filter bucket");
     MT_REQUIRE(variant_ok(bucket, variant), "variant not available for this bucket");
     std::lock_guard<std::mutex> g(g_tune_mu);
     g_variant[bucket] = variant;
@@ -1141,7 +1188,7 @@ void tune_set(int bucket, int variant) {
 
 void tune_reset() {
     std::lock_guard<std::mutex> g(g_tune_mu);
-    for (int c = 0; c < N_CLASSES; c++) {
+    for (int c = 0; c < N_BUCKETS; c++) {
         g_variant[c] = DEFAULT_VARIANT[c];
         for (int v = 0; v < 6; v++) g_tune_ms[c][v] = 0;
         g_tune_pairs[c] = 0;

@@ -977,7 +977,7 @@ static void enqueue_fused(const FusedLaunch &L, Timer *tm, hipStream_t s) {
     fa.flags = a.flags;
     fa.seq = a.seq;
     fa.seq_total = a.total;
-    fa.read_n = a.read_n;
+    fa.read_has_n = a.read_n;
     fa.gate = a.gate;
     // the largest E a fused read can have: E is fixed, or grows with the length
     const u64 maxE = a.e_mode == MT_E_FIXED           ? a.e_value

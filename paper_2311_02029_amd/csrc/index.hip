@@ -25,7 +25,7 @@
 namespace mt {
 
 __global__ void k_genome_meta(const u64 *__restrict__ off, u64 n, const u64 *__restrict__ blk_off,
-                              const u32 *__restrict__ has_n, const u32 *__restrict__ taxon, u64 *__restrict__ glen,
+                              const u8 *__restrict__ has_n, const u32 *__restrict__ taxon, u64 *__restrict__ glen,
                               GenomeMeta *__restrict__ meta) {
     u64 g = (u64)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= n) return;
@@ -174,7 +174,7 @@ void build_index(mt_index &ix, const mt_index_params &p, const mt_seqs &g, const
     DBuf<u32> flags(1);
     MT_HIP(hipMemsetAsync(flags.p, 0, sizeof(u32), s));
     ix.has_n.alloc(g.n);
-    MT_HIP(hipMemsetAsync(ix.has_n.p, 0, (g.n ? g.n : 1) * sizeof(u32), s));
+    MT_HIP(hipMemsetAsync(ix.has_n.p, 0, g.n ? g.n : 1, s));
     pack_sequences(g, 4294901759ull, ERR_READ_TOO_LONG, "genome length must be below 2^32 - 2^16", ix.ref,
                    flags.p, ix.has_n.p, s);
     ix.taxon.alloc(g.n);
@@ -254,7 +254,7 @@ void build_index(mt_index &ix, const mt_index_params &p, const mt_seqs &g, const
 
 u64 index_device_bytes(const mt_index &ix) {
     return ix.ref.lohi.n * sizeof(u64x2) + ix.ref.nb.n * sizeof(u64) + ix.ref.blk_off.n * sizeof(u64) +
-           ix.glen.n * sizeof(u64) + ix.has_n.n * sizeof(u32) + ix.taxon.n * sizeof(u32) +
+           ix.glen.n * sizeof(u64) + ix.has_n.n + ix.taxon.n * sizeof(u32) +
            ix.meta.n * sizeof(GenomeMeta) +
            ix.table.n * sizeof(u64x2) + ix.occ.n * sizeof(u64);
 }

@@ -10,7 +10,7 @@ struct mt_index {
     uint64_t n_minimizers = 0, n_keys = 0, n_multi_occ = 0;
     mt::PackedSeqs ref;          // reference bit planes, genome g at block ref.blk_off[g]
     mt::DBuf<mt::u64> glen;      // genome lengths
-    mt::DBuf<mt::u32> has_n;     // 1 if the genome contains N
+    mt::DBuf<mt::u8> has_n;      // 1 if the genome contains N
     mt::DBuf<mt::u32> taxon;     // taxon of each genome
     mt::DBuf<GenomeMeta> meta;   // per-genome record used by the filter
     mt::DBuf<u64x2> table;     // nbuckets * 4 slots {k-mer, value}

@@ -39,7 +39,7 @@ __global__ __launch_bounds__(256) void k_pack(const u8 *__restrict__ seq, const 
                                               const u64 *__restrict__ blk_off, u64 n, u64 total, u64 cap,
                                               const u32 *__restrict__ map, u64x2 *__restrict__ lohi,
                                               u64 *__restrict__ nbp, u32 *__restrict__ flags,
-                                              u32 *__restrict__ has_n) {
+                                              u8 *__restrict__ has_n) {
     const u64 t = (u64)blockIdx.x * 256 + threadIdx.x;
     const u64 b = t >> 2;
     const u32 quarter = (u32)t & 3u;
@@ -83,7 +83,7 @@ __global__ __launch_bounds__(256) void k_pack(const u8 *__restrict__ seq, const 
 }
 
 void pack_sequences(const mt_seqs &in, u64 len_limit, u32 len_flag, const char *len_message, PackedSeqs &out,
-                    u32 *d_flags, u32 *has_n, hipStream_t s) {
+                    u32 *d_flags, u8 *has_n, hipStream_t s) {
     out.n = in.n;
     out.blk_off.alloc(in.n + 1);
     out.blocks_cap = in.total / 64 + 2 * in.n + 1;

@@ -21,7 +21,7 @@ struct PackedSeqs {
 // ERR_BAD_BYTE in d_flags; has_n (nullable, n entries, zeroed by the caller)
 // receives 1 for sequences containing N.
 void pack_sequences(const mt_seqs &in, u64 len_limit, u32 len_flag, const char *len_message, PackedSeqs &out,
-                    u32 *d_flags, u32 *has_n, hipStream_t s);
+                    u32 *d_flags, u8 *has_n, hipStream_t s);
 
 // Tiled minimizer extraction.  plan() sizes the tiles and counts the
 // minimizers of every tile; after the caller has read n_tiles / n_min back

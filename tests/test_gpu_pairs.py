@@ -96,3 +96,68 @@ def test_pair_counts_around_blocks(mt, case, n):
     sel = np.random.default_rng(n).integers(0, len(case["pairs"][0]), n)
     ap, ac = _run(mt, case, sel)
     assert np.array_equal(ap, case["want"][0][0][sel]) and np.array_equal(ac, case["want"][0][1][sel])
+
+
+# ------------------------------------------------------------- long pairs --
+
+@pytest.fixture(scope="module")
+def long_case(mt):
+    """Long reads with E above 31: exact copies (runs past every staged segment),
+    reads with errors, with one N, with a long deletion; windows past both genome
+    ends, wrong places, and E on both sides of the limits of the staged bands."""
+    rng = np.random.default_rng(17)
+    clean = synth.ACGT[synth.random_codes(rng, 30_000)]
+    dirty = synth.ACGT[synth.random_codes(rng, 20_000)].copy()
+    dirty[rng.integers(0, 20_000, 15)] = ord("N")
+    genomes = [clean, dirty, clean[:500]]
+    ga = synth.SeqSet.from_list([g.tobytes() for g in genomes])
+    reads, rows = [], []
+    for m in (1, 40, 300, 1000, 1900, 2500, 2600, 5000, 9000):
+        for g, start in ((0, 5000), (0, 0), (0, 30_000 - m), (1, 3000)):
+            for kind in ("exact", "errors", "n", "deletion"):
+                body = genomes[g][start:start + m].copy()
+                if kind == "errors":
+                    hit = rng.random(m) < 0.05
+                    body[hit] = synth.ACGT[rng.integers(0, 4, int(hit.sum()))]
+                elif kind == "n":
+                    body[m // 2] = ord("N")
+                elif kind == "deletion" and m > 200:
+                    body = np.concatenate([body[:m // 3], body[m // 3 + 30:]])
+                reads.append(body.tobytes())
+                Es = (32, 100, 303, 599, 600, 601, 1439, 1440, 1441) if m <= 2600 else (32, 250, 600, 601)
+                for E in Es:
+                    rows.append((len(reads) - 1, g, start, E))
+                rows.append((len(reads) - 1, 0, int(rng.integers(0, 20_000)), 60))
+                rows.append((len(reads) - 1, g, start - 40, 50))
+                rows.append((len(reads) - 1, 2, -10, 45))
+                rows.append((len(reads) - 1, 0, 29_990, 77))
+    rs = synth.SeqSet.from_list(reads)
+    r = np.array(rows, np.int64)
+    arr = (r[:, 0].astype(np.uint32), r[:, 1].astype(np.uint32), r[:, 2].copy(), r[:, 3].astype(np.uint16))
+    return dict(ga=ga, ix=mt.Index(ga, 15, 10), rs=rs, dr=mt.to_device(rs), pairs=arr,
+                want=[oracle.Index(ga, 15, 10).filter_pairs(rs, *arr)])
+
+
+@pytest.mark.parametrize("variant", range(5))
+def test_long_pairs_in_segments(mt, long_case, variant):
+    mt.tune_reset()
+    try:
+        for bucket in range(3, 7):
+            try:
+                mt.tune_set(bucket, variant)
+            except mt.MTError:
+                pass  # past the bucket's limit: the default runs
+        ap, ac = _run(mt, long_case, np.arange(len(long_case["pairs"][0])))
+    finally:
+        mt.tune_reset()
+    bad = np.flatnonzero(ap != long_case["want"][0][0])
+    assert len(bad) == 0, [tuple(int(a[i]) for a in long_case["pairs"]) + (int(ap[i]),) for i in bad[:5]]
+    assert np.array_equal(ac, long_case["want"][0][1])
+
+
+def test_one_long_pair_per_bucket_alone(mt, long_case):
+    """A single pair leaves every other group of its wavefront without one."""
+    for i in range(0, len(long_case["pairs"][0]), 97):
+        sel = np.array([i])
+        ap, ac = _run(mt, long_case, sel)
+        assert ap[0] == long_case["want"][0][0][i], i
