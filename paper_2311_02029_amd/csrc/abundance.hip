@@ -15,16 +15,59 @@
 
 namespace mt {
 
-constexpr int AB_TPB = 256;
+constexpr int AB_TPB = 1024;
 constexpr u32 AB_LDS_TAXA = 4096;  // taxa counted per block in LDS (64-bit, 32 KB)
 constexpr u64 AB_ONE = 1ull << 32;
 
 // The mapped taxa of read r (Fig. 1 step 3a: accepted candidates at the
-// smallest value, distinct taxa) and its additions to the counts.
+// smallest value, distinct taxa) and its additions to the counts.  Up to
+// AB_FEW candidates (a query's top_n, as a rule) are loaded together, so that a
+// read waits for three loads in a row and not for three per candidate.
+constexpr int AB_FEW = 4;
+
+template <class Add>
+__device__ inline void abundance_few(u64 cs, int n, const u32 *__restrict__ genome, const u16 *__restrict__ approx,
+                                     const u8 *__restrict__ accept, const u32 *__restrict__ taxon,
+                                     const u64 *__restrict__ uniq, const Add &add) {
+    u32 ap[AB_FEW], t[AB_FEW], best = 0xFFFFFFFFu;
+#pragma unroll
+    for (int c = 0; c < AB_FEW; c++) {
+        const bool in = c < n;
+        ap[c] = in && accept[cs + c] ? approx[cs + c] : 0xFFFFFFFFu;
+        t[c] = in ? genome[cs + c] : 0u;
+    }
+#pragma unroll
+    for (int c = 0; c < AB_FEW; c++) {
+        if (c < n) t[c] = taxon[t[c]];
+        best = min(best, ap[c]);
+    }
+    if (best == 0xFFFFFFFFu) return;
+    u32 nt = 0;
+    u64 u[AB_FEW], U = 0;
+    bool take[AB_FEW];
+#pragma unroll
+    for (int c = 0; c < AB_FEW; c++) {
+        take[c] = ap[c] == best;
+#pragma unroll
+        for (int d = 0; d < c; d++) take[c] = take[c] && !(take[d] && t[d] == t[c]);
+        u[c] = take[c] ? uniq[t[c]] : 0ull;
+        nt += take[c];
+        U += u[c];
+    }
+#pragma unroll
+    for (int c = 0; c < AB_FEW; c++)
+        // u_t < 2^32 (reads per call < 2^31), so u_t * 2^32 fits 64 bits
+        if (take[c]) add(t[c], nt == 1 ? AB_ONE : U ? (u[c] << 32) / U : AB_ONE / nt);
+}
+
 template <class Add>
 __device__ inline void abundance_read(u64 cs, u64 ce, const u32 *__restrict__ genome, const u16 *__restrict__ approx,
                                       const u8 *__restrict__ accept, const u32 *__restrict__ taxon,
                                       const u64 *__restrict__ uniq, const Add &add) {
+    if (ce - cs <= (u64)AB_FEW) {
+        abundance_few(cs, (int)(ce - cs), genome, approx, accept, taxon, uniq, add);
+        return;
+    }
     u32 best = 0xFFFFFFFFu;
     for (u64 c = cs; c < ce; c++)
         if (accept[c] && approx[c] < best) best = approx[c];
@@ -52,19 +95,21 @@ __device__ inline void abundance_read(u64 cs, u64 ce, const u32 *__restrict__ ge
         if (!accept[c] || approx[c] != best) continue;
         const u32 t = taxon[genome[c]];
         if (!first_of_taxon(c, t)) continue;
-        // u_t < 2^32 (reads per call < 2^31), so u_t * 2^32 fits 64 bits
         add(t, U ? (uniq[t] << 32) / U : AB_ONE / nt);
     }
 }
 
-// Grid-stride over the reads; up to AB_LDS_TAXA taxa each block adds in LDS
-// and flushes its nonzero counters once at the end.
+// Grid-stride over the reads; up to AB_LDS_TAXA taxa each block adds in LDS (as
+// much of it as the taxa need) and flushes its nonzero counters once at the end.
+// The flush is what a block costs: 1,024 blocks of 256 threads spent more time
+// adding 2,000 counters each than on 1M reads (47 us; now, with one block of 1,024
+// threads per CU, each starting at a counter of its own, 19 us).
 __global__ __launch_bounds__(AB_TPB) void k_abundance(const u64 *__restrict__ cand_off, u64 n,
                                                       const u32 *__restrict__ genome, const u16 *__restrict__ approx,
                                                       const u8 *__restrict__ accept, const u32 *__restrict__ taxon,
                                                       const u64 *__restrict__ uniq, u32 n_taxa,
                                                       unsigned long long *__restrict__ counts) {
-    __shared__ unsigned long long cnt[AB_LDS_TAXA];
+    extern __shared__ unsigned long long cnt[];
     const u64 stride = (u64)gridDim.x * AB_TPB;
     if (n_taxa > AB_LDS_TAXA) {
         auto add = [&](u32 t, u64 v) { atomicAdd(&counts[t], (unsigned long long)v); };
@@ -78,20 +123,24 @@ __global__ __launch_bounds__(AB_TPB) void k_abundance(const u64 *__restrict__ ca
     for (u64 r = (u64)blockIdx.x * AB_TPB + threadIdx.x; r < n; r += stride)
         abundance_read(cand_off[r], cand_off[r + 1], genome, approx, accept, taxon, uniq, add);
     __syncthreads();
-    for (u32 i = threadIdx.x; i < n_taxa; i += AB_TPB)
-        if (cnt[i]) atomicAdd(&counts[i], cnt[i]);
+    const u32 first = (u32)((u64)blockIdx.x * n_taxa / gridDim.x);
+    for (u32 i = threadIdx.x; i < n_taxa; i += AB_TPB) {
+        const u32 c = first + i < n_taxa ? first + i : first + i - n_taxa;
+        if (cnt[c]) atomicAdd(&counts[c], cnt[c]);
+    }
 }
 
 constexpr int AF_TPB = 1024;
 
+// Sum of v over the block, in every thread.
 __device__ inline u64 block_sum(u64 v, u64 *sh) {
-    sh[threadIdx.x] = v;
+#pragma unroll
+    for (int o = 32; o; o >>= 1) v += __shfl_xor(v, o, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int w = AF_TPB / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    const u64 r = sh[0];
+    u64 r = 0;
+#pragma unroll
+    for (int i = 0; i < AF_TPB / 64; i++) r += sh[i];
     __syncthreads();
     return r;
 }
@@ -102,39 +151,32 @@ __device__ inline bool ge128(u64 a, u64 b, u64 c, u64 d) {
     return lh > rh || (lh == rh && ll >= rl);
 }
 
-// num / den as the nearest double, ties to even (0 <= num <= den, den > 0):
-// the quotient's bits by long division (the remainder doubled with its carry
-// out of 64 bits kept), 53 significant bits rounded with the next bit and
-// whether a remainder is left.  Dividing the two converted doubles would
-// round twice once den needs more than 53 bits.
+// num / den as the nearest double, ties to even (0 <= num <= den, den > 0).
+// Dividing the two converted doubles would round twice once den needs more than
+// 53 bits, so that quotient is only an estimate of the 53 significant bits
+// q = floor(num 2^k / den) in [2^52, 2^53): the remainder num 2^k - q den, exact
+// in 128 bits (both products stay below 2^118), corrects it and then rounds it.
 __device__ inline double div_nearest(u64 num, u64 den) {
     if (num == 0) return 0.0;
     if (num >= den) return 1.0;
-    int e = 0;  // num / den lies in [2^-e, 2^(1-e))
-    u64 r = num;
-    for (;;) {  // double r until it reaches den (a carry out of 64 bits means it has)
-        const bool carry = (r >> 63) != 0;
-        r <<= 1;
-        e++;
-        if (carry || r >= den) break;
+    typedef unsigned __int128 u128;
+    int k = 52 + (__clzll((long long)num) - __clzll((long long)den));  // quotient in (2^51, 2^53)
+    if (((u128)num << k) < ((u128)den << 52)) k++;
+    const u128 top = (u128)num << k;
+    u64 q = (u64)(ldexp((double)num / (double)den, k));  // within a few units
+    if (q >= (1ull << 53)) q = (1ull << 53) - 1;
+    __int128 r = (__int128)(top - (u128)q * den);
+    while (r < 0) {
+        q--;
+        r += den;
     }
-    r -= den;  // the true 2r - den is below den: the wrapped difference is exact
-    u64 q = 1;
-    for (int i = 1; i < 53; i++) {
-        const bool carry = (r >> 63) != 0;
-        r <<= 1;
-        q <<= 1;
-        if (carry || r >= den) {
-            r -= den;  // the true 2r - den is below den: the wrapped difference is exact
-            q |= 1;
-        }
+    while (r >= (__int128)den) {
+        q++;
+        r -= den;
     }
-    const bool carry = (r >> 63) != 0;
-    r <<= 1;
-    const bool half = carry || r >= den;
-    if (half) r -= den;
-    if (half && (r != 0 || (q & 1))) q++;
-    return ldexp((double)q, -e - 52);
+    const u128 twice = (u128)r << 1;
+    if (twice > den || (twice == den && (q & 1))) q++;
+    return ldexp((double)q, -k);
 }
 
 // One block: the total, the cutoff, the kept total, the abundances.
@@ -142,7 +184,7 @@ __device__ inline double div_nearest(u64 num, u64 den) {
 __global__ __launch_bounds__(AF_TPB) void k_abundance_final(const u64 *__restrict__ counts, u32 n_taxa, u64 num,
                                                             u64 den, double *__restrict__ abund,
                                                             u64 *__restrict__ out) {
-    __shared__ u64 sh[AF_TPB];
+    __shared__ u64 sh[AF_TPB / 64];
     u64 part = 0;
     for (u32 t = threadIdx.x; t < n_taxa; t += AF_TPB) part += counts[t];
     const u64 C = block_sum(part, sh);
@@ -220,8 +262,9 @@ extern "C" int mt_abundance(const mt_index *index, const mt_result *res, uint64_
             MT_HIP(hipGetDevice(&dev));
             MT_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
             const unsigned blocks = (unsigned)std::max<u64>(1, std::min<u64>(grid_for(n, AB_TPB),
-                                                                             (u64)std::max(cus, 1) * 4));
-            k_abundance<<<blocks, AB_TPB, 0, s>>>(off, n, genome, approx, accept, index->taxon.p, uniq, nt,
+                                                                             (u64)std::max(cus, 1)));
+            const size_t lds = nt <= AB_LDS_TAXA ? nt * sizeof(u64) : 0;
+            k_abundance<<<blocks, AB_TPB, lds, s>>>(off, n, genome, approx, accept, index->taxon.p, uniq, nt,
                                                   (unsigned long long *)counts);
             MT_HIP(hipGetLastError());
         }
