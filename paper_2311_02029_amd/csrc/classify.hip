@@ -818,7 +818,17 @@ __global__ void k_strand_merge_done(const u64 *__restrict__ cand_off2, u64 n, co
     read_E[r] = read_E2[r];
 }
 
-// Both strands with the obstacle walk in a fused mode: the fused kernel over
+// The fused form serves the fused modes, and the filters other than the obstacle
+// walk in every mode: they have no one-launch-per-step form to keep apart.  A graph
+// holds the obstacle walk only.
+static bool takes_fused(const mt_query_params &q) {
+    return q.mode != MT_MODE_PER_STAGE || q.filter != MT_FILTER_OBSTACLE;
+}
+static bool takes_graph(const mt_query_params &q) {
+    return q.mode == MT_MODE_FUSED_GRAPH && q.filter == MT_FILTER_OBSTACLE;
+}
+
+// Both strands in the fused form: the fused kernels over
 // the two-strand read set (each orientation keeps its own top_n and is
 // filtered), then one merge per read and the reduce per read.
 static void both_strands_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs &two, ReadBatch &rb,
@@ -828,7 +838,7 @@ static void both_strands_fused(const mt_index &ix, const mt_query_params &q, con
     q1.strands = 1;
     mt_result r2;
     mt_result_init(r2, two.n, ix.n_taxa, s);
-    classify_fused(ix, q1, two, rb, r2, tm, s, q.mode == MT_MODE_FUSED_GRAPH);
+    classify_fused(ix, q1, two, rb, r2, tm, s, takes_graph(q));
     DBuf<u32> nmerged(n);
     if (n) {
         k_strand_count_done<<<grid_for(n, 256), 256, 0, s>>>(r2.cand_off.p, n, q.top_n, nmerged.p);
@@ -851,10 +861,10 @@ static void both_strands_fused(const mt_index &ix, const mt_query_params &q, con
     res.n_cands = total;
 }
 
-// Both strands: reads and their reverse complements as one read set.  The
-// obstacle walk in a fused mode goes through the fused kernel; otherwise the
-// per-stage seeding and counting over the two-strand set, one merge per read,
-// then the filter on the oriented sequences and the reduce per read.
+// Both strands: reads and their reverse complements as one read set.  The fused
+// form goes through the fused kernels; otherwise the per-stage seeding and counting
+// over the two-strand set, one merge per read, then the filter on the oriented
+// sequences and the reduce per read.
 static void classify_both_strands(const mt_index &ix, const mt_query_params &q, const mt_seqs &reads,
                                   ReadBatch &rb, mt_result &res, Timer &tm, hipStream_t s) {
     const u64 n = reads.n;
@@ -880,7 +890,7 @@ static void classify_both_strands(const mt_index &ix, const mt_query_params &q, 
         MT_HIP(hipGetLastError());
     }
     const mt_seqs two{(const char *)seq2.p, off2.p, 2 * n, 2 * reads.total};
-    if (q.mode != MT_MODE_PER_STAGE && q.filter == MT_FILTER_OBSTACLE) {
+    if (takes_fused(q)) {
         tm.mark("pack");
         both_strands_fused(ix, q, two, rb, res, tm, s);
         return;
@@ -1013,8 +1023,8 @@ extern "C" int mt_classify(const mt_index *index, const mt_query_params *params,
             tm.begin(s);
             mt::mt_result_init(*res, reads->n, index->n_taxa, s);
             mt::ReadBatch rb;
-            if (params->mode != MT_MODE_PER_STAGE)
-                mt::classify_fused(*index, *params, *reads, rb, *res, tm, s, params->mode == MT_MODE_FUSED_GRAPH);
+            if (mt::takes_fused(*params))
+                mt::classify_fused(*index, *params, *reads, rb, *res, tm, s, mt::takes_graph(*params));
             else
                 mt::classify_staged(*index, *params, *reads, rb, *res, tm, s);
             mt::last_stats().n_cands = res->n_cands;

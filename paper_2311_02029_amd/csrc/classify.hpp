@@ -94,8 +94,9 @@ struct FilterArgs {
 // then each bucket runs the kernel shaped for it.  fixed_E: the E of every
 // pair when the caller knows it, else -1; pairs of one short E need no buckets.
 void launch_filter(const FilterArgs &a, u64 n_cap, int fixed_E, hipStream_t s, Timer *tm = nullptr);
-// Pairs [0, *n_dev) of the fused form (at most cap), every E at most max_E <= 31.
-void launch_filter_fused(const FilterArgs &a, u64 cap, int max_E, hipStream_t s);
+// Pairs [0, *n_dev) of the fused form (at most cap), every E at most max_E <= 31,
+// through filter kind.
+void launch_filter_fused(const FilterArgs &a, u64 cap, int max_E, u32 kind, hipStream_t s);
 // Pairs [0, count) through the Hamming (MT_FILTER_HAMMING), base-counting
 // (MT_FILTER_BASE_COUNT), q-gram (MT_FILTER_QGRAM) or shifted Hamming (MT_FILTER_SHD)
 // filter; count = *n_dev if set, else n_host, at most n.

@@ -443,15 +443,26 @@ __device__ inline Bits64 ascii_block(const FilterArgs &a, u64 at, int cnt) {
                   nb[0] | nb[1] << 16 | (u64)(nb[2] | nb[3] << 16) << 32};
 }
 
+// Block b of a read, from block rb of the planes or byte rb of the ASCII.
+template <bool kAscii>
+__device__ inline Bits64 read_block(const FilterArgs &a, u64 rb, int b, int m) {
+    if constexpr (kAscii) {
+        return ascii_block(a, rb + 64 * (u64)b, m - 64 * b);
+    } else {
+        const u64x2 x = a.read_lohi[rb + b];
+        return Bits64{x.lo, x.hi, a.read_nb[rb + b]};
+    }
+}
+
 // Stages the lane's pair (nbr read blocks, from block rb of the planes or byte
-// rb of the ASCII; nbw window blocks from b0 of its genome) at S and walks it.
-template <int R, int NC, bool kN, bool kAscii>
-__device__ inline int lane_pair(const FilterArgs &a, u32 *S, u64 rb, int nbr, const GenomeMeta &gm, i64 b0, int nbw,
-                                int wofs, int m, int E) {
+// rb of the ASCII; nbw window blocks from b0 of its genome) at S.
+template <bool kN, bool kAscii>
+__device__ inline LdsPair stage_pair(const FilterArgs &a, u32 *S, u64 rb, int nbr, const GenomeMeta &gm, i64 b0,
+                                     int nbw, int m) {
     u64 *q = (u64 *)S;
     for (int b = 0; b < nbr; b++) {
-        if constexpr (kAscii) {
-            const Bits64 x = ascii_block(a, rb + 64 * (u64)b, m - 64 * b);
+        if constexpr (kAscii || kN) {
+            const Bits64 x = read_block<kAscii>(a, rb, b, m);
             q[b] = x.lo;
             q[nbr + b] = x.hi;
             if (kN) q[2 * nbr + b] = x.nb;
@@ -459,7 +470,6 @@ __device__ inline int lane_pair(const FilterArgs &a, u32 *S, u64 rb, int nbr, co
             const u64x2 x = a.read_lohi[rb + b];
             q[b] = x.lo;
             q[nbr + b] = x.hi;
-            if (kN) q[2 * nbr + b] = a.read_nb[rb + b];
         }
     }
     u64 *w = q + (kN ? 3 : 2) * nbr;
@@ -477,12 +487,25 @@ __device__ inline int lane_pair(const FilterArgs &a, u32 *S, u64 rb, int nbr, co
             w[nbw + b] = x.hi;
         }
     }
-    return lane_walk<R, NC, kN>(LdsPair(S, nbr, (const u32 *)w, nbw), wofs, m, E);
+    return LdsPair(S, nbr, (const u32 *)w, nbw);
 }
+
+// A filter that k_filter_lane runs on a staged pair: the obstacle walk with its
+// rows in R words, surviving NC columns ...
+template <int R, int NC>
+struct WalkFilter {
+    static constexpr int MAX_M = 1 << 16;
+    template <bool kN>
+    __device__ static int value(const LdsPair &P, int wofs, int m, int E) {
+        return lane_walk<R, NC, kN>(P, wofs, m, E);
+    }
+    // a pair that does not fit in LDS, by the whole wavefront
+    __device__ static int by_wave(const PairView &v, int E, int lane) { return obstacle_walk<64>(v, E, lane); }
+};
 
 // kAscii: the fused form's pairs, reads of at most 320 bases as ASCII (no pair
 // is too long for the LDS).
-template <int R, int NC, bool kAscii>
+template <class F, bool kAscii>
 __global__ __launch_bounds__(LANE_TPB) void k_filter_lane(FilterArgs a, const u32 *__restrict__ idx, u64 n) {
     __shared__ __align__(16) u32 lds[LANE_TPB / 64][LANE_DW + LANE_PAD];
     if (kAscii && *a.gate) return;
@@ -516,8 +539,9 @@ __global__ __launch_bounds__(LANE_TPB) void k_filter_lane(FilterArgs a, const u3
     int c = 0;
     const u64 any_n = __ballot(with_n);
     const int need = (any_n ? 6 : 4) * (nbr + nbw);
-    u64 todo = __ballot(ok && m > 0 && need <= LANE_DW);
-    u64 big = __ballot(ok && need > LANE_DW);
+    const bool fits = need <= LANE_DW && m <= F::MAX_M;
+    u64 todo = __ballot(ok && m > 0 && fits);
+    u64 big = __ballot(ok && !fits);
     while (todo) {
         int end = ((todo >> lane) & 1) ? need : 0;  // inclusive prefix sum of the lanes left
         const int mine = end;
@@ -528,10 +552,11 @@ __global__ __launch_bounds__(LANE_TPB) void k_filter_lane(FilterArgs a, const u3
         }
         const bool now = mine && end <= LANE_DW;
         if (now) {
+            u32 *at = S + (end - mine);
             if (any_n)
-                c = lane_pair<R, NC, true, kAscii>(a, S + (end - mine), rb, nbr, gm, b0, nbw, wofs, m, E);
+                c = F::template value<true>(stage_pair<true, kAscii>(a, at, rb, nbr, gm, b0, nbw, m), wofs, m, E);
             else
-                c = lane_pair<R, NC, false, kAscii>(a, S + (end - mine), rb, nbr, gm, b0, nbw, wofs, m, E);
+                c = F::template value<false>(stage_pair<false, kAscii>(a, at, rb, nbr, gm, b0, nbw, m), wofs, m, E);
         }
         todo &= ~__ballot(now);
         lds_wave_sync();
@@ -550,7 +575,7 @@ __global__ __launch_bounds__(LANE_TPB) void k_filter_lane(FilterArgs a, const u3
         v.L = (i64)wm.len;
         v.has_n = meta_has_n(wm);
         v.diag = __shfl(diag, l, 64);
-        const int wc = obstacle_walk<64>(v, __shfl(E, l, 64), lane);
+        const int wc = F::by_wave(v, __shfl(E, l, 64), lane);
         if (lane == l) c = wc;
     }
     if (!in) return;
@@ -781,8 +806,8 @@ static void launch_short(const FilterArgs &a, const u32 *idx, u64 cnt, int bucke
     if (cnt == 0) return;
     if (bucket < CLS_LONG && v == 0) {
         const unsigned blocks = grid_for(cnt, LANE_TPB);
-        if (bucket < 2) k_filter_lane<1, 6, false><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
-        else k_filter_lane<2, 7, false><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
+        if (bucket < 2) k_filter_lane<WalkFilter<1, 6>, false><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
+        else k_filter_lane<WalkFilter<2, 7>, false><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
     } else if (bucket == 0 && v == 1) {
         k_filter<32><<<grid_for(cnt * 32, 256), 256, 0, s>>>(a, idx, cnt);
     } else {
@@ -855,9 +880,10 @@ static void bucket_pairs(const FilterArgs &a, u64 n_cap, DBuf<u32> &idx, u32 hc[
 // (base counting) compares the counts of A, C, G and T in the read and in the
 // reference window [diag, diag + m) (N and positions outside the genome are no
 // base) and reports ceil(L1 / 2).  Both saturate at E + 1.
-template <int KIND>
+template <int KIND, bool kAscii>
 __global__ void k_filter_simple(FilterArgs a, u64 n_cap) {
     const u64 p = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+    if (kAscii && *a.gate) return;
     if (p >= pair_count(a, n_cap)) return;
     u32 r, g, err;
     int E;
@@ -870,7 +896,7 @@ __global__ void k_filter_simple(FilterArgs a, u64 n_cap) {
         return;
     }
     const int m = read_len(a, r);
-    const u64 rb = a.read_blk[r];
+    const u64 rb = kAscii ? a.read_off[r] : a.read_blk[r];
     const GenomeMeta gm = a.meta[g];
     const u64x2 *rl = a.ref_lohi + gm.blk;
     const u64 *rn = a.ref_nb + gm.blk;
@@ -880,8 +906,8 @@ __global__ void k_filter_simple(FilterArgs a, u64 n_cap) {
     int c = 0;
     int dA = 0, dC = 0, dG = 0, dT = 0;  // read count minus window count per base
     for (int w0 = 0; w0 < m; w0 += 64) {
-        const u64x2 q = a.read_lohi[rb + (u64)(w0 >> 6)];
-        const u64 qn = a.read_nb[rb + (u64)(w0 >> 6)];
+        const Bits64 q = read_block<kAscii>(a, rb, w0 >> 6, m);
+        const u64 qn = q.nb;
         const int left = m - w0;
         const u64 vm = left >= 64 ? ~0ull : (1ull << left) - 1;
         const Bits64 wb = fetch_ref(rl, rn, L, hn, diag + w0);
@@ -912,7 +938,9 @@ __global__ void k_filter_simple(FilterArgs a, u64 n_cap) {
 constexpr int QG_Q = 5;
 constexpr int QG_WPB = 4;
 
+template <bool kAscii>
 __global__ __launch_bounds__(64 * QG_WPB) void k_filter_qgram(FilterArgs a, u64 n_cap) {
+    if (kAscii && *a.gate) return;
     const u64 n = pair_count(a, n_cap);
     __shared__ int cnt_all[QG_WPB][1 << (2 * QG_Q)];
     const int lane = threadIdx.x & 63;
@@ -954,13 +982,15 @@ __global__ __launch_bounds__(64 * QG_WPB) void k_filter_qgram(FilterArgs a, u64 
             if ((b.nb & QMASK) == 0) atomicAdd(&cnt[kmer_value(b.lo, b.hi, QG_Q)], 1);
         }
         lds_wave_sync();
-        const u64 rb = a.read_blk[r];
+        const u64 rb = kAscii ? a.read_off[r] : a.read_blk[r];
         int shared = 0;
         for (int j0 = 0; j0 <= m - QG_Q; j0 += 64) {
             const int j = j0 + lane;
             bool took = false;
             if (j <= m - QG_Q) {
-                const Bits64 b = fetch_planes(a.read_lohi + rb, a.read_nb + rb, j);
+                Bits64 b;
+                if constexpr (kAscii) b = ascii_block(a, rb + j, min(QG_Q, 16));
+                else b = fetch_planes(a.read_lohi + rb, a.read_nb + rb, j);
                 if ((b.nb & QMASK) == 0) took = atomicSub(&cnt[kmer_value(b.lo, b.hi, QG_Q)], 1) > 0;
             }
             shared += __popcll(__ballot(took));
@@ -975,22 +1005,10 @@ __global__ __launch_bounds__(64 * QG_WPB) void k_filter_qgram(FilterArgs a, u64 
     }
 }
 
-// Shifted Hamming distance (Table 1's SHD), one thread per pair.  Row d's
-// mismatch word w covers columns 64w .. 64w+63 (zero at columns >= m); in
-// each row, a run of one or two zeros with a one on both sides (inside the
-// read) becomes ones; the value is the number of columns where every amended
-// row is one, saturated at E + 1.
-__device__ inline u64 shd_word(const FilterArgs &a, u64 rb, int m, const u64x2 *rl, const u64 *rn, i64 L, bool hn,
-                               i64 diag, int d, int w) {
-    if (w < 0 || 64 * w >= m) return 0;
-    const u64x2 q = a.read_lohi[rb + (u64)w];
-    const u64 qn = a.read_nb[rb + (u64)w];
-    const Bits64 r = fetch_ref(rl, rn, L, hn, diag + d + 64 * (i64)w);
-    const int left = m - 64 * w;
-    const u64 vm = left >= 64 ? ~0ull : (1ull << left) - 1;
-    return ((q.lo ^ r.lo) | (q.hi ^ r.hi) | qn | r.nb) & vm;
-}
-
+// Shifted Hamming distance (Table 1's SHD).  Row d's mismatch word w covers
+// columns 64w .. 64w+63 (zero at columns >= m); in each row, a run of one or two
+// zeros with a one on both sides (inside the read) becomes ones; the value is the
+// number of columns where every amended row is one, saturated at E + 1.
 // Word x of a row with its neighbours xp (columns before) and xn (after),
 // short zero runs between ones set.
 __device__ inline u64 shd_amend(u64 xp, u64 x, u64 xn) {
@@ -1002,70 +1020,87 @@ __device__ inline u64 shd_amend(u64 xp, u64 x, u64 xn) {
     return x | one | first | second;
 }
 
-__global__ void k_filter_shd(FilterArgs a, u64 n_cap) {
-    const u64 p = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= pair_count(a, n_cap)) return;
-    u32 r, g, err;
-    int E;
-    bool ok;
-    pair_fields(a, p, r, g, E, ok, err);
-    if (!ok) {
-        atomicOr(a.flags, err);
-        a.approx[p] = 0xFFFF;
-        a.accept[p] = 0;
-        return;
-    }
-    const int m = read_len(a, r);
-    const u64 rb = a.read_blk[r];
-    const GenomeMeta gm = a.meta[g];
-    const u64x2 *rl = a.ref_lohi + gm.blk;
-    const u64 *rn = a.ref_nb + gm.blk;
-    const i64 L = (i64)gm.len;
-    const bool hn = meta_has_n(gm);
-    const i64 diag = a.pair_diag[p];
-    int c = 0;
-    if (m <= 256) {  // the whole read in four words: rows outer, four accumulators
-        u64 acc[4];
+// ... and SHD, for k_filter_lane: rows outer, the read's words in registers.  Bound
+// by VALU issue (about 25 operations a row and word); 250k pairs of 100 bases at
+// E = 5: 74 us with each row word fetched from global memory, SHD_US us staged.
+struct ShdFilter {
+    static constexpr int WORDS = 5, MAX_M = 64 * WORDS;
+    template <bool kN>
+    __device__ static int value(const LdsPair &P, int wofs, int m, int E) {
+        u64 acc[WORDS];
 #pragma unroll
-        for (int w = 0; w < 4; w++) {
+        for (int w = 0; w < WORDS; w++) {
             const int left = m - 64 * w;
             acc[w] = left >= 64 ? ~0ull : left > 0 ? (1ull << left) - 1 : 0ull;
         }
-        for (int d = -E; d <= E && (acc[0] | acc[1] | acc[2] | acc[3]); d++) {
-            u64 x[4];
+        const u64 *ql = (const u64 *)P.ql, *qh = (const u64 *)P.qh, *qn = (const u64 *)P.qn;
+        for (int row = 0; row <= 2 * E; row++) {
+            u64 x[WORDS];
 #pragma unroll
-            for (int w = 0; w < 4; w++) x[w] = shd_word(a, rb, m, rl, rn, L, hn, diag, d, w);
+            for (int w = 0; w < WORDS; w++) {
+                const int left = m - 64 * w;
+                x[w] = 0;
+                if (left <= 0) continue;
+                const int p = wofs + row + 64 * w, k = p >> 5;
+                const u32 sh = (u32)p & 31u;
+                u64 v = ql[w] ^ word_at(P.wl, k, sh);
+                v |= qh[w] ^ word_at(P.wh, k, sh);
+                if constexpr (kN) v |= qn[w] | word_at(P.wn, k, sh);
+                x[w] = left >= 64 ? v : v & ((1ull << left) - 1);
+            }
+            u64 any = 0;
 #pragma unroll
-            for (int w = 0; w < 4; w++) acc[w] &= shd_amend(w ? x[w - 1] : 0ull, x[w], w < 3 ? x[w + 1] : 0ull);
+            for (int w = 0; w < WORDS; w++) {
+                acc[w] &= shd_amend(w ? x[w - 1] : 0ull, x[w], w + 1 < WORDS ? x[w + 1] : 0ull);
+                any |= acc[w];
+            }
+            if (any == 0) break;
         }
-        c = __popcll(acc[0]) + __popcll(acc[1]) + __popcll(acc[2]) + __popcll(acc[3]);
-    } else {  // longer reads: words outer, each row word with its neighbours
-        const int nw = (m + 63) / 64;
-        for (int w = 0; w < nw && c <= E; w++) {
-            const int left = m - 64 * w;
-            u64 acc = left >= 64 ? ~0ull : (1ull << left) - 1;
-            for (int d = -E; d <= E && acc; d++)
-                acc &= shd_amend(shd_word(a, rb, m, rl, rn, L, hn, diag, d, w - 1),
-                                 shd_word(a, rb, m, rl, rn, L, hn, diag, d, w),
-                                 shd_word(a, rb, m, rl, rn, L, hn, diag, d, w + 1));
-            c += __popcll(acc);
-        }
+        int c = 0;
+#pragma unroll
+        for (int w = 0; w < WORDS; w++) c += __popcll(acc[w]);
+        return c;
     }
-    const int v = c < E + 1 ? c : E + 1;
-    a.approx[p] = (u16)v;
-    a.accept[p] = v <= E;
-}
+    // 64 bits of a plane from bit sh of dword k
+    __device__ static u64 word_at(const u32 *d, int k, u32 sh) {
+        const u32 mid = d[k + 1];
+        return (u64)__builtin_amdgcn_alignbit(d[k + 2], mid, sh) << 32 | __builtin_amdgcn_alignbit(mid, d[k], sh);
+    }
+    // longer reads: a lane per word, each row word with its neighbours
+    __device__ static u64 row_word(const PairView &v, int d, int w) {
+        const int left = v.m - 64 * w;
+        if (w < 0 || left <= 0) return 0;
+        const u64x2 q = v.qlohi[w];
+        const Bits64 r = fetch_ref(v.rlohi, v.rnb, v.L, v.has_n, v.diag + d + 64 * (i64)w);
+        const u64 x = (q.lo ^ r.lo) | (q.hi ^ r.hi) | v.qnb[w] | r.nb;
+        return left >= 64 ? x : x & ((1ull << left) - 1);
+    }
+    __device__ static int by_wave(const PairView &v, int E, int lane) {
+        int c = 0;
+        for (int w0 = 0; 64 * w0 < v.m && c <= E; w0 += 64) {
+            const int w = w0 + lane, left = v.m - 64 * w;
+            u64 acc = left >= 64 ? ~0ull : left > 0 ? (1ull << left) - 1 : 0ull;
+            for (int d = -E; d <= E && acc; d++)
+                acc &= shd_amend(row_word(v, d, w - 1), row_word(v, d, w), row_word(v, d, w + 1));
+            int t = __popcll(acc);
+#pragma unroll
+            for (int o = 32; o; o >>= 1) t += __shfl_xor(t, o, 64);
+            c += t;
+        }
+        return c;
+    }
+};
 
 void launch_filter_simple(const FilterArgs &a, u64 n, u32 kind, hipStream_t s) {
     if (n == 0) return;  // n: the capacity; the kernels read the count itself
     if (kind == MT_FILTER_HAMMING)
-        k_filter_simple<1><<<grid_for(n, 256), 256, 0, s>>>(a, n);
+        k_filter_simple<1, false><<<grid_for(n, 256), 256, 0, s>>>(a, n);
     else if (kind == MT_FILTER_BASE_COUNT)
-        k_filter_simple<2><<<grid_for(n, 256), 256, 0, s>>>(a, n);
+        k_filter_simple<2, false><<<grid_for(n, 256), 256, 0, s>>>(a, n);
     else if (kind == MT_FILTER_SHD)
-        k_filter_shd<<<grid_for(n, 256), 256, 0, s>>>(a, n);
+        k_filter_lane<ShdFilter, false><<<grid_for(n, LANE_TPB), LANE_TPB, 0, s>>>(a, nullptr, n);
     else if (kind == MT_FILTER_QGRAM)
-        k_filter_qgram<<<(unsigned)std::min<u64>(grid_for(n, QG_WPB), 65536), 64 * QG_WPB, 0, s>>>(a, n);
+        k_filter_qgram<false><<<(unsigned)std::min<u64>(grid_for(n, QG_WPB), 65536), 64 * QG_WPB, 0, s>>>(a, n);
     else
         throw Error(MT_EINVAL, "unknown filter kind");
     MT_HIP(hipGetLastError());
@@ -1104,11 +1139,30 @@ void launch_filter(const FilterArgs &a, u64 n_cap, int fixed_E, hipStream_t s, T
     }
 }
 
-void launch_filter_fused(const FilterArgs &a, u64 cap, int max_E, hipStream_t s) {
+void launch_filter_fused(const FilterArgs &a, u64 cap, int max_E, u32 kind, hipStream_t s) {
     if (cap == 0) return;
     const unsigned blocks = grid_for(cap, LANE_TPB);
-    if (max_E <= 15) k_filter_lane<1, 6, true><<<blocks, LANE_TPB, 0, s>>>(a, nullptr, cap);
-    else k_filter_lane<2, 7, true><<<blocks, LANE_TPB, 0, s>>>(a, nullptr, cap);
+    static_assert(LANE_TPB == 256, "the simple filters share the grid");
+    switch (kind) {
+    case MT_FILTER_OBSTACLE:
+        if (max_E <= 15) k_filter_lane<WalkFilter<1, 6>, true><<<blocks, LANE_TPB, 0, s>>>(a, nullptr, cap);
+        else k_filter_lane<WalkFilter<2, 7>, true><<<blocks, LANE_TPB, 0, s>>>(a, nullptr, cap);
+        break;
+    case MT_FILTER_HAMMING:
+        k_filter_simple<1, true><<<blocks, LANE_TPB, 0, s>>>(a, cap);
+        break;
+    case MT_FILTER_BASE_COUNT:
+        k_filter_simple<2, true><<<blocks, LANE_TPB, 0, s>>>(a, cap);
+        break;
+    case MT_FILTER_SHD:
+        k_filter_lane<ShdFilter, true><<<blocks, LANE_TPB, 0, s>>>(a, nullptr, cap);
+        break;
+    case MT_FILTER_QGRAM:
+        k_filter_qgram<true><<<(unsigned)std::min<u64>(grid_for(cap, QG_WPB), 65536), 64 * QG_WPB, 0, s>>>(a, cap);
+        break;
+    default:
+        throw Error(MT_EINVAL, "unknown filter kind");
+    }
     MT_HIP(hipGetLastError());
 }
 

@@ -10,7 +10,8 @@
 //                 read sets (which would leave most of the chip idle with 64
 //                 reads a wavefront) and minimizer windows without a lane instance;
 //   k_compact_seeds   candidates to their places in the result;
-//   k_filter_lane     the obstacle walk, one lane per pair (filter.hip);
+//   k_filter_lane     the obstacle walk, one lane per pair (filter.hip), or the
+//                     kernel of the query's other filter;
 //   k_reduce          accept flag and taxon counts per read (classify.hip).
 // The launches follow one another without the host.  Reads beyond the kernels'
 // limits (longer than 320 bases, or 256 in k_seed_wave; E above 31; more than
@@ -933,6 +934,7 @@ __global__ void k_compact_seeds(const u32 *__restrict__ gate, const u64 *__restr
 struct FusedLaunch {
     SeedArgs a;
     const mt_index *ix;
+    u32 filter;
     u32 *ctl;
     u32 *pair_read;
     unsigned lane_blocks, wave_blocks;  // lane_blocks 0: every read in k_seed_wave
@@ -983,7 +985,7 @@ static void enqueue_fused(const FusedLaunch &L, Timer *tm, hipStream_t s) {
     const u64 maxE = a.e_mode == MT_E_FIXED           ? a.e_value
                      : a.e_mode == MT_E_CEIL_PERMILLE ? ((u64)LN_MAX_M * a.e_value + 999) / 1000
                                                       : ((u64)LN_MAX_M * a.e_value) / 1000;
-    launch_filter_fused(fa, res.cap, (int)std::min<u64>(maxE, F_MAX_E), s);
+    launch_filter_fused(fa, res.cap, (int)std::min<u64>(maxE, F_MAX_E), L.filter, s);
     if (tm) tm->mark("filter");
     launch_reduce(res, *L.ix, a.read_E, a.gate, s);
     k_fused_summary<<<ST_COUNT, SUM_TPB, 0, s>>>(L.ctl, res.cand_off.p + a.n, a.stats_part,
@@ -1035,7 +1037,7 @@ static void launch_fused_graph(const FusedLaunch &L, hipStream_t s) {
 
 void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs &reads, ReadBatch &rb,
                     mt_result &res, Timer &tm, hipStream_t s, bool graph) {
-    if (q.filter != MT_FILTER_OBSTACLE || q.strands == 2) {  // the fused kernel: obstacle walk, forward strand
+    if (q.strands == 2) {  // the two-strand read set comes back here
         classify_staged(ix, q, reads, rb, res, tm, s);
         return;
     }
@@ -1107,6 +1109,7 @@ void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs 
     a.gate = ctl.p + CTL_GATE;
     a.stats_part = stats_part.p;
     L.ix = &ix;
+    L.filter = q.filter;
     L.ctl = ctl.p;
     L.pair_read = pair_read.p;
     L.lane_blocks = (unsigned)lane_blocks;

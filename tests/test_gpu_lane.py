@@ -101,3 +101,18 @@ def test_low_complexity_and_whole_n_reads(mt, db):
     reads = synth.SeqSet.concat([synth.SeqSet.from_list(own), _cut(rng, db, N_READS, np.full(N_READS, 150), 0.01, 0.0)])
     _check(mt, db, reads, 21, 11)
     _check(mt, db, reads, 5, 10, min_hits=1, max_occ=100)
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("kind", [1, 2, 3, 4])
+def test_other_filters_in_every_mode(mt, db, kind, mode):
+    """The filters other than the obstacle walk on reads of 0 to 340 bases (past
+    the lane's length and its words), small and large read sets, one and both strands."""
+    rng = np.random.default_rng(40 + kind)
+    ix, oix = mt.Index(db, 21, 11, 200), oracle.Index(db, 21, 11, 200)
+    for n, strands, q in ((300, 1, dict(e_value=3)), (N_READS, 1, dict(e_mode=1, e_value=50)), (5000, 2, dict(e_value=40))):
+        reads = _cut(rng, db, n, rng.integers(0, 341, n), 0.02, 0.001)
+        got = ix.classify(mt.to_device(reads), mode=mode, filter_kind=kind, strands=strands, **q).to_host()
+        ref = oix.classify(reads, 3, 3, q.get("e_mode", 0), q["e_value"], filter_kind=kind, strands=strands)
+        for f in FIELDS:
+            assert np.array_equal(got[f], ref[f]), (f, n, strands)
