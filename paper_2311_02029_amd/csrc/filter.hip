@@ -301,7 +301,7 @@ __device__ inline void lds_wave_sync() {
 // at a time.  Bound by VALU issue: rows in lanes (k_filter) spends a group of
 // 16 to 64 lanes on a step of the same length.
 // 1M pairs of 150 bases at E = 7, half of them wrong places: 298 us with 16
-// lanes a pair, 79 us here.
+// lanes a pair, 58 us here.
 //
 // The pair's read and window planes are staged in LDS: every step reads them at
 // places of its own per lane, which the vector cache serves one line at a time.
@@ -418,29 +418,35 @@ __device__ inline int lane_walk(const LdsPair &P, int wofs, int m, int E) {
     return c;
 }
 
-// One 64-base block of a read's planes from its ASCII (cnt bases from byte at).
-__device__ inline Bits64 ascii_block(const FilterArgs &a, u64 at, int cnt) {
+// Planes of 64 bases of ASCII (nb of a byte past the wanted ones is whatever lies
+// there).
+__device__ inline Bits64 ascii_planes(const u32 (&v)[4][4]) {
     u32 lo[4], hi[4], nb[4];
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-        u32 v[4] = {0, 0, 0, 0};
-        const int c = min(16, cnt - 16 * i);
-        lo[i] = hi[i] = 0;
-        nb[i] = 0xFFFFu;
-        if (c > 0) {
-            if (at + 16 * i + 16 <= a.seq_total) {
-                load16(a.seq + at + 16 * i, v);
-            } else {
-#pragma unroll
-                for (int t = 0; t < 16; t++)
-                    if (t < c) v[t >> 2] |= (u32)a.seq[at + 16 * i + t] << (8 * (t & 3));
-            }
-            plane_bits16(v, &lo[i], &hi[i], &nb[i]);
-        }
-    }
+    for (int i = 0; i < 4; i++) plane_bits16(v[i], &lo[i], &hi[i], &nb[i]);
     return Bits64{lo[0] | lo[1] << 16 | (u64)(lo[2] | lo[3] << 16) << 32,
                   hi[0] | hi[1] << 16 | (u64)(hi[2] | hi[3] << 16) << 32,
                   nb[0] | nb[1] << 16 | (u64)(nb[2] | nb[3] << 16) << 32};
+}
+
+// The planes of cnt bases from byte at, 16 bytes to a load as long as they lie in
+// the set.
+__device__ inline Bits64 ascii_block(const FilterArgs &a, u64 at, int cnt) {
+    u32 v[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const int c = min(16, cnt - 16 * i);
+        v[i][0] = v[i][1] = v[i][2] = v[i][3] = 0;
+        if (c <= 0) continue;
+        if (at + 16 * i + 16 <= a.seq_total) {
+            load16(a.seq + at + 16 * i, v[i]);
+        } else {
+#pragma unroll
+            for (int t = 0; t < 16; t++)
+                if (t < c) v[i][t >> 2] |= (u32)a.seq[at + 16 * i + t] << (8 * (t & 3));
+        }
+    }
+    return ascii_planes(v);
 }
 
 // Block b of a read, from block rb of the planes or byte rb of the ASCII.
@@ -455,27 +461,66 @@ __device__ inline Bits64 read_block(const FilterArgs &a, u64 rb, int b, int m) {
 }
 
 // Stages the lane's pair (nbr read blocks, from block rb of the planes or byte
-// rb of the ASCII; nbw window blocks from b0 of its genome) at S.
-template <bool kN, bool kAscii>
+// rb of the ASCII; nbw window blocks from b0 of its genome) at S.  kAhead: the
+// window's and the read's first blocks are all requested before any is waited for.
+// Block by block, a wavefront spent most of its life in seven round trips to
+// memory (1M pairs of the fused form: 153 us, 93 us ahead); SHD, whose words take
+// the registers that this needs, is better off without (36 against 40 us).
+template <bool kN, bool kAscii, bool kAhead>
 __device__ inline LdsPair stage_pair(const FilterArgs &a, u32 *S, u64 rb, int nbr, const GenomeMeta &gm, i64 b0,
                                      int nbw, int m) {
-    u64 *q = (u64 *)S;
-    for (int b = 0; b < nbr; b++) {
-        if constexpr (kAscii || kN) {
-            const Bits64 x = read_block<kAscii>(a, rb, b, m);
-            q[b] = x.lo;
-            q[nbr + b] = x.hi;
-            if (kN) q[2 * nbr + b] = x.nb;
-        } else {
-            const u64x2 x = a.read_lohi[rb + b];
-            q[b] = x.lo;
-            q[nbr + b] = x.hi;
-        }
-    }
-    u64 *w = q + (kN ? 3 : 2) * nbr;
+    constexpr int AHEAD_W = kAhead && !kN ? 5 : 0, AHEAD_Q = !kAhead ? 0 : kAscii ? 3 : kN ? 0 : 4;
+    u64 *q = (u64 *)S, *w = q + (kN ? 3 : 2) * nbr;
     const u64x2 *rl = a.ref_lohi + gm.blk;
     const u64 *rn = a.ref_nb + gm.blk;
-    for (int b = 0; b < nbw; b++) {
+    u64x2 wv[AHEAD_W ? AHEAD_W : 1];
+#pragma unroll
+    for (int b = 0; b < AHEAD_W; b++)
+        if (b < nbw) wv[b] = rl[b0 + b];
+    auto put_read = [&](int b, const Bits64 &x) {
+        q[b] = x.lo;
+        q[nbr + b] = x.hi;
+        if (kN) q[2 * nbr + b] = x.nb;
+    };
+    int done = 0;  // read blocks staged
+    if constexpr (kAscii && kAhead) {
+        if (rb + 64 * (u64)nbr <= a.seq_total) {  // whole blocks lie in the set (all but its last reads)
+            u32 t[AHEAD_Q][4][4];
+#pragma unroll
+            for (int b = 0; b < AHEAD_Q; b++)
+                if (b < nbr)
+#pragma unroll
+                    for (int i = 0; i < 4; i++) load16(a.seq + rb + 64 * b + 16 * i, t[b][i]);
+#pragma unroll
+            for (int b = 0; b < AHEAD_Q; b++)
+                if (b < nbr) put_read(b, ascii_planes(t[b]));
+            done = AHEAD_Q;
+        }
+    } else if constexpr (kAhead && !kN) {
+        u64x2 t[AHEAD_Q];
+#pragma unroll
+        for (int b = 0; b < AHEAD_Q; b++)
+            if (b < nbr) t[b] = a.read_lohi[rb + b];
+#pragma unroll
+        for (int b = 0; b < AHEAD_Q; b++)
+            if (b < nbr) put_read(b, Bits64{t[b].lo, t[b].hi, 0});
+        done = AHEAD_Q;
+    }
+    for (int b = done; b < nbr; b++) {
+        if constexpr (kAscii || kN) {
+            put_read(b, read_block<kAscii>(a, rb, b, m));
+        } else {
+            const u64x2 x = a.read_lohi[rb + b];
+            put_read(b, Bits64{x.lo, x.hi, 0});
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < AHEAD_W; b++)
+        if (b < nbw) {
+            w[b] = wv[b].lo;
+            w[nbw + b] = wv[b].hi;
+        }
+    for (int b = AHEAD_W; b < nbw; b++) {
         if constexpr (kN) {
             const Bits64 x = ref_block(rl, rn, (i64)gm.len, meta_has_n(gm), b0 + b);
             w[b] = x.lo;
@@ -495,6 +540,7 @@ __device__ inline LdsPair stage_pair(const FilterArgs &a, u32 *S, u64 rb, int nb
 template <int R, int NC>
 struct WalkFilter {
     static constexpr int MAX_M = 1 << 16;
+    static constexpr bool AHEAD = true;
     template <bool kN>
     __device__ static int value(const LdsPair &P, int wofs, int m, int E) {
         return lane_walk<R, NC, kN>(P, wofs, m, E);
@@ -506,34 +552,49 @@ struct WalkFilter {
 // kAscii: the fused form's pairs, reads of at most 320 bases as ASCII (no pair
 // is too long for the LDS).
 template <class F, bool kAscii>
-__global__ __launch_bounds__(LANE_TPB) void k_filter_lane(FilterArgs a, const u32 *__restrict__ idx, u64 n) {
+__global__ __launch_bounds__(LANE_TPB) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_filter_lane(FilterArgs a, const u32 *__restrict__ idx, u64 n) {
     __shared__ __align__(16) u32 lds[LANE_TPB / 64][LANE_DW + LANE_PAD];
-    if (kAscii && *a.gate) return;
-    const u64 np = idx ? n : pair_count(a, n);
-    const u64 t = (u64)blockIdx.x * LANE_TPB + threadIdx.x;
-    if (t - (threadIdx.x & 63) >= np) return;  // the whole wavefront is past the end
     const int lane = threadIdx.x & 63;
     u32 *S = lds[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)];
+    const u64 t = (u64)blockIdx.x * LANE_TPB + threadIdx.x;
+    // the pair's fields are requested along with the number of pairs (n bounds
+    // their arrays) and looked at after it
+    const bool inside = t < n;
+    const u64 p = !inside ? 0 : idx ? idx[t] : t;
+    const u32 gate = kAscii ? *a.gate : 0u;
+    const u64 np = idx ? n : pair_count(a, n);
+    u32 r = 0, g = 0;
+    i64 diag = 0;
+    if (inside) {
+        r = a.pair_read[p];
+        g = a.pair_genome[p];
+        diag = a.pair_diag[p];
+    }
+    if (gate || t - lane >= np) return;  // malformed offsets; the whole wavefront is past the end
     const bool in = t < np;
-    const u64 p = !in ? 0 : idx ? idx[t] : t;
-    u32 r = 0, g = 0, err = 0;
+    u32 err = 0;
     int E = 0, m = 0, nbr = 0, nbw = 0, wofs = 0;
     bool ok = false, with_n = false;
     u64 rb = 0;
-    i64 diag = 0, b0 = 0;
+    i64 b0 = 0;
     GenomeMeta gm{};
     if (in) {
-        pair_fields(a, p, r, g, E, ok, err);
-        if (ok) {
-            m = read_len(a, r);
-            rb = kAscii ? a.read_off[r] : a.read_blk[r];
-            diag = a.pair_diag[p];
+        if (r >= a.n_reads || g >= a.n_genomes) {
+            err = ERR_PAIR_RANGE;
+        } else {
+            E = a.pair_E ? a.pair_E[p] : a.read_E[r];
+            const u64 o = a.read_off[r];
+            m = (int)(a.read_off[r + 1] - o);
+            rb = kAscii ? o : a.read_blk[r];
             gm = a.meta[g];
+            const bool read_n = a.read_has_n[r] != 0;
+            ok = E <= 65534;
+            err = ok ? 0u : (u32)ERR_E_TOO_LARGE;
             b0 = (diag - E) >> 6;  // floor: the window starts left of the genome for some
             wofs = (int)(diag - E - 64 * b0);
             nbr = (m + 63) / 64;
             nbw = (wofs + 2 * E + m + 63) / 64;
-            with_n = pair_with_n(a, r, gm, diag, m, E);
+            with_n = ok && (read_n || meta_has_n(gm) || diag - E < 0 || diag + m + E > (i64)gm.len);
         }
     }
     int c = 0;
@@ -554,9 +615,11 @@ __global__ __launch_bounds__(LANE_TPB) void k_filter_lane(FilterArgs a, const u3
         if (now) {
             u32 *at = S + (end - mine);
             if (any_n)
-                c = F::template value<true>(stage_pair<true, kAscii>(a, at, rb, nbr, gm, b0, nbw, m), wofs, m, E);
+                c = F::template value<true>(stage_pair<true, kAscii, F::AHEAD>(a, at, rb, nbr, gm, b0, nbw, m), wofs, m,
+                                            E);
             else
-                c = F::template value<false>(stage_pair<false, kAscii>(a, at, rb, nbr, gm, b0, nbw, m), wofs, m, E);
+                c = F::template value<false>(stage_pair<false, kAscii, F::AHEAD>(a, at, rb, nbr, gm, b0, nbw, m), wofs,
+                                             m, E);
         }
         todo &= ~__ballot(now);
         lds_wave_sync();
@@ -1025,6 +1088,7 @@ __device__ inline u64 shd_amend(u64 xp, u64 x, u64 xn) {
 // E = 5: 74 us with each row word fetched from global memory, SHD_US us staged.
 struct ShdFilter {
     static constexpr int WORDS = 5, MAX_M = 64 * WORDS;
+    static constexpr bool AHEAD = false;
     template <bool kN>
     __device__ static int value(const LdsPair &P, int wofs, int m, int E) {
         u64 acc[WORDS];
