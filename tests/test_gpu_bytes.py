@@ -69,3 +69,25 @@ def test_bases_in_either_case_at_every_place(mt, db, mode):
     ref = db["oix"].classify(rs, 1, 3, 0, 7)
     for f in ("cand_offsets", "genome", "diag", "hits", "approx", "accept", "read_accepted", "unique", "multi"):
         assert np.array_equal(got[f], ref[f]), f
+
+
+def test_complements_in_either_case_at_every_length(mt, db):
+    """Both strands: pieces of 16 bytes of a read and their mirror, reads of every
+    length up to 70 and around 256, lower case and N among them."""
+    rng = np.random.default_rng(4)
+    reads = []
+    for m in [*range(0, 70), 150, 255, 256, 257, 271, 272, 273, 300, 520]:
+        a = db["g"][700:700 + m].copy()
+        a[rng.random(m) < 0.3] |= 0x20
+        if m > 30:
+            a[rng.integers(0, m)] = ord("n")
+        reads.append(a.tobytes())
+    rs = synth.from_reverse_strand(rng, synth.SeqSet.from_list(reads * 2), 0.5)
+    for mode in (0, 1):
+        got = db["ix"].classify(mt.to_device(rs), min_hits=1, mode=mode, strands=2).to_host()
+        ref = db["oix"].classify(rs, 1, 3, 0, 7, strands=2)
+        for f in ("cand_offsets", "genome", "diag", "hits", "approx", "accept", "strand", "unique", "multi"):
+            assert np.array_equal(got[f], ref[f]), f
+    bad = synth.SeqSet.from_list([reads[40], b"ACGTACGTACGTACGTAC*TACGTACGTACGT"])
+    with pytest.raises(mt.MTError):
+        db["ix"].classify(mt.to_device(bad), mode=1, strands=2)
