@@ -14,9 +14,9 @@
 //                     kernel of the query's other filter;
 //   k_reduce          accept flag and taxon counts per read (classify.hip).
 // The launches follow one another without the host.  Reads beyond the kernels'
-// limits (longer than 320 bases, or 256 in k_seed_wave; E above 31; more than
-// 256 seed hits; more than 8 candidates when every candidate is kept) are queued
-// and finished by the per-stage kernels, so every read gets the same result as
+// limits (longer than 320 bases; E above 31; more than 256 seed hits; more than 8
+// candidates when every candidate is kept) are queued and finished by the per-stage
+// kernels, so every read gets the same result as
 // in per-stage mode; top_n above 8 runs per stage throughout.
 #include <algorithm>
 
@@ -26,7 +26,8 @@
 namespace mt {
 
 constexpr int F_WPB = 4;         // wavefronts per block
-constexpr int F_MAX_M = 256;     // longest read of k_seed_wave
+constexpr int F_MAX_M = LN_MAX_M;  // longest read of k_seed_wave
+constexpr int F_ROUNDS = F_MAX_M / 64;  // of 64 positions; a read takes those it reaches
 constexpr int F_HIT_CAP = 256;   // seed hits per read (distinct locations fit the table)
 constexpr int F_TSLOTS = 256;    // per-read LDS hash table of locations
 constexpr int F_MAX_E = 31;      // 2E + 1 rows fit two words of the filter
@@ -354,16 +355,17 @@ __device__ inline int window_argmin_any(const u64 *hh, int ws, int win) {
 struct ReadBytes {
     u64 beg;
     int m;
-    u32 b[4];
+    u32 b[F_ROUNDS];
 };
 
 __device__ inline void issue_read_bytes(const SeedArgs &a, u64 r, int lane, ReadBytes &rb) {
     rb.beg = a.off[r];
     rb.m = (int)(a.off[r + 1] - rb.beg);
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
+    for (int q = 0; q < F_ROUNDS; q++) {
         int i = 64 * q + lane;
-        rb.b[q] = (rb.m <= F_MAX_M && i < rb.m) ? (u32)a.seq[rb.beg + i] : (u32)'N';
+        rb.b[q] = 'N';
+        if (64 * q < rb.m && rb.m <= F_MAX_M && i < rb.m) rb.b[q] = (u32)a.seq[rb.beg + i];
     }
 }
 
@@ -405,7 +407,7 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
     __shared__ u16 sh_pos[F_WPB][F_MAX_M];   // minimizer positions; later candidate hit counts
     __shared__ u8 sh_pick[F_WPB][F_MAX_M];   // window picks
     __shared__ u32 sh_st[F_WPB][F_WORDS];    // big-endian 2-bit stream of the read
-    __shared__ u64 sh_nb[F_WPB][4];          // N plane (1 past the end)
+    __shared__ u64 sh_nb[F_WPB][F_ROUNDS];          // N plane (1 past the end)
     __shared__ u64 sh_stats[F_WPB][ST_COUNT];
     __shared__ u8 sh_tlist[F_WPB][F_TSLOTS];  // slots of the per-read table in use
     __shared__ u32 sh_tn[F_WPB];             // ... and their number
@@ -472,14 +474,17 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
         if (more) noff = a.off[rn + (u64)(lane & 1)];
         wave_sync();
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            int i = 64 * q + lane;
-            u32 c = i < m ? base_code(cur.b[q]) : 4u;
-            bad |= c == 5;
-            const u64 nb = ballot64(c >= 4);
+        for (int q = 0; q < F_ROUNDS; q++) {
+            u64 nb = ~0ull;
+            if (64 * q < m) {  // (wave-uniform)
+                int i = 64 * q + lane;
+                u32 c = i < m ? base_code(cur.b[q]) : 4u;
+                bad |= c == 5;
+                nb = ballot64(c >= 4);
+                has_n |= i < m && c == 4;
+                if (c < 4 && c > 0) atomicOr(&stream[i >> 4], c << (30 - 2 * (i & 15)));
+            }
             if (lane == 0) nbp[q] = nb;
-            has_n |= i < m && c == 4;
-            if (c < 4 && c > 0) atomicOr(&stream[i >> 4], c << (30 - 2 * (i & 15)));
         }
         // (the next read's bytes are requested after the probes)
         const u64 nbeg = readlane64(noff, 0), nend = readlane64(noff, 1);
@@ -498,10 +503,11 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
         // 2. k-mer hashes (~0 for k-mers with an N)
         const int nk = m - (int)k + 1;
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
+        for (int q = 0; q < F_ROUNDS; q++) {
+            if (64 * q >= nk) continue;
             int i = 64 * q + lane;
             if (i < nk) {
-                u64 nb = funnel(nbp[q], q < 3 ? nbp[q + 1] : ~0ull, (u32)lane);
+                u64 nb = funnel(nbp[q], q + 1 < F_ROUNDS ? nbp[q + 1] : ~0ull, (u32)lane);
                 hh[i] = (nb & kmask) == 0 ? mix64(stream_kmer(stream, i, k)) : ~0ull;
             }
             pick[i] = 0;
@@ -516,7 +522,8 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
             const int win = nk < (int)a.w ? nk : (int)a.w;
             const int nws = nk - win + 1;
 #pragma unroll 1
-            for (int q = 0; q < 4; q++) {
+            for (int q = 0; q < F_ROUNDS; q++) {
+                if (64 * q >= nws) break;
                 int ws = 64 * q + lane;
                 if (ws < nws) {
                     const int best = window_argmin_any(hh, ws, win);
@@ -525,7 +532,8 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
             }
             wave_sync();
 #pragma unroll
-            for (int q = 0; q < 4; q++) {
+            for (int q = 0; q < F_ROUNDS; q++) {
+                if (64 * q >= nk) continue;
                 int i = 64 * q + lane;
                 bool chosen = i < nk && pick[i];
                 u64 cm = ballot64(chosen);
@@ -648,9 +656,10 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
             nxt.beg = nbeg;
             nxt.m = (int)(nend - nbeg);
 #pragma unroll
-            for (int q = 0; q < 4; q++) {
+            for (int q = 0; q < F_ROUNDS; q++) {
                 int i = 64 * q + lane;
-                nxt.b[q] = (nxt.m <= F_MAX_M && i < nxt.m) ? (u32)a.seq[nbeg + i] : (u32)'N';
+                nxt.b[q] = 'N';
+                if (64 * q < nxt.m && nxt.m <= F_MAX_M && i < nxt.m) nxt.b[q] = (u32)a.seq[nbeg + i];
             }
         }
         wave_sync();
@@ -1306,7 +1315,7 @@ __global__ __launch_bounds__(64 * F_WPB) void k_contain_wave(ContainArgs a, cons
     __shared__ u16 sh_pos[F_WPB][F_MAX_M];
     __shared__ u8 sh_pick[F_WPB][F_MAX_M];
     __shared__ u32 sh_st[F_WPB][F_WORDS];
-    __shared__ u64 sh_nb[F_WPB][4];
+    __shared__ u64 sh_nb[F_WPB][F_ROUNDS];
     extern __shared__ unsigned long long cnt[];  // one counter per genome when they fit (sized at launch)
     if (*a.gate) return;  // malformed offsets: the whole grid leaves
     const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1330,12 +1339,12 @@ __global__ __launch_bounds__(64 * F_WPB) void k_contain_wave(ContainArgs a, cons
     // the read in hand: its length and its bytes, one per lane per 64-base
     // round (the next read's are requested while this one is probed)
     int m = 0;
-    u32 b[4];
+    u32 b[F_ROUNDS];
     if (i < n) {
         const u64 beg = a.off[r];
         m = (int)(a.off[r + 1] - beg);
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
+        for (int q = 0; q < F_ROUNDS; q++) {
             const int i = 64 * q + lane;
             b[q] = (m <= F_MAX_M && i < m) ? (u32)a.seq[beg + i] : (u32)'N';
         }
@@ -1353,7 +1362,7 @@ __global__ __launch_bounds__(64 * F_WPB) void k_contain_wave(ContainArgs a, cons
             const u64 nbeg = readlane64(noff, 0);
             m = (int)(readlane64(noff, 1) - nbeg);
 #pragma unroll
-            for (int q = 0; q < 4; q++) {
+            for (int q = 0; q < F_ROUNDS; q++) {
                 const int i = 64 * q + lane;
                 b[q] = (more && m <= F_MAX_M && i < m) ? (u32)a.seq[nbeg + i] : (u32)'N';
             }
@@ -1364,13 +1373,16 @@ __global__ __launch_bounds__(64 * F_WPB) void k_contain_wave(ContainArgs a, cons
         wave_sync();
         bool bad = false;
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const int i = 64 * q + lane;
-            const u32 c = i < m ? base_code(b[q]) : 4u;
-            bad |= c == 5;
-            const u64 nb = ballot64(c >= 4);
+        for (int q = 0; q < F_ROUNDS; q++) {
+            u64 nb = ~0ull;
+            if (64 * q < m) {  // (wave-uniform)
+                const int i = 64 * q + lane;
+                const u32 c = i < m ? base_code(b[q]) : 4u;
+                bad |= c == 5;
+                nb = ballot64(c >= 4);
+                if (c < 4 && c > 0) atomicOr(&stream[i >> 4], c << (30 - 2 * (i & 15)));
+            }
             if (lane == 0) nbp[q] = nb;
-            if (c < 4 && c > 0) atomicOr(&stream[i >> 4], c << (30 - 2 * (i & 15)));
         }
         if (ballot64(bad)) {
             wflags |= ERR_BAD_BYTE;  // the call fails; the grid still reads no further bytes
@@ -1381,10 +1393,11 @@ __global__ __launch_bounds__(64 * F_WPB) void k_contain_wave(ContainArgs a, cons
         // 2. k-mer hashes (~0 for k-mers with an N)
         const int nk = m - (int)k + 1;
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
+        for (int q = 0; q < F_ROUNDS; q++) {
+            if (64 * q >= nk) continue;
             const int i = 64 * q + lane;
             if (i < nk) {
-                const u64 nb = funnel(nbp[q], q < 3 ? nbp[q + 1] : ~0ull, (u32)lane);
+                const u64 nb = funnel(nbp[q], q + 1 < F_ROUNDS ? nbp[q + 1] : ~0ull, (u32)lane);
                 hh[i] = (nb & kmask) == 0 ? mix64(stream_kmer(stream, i, k)) : ~0ull;
             }
             pick[i] = 0;
@@ -1397,7 +1410,8 @@ __global__ __launch_bounds__(64 * F_WPB) void k_contain_wave(ContainArgs a, cons
             const int win = nk < (int)a.w ? nk : (int)a.w;
             const int nws = nk - win + 1;
 #pragma unroll 1
-            for (int q = 0; q < 4; q++) {
+            for (int q = 0; q < F_ROUNDS; q++) {
+                if (64 * q >= nws) break;
                 const int ws = 64 * q + lane;
                 if (ws < nws) {
                     const int best = window_argmin_any(hh, ws, win);
@@ -1406,7 +1420,8 @@ __global__ __launch_bounds__(64 * F_WPB) void k_contain_wave(ContainArgs a, cons
             }
             wave_sync();
 #pragma unroll
-            for (int q = 0; q < 4; q++) {
+            for (int q = 0; q < F_ROUNDS; q++) {
+                if (64 * q >= nk) continue;
                 const int i = 64 * q + lane;
                 const bool chosen = i < nk && pick[i];
                 const u64 cm = ballot64(chosen);
@@ -1420,7 +1435,7 @@ __global__ __launch_bounds__(64 * F_WPB) void k_contain_wave(ContainArgs a, cons
             const u64 nbeg = readlane64(noff, 0);
             const int nm = (int)(readlane64(noff, 1) - nbeg);
 #pragma unroll
-            for (int q = 0; q < 4; q++) {
+            for (int q = 0; q < F_ROUNDS; q++) {
                 const int i = 64 * q + lane;
                 b[q] = (more && nm <= F_MAX_M && i < nm) ? (u32)a.seq[nbeg + i] : (u32)'N';
             }
