@@ -520,7 +520,8 @@ void launch_reduce_slots(const mt_result &res, const mt_index &ix, const u64 *sl
 
 // ----------------------------------------------------------------- driver --
 
-void ReadBatch::prepare(const mt_seqs &reads, u32 e_mode, u32 e_value, hipStream_t s) {
+void ReadBatch::prepare(const mt_seqs &reads, u32 e_mode, u32 e_value, hipStream_t s, const u64 *src,
+                        u64 src_total) {
     n = reads.n;
     flags.alloc(1);
     MT_HIP(hipMemsetAsync(flags.p, 0, sizeof(u32), s));
@@ -531,7 +532,8 @@ void ReadBatch::prepare(const mt_seqs &reads, u32 e_mode, u32 e_value, hipStream
     }
     has_n.alloc(n);
     MT_HIP(hipMemsetAsync(has_n.p, 0, n ? n : 1, s));
-    pack_sequences(reads, 65535, ERR_READ_TOO_LONG, "read longer than 65535 bases", planes, flags.p, has_n.p, s);
+    pack_sequences(reads, 65535, ERR_READ_TOO_LONG, "read longer than 65535 bases", planes, flags.p, has_n.p, s,
+                   src, src_total);
 }
 
 void validate_query(const mt_query_params &q) {

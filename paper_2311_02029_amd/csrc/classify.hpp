@@ -57,7 +57,9 @@ struct ReadBatch {
     DBuf<u16> read_E;  // E per read
     DBuf<u8> has_n;    // 1 if the read has an N
     PackedSeqs planes; // read bit planes
-    void prepare(const mt_seqs &reads, u32 e_mode, u32 e_value, hipStream_t s);
+    // src, src_total: a subset that was not gathered, see pack_sequences
+    void prepare(const mt_seqs &reads, u32 e_mode, u32 e_value, hipStream_t s, const u64 *src = nullptr,
+                 u64 src_total = 0);
 };
 
 // Pair lists handed to the filter kernels.
@@ -121,7 +123,8 @@ void classify_per_stage(const mt_index &ix, const mt_query_params &q, const mt_s
 // containment_per_stage adds to hits).  containment runs reads of up to 256 bases in one
 // fused kernel and the rest through containment_per_stage.
 void containment(const mt_index &ix, const mt_seqs &reads, u64 *hits, hipStream_t s);
-void containment_per_stage(const mt_index &ix, const mt_seqs &reads, u64 *hits, hipStream_t s);
+void containment_per_stage(const mt_index &ix, const mt_seqs &reads, const u64 *src, u64 src_total, u64 *hits,
+                           hipStream_t s);
 
 // The per-stage form end to end: packing and validation, classify_per_stage,
 // flags, candidate count.

@@ -142,10 +142,11 @@ static unsigned contain_blocks(u64 n_min) {
     return (unsigned)std::max<u64>(1, std::min<u64>(grid_for(n_min, CT_TPB), (u64)std::max(cus, 1) * 8));
 }
 
-void containment_per_stage(const mt_index &ix, const mt_seqs &reads, u64 *hits, hipStream_t s) {
+void containment_per_stage(const mt_index &ix, const mt_seqs &reads, const u64 *src, u64 src_total, u64 *hits,
+                           hipStream_t s) {
     if (reads.n == 0 || ix.n_genomes == 0) return;
     ReadBatch rb;
-    rb.prepare(reads, MT_E_FIXED, 0, s);  // validates lengths and bytes; E is unused here
+    rb.prepare(reads, MT_E_FIXED, 0, s, src, src_total);  // validates lengths and bytes; E is unused here
     MinimizerPlan mp;
     const int tile = reads.total / reads.n > 512 ? 1024 : 256;
     minimizer_plan(reads, rb.planes, ix.k, ix.w, tile, mp, s);

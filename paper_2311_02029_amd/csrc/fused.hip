@@ -59,6 +59,7 @@ struct SeedArgs {
     u8 *read_n;  // 1 if the read has an N
     u32 *slow_list, *slow_count;  // reads for k_seed_wave
     u32 *fb_list, *fb_count;      // reads for the per-stage kernels
+    unsigned long long *fb_bases; // ... and their bases
     u32 *flags;
     const u32 *gate;  // offsets check result: nonzero skips the whole launch
     u64 *stats_part;  // ST_COUNT work counts per block
@@ -109,6 +110,15 @@ __device__ inline u32 wave_sum(u32 v) {
     return v;
 }
 
+// ... and their bases to *bases.
+__device__ inline void list_append(bool add, u64 r, int m, int lane, u32 *list, u32 *count,
+                                   unsigned long long *bases) {
+    if (!ballot64(add)) return;
+    list_append(add, r, lane, list, count);
+    const u32 t = wave_sum(add ? (u32)m : 0u);
+    if (lane == 0) atomicAdd(bases, (unsigned long long)t);
+}
+
 // One lane per read.  MAXD: locations a lane's list holds; MAXM: longest read.  The list is searched
 // from its front for every hit; the first location, usually the only one, stays
 // in registers.
@@ -146,6 +156,7 @@ __global__ __launch_bounds__(LN_TPB) void k_seed_lane(SeedArgs a) {
         slow = !fall && m > MAXM;
     }
     const bool take = in && !fall && !slow;
+    const int length = m;
     if (!take) m = 0;
     const int max_m = wave_max(m);
     const LaneRead rd = lane_decode(a.seq, beg, m, a.total, lane, max_m, L);
@@ -254,7 +265,7 @@ __global__ __launch_bounds__(LN_TPB) void k_seed_lane(SeedArgs a) {
         a.read_n[r] = rd.has_n;
     }
     list_append(in && slow && !fall, r, lane, a.slow_list, a.slow_count);
-    list_append(in && fall, r, lane, a.fb_list, a.fb_count);
+    list_append(in && fall, r, length, lane, a.fb_list, a.fb_count, a.fb_bases);
     if (wflags) atomicOr(a.flags, wflags);
     // work counts: one record per block, summed by k_fused_summary
     const bool done = take && !slow && !fall;
@@ -456,6 +467,7 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
         if (m > F_MAX_M || E > F_MAX_E) {
             if (lane == 0) {
                 a.fb_list[atomicAdd(a.fb_count, 1u)] = (u32)r;
+                atomicAdd(a.fb_bases, (unsigned long long)m);
                 a.ncand[r] = 0;  // until the per-stage kernels fill it in
                 a.read_n[r] = 0;
             }
@@ -671,6 +683,7 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
             if (lane == 0) {
                 *tn = 0;
                 a.fb_list[atomicAdd(a.fb_count, 1u)] = (u32)r;
+                atomicAdd(a.fb_bases, (unsigned long long)m);
                 a.ncand[r] = 0;
                 a.read_n[r] = has_n;
             }
@@ -708,6 +721,7 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
             // keep-all with more candidates than staging slots: per-stage finish
             if (lane == 0) {
                 a.fb_list[atomicAdd(a.fb_count, 1u)] = (u32)r;
+                atomicAdd(a.fb_bases, (unsigned long long)m);
                 a.ncand[r] = 0;
                 a.read_n[r] = has_n;
             }
@@ -759,13 +773,14 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
 }
 
 // Control words of one fused call: [0] offsets check, [1] run flags,
-// [2] reads for the per-stage kernels, [3] reads for k_seed_wave.
-constexpr int CTL_GATE = 0, CTL_FLAGS = 1, CTL_FB = 2, CTL_SLOW = 3, CTL_WORDS = 4;
+// [2] reads for the per-stage kernels, [3] reads for k_seed_wave, [4..5] bases of
+// the former.
+constexpr int CTL_GATE = 0, CTL_FLAGS = 1, CTL_FB = 2, CTL_SLOW = 3, CTL_FB_BASES = 4, CTL_WORDS = 6;
 
 // Host-visible summary of one fused call, read back with a single copy.
 struct FusedSummary {
     u32 gate, flags, nfb, pad;
-    u64 n_cands;
+    u64 fb_bases, n_cands;
     u64 stats[ST_COUNT];
 };
 
@@ -800,6 +815,7 @@ __global__ __launch_bounds__(SUM_TPB) void k_fused_summary(const u32 *__restrict
             out->flags = ctl[CTL_FLAGS];
             out->nfb = ctl[CTL_FB];
             out->pad = 0;
+            out->fb_bases = ctl[CTL_FB_BASES] | (u64)ctl[CTL_FB_BASES + 1] << 32;
             out->n_cands = ctl[CTL_GATE] ? 0 : *cand_end;
         }
     }
@@ -849,20 +865,28 @@ static void enqueue_begin(const u64 *off, u64 n, u64 total, u32 *ctl, u64 *count
     MT_HIP(hipGetLastError());
 }
 
-// Subset of reads (the fallback list) gathered into a contiguous batch.
-__global__ void k_subset_lengths(const u64 *__restrict__ off, const u32 *__restrict__ list, u64 n,
-                                 u64 *__restrict__ len) {
+// Lengths and first bytes of a subset of the reads (the fallback list).
+__global__ void k_subset(const u64 *__restrict__ off, const u32 *__restrict__ list, u64 n, u64 *__restrict__ len,
+                         u64 *__restrict__ src) {
     u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) len[i] = off[list[i] + 1] - off[list[i]];
+    if (i >= n) return;
+    src[i] = off[list[i]];
+    len[i] = off[list[i] + 1] - src[i];
 }
 
-__global__ void k_subset_copy(const u8 *__restrict__ seq, const u64 *__restrict__ off, const u32 *__restrict__ list,
-                              u64 n, const u64 *__restrict__ sub_off, u8 *__restrict__ sub_seq) {
-    u64 i = blockIdx.x;
-    if (i >= n) return;
-    u64 src = off[list[i]], dst = sub_off[i], len = sub_off[i + 1] - dst;
-    for (u64 t = threadIdx.x; t < len; t += blockDim.x) sub_seq[dst + t] = seq[src + t];
-}
+// The subset as a read set that shares the bytes: off its lengths' offsets, src its
+// reads' first bytes.
+struct Subset {
+    DBuf<u64> off, src;
+    mt_seqs seqs;
+    Subset(const mt_seqs &reads, const u32 *list, u64 n, u64 bases, hipStream_t s)
+        : off(n + 1), src(n), seqs{reads.seq, off.p, n, bases} {
+        DBuf<u64> len(n);
+        k_subset<<<grid_for(n, 256), 256, 0, s>>>(reads.offsets, list, n, len.p, src.p);
+        MT_HIP(hipGetLastError());
+        scan_u64(len.p, off.p, n, s);
+    }
+};
 
 // Counts and accept flags of the per-stage finished reads.
 __global__ void k_subset_counts(const u32 *__restrict__ list, u64 n, const u64 *__restrict__ sub_off,
@@ -1114,6 +1138,7 @@ void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs 
     a.slow_count = ctl.p + CTL_SLOW;
     a.fb_list = fb_list.p;
     a.fb_count = ctl.p + CTL_FB;
+    a.fb_bases = (unsigned long long *)(ctl.p + CTL_FB_BASES);
     a.flags = ctl.p + CTL_FLAGS;
     a.gate = ctl.p + CTL_GATE;
     a.stats_part = stats_part.p;
@@ -1154,26 +1179,14 @@ void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs 
     const u32 nfb = h.nfb;
     if (nfb == 0) return;
 
-    // Reads past the fused kernels' limits: finish them per stage on a
-    // gathered subset, and make room for their candidates among the others'.
-    DBuf<u64> sub_len(nfb), sub_off(nfb + 1);
-    k_subset_lengths<<<grid_for(nfb, 256), 256, 0, s>>>(reads.offsets, fb_list.p, nfb, sub_len.p);
-    MT_HIP(hipGetLastError());
-    scan_u64(sub_len.p, sub_off.p, nfb, s);
-    u64 sub_total = 0;
-    read_back(s, sub_off.p + nfb, &sub_total, sizeof sub_total);
-    DBuf<u8> sub_seq(sub_total);
-    k_subset_copy<<<nfb, 256, 0, s>>>((const u8 *)reads.seq, reads.offsets, fb_list.p, nfb, sub_off.p, sub_seq.p);
-    MT_HIP(hipGetLastError());
-    mt_seqs sub{(const char *)sub_seq.p, sub_off.p, nfb, sub_total};
+    // Reads past the fused kernels' limits: finish them per stage, as a subset
+    // that shares the bytes, and make room for their candidates among the others'.
+    const Subset sub(reads, fb_list.p, nfb, h.fb_bases, s);
     mt_result tmp;
     mt_result_init(tmp, nfb, ix.n_taxa, s);
     ReadBatch srb;
-    srb.prepare(sub, q.e_mode, q.e_value, s);
-    classify_per_stage(ix, q, sub, srb, tmp, tm, s);
-    u32 f2 = 0;
-    read_back(s, srb.flags.p, &f2, sizeof f2);
-    check_flags(f2);
+    srb.prepare(sub.seqs, q.e_mode, q.e_value, s, sub.src.p, reads.total);
+    classify_per_stage(ix, q, sub.seqs, srb, tmp, tm, s);
     k_subset_counts<<<grid_for(nfb, 256), 256, 0, s>>>(fb_list.p, nfb, tmp.cand_off.p, tmp.read_accepted.p, ncand.p,
                                                        res.read_accepted.p);
     MT_HIP(hipGetLastError());
@@ -1193,8 +1206,11 @@ void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs 
     const auto old_approx = res.approx;
     const auto old_accept = res.accept;
     scan_u32(ncand.p, res.cand_off.p, n, s);
+    u32 f2 = 0;
     u64 total = 0;
+    MT_HIP(hipMemcpyAsync(&f2, srb.flags.p, sizeof f2, hipMemcpyDeviceToHost, s));
     read_back(s, res.cand_off.p + n, &total, sizeof total);
+    check_flags(f2);
     res.alloc_cands(total);
     k_move_cands<<<grid_for(n, 256), 256, 0, s>>>(old_off.p, res.cand_off.p, n, old_genome.p, old_diag.p, old_hits.p,
                                                   old_approx.p, old_accept.p, res.genome.p, res.diag.p, res.hits.p,
@@ -1230,6 +1246,7 @@ struct ContainArgs {
     unsigned long long *hits;
     u32 *slow_list, *slow_count;  // reads for k_contain_wave
     u32 *fb_list, *fb_count;
+    unsigned long long *fb_bases;
     u32 *flags;
     const u32 *gate;  // offsets check result: nonzero skips the whole launch
 };
@@ -1277,6 +1294,7 @@ __global__ __launch_bounds__(LN_TPB) void k_contain_lane(ContainArgs a) {
         const bool fall = m > LN_MAX_M;
         bool slow = !fall && m > MAXM;
         const bool take = in && !fall && !slow;
+        const int length = m;
         if (!take) m = 0;
         const int max_m = wave_max(m);
         const LaneRead rd = lane_decode(a.seq, beg, m, a.total, lane, max_m, L);
@@ -1298,7 +1316,7 @@ __global__ __launch_bounds__(LN_TPB) void k_contain_lane(ContainArgs a) {
             }
         }
         list_append(in && slow, r, lane, a.slow_list, a.slow_count);
-        list_append(in && fall, r, lane, a.fb_list, a.fb_count);
+        list_append(in && fall, r, length, lane, a.fb_list, a.fb_count, a.fb_bases);
     }
     if (wflags) atomicOr(a.flags, wflags);
     if (in_lds) {
@@ -1358,7 +1376,10 @@ __global__ __launch_bounds__(64 * F_WPB) void k_contain_wave(ContainArgs a, cons
         u64 noff = 0;
         if (more) noff = a.off[rn + (u64)(lane & 1)];
         if (m > F_MAX_M) {
-            if (lane == 0) a.fb_list[atomicAdd(a.fb_count, 1u)] = (u32)r;
+            if (lane == 0) {
+                a.fb_list[atomicAdd(a.fb_count, 1u)] = (u32)r;
+                atomicAdd(a.fb_bases, (unsigned long long)m);
+            }
             const u64 nbeg = readlane64(noff, 0);
             m = (int)(readlane64(noff, 1) - nbeg);
 #pragma unroll
@@ -1477,7 +1498,8 @@ void containment(const mt_index &ix, const mt_seqs &reads, u64 *hits, hipStream_
     const size_t lds = ix.n_genomes <= CF_LDS_GENOMES ? ix.n_genomes * sizeof(unsigned long long) : 0;
     const ContainArgs a{(const u8 *)reads.seq, reads.offsets, n, reads.total, ix.k, ix.w, ix.table.p, ix.nbuckets,
                         ix.occ.p, ix.n_genomes, (unsigned long long *)hits, slow_list.p, ctl.p + CTL_SLOW, fb_list.p,
-                        ctl.p + CTL_FB, ctl.p + CTL_FLAGS, ctl.p + CTL_GATE};
+                        ctl.p + CTL_FB, (unsigned long long *)(ctl.p + CTL_FB_BASES), ctl.p + CTL_FLAGS,
+                        ctl.p + CTL_GATE};
     const u64 wave_blocks = std::min<u64>(grid_for(n, F_WPB), (u64)std::max(cus, 1) * (lanes ? 8 : 32));
     if (lanes) {
         const unsigned blocks = (unsigned)std::min<u64>(grid_for(n, LN_TPB), (u64)std::max(cus, 1) * 16);
@@ -1497,18 +1519,10 @@ void containment(const mt_index &ix, const mt_seqs &reads, u64 *hits, hipStream_
     check_flags(h[CTL_GATE] | h[CTL_FLAGS]);
     const u32 nfb = h[CTL_FB];
     if (nfb == 0) return;
-    // longer reads: the per-stage chain on a gathered subset, adding to hits
-    DBuf<u64> sub_len(nfb), sub_off(nfb + 1);
-    k_subset_lengths<<<grid_for(nfb, 256), 256, 0, s>>>(reads.offsets, fb_list.p, nfb, sub_len.p);
-    MT_HIP(hipGetLastError());
-    scan_u64(sub_len.p, sub_off.p, nfb, s);
-    u64 sub_total = 0;
-    read_back(s, sub_off.p + nfb, &sub_total, sizeof sub_total);
-    DBuf<u8> sub_seq(sub_total);
-    k_subset_copy<<<nfb, 256, 0, s>>>((const u8 *)reads.seq, reads.offsets, fb_list.p, nfb, sub_off.p, sub_seq.p);
-    MT_HIP(hipGetLastError());
-    const mt_seqs sub{(const char *)sub_seq.p, sub_off.p, nfb, sub_total};
-    containment_per_stage(ix, sub, hits, s);
+    // longer reads: the per-stage chain, adding to hits
+    const u64 bases = h[CTL_FB_BASES] | (u64)h[CTL_FB_BASES + 1] << 32;
+    const Subset sub(reads, fb_list.p, nfb, bases, s);
+    containment_per_stage(ix, sub.seqs, sub.src.p, reads.total, hits, s);
 }
 
 }  // namespace mt

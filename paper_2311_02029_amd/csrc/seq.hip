@@ -36,7 +36,8 @@ __global__ void k_seq_blocks(const u64 *__restrict__ off, u64 n, u64 total, u64 
 // reads of 150 bases 171 -> 44 us, 500 Mbp of genomes 637 -> 205 us against one
 // thread per block going base by base.
 __global__ __launch_bounds__(256) void k_pack(const u8 *__restrict__ seq, const u64 *__restrict__ off,
-                                              const u64 *__restrict__ blk_off, u64 n, u64 total, u64 cap,
+                                              const u64 *__restrict__ src, const u64 *__restrict__ blk_off, u64 n,
+                                              u64 total, u64 cap,
                                               const u32 *__restrict__ map, u64x2 *__restrict__ lohi,
                                               u64 *__restrict__ nbp, u32 *__restrict__ flags,
                                               u8 *__restrict__ has_n) {
@@ -45,7 +46,8 @@ __global__ __launch_bounds__(256) void k_pack(const u8 *__restrict__ seq, const 
     const u32 quarter = (u32)t & 3u;
     if (b >= blk_off[n] || b >= cap) return;  // whole quads leave
     const u32 s = map[b];
-    const u64 beg = off[s] + 64 * (b - blk_off[s]) + 16 * quarter, end = off[s + 1];
+    const u64 first = src ? src[s] : off[s];
+    const u64 beg = first + 64 * (b - blk_off[s]) + 16 * quarter, end = first + (off[s + 1] - off[s]);
     u32 lo = 0, hi = 0, nb = 0xFFFFu;
     if (beg < end) {
         const u32 cnt = end - beg < 16 ? (u32)(end - beg) : 16u;
@@ -83,7 +85,7 @@ __global__ __launch_bounds__(256) void k_pack(const u8 *__restrict__ seq, const 
 }
 
 void pack_sequences(const mt_seqs &in, u64 len_limit, u32 len_flag, const char *len_message, PackedSeqs &out,
-                    u32 *d_flags, u8 *has_n, hipStream_t s) {
+                    u32 *d_flags, u8 *has_n, hipStream_t s, const u64 *src, u64 src_total) {
     out.n = in.n;
     out.blk_off.alloc(in.n + 1);
     out.blocks_cap = in.total / 64 + 2 * in.n + 1;
@@ -97,17 +99,19 @@ void pack_sequences(const mt_seqs &in, u64 len_limit, u32 len_flag, const char *
     k_seq_blocks<<<grid_for(in.n, 256), 256, 0, s>>>(in.offsets, in.n, in.total, len_limit, len_flag, nblk.p,
                                                       d_flags);
     MT_HIP(hipGetLastError());
-    // The offsets decide every later address: refuse bad ones before any
-    // kernel reads sequence bytes through them.
-    u32 f = 0;
-    read_back(s, d_flags, &f, sizeof f);
-    if (f & len_flag) throw Error(MT_EINVAL, len_message);
-    check_flags(f);
+    if (!src) {
+        // The offsets decide every later address: refuse bad ones before any
+        // kernel reads sequence bytes through them.
+        u32 f = 0;
+        read_back(s, d_flags, &f, sizeof f);
+        if (f & len_flag) throw Error(MT_EINVAL, len_message);
+        check_flags(f);
+    }
     scan_u64(nblk.p, out.blk_off.p, in.n, s);
     DBuf<u32> map(out.blocks_cap);
     segment_map(out.blk_off.p, in.n, map.p, out.blocks_cap, s);
-    k_pack<<<grid_for(out.blocks_cap * 4, 256), 256, 0, s>>>((const u8 *)in.seq, in.offsets, out.blk_off.p, in.n,
-                                                              in.total, out.blocks_cap, map.p, out.lohi.p, out.nb.p,
+    k_pack<<<grid_for(out.blocks_cap * 4, 256), 256, 0, s>>>((const u8 *)in.seq, in.offsets, src, out.blk_off.p,
+                                                              in.n, src ? src_total : in.total, out.blocks_cap, map.p, out.lohi.p, out.nb.p,
                                                               d_flags, has_n);
     MT_HIP(hipGetLastError());
 }

@@ -20,8 +20,11 @@ struct PackedSeqs {
 // len_message, malformed offsets with MT_EINVAL.  Bad bytes raise
 // ERR_BAD_BYTE in d_flags; has_n (nullable, n entries, zeroed by the caller)
 // receives 1 for sequences containing N.
+// src (nullable): sequence i's bytes start at in.seq + src[i] instead of its offset
+// (a subset of a set of src_total bytes, not gathered; the offsets give its lengths
+// and were checked with the set's).
 void pack_sequences(const mt_seqs &in, u64 len_limit, u32 len_flag, const char *len_message, PackedSeqs &out,
-                    u32 *d_flags, u8 *has_n, hipStream_t s);
+                    u32 *d_flags, u8 *has_n, hipStream_t s, const u64 *src = nullptr, u64 src_total = 0);
 
 // Tiled minimizer extraction.  plan() sizes the tiles and counts the
 // minimizers of every tile; after the caller has read n_tiles / n_min back
