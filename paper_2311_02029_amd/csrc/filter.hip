@@ -736,7 +736,9 @@ __device__ inline void filter_long(const FilterArgs &a, const u32 *__restrict__ 
         }
         lds_wave_sync();
         const bool wide = __ballot(live && strip > 2) != 0;  // some group's strips pass two words
-        if (live) {
+        // (Alone in its wavefront, a pair steps on until it is done or its segment is:
+        // one pair of 8-10 kbp takes 0.37 ms so, 0.42 with the staging asked at each step.)
+        if (live) do {
             const LdsPair L((const u32 *)S, nbr, (const u32 *)(S + PLANES * nbr), nbw);
             const int jl = j - 64 * sb, left = end - j;  // column in the segment; columns left of it
             int best = 0;
@@ -747,7 +749,9 @@ __device__ inline void filter_long(const FilterArgs &a, const u32 *__restrict__ 
                 if (wide)
                     for (; r0 < rows; r0 += 128)
                         best = max(best, rows_step<4, 6, kN>(L, ql, qh, qn, jl, wofs + jl + r0, jl + left, rows - r0));
-                else if (r0 < rows)
+                else if (G == 64 && strip == 1) {  // (one pair a wavefront: uniform)
+                    if (r0 < rows) best = rows_step<1, 6, kN>(L, ql, qh, qn, jl, wofs + jl + r0, jl + left, rows - r0);
+                } else if (r0 < rows)
                     best = rows_step<2, 6, kN>(L, ql, qh, qn, jl, wofs + jl + r0, jl + left, rows - r0);
             }
             best = long_group_max<G>(best);
@@ -773,7 +777,7 @@ __device__ inline void filter_long(const FilterArgs &a, const u32 *__restrict__ 
                     a.accept[p] = ap <= E;
                 }
             }
-        }
+        } while (G == 64 && live && !stage);
         lds_wave_sync();  // a group's planes are read before its next ones come in
     }
 }
@@ -802,8 +806,8 @@ struct BucketDesc {
 
 // Variant 0 of a short bucket is one lane per pair; it keeps the name of the
 // narrowest group, which it replaces, so that saved selections go on loading.
-// Variant v of a long bin: v < 4 -> pairs in LDS, 8 per wavefront for the default
-// variant and half as many with each below it; v == 4 -> rows in lanes from global
+// Variant v of a long bin: v < 4 -> pairs in LDS, up to 8 per wavefront for the
+// default variant and half as many with each below it; v == 4 -> rows in lanes from global
 // memory.  (The names count the wavefronts that shared a block when a pair took a
 // whole wavefront and its whole planes; their limits stay, so that the same
 // selections are taken and refused as ever.)
@@ -885,7 +889,14 @@ static void launch_bucket(const FilterArgs &a, const Buckets &B, int bucket, int
     const u32 *idx = B.of(bucket);
     if (bucket >= CLS_LONG && bucket < CLS_LONG + LONG_BINS) {
         const int b = bucket - CLS_LONG, cn = CLS_LONG_N + b, cw = CLS_LONG_WIDE + b;
-        const int below = DEFAULT_VARIANT[bucket] - v;  // the default is the last that fits
+        int below = DEFAULT_VARIANT[bucket] - v;  // the default is the last that fits
+        // A few pairs leave the chip idle whatever their layout: more lanes each make
+        // a step shorter (1,024 pairs of 4-5 kbp: 0.29 ms with 64 lanes, 0.35 with 32,
+        // 0.36 with 8; 1,024 of 8-10 kbp: 0.58 ms with 32 lanes, 0.75 with 8; 4,096: 0.71
+        // with 16, 0.81 with 32, 0.86 with 8; 16,384: 1.16 and 1.19 with 16 and 8;
+        // 40,000: 2.54 and 2.30).
+        const u64 pairs = cnt + B.count[cn];
+        if (below <= 0) below = pairs <= 1024 ? 3 : pairs <= 2048 ? 2 : pairs <= 8192 ? 1 : 0;
         if (v == 4) {
             for (int c : {bucket, cn, cw})
                 if (B.count[c])
