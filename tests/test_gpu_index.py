@@ -60,3 +60,35 @@ def test_index_lists_every_occurrence(mt, kind, max_occ):
     ref = oix.classify(reads, 1, 0, 0, 3)
     for f in ("cand_offsets", "genome", "diag", "hits", "approx"):
         assert np.array_equal(got[f], ref[f]), f
+
+
+# Tables from 3 x 2^20 minimizers on are built by regions of 512 buckets; with
+# w = 1 every start is a minimizer, so that small genomes reach them.
+@pytest.mark.parametrize("kind", ["below", "at", "strains", "one region over full"])
+def test_index_by_regions_lists_every_occurrence(mt, kind):
+    rng = np.random.default_rng(78)
+    least, k = 3 << 20, 17
+    if kind == "strains":  # most k-mers several times
+        gen = synth.make_strain_genomes(rng, 8, 500_000, 4)
+        ga = synth.SeqSet.from_list([gen.ascii().get(i) for i in range(gen.n)])
+    else:
+        g = synth.ACGT[synth.random_codes(rng, least + k - 1)].tobytes()
+        more = {"below": [g[:-1]], "at": [g],  # the last minimizer decides
+                "one region over full": [g[:-1], b"A" * 300_000, b"ACG" * 60_000]}[kind]
+        ga = synth.SeqSet.from_list(more)
+    ix, oix = mt.Index(ga, k, 1), oracle.Index(ga, k, 1)
+    keys, counts = np.unique(oix.occurrences()[0], return_counts=True)
+    info = ix.info()
+    assert info["n_minimizers"] == int(counts.sum()) and info["n_keys"] == len(keys)
+    assert (info["n_minimizers"] >= least) == (kind != "below")
+    assert info["n_multi_occ"] == int(counts[counts >= 2].sum())
+    reads = synth.SeqSet.from_list([ga.get(0)[a:a + 5000] for a in range(0, len(ga.get(0)) - 5000, 4900)]
+                                   + [ga.get(i)[:150] for i in range(ga.n)])
+    if kind != "one region over full":  # every k-mer of the first genome has its occurrences
+        hits = ix.containment(mt.to_device(reads)).cpu().numpy().view(np.uint64)
+        assert np.array_equal(hits, oix.containment(reads))
+    short = synth.SeqSet.from_list([ga.get(0)[a:a + 150] for a in range(0, len(ga.get(0)) - 150, 1501)])
+    got = ix.classify(mt.to_device(short), min_hits=1, top_n=0, e_value=3).to_host()
+    ref = oix.classify(short, 1, 0, 0, 3)
+    for f in ("cand_offsets", "genome", "diag", "hits", "approx"):
+        assert np.array_equal(got[f], ref[f]), f
