@@ -560,8 +560,8 @@ static void stage_seed_count(const mt_index &ix, const mt_query_params &q, const
     // seeds
     MinimizerPlan mp;
     // tiles of 256 k-mer starts fit short reads; long reads amortize the
-    // window halo and the block over tiles of 1024
-    const int tile = reads.n && reads.total / reads.n > 512 ? 1024 : 256;
+    // window halo and the block over tiles of 1,216
+    const int tile = reads.n && reads.total / reads.n > 512 ? MIN_TILE : MIN_TILE_SHORT;
     minimizer_plan(reads, rb.planes, ix.k, ix.w, tile, mp, s);
     tm.mark("seed_count");
     u32 hf = 0;

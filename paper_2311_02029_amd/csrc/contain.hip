@@ -148,7 +148,7 @@ void containment_per_stage(const mt_index &ix, const mt_seqs &reads, const u64 *
     ReadBatch rb;
     rb.prepare(reads, MT_E_FIXED, 0, s, src, src_total);  // validates lengths and bytes; E is unused here
     MinimizerPlan mp;
-    const int tile = reads.total / reads.n > 512 ? 1024 : 256;
+    const int tile = reads.total / reads.n > 512 ? MIN_TILE : MIN_TILE_SHORT;
     minimizer_plan(reads, rb.planes, ix.k, ix.w, tile, mp, s);
     u32 f = 0;
     u64 n_min = 0;

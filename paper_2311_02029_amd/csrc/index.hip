@@ -528,7 +528,7 @@ void build_index(mt_index &ix, const mt_index_params &p, const mt_seqs &g, const
     tm.mark("index_pack");
 
     MinimizerPlan mp;
-    minimizer_plan(g, ix.ref, p.k, p.w, 1024, mp, s);
+    minimizer_plan(g, ix.ref, p.k, p.w, MIN_TILE, mp, s);
     u32 f0 = 0;
     read_back(s, flags.p, &f0, sizeof(u32));
     check_flags(f0);

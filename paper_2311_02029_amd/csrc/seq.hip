@@ -170,24 +170,93 @@ __device__ inline int lds_window_argmin_any(const u64 *sh, int i, int win) {
     }
 }
 
+// MIN_RUN windows of W starts, the first at sh[i]: calls f(q, t) for each window q
+// with a valid k-mer, t its leftmost smallest hash's place from i.  The W - 4
+// hashes that all five windows have are compared once, with the suffix minima of
+// the four before them and the prefix minima of the four after: W + 9 comparisons
+// and W + 4 LDS reads for the five, 5 (W - 1) and 5 W one window at a time.
+constexpr int MIN_RUN = 5;
+
+struct MinHash {
+    u64 h;
+    int t;
+    // the smaller of this and one to the right of it
+    __device__ MinHash or_right(const MinHash &o) const {
+        const bool r = o.h < h;
+        return MinHash{r ? o.h : h, r ? o.t : t};
+    }
+};
+
+template <int W, class F>
+__device__ inline void lds_window_run(const u64 *sh, int i, F &&f) {
+    static_assert(W >= MIN_RUN && MIN_RUN == 5, "the windows have a start in common");
+    u64 v[W + 4];
+#pragma unroll
+    for (int t = 0; t < W + 4; t++) v[t] = sh[i + t];
+    MinHash mid{v[4], 4};
+#pragma unroll
+    for (int t = 5; t < W; t++) mid = mid.or_right(MinHash{v[t], t});
+    MinHash win[MIN_RUN];
+    win[4] = mid;
+    MinHash left{v[3], 3};
+    win[3] = left.or_right(mid);
+#pragma unroll
+    for (int q = 2; q >= 0; q--) {
+        left = MinHash{v[q], q}.or_right(left);
+        win[q] = left.or_right(mid);
+    }
+    MinHash right{v[W], W};
+    win[1] = win[1].or_right(right);
+#pragma unroll
+    for (int q = 2; q < MIN_RUN; q++) {
+        right = right.or_right(MinHash{v[W + q - 1], W + q - 1});
+        win[q] = win[q].or_right(right);
+    }
+#pragma unroll
+    for (int q = 0; q < MIN_RUN; q++)
+        if (win[q].h != ~0ull) f(q, win[q].t);
+}
+
+template <class F>
+__device__ inline void lds_window_run_any(const u64 *sh, int i, int n, int win, F &&f) {
+    switch (win) {
+#define MT_W(W)                      \
+    case W:                          \
+        lds_window_run<W>(sh, i, f); \
+        break;
+        MT_W(5) MT_W(6) MT_W(7) MT_W(8) MT_W(9) MT_W(10) MT_W(11) MT_W(12) MT_W(13) MT_W(14) MT_W(15) MT_W(16)
+        MT_W(17) MT_W(18) MT_W(19) MT_W(20)
+#undef MT_W
+    default:
+        for (int q = 0; q < n; q++) {
+            const int best = lds_window_argmin_any(sh, i + q, win);
+            if (best >= 0) f(q, best - i);
+        }
+    }
+}
+
 // One block per tile of TILE consecutive k-mer starts of one sequence.  The
 // hashes of the tile plus a halo of w - 1 starts on each side go to LDS; every
 // window that overlaps the tile picks its smallest (hash, position) among the
 // valid k-mers, and picks inside the tile are marked.  The marks leave as one
 // 64-bit word per 64 starts (tile_bits, TILE / 64 words per tile) with their
 // count in tile_count.
+// Bound by VALU issue.  A thread takes MIN_RUN windows in a row (in LDS their
+// first hashes are 10 banks apart, so that 32 lanes read 32 pairs of banks), and
+// the tile with the halo of usual windows is just under TPB * MIN_RUN starts.
+// 500 Mbp at k = 21, w = 11: 1.95 ms with a window per thread, tiles of 1,024 and a
+// byte per start for the marks, 1.16 ms so.
 template <int TPB, int TILE>
 __global__ __launch_bounds__(TPB) void k_min_tiles(const u64x2 *__restrict__ lohi, const u64 *__restrict__ nbp,
                                                    const u64 *__restrict__ blk_off, const u64 *__restrict__ off,
                                                    const u64 *__restrict__ tile_off, const u32 *__restrict__ tile_map,
                                                    u64 n, u32 k, u32 w, u32 *__restrict__ tile_count,
                                                    u64 *__restrict__ tile_bits) {
-    static_assert(TILE % TPB == 0 && TPB % 64 == 0, "tile of whole wavefront passes");
+    static_assert(TILE % 64 == 0 && TILE / 64 <= 64 && TPB % 64 == 0, "a lane of one wavefront for each word of marks");
     static_assert((TILE + 2 * MAX_HALO) / TPB + 1 + 31 <= 64, "a thread's starts and k-mers fit its 64-base window");
-    constexpr int SPAN = TILE + 2 * MAX_HALO;
-    __shared__ u64 sh_h[SPAN];
-    __shared__ u8 chosen[TILE];
-    __shared__ u32 total;
+    constexpr int SPAN = TILE + 2 * MAX_HALO, WORDS = TILE / 64;
+    __shared__ u64 sh_h[SPAN + MIN_RUN];  // the last thread's windows past the last one read on
+    __shared__ u32 marks[2 * WORDS];
     const u64 t = blockIdx.x;
     if (t >= tile_off[n]) return;
     const u32 s = tile_map[t];
@@ -218,30 +287,32 @@ __global__ __launch_bounds__(TPB) void k_min_tiles(const u64x2 *__restrict__ loh
             sh_h[c0 + j] = ((b.nb >> j) & kmask) == 0 ? mix64(x) : ~0ull;
         }
     }
-    for (int i = threadIdx.x; i < TILE; i += TPB) chosen[i] = 0;
-    if (threadIdx.x == 0) total = 0;
+    for (int i = threadIdx.x; i < 2 * WORDS; i += TPB) marks[i] = 0;
     __syncthreads();
-    const i64 ws1 = t1 - 1 < nk - win ? t1 - 1 : nk - win;
-    for (i64 ws = h0 + threadIdx.x; ws <= ws1; ws += TPB) {
-        const int best = lds_window_argmin_any(sh_h, (int)(ws - h0), (int)win);
-        if (best >= 0) {
-            const i64 p = h0 + best;
-            if (p >= t0 && p < t1) chosen[p - t0] = 1;
-        }
+    // windows from h0 to the last that starts in the tile and ends in the sequence
+    const int nw = (int)((t1 - 1 < nk - win ? t1 - 1 : nk - win) - h0) + 1, lead = (int)(t0 - h0);
+    for (int w0 = (int)threadIdx.x * MIN_RUN; w0 < nw; w0 += TPB * MIN_RUN) {
+        const int cnt = min(MIN_RUN, nw - w0);
+        int last = -1;  // a pick is marked once for the windows in a row that share it
+        lds_window_run_any(sh_h, w0, cnt, (int)win, [&](int q, int b) {
+            const int p = w0 + b - lead;
+            if (q < cnt && b != last && p >= 0 && p < TILE) atomicOr(&marks[p >> 5], 1u << (p & 31));
+            last = b;
+        });
     }
     __syncthreads();
-    const u32 lane = threadIdx.x & 63;
+    if (threadIdx.x < 64) {
+        const int i = (int)threadIdx.x;
+        u64 m = 0;
+        if (i < WORDS) {
+            m = (u64)marks[2 * i] | (u64)marks[2 * i + 1] << 32;
+            tile_bits[t * WORDS + i] = m;
+        }
+        u32 total = (u32)__popcll(m);
 #pragma unroll
-    for (int u = 0; u < TILE / TPB; u++) {
-        const int i = u * TPB + (int)threadIdx.x;  // 64 consecutive starts per wavefront
-        const u64 m = __ballot(chosen[i] != 0);
-        if (lane == 0) {
-            tile_bits[t * (TILE / 64) + i / 64] = m;
-            if (m) atomicAdd(&total, (u32)__popcll(m));
-        }
+        for (int o = 32; o; o >>= 1) total += __shfl_xor(total, o, 64);
+        if (i == 0) tile_count[t] = total;
     }
-    __syncthreads();
-    if (threadIdx.x == 0) tile_count[t] = total;
 }
 
 // One wavefront per tile: the marked starts are first listed in LDS, then
@@ -270,9 +341,12 @@ __global__ __launch_bounds__(64 * EMIT_WPB) void k_min_emit(const u64x2 *__restr
     const i64 t0 = (i64)(t - tile_off[s]) * TILE;
     const u64 below = lane ? (~0ull) >> (64 - lane) : 0ull;
     u32 nl = 0;
+    static_assert(TILE / 64 <= 64, "a lane for each word of marks");
+    const u64 mine = lane < TILE / 64 ? tile_bits[t * (TILE / 64) + lane] : 0;
 #pragma unroll 1
     for (int q = 0; q < TILE / 64; q++) {
-        const u64 m = tile_bits[t * (TILE / 64) + q];
+        const u64 m = ((u64)(u32)__builtin_amdgcn_readlane((int)(mine >> 32), q) << 32) |
+                      (u32)__builtin_amdgcn_readlane((int)mine, q);
         if ((m >> lane) & 1) list[nl + (u32)__popcll(m & below)] = (u16)(64 * q + lane);
         nl += (u32)__popcll(m);
     }
@@ -320,7 +394,7 @@ void minimizer_plan(const mt_seqs &in, const PackedSeqs &ps, u32 k, u32 w, int t
     mp.tile_count.alloc(mp.tiles_cap);
     mp.min_off.alloc(mp.tiles_cap + 1);
     mp.tile_bits.alloc(mp.tiles_cap * (u64)(tile / 64));
-    if (tile != 256 && tile != 1024) throw Error(MT_EINTERNAL, "unsupported minimizer tile");
+    if (tile != MIN_TILE_SHORT && tile != MIN_TILE) throw Error(MT_EINTERNAL, "unsupported minimizer tile");
     if (in.n == 0) {  // no tiles: every offset is 0 (callers read min_off[tiles_cap])
         MT_HIP(hipMemsetAsync(mp.tile_off.p, 0, sizeof(u64), s));
         MT_HIP(hipMemsetAsync(mp.min_off.p, 0, (mp.tiles_cap + 1) * sizeof(u64), s));
@@ -332,10 +406,10 @@ void minimizer_plan(const mt_seqs &in, const PackedSeqs &ps, u32 k, u32 w, int t
     scan_u64(ntile.p, mp.tile_off.p, in.n, s);
     segment_map(mp.tile_off.p, in.n, mp.tile_map.p, mp.tiles_cap, s);
     MT_HIP(hipMemsetAsync(mp.tile_count.p, 0, mp.tiles_cap * sizeof(u32), s));
-    if (tile == 1024)
-        launch_tiles<256, 1024>(in, ps, k, w, mp, s);
+    if (tile == MIN_TILE)
+        launch_tiles<256, MIN_TILE>(in, ps, k, w, mp, s);
     else
-        launch_tiles<128, 256>(in, ps, k, w, mp, s);
+        launch_tiles<64, MIN_TILE_SHORT>(in, ps, k, w, mp, s);
     // min_off over the full tile bound: tiles past the real count hold 0.
     scan_u32(mp.tile_count.p, mp.min_off.p, mp.tiles_cap, s);
 }
@@ -344,10 +418,10 @@ void minimizer_emit(const mt_seqs &in, const PackedSeqs &ps, u32 k, u32 w, Minim
                     u32 *out_seq, u32 *out_pos, hipStream_t s) {
     (void)w;
     if (in.n == 0) return;
-    if (mp.tile == 1024)
-        launch_emit<1024>(in, ps, k, mp, out_x, out_seq, out_pos, s);
+    if (mp.tile == MIN_TILE)
+        launch_emit<MIN_TILE>(in, ps, k, mp, out_x, out_seq, out_pos, s);
     else
-        launch_emit<256>(in, ps, k, mp, out_x, out_seq, out_pos, s);
+        launch_emit<MIN_TILE_SHORT>(in, ps, k, mp, out_x, out_seq, out_pos, s);
 }
 
 }  // namespace mt

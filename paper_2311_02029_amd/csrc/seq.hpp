@@ -29,12 +29,14 @@ void pack_sequences(const mt_seqs &in, u64 len_limit, u32 len_flag, const char *
 // Tiled minimizer extraction.  plan() sizes the tiles and counts the
 // minimizers of every tile; after the caller has read n_tiles / n_min back
 // (tile_off[n] and min_off[n_tiles]), emit() writes them in sequence order.
+constexpr int MIN_TILE = 1216, MIN_TILE_SHORT = 256;  // k-mer starts per tile: long sequences, short ones
+
 struct MinimizerPlan {
     int tile = 0;
     DBuf<u64> tile_off;   // n + 1
     DBuf<u32> tile_map;   // tile -> sequence
     DBuf<u32> tile_count;
-    DBuf<u64> tile_bits;  // TILE / 64 words of chosen starts per tile
+    DBuf<u64> tile_bits;  // tile / 64 words of chosen starts per tile
     DBuf<u64> min_off;    // n_tiles + 1 (allocated for the tile bound)
     u64 tiles_cap = 0;
 };

@@ -92,3 +92,32 @@ def test_index_by_regions_lists_every_occurrence(mt, kind):
     ref = oix.classify(short, 1, 0, 0, 3)
     for f in ("cand_offsets", "genome", "diag", "hits", "approx"):
         assert np.array_equal(got[f], ref[f]), f
+
+
+# Minimizers are picked five windows to a thread, in tiles of 1,216 starts of long
+# sequences and 256 of short ones: lengths around both, windows with an unrolled
+# instance (5 to 20) and beside them.
+@pytest.mark.parametrize("w", [4, 5, 6, 11, 20, 21, 255])
+def test_minimizers_around_tiles(mt, w):
+    rng = np.random.default_rng(79 + w)
+    k = 15
+
+    def seq(m):
+        s = synth.random_codes(rng, m) % 4
+        text = synth.ACGT[s].copy()
+        if m > 400:  # a repeat, and an N now and then
+            text[m // 2:m // 2 + 100] = np.tile(text[:5], 20)
+            text[rng.integers(0, m, m // 300)] = ord("N")
+        return text.tobytes()
+
+    starts = [0, 1, 2, 4, 5, 6, w - 1, w, w + 1, 255, 256, 257, 320, 511, 512, 513, 1215, 1216, 1217, 1221,
+              2431, 2432, 2433, 3648]
+    ga = synth.SeqSet.from_list([seq(max(0, n) + k - 1) for n in starts])
+    ix, oix = mt.Index(ga, k, w), oracle.Index(ga, k, w)
+    x = oix.occurrences()[0]
+    info = ix.info()
+    assert info["n_minimizers"] == len(x) and info["n_keys"] == len(np.unique(x))
+    for keep in (range(ga.n), [i for i in range(ga.n) if starts[i] < 514]):  # long tiles, short tiles
+        reads = synth.SeqSet.from_list([ga.get(i) for i in keep])
+        hits = ix.containment(mt.to_device(reads)).cpu().numpy().view(np.uint64)
+        assert np.array_equal(hits, oix.containment(reads))
