@@ -464,7 +464,7 @@ __device__ inline Bits64 read_block(const FilterArgs &a, u64 rb, int b, int m) {
 // rb of the ASCII; nbw window blocks from b0 of its genome) at S.  kAhead: the
 // window's and the read's first blocks are all requested before any is waited for.
 // Block by block, a wavefront spent most of its life in seven round trips to
-// memory (1M pairs of the fused form: 153 us, 93 us ahead); SHD, whose words take
+// memory (1M pairs of the fused form: 153 us, 91 us ahead); SHD, whose words take
 // the registers that this needs, is better off without (36 against 40 us).
 template <bool kN, bool kAscii, bool kAhead>
 __device__ inline LdsPair stage_pair(const FilterArgs &a, u32 *S, u64 rb, int nbr, const GenomeMeta &gm, i64 b0,
@@ -482,6 +482,16 @@ __device__ inline LdsPair stage_pair(const FilterArgs &a, u32 *S, u64 rb, int nb
         q[nbr + b] = x.hi;
         if (kN) q[2 * nbr + b] = x.nb;
     };
+    // The window, requested first, is put away before the read is decoded (after it,
+    // its registers spilled 56 bytes a pair: 27M pairs of strains 1.86 against 1.81 ms).
+    auto put_window = [&] {
+#pragma unroll
+        for (int b = 0; b < AHEAD_W; b++)
+            if (b < nbw) {
+                w[b] = wv[b].lo;
+                w[nbw + b] = wv[b].hi;
+            }
+    };
     int done = 0;  // read blocks staged
     if constexpr (kAscii && kAhead) {
         if (rb + 64 * (u64)nbr <= a.seq_total) {  // whole blocks lie in the set (all but its last reads)
@@ -491,16 +501,20 @@ __device__ inline LdsPair stage_pair(const FilterArgs &a, u32 *S, u64 rb, int nb
                 if (b < nbr)
 #pragma unroll
                     for (int i = 0; i < 4; i++) load16(a.seq + rb + 64 * b + 16 * i, t[b][i]);
+            put_window();
 #pragma unroll
             for (int b = 0; b < AHEAD_Q; b++)
                 if (b < nbr) put_read(b, ascii_planes(t[b]));
             done = AHEAD_Q;
+        } else {
+            put_window();
         }
     } else if constexpr (kAhead && !kN) {
         u64x2 t[AHEAD_Q];
 #pragma unroll
         for (int b = 0; b < AHEAD_Q; b++)
             if (b < nbr) t[b] = a.read_lohi[rb + b];
+        put_window();
 #pragma unroll
         for (int b = 0; b < AHEAD_Q; b++)
             if (b < nbr) put_read(b, Bits64{t[b].lo, t[b].hi, 0});
@@ -514,12 +528,6 @@ __device__ inline LdsPair stage_pair(const FilterArgs &a, u32 *S, u64 rb, int nb
             put_read(b, Bits64{x.lo, x.hi, 0});
         }
     }
-#pragma unroll
-    for (int b = 0; b < AHEAD_W; b++)
-        if (b < nbw) {
-            w[b] = wv[b].lo;
-            w[nbw + b] = wv[b].hi;
-        }
     for (int b = AHEAD_W; b < nbw; b++) {
         if constexpr (kN) {
             const Bits64 x = ref_block(rl, rn, (i64)gm.len, meta_has_n(gm), b0 + b);

@@ -1424,7 +1424,7 @@ __global__ __launch_bounds__(64 * F_WPB) void k_contain_wave(ContainArgs a, cons
             pick[i] = 0;
         }
         wave_sync();
-        // 3. window minima (~0 marks an invalid k-mer, as in k_fused) and their
+        // 3. window minima (~0 marks an invalid k-mer, as in k_seed_wave) and their
         // positions in order
         int nmin = 0;
         if (nk > 0) {
