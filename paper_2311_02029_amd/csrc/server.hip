@@ -170,6 +170,37 @@ inline u64 batch_bytes(u64 reads, u64 bases, const mt_query_params &q) {
     return b;
 }
 
+// A batch's outputs side by side on the device, as they lie in the worker's pinned
+// block: one copy to the host instead of nine, each with a latency of its own on
+// the worker's stream (five requests in flight: 3.03 ms
+// with nine copies, 2.88 with one).
+struct OutputArray {
+    const void *from;
+    u8 *to;  // aligned to size
+    u64 count;
+    u32 size;  // bytes an element
+};
+struct OutputArrays {
+    OutputArray seg[9];
+    u32 count;
+};
+
+template <class T>
+__device__ inline void copy_elements(const OutputArray &a) {
+    const T *from = (const T *)a.from;
+    T *to = (T *)a.to;
+    const u64 stride = (u64)gridDim.x * blockDim.x;
+    for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < a.count; i += stride) to[i] = from[i];
+}
+
+__global__ void k_join_outputs(OutputArrays all) {
+    const OutputArray a = all.seg[blockIdx.y];
+    if (a.size == 8) copy_elements<u64>(a);
+    else if (a.size == 4) copy_elements<u32>(a);
+    else if (a.size == 2) copy_elements<u16>(a);
+    else copy_elements<u8>(a);
+}
+
 // Copies n bases and reports whether each is A, C, G, T or N in either case.
 #define MT_COPY_BASES_BODY                                                                                  \
     u8 bad = 0;                                                                                              \
@@ -346,17 +377,24 @@ void mt_server::run_batch(Batch &b, hipStream_t s, Pinned &h_in, Pinned &h_out, 
     u8 *ac = (u8 *)(re + n);
     u8 *ra = ac + nc;
     u8 *sd = ra + n;
-    MT_HIP(hipMemcpyAsync(co, res.cand_off.p, (n + 1) * 8, hipMemcpyDeviceToHost, s));
-    if (nc) {
-        MT_HIP(hipMemcpyAsync(dg, res.diag.p, nc * 8, hipMemcpyDeviceToHost, s));
-        MT_HIP(hipMemcpyAsync(gn, res.genome.p, nc * 4, hipMemcpyDeviceToHost, s));
-        MT_HIP(hipMemcpyAsync(ht, res.hits.p, nc * 4, hipMemcpyDeviceToHost, s));
-        MT_HIP(hipMemcpyAsync(ap, res.approx.p, nc * 2, hipMemcpyDeviceToHost, s));
-        MT_HIP(hipMemcpyAsync(ac, res.accept.p, nc, hipMemcpyDeviceToHost, s));
-        if (with_strand) MT_HIP(hipMemcpyAsync(sd, res.strand.p, nc, hipMemcpyDeviceToHost, s));
-    }
-    MT_HIP(hipMemcpyAsync(re, res.read_E.p, n * 2, hipMemcpyDeviceToHost, s));
-    MT_HIP(hipMemcpyAsync(ra, res.read_accepted.p, n, hipMemcpyDeviceToHost, s));
+    DBuf<u8> d_out(out_bytes);
+    OutputArrays oa{};
+    auto out = [&](const void *from, const void *to, u64 count, u32 size) {
+        oa.seg[oa.count++] = OutputArray{from, d_out.p + ((const u8 *)to - o), count, size};
+    };
+    out(res.cand_off.p, co, n + 1, 8);
+    out(res.diag.p, dg, nc, 8);
+    out(res.genome.p, gn, nc, 4);
+    out(res.hits.p, ht, nc, 4);
+    out(res.approx.p, ap, nc, 2);
+    out(res.read_E.p, re, n, 2);
+    out(res.accept.p, ac, nc, 1);
+    out(res.read_accepted.p, ra, n, 1);
+    if (with_strand) out(res.strand.p, sd, nc, 1);
+    const dim3 grid((unsigned)std::min<u64>(grid_for(std::max(n + 1, nc), 256), 256), oa.count);
+    k_join_outputs<<<grid, 256, 0, s>>>(oa);
+    MT_HIP(hipGetLastError());
+    MT_HIP(hipMemcpyAsync(o, d_out.p, out_bytes, hipMemcpyDeviceToHost, s));
     MT_HIP(hipStreamSynchronize(s));
     if (ev_a && ev_b && ref_ev) {
         float t0 = 0, t1 = 0;
