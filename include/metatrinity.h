@@ -243,7 +243,8 @@ int mt_last_stats(mt_stats *out);
  *   reads        host struct with device seq/offsets.
  *   pair_read    device, n_pairs read indices (< reads->n).
  *   pair_genome  device, n_pairs genome indices (< number of genomes).
- *   pair_diag    device, n_pairs diagonals (reference position of read base 0).
+ *   pair_diag    device, n_pairs diagonals (reference position of read base 0;
+ *                any value, a place outside the genome matches nothing).
  *   pair_E       device, n_pairs thresholds.
  *   approx_out   device, n_pairs outputs: obstacle count saturated at E + 1.
  *   accept_out   device, n_pairs outputs: approx <= E.

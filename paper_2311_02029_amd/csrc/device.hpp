@@ -123,6 +123,19 @@ __host__ __device__ inline u64 mix64(u64 z) {
     return z ^ (z >> 31);
 }
 
+// A caller's diagonal brought near the genome: it may be any 64-bit value, and sums
+// with it would wrap.  Past 2^33 either way no column of a read (65,535 bases, E up to
+// 65,534) lies in a genome (below 2^32 bases), so the columns compared stay the same.
+constexpr i64 DIAG_FAR = 1ll << 40;
+__host__ __device__ inline i64 near_diag(i64 diag) {
+    return diag < -DIAG_FAR ? -DIAG_FAR : diag > DIAG_FAR ? DIAG_FAR : diag;
+}
+
+// Whether every column of the band lies in a genome of length L (diag through near_diag).
+__host__ __device__ inline bool window_inside(i64 diag, int m, int E, i64 L) {
+    return diag - E >= 0 && diag + m + E <= L;
+}
+
 // Spreads the low 32 bits of x to the even bit positions of a 64-bit word.
 __device__ inline u64 spread_even(u64 x) {
     x = (x | (x << 16)) & 0x0000FFFF0000FFFFull;
@@ -196,10 +209,10 @@ __device__ inline Bits64 fetch_ref(const u64x2 *__restrict__ lohi, const u64 *__
 // with its bounds applied: a block before the genome or wholly past its end
 // reads as invalid (nb = 1), and positions at or past L inside the last
 // block get nb = 1.  has_n = 0 skips the N plane (the genome has no N).
-__device__ inline Bits64 ref_block(const u64x2 *__restrict__ lohi, const u64 *__restrict__ nb, i64 L, bool has_n,
-                                   i64 blk) {
+__host__ __device__ inline Bits64 ref_block(const u64x2 *__restrict__ lohi, const u64 *__restrict__ nb, i64 L,
+                                            bool has_n, i64 blk) {
     Bits64 r;
-    if (blk < 0 || blk * 64 >= L) {
+    if (blk < 0 || blk >= (L + 63) >> 6) {  // (blk * 64 could wrap)
         r.lo = r.hi = 0;
         r.nb = ~0ull;
         return r;

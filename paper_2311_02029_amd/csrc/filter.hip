@@ -58,6 +58,8 @@ __device__ inline void pair_fields(const FilterArgs &a, u64 p, u32 &r, u32 &g, i
     }
 }
 
+__device__ inline i64 pair_diag(const FilterArgs &a, u64 p) { return near_diag(a.pair_diag[p]); }
+
 __device__ inline int read_len(const FilterArgs &a, u32 r) { return (int)(a.read_off[r + 1] - a.read_off[r]); }
 
 // Blocks the long kernel stages for a pair: the read's (with its padding
@@ -71,7 +73,7 @@ __device__ inline void long_blocks(int m, int E, int &nrb, int &nwb) {
 // Whether any compared column of a pair can meet an N or a position outside the
 // genome.
 __device__ inline bool pair_with_n(const FilterArgs &a, u32 r, const GenomeMeta &gm, i64 diag, int m, int E) {
-    return meta_has_n(gm) || diag - E < 0 || diag + m + E > (i64)gm.len || a.read_has_n[r];
+    return meta_has_n(gm) || !window_inside(diag, m, E, (i64)gm.len) || a.read_has_n[r];
 }
 
 __device__ inline u8 pair_class(const FilterArgs &a, u64 p) {
@@ -89,7 +91,7 @@ __device__ inline u8 pair_class(const FilterArgs &a, u64 p) {
     for (int b = 0; b < LONG_BINS; b++)
         if (nrb + nwb <= LONG_CAP[b])
         {
-            const bool with_n = pair_with_n(a, r, a.meta[g], a.pair_diag[p], m, E);
+            const bool with_n = pair_with_n(a, r, a.meta[g], pair_diag(a, p), m, E);
             return (u8)((E > (with_n ? LONG_MAX_E_N : LONG_MAX_E) ? CLS_LONG_WIDE : with_n ? CLS_LONG_N : CLS_LONG) + b);
         }
     return CLS_GENERAL;
@@ -265,7 +267,7 @@ __global__ __launch_bounds__(256) void k_filter(FilterArgs a, const u32 *__restr
     v.rnb = a.ref_nb + gm.blk;
     v.L = (i64)gm.len;
     v.has_n = meta_has_n(gm);
-    v.diag = a.pair_diag[p];
+    v.diag = pair_diag(a, p);
     const int rows = 2 * E + 1;
     int approx;
     // One band row per lane and reads of up to 256 bases (the E <= 7 / 15 / 31
@@ -576,7 +578,7 @@ __global__ __launch_bounds__(LANE_TPB) __attribute__((amdgpu_waves_per_eu(4, 8))
     if (inside) {
         r = a.pair_read[p];
         g = a.pair_genome[p];
-        diag = a.pair_diag[p];
+        diag = pair_diag(a, p);
     }
     if (gate || t - lane >= np) return;  // malformed offsets; the whole wavefront is past the end
     const bool in = t < np;
@@ -602,7 +604,7 @@ __global__ __launch_bounds__(LANE_TPB) __attribute__((amdgpu_waves_per_eu(4, 8))
             wofs = (int)(diag - E - 64 * b0);
             nbr = (m + 63) / 64;
             nbw = (wofs + 2 * E + m + 63) / 64;
-            with_n = ok && (read_n || meta_has_n(gm) || diag - E < 0 || diag + m + E > (i64)gm.len);
+            with_n = ok && (read_n || meta_has_n(gm) || !window_inside(diag, m, E, (i64)gm.len));
         }
     }
     int c = 0;
@@ -704,7 +706,7 @@ __device__ inline void filter_long(const FilterArgs &a, const u32 *__restrict__ 
             bool ok;
             pair_fields(a, p, r, g, E, ok, err);
             m = read_len(a, r);
-            const i64 from = a.pair_diag[p] - E;
+            const i64 from = pair_diag(a, p) - E;
             b0 = from >> 6;  // first window block (floor)
             wofs = (int)(from - 64 * b0);
             strip = ((2 * E + 32) / 32 + G - 1) / G;  // words of 32 rows per lane
@@ -766,7 +768,7 @@ __device__ inline void filter_long(const FilterArgs &a, const u32 *__restrict__ 
             if (best >= left && end < m) {  // a run leaves the segment
                 const GenomeMeta gm = a.meta[g];
                 const PairView v{a.read_lohi + a.read_blk[r], a.read_nb + a.read_blk[r], m, a.ref_lohi + gm.blk,
-                                 a.ref_nb + gm.blk, (i64)gm.len, meta_has_n(gm), a.pair_diag[p]};
+                                 a.ref_nb + gm.blk, (i64)gm.len, meta_has_n(gm), pair_diag(a, p)};
                 best = 0;
                 for (int row = lg; row <= 2 * E; row += G) best = max(best, row_run(v, row - E, j));
                 best = long_group_max<G>(best);
@@ -984,7 +986,7 @@ __global__ void k_filter_simple(FilterArgs a, u64 n_cap) {
     const u64 *rn = a.ref_nb + gm.blk;
     const i64 L = (i64)gm.len;
     const bool hn = meta_has_n(gm);
-    const i64 diag = a.pair_diag[p];
+    const i64 diag = pair_diag(a, p);
     int c = 0;
     int dA = 0, dC = 0, dG = 0, dT = 0;  // read count minus window count per base
     for (int w0 = 0; w0 < m; w0 += 64) {
@@ -1057,7 +1059,7 @@ __global__ __launch_bounds__(64 * QG_WPB) void k_filter_qgram(FilterArgs a, u64 
         const u64 *rn = a.ref_nb + gm.blk;
         const i64 L = (i64)gm.len;
         const bool hn = meta_has_n(gm);
-        const i64 w0 = a.pair_diag[p] - E;
+        const i64 w0 = pair_diag(a, p) - E;
         const i64 nwq = (i64)m + 2 * (i64)E - QG_Q + 1;
         for (i64 t = lane; t < nwq; t += 64) {
             const Bits64 b = fetch_ref(rl, rn, L, hn, w0 + t);

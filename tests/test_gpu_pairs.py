@@ -161,3 +161,41 @@ def test_one_long_pair_per_bucket_alone(mt, long_case):
         sel = np.array([i])
         ap, ac = _run(mt, long_case, sel)
         assert ap[0] == long_case["want"][0][0][i], i
+
+
+# ---------------------------------------------------- places outside genomes --
+
+@pytest.mark.parametrize("kind", range(5))
+def test_diagonals_to_the_ends_of_64_bits(mt, kind):
+    """Any diagonal is a place; one far outside the genome matches nothing there, also
+    where a sum with it would wrap (the smallest value stands for "no place" in many
+    programs)."""
+    rng = np.random.default_rng(23)
+    clean = synth.ACGT[synth.random_codes(rng, 12_000)]
+    dirty = clean.copy()
+    dirty[5000] = ord("N")
+    ga = synth.SeqSet.from_list([clean.tobytes(), dirty.tobytes()])
+    top = 2**63 - 1
+    far = [-top - 1, -top, -top + 5, -top + 70_000, -2**40, -2**33, 2**32, 2**33, 2**40, 2**57 * 3, top - 140_000,
+           top - 65_600, top - 9_100, top - 1000, top - 200, top - 64, top - 7, top - 1, top]
+    reads, rows = [], []
+    for m in (1, 40, 150, 300, 700, 2500, 9000):
+        body = clean[100:100 + m].copy()
+        for with_n in (False, True):
+            if with_n:
+                body[m // 2] = ord("N")
+            reads.append(body.tobytes())
+            for E in (0, 1, 7, 15, 31, 32, 60, 700, 1500):
+                rows += [(len(reads) - 1, g, d, E) for g in (0, 1) for d in far + [100]]
+    rs = synth.SeqSet.from_list(reads)
+    r = np.array(rows, np.int64)
+    pr, pg, pe = r[:, 0].astype(np.uint32), r[:, 1].astype(np.uint32), r[:, 3].astype(np.uint16)
+    near = np.clip(r[:, 2], -2**33, 2**33)  # the oracle adds to it
+    want = oracle.Index(ga, 15, 10).filter_pairs(rs, pr, pg, near, pe, kind=kind)
+    case = dict(ix=mt.Index(ga, 15, 10), dr=mt.to_device(rs), pairs=(pr, pg, r[:, 2].copy(), pe))
+    classes = [np.flatnonzero((pe > 31) == long) for long in (False, True)]
+    for sel in [np.arange(len(rows)), *classes, *(np.flatnonzero(pe == E) for E in (7, 15, 31))]:
+        ap, ac = _run(mt, case, sel, kind)
+        bad = np.flatnonzero(ap != want[0][sel])
+        assert len(bad) == 0, [rows[sel[i]] for i in bad[:5]]
+        assert np.array_equal(ac, want[1][sel])
