@@ -173,7 +173,7 @@ __global__ __launch_bounds__(64 * CW_WPB) void k_count_wave(const u64 *__restric
                                                             u32 *__restrict__ stage_hits, u32 *__restrict__ ncand,
                                                             u32 *__restrict__ mid_list, u32 *__restrict__ n_mid) {
     const u32 lane = threadIdx.x & 63;
-    const u64 r = (u64)blockIdx.x * CW_WPB + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const u64 r = wide_block() * CW_WPB + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (r >= n) return;
     const u64 hs = read_hs[r], H = read_hs[r + 1] - hs;
     const u32 T = min_hits ? min_hits : 1;
@@ -604,7 +604,7 @@ static void stage_seed_count(const mt_index &ix, const mt_query_params &q, const
     last_stats().n_minimizers += n_min;
     last_stats().n_hits += H;
     if (n) {
-        k_count_wave<<<grid_for(n, CW_WPB), 64 * CW_WPB, 0, s>>>(hit_key.p, sc.read_hs.p, n, q.min_hits, q.top_n,
+        k_count_wave<<<wide_grid(n, CW_WPB, 64 * CW_WPB), 64 * CW_WPB, 0, s>>>(hit_key.p, sc.read_hs.p, n, q.min_hits, q.top_n,
                                                                   sc.stage_key.p, sc.stage_hits.p, sc.ncand.p,
                                                                   mid_list.p, n_mid);
         MT_HIP(hipGetLastError());
@@ -718,7 +718,7 @@ constexpr int SR_LANES = 16;  // lanes per read: 256 bases a pass
 // offsets passed k_strand_offsets.
 __global__ __launch_bounds__(256) void k_strand_bytes(const u8 *__restrict__ seq, const u64 *__restrict__ off, u64 n,
                                                       u8 *__restrict__ fwd, u8 *__restrict__ rev) {
-    const u64 r = ((u64)blockIdx.x * 256 + threadIdx.x) / SR_LANES;
+    const u64 r = (wide_block() * 256 + threadIdx.x) / SR_LANES;
     if (r >= n) return;
     const u64 a = off[r], m = off[r + 1] - a;
     for (u64 j = 16 * (threadIdx.x % SR_LANES); j < m; j += 16 * SR_LANES) {
@@ -894,8 +894,8 @@ static void classify_both_strands(const mt_index &ix, const mt_query_params &q, 
         check_flags(fh);
     }
     if (n) {
-        k_strand_bytes<<<grid_for(n * SR_LANES, 256), 256, 0, s>>>((const u8 *)reads.seq, reads.offsets, n, seq2.p,
-                                                                   seq2.p + reads.total);
+        k_strand_bytes<<<wide_grid(n, 256 / SR_LANES, 256), 256, 0, s>>>((const u8 *)reads.seq, reads.offsets, n,
+                                                                         seq2.p, seq2.p + reads.total);
         MT_HIP(hipGetLastError());
     }
     const mt_seqs two{(const char *)seq2.p, off2.p, 2 * n, 2 * reads.total};

@@ -31,6 +31,9 @@ struct alignas(16) u64x2 {
     u64 lo, hi;
 };
 
+// Number of the block in a grid of wide_grid().
+__device__ inline u64 wide_block() { return (u64)blockIdx.y * gridDim.x + blockIdx.x; }
+
 // Input-validation flags raised by kernels (OR-ed into one device word).
 enum : u32 {
     ERR_BAD_BYTE = 1u,

@@ -241,7 +241,7 @@ __device__ inline int walk_in_registers(const PairView &v, int E, int lane) {
 // null (n then also bounded by the pairs there are).
 template <int G>
 __global__ __launch_bounds__(256) void k_filter(FilterArgs a, const u32 *__restrict__ idx, u64 n) {
-    u64 tid = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+    u64 tid = wide_block() * blockDim.x + threadIdx.x;
     u64 t = tid / G;
     int lane = (int)(tid % G);
     if (t >= (idx ? n : pair_count(a, n))) return;
@@ -566,7 +566,7 @@ __global__ __launch_bounds__(LANE_TPB) __attribute__((amdgpu_waves_per_eu(4, 8))
     __shared__ __align__(16) u32 lds[LANE_TPB / 64][LANE_DW + LANE_PAD];
     const int lane = threadIdx.x & 63;
     u32 *S = lds[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)];
-    const u64 t = (u64)blockIdx.x * LANE_TPB + threadIdx.x;
+    const u64 t = wide_block() * LANE_TPB + threadIdx.x;
     // the pair's fields are requested along with the number of pairs (n bounds
     // their arrays) and looked at after it
     const bool inside = t < n;
@@ -882,13 +882,13 @@ struct Buckets {
 static void launch_short(const FilterArgs &a, const u32 *idx, u64 cnt, int bucket, int v, hipStream_t s) {
     if (cnt == 0) return;
     if (bucket < CLS_LONG && v == 0) {
-        const unsigned blocks = grid_for(cnt, LANE_TPB);
+        const dim3 blocks = wide_grid(cnt, LANE_TPB, LANE_TPB);
         if (bucket < 2) k_filter_lane<WalkFilter<1, 6>, false><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
         else k_filter_lane<WalkFilter<2, 7>, false><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
     } else if (bucket == 0 && v == 1) {
-        k_filter<32><<<grid_for(cnt * 32, 256), 256, 0, s>>>(a, idx, cnt);
+        k_filter<32><<<wide_grid(cnt, 8, 256), 256, 0, s>>>(a, idx, cnt);
     } else {
-        k_filter<64><<<grid_for(cnt * 64, 256), 256, 0, s>>>(a, idx, cnt);
+        k_filter<64><<<wide_grid(cnt, 4, 256), 256, 0, s>>>(a, idx, cnt);
     }
     MT_HIP(hipGetLastError());
 }
@@ -910,7 +910,7 @@ static void launch_bucket(const FilterArgs &a, const Buckets &B, int bucket, int
         if (v == 4) {
             for (int c : {bucket, cn, cw})
                 if (B.count[c])
-                    k_filter<64><<<grid_for((u64)B.count[c] * 64, 256), 256, 0, s>>>(a, B.of(c), B.count[c]);
+                    k_filter<64><<<wide_grid(B.count[c], 4, 256), 256, 0, s>>>(a, B.of(c), B.count[c]);
         } else {
             if (below <= 0)
                 launch_long<8>(a, idx, cnt, LONG_TILE, B.of(cn), B.count[cn], LONG_TILE_N, s);
@@ -966,7 +966,7 @@ static void bucket_pairs(const FilterArgs &a, u64 n_cap, DBuf<u32> &idx, u32 hc[
 // base) and reports ceil(L1 / 2).  Both saturate at E + 1.
 template <int KIND, bool kAscii>
 __global__ void k_filter_simple(FilterArgs a, u64 n_cap) {
-    const u64 p = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+    const u64 p = wide_block() * blockDim.x + threadIdx.x;
     if (kAscii && *a.gate) return;
     if (p >= pair_count(a, n_cap)) return;
     u32 r, g, err;
@@ -1179,11 +1179,11 @@ struct ShdFilter {
 void launch_filter_simple(const FilterArgs &a, u64 n, u32 kind, hipStream_t s) {
     if (n == 0) return;  // n: the capacity; the kernels read the count itself
     if (kind == MT_FILTER_HAMMING)
-        k_filter_simple<1, false><<<grid_for(n, 256), 256, 0, s>>>(a, n);
+        k_filter_simple<1, false><<<wide_grid(n, 256, 256), 256, 0, s>>>(a, n);
     else if (kind == MT_FILTER_BASE_COUNT)
-        k_filter_simple<2, false><<<grid_for(n, 256), 256, 0, s>>>(a, n);
+        k_filter_simple<2, false><<<wide_grid(n, 256, 256), 256, 0, s>>>(a, n);
     else if (kind == MT_FILTER_SHD)
-        k_filter_lane<ShdFilter, false><<<grid_for(n, LANE_TPB), LANE_TPB, 0, s>>>(a, nullptr, n);
+        k_filter_lane<ShdFilter, false><<<wide_grid(n, LANE_TPB, LANE_TPB), LANE_TPB, 0, s>>>(a, nullptr, n);
     else if (kind == MT_FILTER_QGRAM)
         k_filter_qgram<false><<<(unsigned)std::min<u64>(grid_for(n, QG_WPB), 65536), 64 * QG_WPB, 0, s>>>(a, n);
     else
@@ -1226,7 +1226,7 @@ void launch_filter(const FilterArgs &a, u64 n_cap, int fixed_E, hipStream_t s, T
 
 void launch_filter_fused(const FilterArgs &a, u64 cap, int max_E, u32 kind, hipStream_t s) {
     if (cap == 0) return;
-    const unsigned blocks = grid_for(cap, LANE_TPB);
+    const dim3 blocks = wide_grid(cap, LANE_TPB, LANE_TPB);
     static_assert(LANE_TPB == 256, "the simple filters share the grid");
     switch (kind) {
     case MT_FILTER_OBSTACLE:

@@ -293,7 +293,7 @@ __global__ void k_segment_map(const u64 *__restrict__ off, u64 n, u32 *__restric
 
 // One wavefront per segment.
 __global__ void k_segment_map_wave(const u64 *__restrict__ off, u64 n, u32 *__restrict__ map, u64 cap) {
-    const u64 sidx = ((u64)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    const u64 sidx = (wide_block() * blockDim.x + threadIdx.x) >> 6;
     if (sidx >= n) return;
     const u64 e = off[sidx + 1] < cap ? off[sidx + 1] : cap;
     for (u64 b = off[sidx] + (threadIdx.x & 63); b < e; b += 64) map[b] = (u32)sidx;
@@ -323,7 +323,7 @@ void segment_map(const u64 *off, u64 n, u32 *map, u64 cap, hipStream_t s) {
     if (n <= 4096)
         k_segment_search<<<grid_for(cap, 256), 256, 0, s>>>(off, n, map, cap);
     else if (cap / n >= 16)
-        k_segment_map_wave<<<grid_for(n * 64, 256), 256, 0, s>>>(off, n, map, cap);
+        k_segment_map_wave<<<wide_grid(n, 4, 256), 256, 0, s>>>(off, n, map, cap);
     else
         k_segment_map<<<grid_for(n, 256), 256, 0, s>>>(off, n, map, cap);
     MT_HIP(hipGetLastError());

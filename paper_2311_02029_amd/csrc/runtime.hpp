@@ -125,6 +125,17 @@ inline unsigned grid_for(u64 items, u64 per_block) {
     return (unsigned)g;
 }
 
+// Grid of a 1-D launch with more threads than one dimension holds (HIP:
+// gridDim.x * blockDim.x below 2^32): the blocks go on in y, and a kernel numbers
+// them by wide_block().  The last row may have blocks past the items.
+inline dim3 wide_grid(u64 items, u64 per_block, u32 threads) {
+    const u64 blocks = items / per_block + (items % per_block != 0), row = 0xFFFFFFFFull / threads;
+    if (blocks <= row) return dim3((unsigned)(blocks ? blocks : 1));
+    const u64 rows = (blocks - 1) / row + 1;
+    if (rows > 65535) throw Error(MT_EINVAL, "launch too large");
+    return dim3((unsigned)row, (unsigned)rows);
+}
+
 // HIP-event timing of named launches on one stream (enabled by mt_set_timing).
 struct Timer {
     hipStream_t stream = nullptr;

@@ -71,7 +71,7 @@ __global__ __launch_bounds__(256) void k_pack(const u8 *__restrict__ seq, const 
                                               const u32 *__restrict__ map, u64x2 *__restrict__ lohi,
                                               u64 *__restrict__ nbp, u32 *__restrict__ flags,
                                               u8 *__restrict__ has_n) {
-    const u64 t = (u64)blockIdx.x * 256 + threadIdx.x;
+    const u64 t = wide_block() * 256 + threadIdx.x;
     const u64 b = t >> 2;
     const u32 quarter = (u32)t & 3u;
     if (b >= blk_off[n] || b >= cap) return;  // whole quads leave
@@ -140,9 +140,9 @@ void pack_sequences(const mt_seqs &in, u64 len_limit, u32 len_flag, const char *
     scan_u64(nblk.p, out.blk_off.p, in.n, s);
     DBuf<u32> map(out.blocks_cap);
     segment_map(out.blk_off.p, in.n, map.p, out.blocks_cap, s);
-    k_pack<<<grid_for(out.blocks_cap * 4, 256), 256, 0, s>>>((const u8 *)in.seq, in.offsets, src, out.blk_off.p,
-                                                              in.n, src ? src_total : in.total, out.blocks_cap, map.p, out.lohi.p, out.nb.p,
-                                                              d_flags, has_n);
+    k_pack<<<wide_grid(out.blocks_cap, 64, 256), 256, 0, s>>>((const u8 *)in.seq, in.offsets, src, out.blk_off.p, in.n,
+                                                              src ? src_total : in.total, out.blocks_cap, map.p,
+                                                              out.lohi.p, out.nb.p, d_flags, has_n);
     MT_HIP(hipGetLastError());
 }
 
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(TPB) void k_min_tiles(const u64x2 *__restrict__ loh
     constexpr int SPAN = TILE + 2 * MAX_HALO, WORDS = TILE / 64;
     __shared__ u64 sh_h[SPAN + MIN_RUN];  // the last thread's windows past the last one read on
     __shared__ u32 marks[2 * WORDS];
-    const u64 t = blockIdx.x;
+    const u64 t = wide_block();
     if (t >= tile_off[n]) return;
     const u32 s = tile_map[t];
     const i64 lt = (i64)(t - tile_off[s]);
@@ -364,7 +364,7 @@ __global__ __launch_bounds__(64 * EMIT_WPB) void k_min_emit(const u64x2 *__restr
     __shared__ u16 list_all[EMIT_WPB][TILE];
     const u32 lane = threadIdx.x & 63;
     const u32 wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const u64 t = (u64)blockIdx.x * EMIT_WPB + wid;
+    const u64 t = wide_block() * EMIT_WPB + wid;
     if (t >= tile_off[n]) return;
     u16 *list = list_all[wid];
     const u32 s = tile_map[t];
@@ -400,7 +400,7 @@ __global__ __launch_bounds__(64 * EMIT_WPB) void k_min_emit(const u64x2 *__restr
 
 template <int TPB, int TILE>
 static void launch_tiles(const mt_seqs &in, const PackedSeqs &ps, u32 k, u32 w, MinimizerPlan &mp, hipStream_t s) {
-    k_min_tiles<TPB, TILE><<<grid_for(mp.tiles_cap, 1), TPB, 0, s>>>(ps.lohi.p, ps.nb.p, ps.blk_off.p, in.offsets,
+    k_min_tiles<TPB, TILE><<<wide_grid(mp.tiles_cap, 1, TPB), TPB, 0, s>>>(ps.lohi.p, ps.nb.p, ps.blk_off.p, in.offsets,
                                                                       mp.tile_off.p, mp.tile_map.p, in.n, k, w,
                                                                       mp.tile_count.p, mp.tile_bits.p);
     MT_HIP(hipGetLastError());
@@ -409,7 +409,7 @@ static void launch_tiles(const mt_seqs &in, const PackedSeqs &ps, u32 k, u32 w, 
 template <int TILE>
 static void launch_emit(const mt_seqs &in, const PackedSeqs &ps, u32 k, MinimizerPlan &mp, u64 *out_x,
                         u32 *out_seq, u32 *out_pos, hipStream_t s) {
-    k_min_emit<TILE><<<grid_for(mp.tiles_cap, EMIT_WPB), 64 * EMIT_WPB, 0, s>>>(
+    k_min_emit<TILE><<<wide_grid(mp.tiles_cap, EMIT_WPB, 64 * EMIT_WPB), 64 * EMIT_WPB, 0, s>>>(
         ps.lohi.p, ps.nb.p, ps.blk_off.p, mp.tile_off.p, mp.tile_map.p, in.n, k, mp.tile_bits.p, mp.min_off.p, out_x,
         out_seq, out_pos);
     MT_HIP(hipGetLastError());

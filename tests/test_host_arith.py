@@ -1,6 +1,7 @@
 """Host arithmetic shared with the kernels, compiled for the host alone: positions of
 a read's band on a genome for diagonals up to the ends of 64 bits, where the sums and
-products wrap, and every block of a genome against its bounds.
+products wrap, every block of a genome against its bounds, and grids of more threads
+than a dimension holds.
 """
 import os
 import subprocess
@@ -94,10 +95,32 @@ static int blocks() {
     return 0;
 }
 
+static int grids() {
+    const u64 per[] = {1, 4, 8, 16, 64, 256};
+    for (u64 p : per)
+        for (int s = 0; s < 40; s++)
+            for (i64 o = -2; o <= 2; o++) {
+                const i64 items = (1ll << s) + o;
+                if (items < 0 || items / (i64)p > (1ll << 38)) continue;
+                const dim3 g = wide_grid((u64)items, p, 256);
+                CHECK((u64)g.x * 256 < (1ull << 32) && g.y <= 65535 && g.z == 1, "%lld", (long long)items);
+                CHECK((u64)g.x * g.y >= ((u64)items + p - 1) / p, "%lld", (long long)items);
+                CHECK((u64)g.x * (g.y - 1) < ((u64)items + p - 1) / p || g.y == 1, "%lld", (long long)items);
+            }
+    try {
+        wide_grid(~0ull, 1, 1024);
+        CHECK(false, "not refused");
+    } catch (const Error &e) {
+        CHECK(e.status == MT_EINVAL, "%d", e.status);
+    }
+    return 0;
+}
+
 int main(int, char **argv) {
     const std::string what = argv[1];
     if (what == "diagonals") return diagonals();
     if (what == "blocks") return blocks();
+    if (what == "grids") return grids();
     return 2;
 }
 """
@@ -113,7 +136,7 @@ def program(tmp_path_factory):
     return str(exe)
 
 
-@pytest.mark.parametrize("what", ["diagonals", "blocks"])
+@pytest.mark.parametrize("what", ["diagonals", "blocks", "grids"])
 def test_arithmetic(program, what):
     r = subprocess.run([program, what], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, (r.returncode, r.stdout)
