@@ -504,7 +504,8 @@ typedef struct mt_mem_stats {
 } mt_mem_stats;
 int mt_memory_stats(mt_mem_stats *out);
 
-/* Releases device memory cached by the library's allocator (not held by any handle). */
+/* Releases device memory cached by the library's allocator (not held by any handle),
+ * and the library's pinned host memory when no call is using it. */
 int mt_trim(void);
 /* Description of the last error on the calling thread ("" if none). */
 const char *mt_last_error(void);

@@ -398,6 +398,7 @@ extern "C" int mt_abi_version(void) { return MT_ABI_VERSION; }
 
 extern "C" int mt_trim(void) {
     mt::pool_trim();
+    mt::trim_host_words();
     return MT_OK;
 }
 

@@ -149,6 +149,9 @@ struct Timer {
 
 bool timing_enabled();
 
+// Gives back the pinned memory of read_back when no call is using it.
+void trim_host_words();
+
 // Work counts of the last classification on this thread (mt_last_stats).
 mt_stats &last_stats();
 

@@ -2,41 +2,75 @@
 // (seeding, Fig. 1 steps 2a and 2b).
 #include <cstdint>
 #include <cstring>
+#include <mutex>
 
 #include "seq.hpp"
 
 namespace mt {
 
 // Small results (counts, flags, a call's summary) are written by a kernel into
-// pinned memory of the host thread and read after the wait: a copy to pageable
+// pinned memory and read after the wait: a copy to pageable
 // memory goes through the runtime's staging and is waited for there as well (16 reads
 // classified and taken to the host 131 us, 116 us so; 1M explicit pairs, with two
 // such waits, 243 and 208 us).  Bound by latency.
-constexpr u32 READ_WORDS = 256;
+// The library has one block of WORD_SLOTS places, for as many calls waiting at once;
+// the next one copies.  (A place per host thread cost a program that starts a thread
+// for each call an allocation each: 0.21 ms a call of 16 reads, 0.15 so; and its release
+// at the thread's end waits for the whole device.)
+constexpr u32 READ_WORDS = 256, WORD_SLOTS = 64;
 
-struct HostWords {
+static struct {
+    std::mutex mu;
     u32 *p = nullptr;
-    ~HostWords() {
-        if (p) (void)hipHostFree(p);
+    u64 used = 0;  // bit i: place i
+} g_words;
+
+// A free place, or null when there is none.
+static u32 *take_words() {
+    std::lock_guard<std::mutex> g(g_words.mu);
+    if (!g_words.p && hipHostMalloc((void **)&g_words.p, WORD_SLOTS * READ_WORDS * sizeof(u32),
+                                    hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();
+        g_words.p = nullptr;
     }
-};
-static thread_local HostWords g_words;
+    if (!g_words.p || g_words.used == ~0ull) return nullptr;
+    const int i = __builtin_ctzll(~g_words.used);
+    g_words.used |= 1ull << i;
+    return g_words.p + i * READ_WORDS;
+}
+
+static void give_words(u32 *w) {
+    std::lock_guard<std::mutex> g(g_words.mu);
+    g_words.used &= ~(1ull << ((w - g_words.p) / READ_WORDS));
+}
+
+void trim_host_words() {
+    std::lock_guard<std::mutex> g(g_words.mu);
+    if (!g_words.p || g_words.used) return;
+    (void)hipHostFree(g_words.p);
+    g_words.p = nullptr;
+}
 
 __global__ void k_read_back(const u32 *__restrict__ dev, u32 n, u32 *__restrict__ host) {
     if (threadIdx.x < n) __hip_atomic_store(&host[threadIdx.x], dev[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 void read_back(hipStream_t s, const void *dev, void *host, size_t bytes) {
-    if (bytes == 0 || bytes > READ_WORDS * sizeof(u32) || bytes % sizeof(u32) || (uintptr_t)dev % sizeof(u32)) {
+    static_assert(WORD_SLOTS == 64, "a bit of a word each");
+    const bool small = bytes && bytes <= READ_WORDS * sizeof(u32) && bytes % sizeof(u32) == 0 &&
+                       (uintptr_t)dev % sizeof(u32) == 0;
+    u32 *words = small ? take_words() : nullptr;
+    if (!words) {
         MT_HIP(hipMemcpyAsync(host, dev, bytes, hipMemcpyDeviceToHost, s));
         MT_HIP(hipStreamSynchronize(s));
         return;
     }
-    if (!g_words.p) MT_HIP(hipHostMalloc((void **)&g_words.p, READ_WORDS * sizeof(u32), hipHostMallocPortable));
-    k_read_back<<<1, READ_WORDS, 0, s>>>((const u32 *)dev, (u32)(bytes / sizeof(u32)), g_words.p);
+    // (a place whose kernel is not known to have ended is not given back)
+    k_read_back<<<1, READ_WORDS, 0, s>>>((const u32 *)dev, (u32)(bytes / sizeof(u32)), words);
     MT_HIP(hipGetLastError());
     MT_HIP(hipStreamSynchronize(s));
-    std::memcpy(host, g_words.p, bytes);
+    std::memcpy(host, words, bytes);
+    give_words(words);
 }
 
 // ------------------------------------------------------------------ packing --
