@@ -523,8 +523,8 @@ void launch_reduce_slots(const mt_result &res, const mt_index &ix, const u64 *sl
 void ReadBatch::prepare(const mt_seqs &reads, u32 e_mode, u32 e_value, hipStream_t s, const u64 *src,
                         u64 src_total) {
     n = reads.n;
-    flags.alloc(1);
-    MT_HIP(hipMemsetAsync(flags.p, 0, sizeof(u32), s));
+    flags.alloc(2);
+    MT_HIP(hipMemsetAsync(flags.p, 0, 2 * sizeof(u32), s));
     read_E.alloc(n);
     if (n) {
         k_read_setup<<<grid_for(n, 256), 256, 0, s>>>(reads.offsets, n, e_mode, e_value, read_E.p, flags.p);
@@ -638,6 +638,7 @@ static void stage_filter_reduce(const mt_index &ix, const mt_query_params &q, co
     fa.read_lohi = rb.planes.lohi.p;
     fa.read_nb = rb.planes.nb.p;
     fa.read_has_n = rb.has_n.p;
+    fa.max_len = rb.planes.max_len;
     fa.n_genomes = ix.n_genomes;
     fa.meta = ix.meta.p;
     fa.ref_lohi = ix.ref.lohi.p;
@@ -1163,6 +1164,7 @@ extern "C" int mt_filter_pairs_kind(const mt_index *index, const mt_seqs *reads,
         fa.read_lohi = rb.planes.lohi.p;
         fa.read_nb = rb.planes.nb.p;
         fa.read_has_n = rb.has_n.p;
+        fa.max_len = rb.planes.max_len;
         fa.n_genomes = index->n_genomes;
         fa.meta = index->meta.p;
         fa.ref_lohi = index->ref.lohi.p;

@@ -53,7 +53,7 @@ namespace mt {
 // Per-call read state shared by both execution forms.
 struct ReadBatch {
     u64 n = 0;
-    DBuf<u32> flags;   // validation flags
+    DBuf<u32> flags;   // validation flags, longest read
     DBuf<u16> read_E;  // E per read
     DBuf<u8> has_n;    // 1 if the read has an N
     PackedSeqs planes; // read bit planes
@@ -77,6 +77,8 @@ struct FilterArgs {
     const u64x2 *read_lohi;
     const u64 *read_nb;
     const u8 *read_has_n;
+    u32 max_len;      // of the reads (at most)
+    int far_len;      // short E: reads past it take groups of lanes (set by launch_filter)
     u64 n_genomes;
     const GenomeMeta *meta;
     const u64x2 *ref_lohi;
@@ -94,7 +96,8 @@ struct FilterArgs {
 // Filters pairs [0, n) (n = *n_dev if set, else n_host; n_cap bounds it):
 // pairs are bucketed by their E (one synchronization to size the buckets),
 // then each bucket runs the kernel shaped for it.  fixed_E: the E of every
-// pair when the caller knows it, else -1; pairs of one short E need no buckets.
+// pair when the caller knows it, else -1; pairs of one short E need no buckets unless
+// some of many are of long reads.
 void launch_filter(const FilterArgs &a, u64 n_cap, int fixed_E, hipStream_t s, Timer *tm = nullptr);
 // Pairs [0, *n_dev) of the fused form (at most cap), every E at most max_E <= 31,
 // through filter kind.

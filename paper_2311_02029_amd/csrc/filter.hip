@@ -3,8 +3,9 @@
 //
 // Pairs are bucketed by their threshold E, and long pairs by the LDS they
 // need, so that each bucket gets the kernel shaped for it (uneven batching):
-//   E <= 31  one lane per pair, the rows as the bits of one or two words; or
-//            groups of G lanes per pair, one band row per lane (G = 32 or 64 for
+//   E <= 31  one lane per pair, the rows as the bits of one or two words; groups of G
+//            lanes per pair, one band row per lane, for longer reads (see far_len; G = 16
+//            for E <= 7, 32 for E <= 15, else 64), or for all (G = 32 or 64 for
 //            E <= 7, 64 for E <= 15)
 //   E > 31   long reads, four bins by the 64-base blocks of read plus
 //            reference window they stage in LDS (<= 96, 192, 384, 768): 1, 2, 4
@@ -14,6 +15,7 @@
 //   larger   the rows-in-lanes kernel.
 // The variant of each bucket (lane or G, pairs per wavefront, layout) is chosen by the autotuner
 // (mt_autotune) or set by mt_tune_set; every variant gives the same result.
+#include <algorithm>
 #include <mutex>
 #include <string>
 
@@ -26,11 +28,11 @@ constexpr int CLS_LONG = 3, LONG_BINS = 4, CLS_GENERAL = 7;
 // Classes are the buckets, and the long bins twice more: for the pairs with an N
 // in read or window, or a window past a genome end, which stage and compare a
 // third plane (CLS_LONG_N), and for bands too wide to stage in segments
-// (CLS_LONG_WIDE).
-constexpr int CLS_LONG_N = N_BUCKETS, CLS_LONG_WIDE = CLS_LONG_N + LONG_BINS;
-constexpr int N_CLASSES = CLS_LONG_WIDE + LONG_BINS;
+// (CLS_LONG_WIDE); and the short ones once more, for reads past far_len (CLS_FAR).
+constexpr int CLS_LONG_N = N_BUCKETS, CLS_LONG_WIDE = CLS_LONG_N + LONG_BINS, CLS_FAR = CLS_LONG_WIDE + LONG_BINS;
+constexpr int N_CLASSES = CLS_FAR + CLS_LONG;
 __host__ __device__ inline int class_bucket(int c) {
-    return c < N_BUCKETS ? c : CLS_LONG + (c - N_BUCKETS) % LONG_BINS;
+    return c < N_BUCKETS ? c : c >= CLS_FAR ? c - CLS_FAR : CLS_LONG + (c - N_BUCKETS) % LONG_BINS;
 }
 constexpr int LONG_CAP[LONG_BINS] = {96, 192, 384, 768};  // 64-base blocks staged per wavefront
 constexpr int LDS_BLOCK_BYTES = 24;                        // {lo, hi} + nb of one 64-base block
@@ -82,9 +84,10 @@ __device__ inline u8 pair_class(const FilterArgs &a, u64 p) {
     bool ok;
     pair_fields(a, p, r, g, E, ok, err);
     if (!ok) return CLS_GENERAL;  // the general kernel reports the error
-    if (E <= 7) return 0;
-    if (E <= 15) return 1;
-    if (E <= 31) return 2;
+    if (E <= 31) {
+        const int b = E <= 7 ? 0 : E <= 15 ? 1 : 2;
+        return (u8)(a.max_len > (u32)a.far_len && read_len(a, r) > a.far_len ? CLS_FAR + b : b);
+    }
     int nrb, nwb;
     const int m = read_len(a, r);
     long_blocks(m, E, nrb, nwb);
@@ -292,6 +295,21 @@ __device__ inline void lds_wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Longest read of a short E whose pair takes one lane, of n pairs.  A lane's time goes
+// with the read and hardly with the number of pairs (1 kbp at E = 7, 2,000 pairs to
+// 120,000: 0.14 to 0.19 ms the whole call), that of groups with the number of pairs and
+// hardly with the read (0.09 to 0.18 ms), so they meet at a ratio, about 90 pairs a base
+// for E = 7 and 50 for E = 31.  Lanes and groups at E = 7 (E = 31): 300 bases, 2,000
+// pairs 0.10 and 0.09 ms (0.13, 0.10), 400,000 0.17 and 0.36 (0.26, 1.44); 1 kbp, 2,000
+// 0.19 and 0.10 (0.29, 0.10), 120,000 0.24 and 0.25 (0.36, 0.62); 2 kbp, 60,000 0.41 and
+// 0.21 (0.73, 0.45); 10 kbp, 12,000 3.3 and 0.16.  Reads up to 256 bases keep to lanes;
+// past 1 kbp too few pairs fit a wavefront's LDS at once.
+constexpr int FAR_LEAST = 256, FAR_MOST = 1024;
+constexpr u64 FAR_PAIRS = 64;  // pairs a base
+static int far_len(u64 n) {
+    return (int)std::min<u64>(std::max<u64>(n / FAR_PAIRS, FAR_LEAST), FAR_MOST);
+}
+
 // One lane per pair, E <= 31.  The walk is a serial chain of a few steps, each
 // over the 2E+1 rows; here a lane takes a pair's whole step with the rows as
 // the bits of R 32-bit words.  Column t of all rows at once: the window's planes
@@ -308,8 +326,9 @@ __device__ inline void lds_wave_sync() {
 // The pair's read and window planes are staged in LDS: every step reads them at
 // places of its own per lane, which the vector cache serves one line at a time.
 // A wavefront's 64 pairs share LANE_DW dwords (a pair of 150 bases takes 24 to
-// 28, with the N planes 42); longer pairs go in several batches, and one that
-// does not fit at all (reads past 20 kbp) takes the whole wavefront.
+// 28, with the N planes 42); longer pairs go in several batches.  The whole read is
+// staged, by its lane, however soon the walk ends, so longer reads (past far_len) are
+// left to the groups of lanes, which read what a step touches.
 constexpr int LANE_TPB = 256, LANE_DW = 2552, LANE_PAD = 8;  // 40 KB a block: four blocks a CU
 
 // A pair's planes in LDS as dwords of 32 bases: the read's from its first base, the
@@ -549,18 +568,17 @@ __device__ inline LdsPair stage_pair(const FilterArgs &a, u32 *S, u64 rb, int nb
 // rows in R words, surviving NC columns ...
 template <int R, int NC>
 struct WalkFilter {
-    static constexpr int MAX_M = 1 << 16;
-    static constexpr bool AHEAD = true;
+    static constexpr int MAX_M = FAR_MOST;
+    static constexpr bool AHEAD = true, ALL_FIT = true;
     template <bool kN>
     __device__ static int value(const LdsPair &P, int wofs, int m, int E) {
         return lane_walk<R, NC, kN>(P, wofs, m, E);
     }
-    // a pair that does not fit in LDS, by the whole wavefront
-    __device__ static int by_wave(const PairView &v, int E, int lane) { return obstacle_walk<64>(v, E, lane); }
 };
 
-// kAscii: the fused form's pairs, reads of at most 320 bases as ASCII (no pair
-// is too long for the LDS).
+// kAscii: the fused form's pairs, reads of at most 320 bases as ASCII.  A pair that
+// does not fit in LDS (F::ALL_FIT: there is none, by its class) takes the whole
+// wavefront.
 template <class F, bool kAscii>
 __global__ __launch_bounds__(LANE_TPB) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_filter_lane(FilterArgs a, const u32 *__restrict__ idx, u64 n) {
     __shared__ __align__(16) u32 lds[LANE_TPB / 64][LANE_DW + LANE_PAD];
@@ -612,7 +630,6 @@ __global__ __launch_bounds__(LANE_TPB) __attribute__((amdgpu_waves_per_eu(4, 8))
     const int need = (any_n ? 6 : 4) * (nbr + nbw);
     const bool fits = need <= LANE_DW && m <= F::MAX_M;
     u64 todo = __ballot(ok && m > 0 && fits);
-    u64 big = __ballot(ok && !fits);
     while (todo) {
         int end = ((todo >> lane) & 1) ? need : 0;  // inclusive prefix sum of the lanes left
         const int mine = end;
@@ -634,22 +651,30 @@ __global__ __launch_bounds__(LANE_TPB) __attribute__((amdgpu_waves_per_eu(4, 8))
         todo &= ~__ballot(now);
         lds_wave_sync();
     }
-    while (!kAscii && big) {
-        const int l = __builtin_ctzll(big);
-        big &= big - 1;
-        const u32 wr = __shfl(r, l, 64), wg = __shfl(g, l, 64);
-        const GenomeMeta wm = a.meta[wg];
-        PairView v;
-        v.qlohi = a.read_lohi + a.read_blk[wr];
-        v.qnb = a.read_nb + a.read_blk[wr];
-        v.m = read_len(a, wr);
-        v.rlohi = a.ref_lohi + wm.blk;
-        v.rnb = a.ref_nb + wm.blk;
-        v.L = (i64)wm.len;
-        v.has_n = meta_has_n(wm);
-        v.diag = __shfl(diag, l, 64);
-        const int wc = F::by_wave(v, __shfl(E, l, 64), lane);
-        if (lane == l) c = wc;
+    if constexpr (kAscii || F::ALL_FIT) {
+        if (ok && !fits) {
+            ok = false;
+            err = ERR_INTERNAL;
+        }
+    } else {
+        u64 big = __ballot(ok && !fits);
+        while (big) {
+            const int l = __builtin_ctzll(big);
+            big &= big - 1;
+            const u32 wr = __shfl(r, l, 64), wg = __shfl(g, l, 64);
+            const GenomeMeta wm = a.meta[wg];
+            PairView v;
+            v.qlohi = a.read_lohi + a.read_blk[wr];
+            v.qnb = a.read_nb + a.read_blk[wr];
+            v.m = read_len(a, wr);
+            v.rlohi = a.ref_lohi + wm.blk;
+            v.rnb = a.ref_nb + wm.blk;
+            v.L = (i64)wm.len;
+            v.has_n = meta_has_n(wm);
+            v.diag = __shfl(diag, l, 64);
+            const int wc = F::by_wave(v, __shfl(E, l, 64), lane);
+            if (lane == l) c = wc;
+        }
     }
     if (!in) return;
     if (!ok) atomicOr(a.flags, err);
@@ -878,14 +903,16 @@ struct Buckets {
     const u32 *of(int cls) const { return idx ? idx + at[cls] : nullptr; }
 };
 
-// Launches the pairs of a short bucket or the general one.
-static void launch_short(const FilterArgs &a, const u32 *idx, u64 cnt, int bucket, int v, hipStream_t s) {
+// Launches the pairs of a short bucket or the general one.  far: of reads past far_len.
+static void launch_short(const FilterArgs &a, const u32 *idx, u64 cnt, int bucket, int v, bool far, hipStream_t s) {
     if (cnt == 0) return;
-    if (bucket < CLS_LONG && v == 0) {
+    if (bucket == 0 && v == 0 && far) {
+        k_filter<16><<<wide_grid(cnt, 16, 256), 256, 0, s>>>(a, idx, cnt);
+    } else if (bucket < CLS_LONG && v == 0 && !far) {
         const dim3 blocks = wide_grid(cnt, LANE_TPB, LANE_TPB);
         if (bucket < 2) k_filter_lane<WalkFilter<1, 6>, false><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
         else k_filter_lane<WalkFilter<2, 7>, false><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
-    } else if (bucket == 0 && v == 1) {
+    } else if ((bucket == 0 && v == 1) || (bucket == 1 && v == 0)) {
         k_filter<32><<<wide_grid(cnt, 8, 256), 256, 0, s>>>(a, idx, cnt);
     } else {
         k_filter<64><<<wide_grid(cnt, 4, 256), 256, 0, s>>>(a, idx, cnt);
@@ -924,7 +951,8 @@ static void launch_bucket(const FilterArgs &a, const Buckets &B, int bucket, int
         }
         MT_HIP(hipGetLastError());
     } else {
-        launch_short(a, idx, cnt, bucket, v, s);
+        launch_short(a, idx, cnt, bucket, v, false, s);
+        if (bucket < CLS_LONG) launch_short(a, B.of(CLS_FAR + bucket), B.count[CLS_FAR + bucket], bucket, v, true, s);
     }
 }
 
@@ -1109,7 +1137,7 @@ __device__ inline u64 shd_amend(u64 xp, u64 x, u64 xn) {
 // E = 5: 74 us with each row word fetched from global memory, SHD_US us staged.
 struct ShdFilter {
     static constexpr int WORDS = 5, MAX_M = 64 * WORDS;
-    static constexpr bool AHEAD = false;
+    static constexpr bool AHEAD = false, ALL_FIT = false;
     template <bool kN>
     __device__ static int value(const LdsPair &P, int wofs, int m, int E) {
         u64 acc[WORDS];
@@ -1203,13 +1231,17 @@ static const char *const BUCKET_MARKS[N_BUCKETS] = {"filter E<=7",     "filter E
                                                     "filter long<=96", "filter long<=192", "filter long<=384",
                                                     "filter long<=768", "filter general"};
 
-void launch_filter(const FilterArgs &a, u64 n_cap, int fixed_E, hipStream_t s, Timer *tm) {
+void launch_filter(const FilterArgs &args, u64 n_cap, int fixed_E, hipStream_t s, Timer *tm) {
     if (n_cap == 0) return;
-    if (fixed_E >= 0 && fixed_E <= 31) {
+    FilterArgs a = args;
+    a.far_len = far_len(n_cap);
+    const bool near = a.max_len <= (u32)a.far_len;
+    if (fixed_E >= 0 && fixed_E <= 31 && (near || a.far_len == FAR_LEAST)) {
         // one class, known without looking at the pairs: no bucketing and no
-        // synchronization (pairs out of range are reported by every kernel)
+        // synchronization (pairs out of range are reported by every kernel; a few pairs
+        // are not worth telling long reads from short ones either)
         const int c = fixed_E <= 7 ? 0 : fixed_E <= 15 ? 1 : 2;
-        launch_short(a, nullptr, n_cap, c, current_variant(c), s);
+        launch_short(a, nullptr, n_cap, c, current_variant(c), !near, s);
         if (tm) tm->mark(BUCKET_MARKS[c]);
         return;
     }
@@ -1253,8 +1285,10 @@ void launch_filter_fused(const FilterArgs &a, u64 cap, int max_E, u32 kind, hipS
 
 // Times every variant of every bucket that holds pairs (best of `reps`
 // launches each, after one untimed launch) and keeps the fastest.
-void autotune_filter(const FilterArgs &a, u64 n_pairs, u32 reps, hipStream_t s) {
+void autotune_filter(const FilterArgs &args, u64 n_pairs, u32 reps, hipStream_t s) {
     if (n_pairs == 0) return;
+    FilterArgs a = args;
+    a.far_len = far_len(n_pairs);
     DBuf<u32> idx;
     u32 hc[N_CLASSES], hb[N_CLASSES];
     bucket_pairs(a, n_pairs, idx, hc, hb, s);

@@ -510,8 +510,8 @@ void build_index(mt_index &ix, const mt_index_params &p, const mt_seqs &g, const
     ix.n_genomes = g.n;
     ix.total_bases = g.total;
 
-    DBuf<u32> flags(1);
-    MT_HIP(hipMemsetAsync(flags.p, 0, sizeof(u32), s));
+    DBuf<u32> flags(2);
+    MT_HIP(hipMemsetAsync(flags.p, 0, 2 * sizeof(u32), s));
     ix.has_n.alloc(g.n);
     MT_HIP(hipMemsetAsync(ix.has_n.p, 0, g.n ? g.n : 1, s));
     pack_sequences(g, 4294901759ull, ERR_READ_TOO_LONG, "genome length must be below 2^32 - 2^16", ix.ref,

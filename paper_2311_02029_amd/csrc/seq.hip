@@ -1,5 +1,6 @@
 // Packing sequences into bit planes and tiled minimizer extraction
 // (seeding, Fig. 1 steps 2a and 2b).
+#include <algorithm>
 #include <cstdint>
 #include <cstring>
 #include <mutex>
@@ -76,21 +77,35 @@ void read_back(hipStream_t s, const void *dev, void *host, size_t bytes) {
 // ------------------------------------------------------------------ packing --
 
 // Blocks per sequence: ceil(len / 64) + 1 (the last one is padding).  Also
-// checks the offsets: 0 first, never decreasing, `total` last.
-__global__ void k_seq_blocks(const u64 *__restrict__ off, u64 n, u64 total, u64 len_limit, u32 len_flag,
-                             u64 *__restrict__ nblk, u32 *__restrict__ flags) {
-    u64 s = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    u64 a = off[s], b = off[s + 1];
-    u32 f = 0;
-    if (b < a || b > total || (s == 0 && a != 0) || (s == n - 1 && b != total)) f |= ERR_OFFSETS;
-    u64 len = b >= a ? b - a : 0;
-    if (len > len_limit) f |= len_flag;
-    if (f) {
-        atomicOr(flags, f);
-        len = 0;
+// checks the offsets: 0 first, never decreasing, `total` last; and leaves the longest
+// length in flags[1], an atomic a block (an atomic a wavefront on that one word took
+// 35 us for 300k reads).
+constexpr int SB_TPB = 1024, SB_BLOCKS = 512;
+
+__global__ __launch_bounds__(SB_TPB) void k_seq_blocks(const u64 *__restrict__ off, u64 n, u64 total, u64 len_limit,
+                                                       u32 len_flag, u64 *__restrict__ nblk, u32 *__restrict__ flags) {
+    __shared__ u32 longest;
+    if (threadIdx.x == 0) longest = 0;
+    __syncthreads();
+    u32 mine = 0;
+    for (u64 s = (u64)blockIdx.x * SB_TPB + threadIdx.x; s < n; s += (u64)gridDim.x * SB_TPB) {
+        const u64 a = off[s], b = off[s + 1];
+        u32 f = 0;
+        if (b < a || b > total || (s == 0 && a != 0) || (s == n - 1 && b != total)) f |= ERR_OFFSETS;
+        u64 len = b >= a ? b - a : 0;
+        if (len > len_limit) f |= len_flag;
+        if (f) {
+            atomicOr(flags, f);
+            len = 0;
+        }
+        mine = max(mine, (u32)len);  // (lengths that pass stay below 2^32)
+        nblk[s] = (len + 63) / 64 + 1;
     }
-    nblk[s] = (len + 63) / 64 + 1;
+#pragma unroll
+    for (int o = 32; o; o >>= 1) mine = max(mine, (u32)__shfl_xor((int)mine, o, 64));
+    if ((threadIdx.x & 63) == 0) atomicMax(&longest, mine);
+    __syncthreads();
+    if (threadIdx.x == 0 && longest) atomicMax(flags + 1, longest);
 }
 
 // Four lanes per 64-base block, 16 bytes each in one load (a byte at a time
@@ -151,6 +166,7 @@ __global__ __launch_bounds__(256) void k_pack(const u8 *__restrict__ seq, const 
 void pack_sequences(const mt_seqs &in, u64 len_limit, u32 len_flag, const char *len_message, PackedSeqs &out,
                     u32 *d_flags, u8 *has_n, hipStream_t s, const u64 *src, u64 src_total) {
     out.n = in.n;
+    out.max_len = src ? ~0u : 0u;
     out.blk_off.alloc(in.n + 1);
     out.blocks_cap = in.total / 64 + 2 * in.n + 1;
     out.lohi.alloc(out.blocks_cap);
@@ -160,16 +176,17 @@ void pack_sequences(const mt_seqs &in, u64 len_limit, u32 len_flag, const char *
         return;
     }
     DBuf<u64> nblk(in.n);
-    k_seq_blocks<<<grid_for(in.n, 256), 256, 0, s>>>(in.offsets, in.n, in.total, len_limit, len_flag, nblk.p,
-                                                      d_flags);
+    const unsigned sb = (unsigned)std::min<u64>(SB_BLOCKS, (in.n + SB_TPB - 1) / SB_TPB);
+    k_seq_blocks<<<sb, SB_TPB, 0, s>>>(in.offsets, in.n, in.total, len_limit, len_flag, nblk.p, d_flags);
     MT_HIP(hipGetLastError());
     if (!src) {
         // The offsets decide every later address: refuse bad ones before any
         // kernel reads sequence bytes through them.
-        u32 f = 0;
-        read_back(s, d_flags, &f, sizeof f);
-        if (f & len_flag) throw Error(MT_EINVAL, len_message);
-        check_flags(f);
+        u32 f[2] = {0, 0};
+        read_back(s, d_flags, f, sizeof f);
+        if (f[0] & len_flag) throw Error(MT_EINVAL, len_message);
+        check_flags(f[0]);
+        out.max_len = f[1];
     }
     scan_u64(nblk.p, out.blk_off.p, in.n, s);
     DBuf<u32> map(out.blocks_cap);

@@ -13,18 +13,21 @@ struct PackedSeqs {
     DBuf<u64> blk_off;  // n + 1: first block of each sequence
     u64 n = 0;
     u64 blocks_cap = 0;
+    u32 max_len = 0;    // longest sequence (of a subset: all ones)
 };
 
 // Packs `in` (device ASCII) into planes.  The offsets are checked first (a
 // synchronizing step): a sequence longer than len_limit fails with
 // len_message, malformed offsets with MT_EINVAL.  Bad bytes raise
-// ERR_BAD_BYTE in d_flags; has_n (nullable, n entries, zeroed by the caller)
+// ERR_BAD_BYTE in d_flags (two words, zeroed by the caller: the flags and the longest
+// length); has_n (nullable, n entries, zeroed by the caller)
 // receives 1 for sequences containing N.
 // src (nullable): sequence i's bytes start at in.seq + src[i] instead of its offset
 // (a subset of a set of src_total bytes, not gathered; the offsets give its lengths
 // and were checked with the set's).
 void pack_sequences(const mt_seqs &in, u64 len_limit, u32 len_flag, const char *len_message, PackedSeqs &out,
-                    u32 *d_flags, u8 *has_n, hipStream_t s, const u64 *src = nullptr, u64 src_total = 0);
+                    u32 *d_flags, u8 *has_n, hipStream_t s, const u64 *src = nullptr,
+                    u64 src_total = 0);
 
 // Tiled minimizer extraction.  plan() sizes the tiles and counts the
 // minimizers of every tile; after the caller has read n_tiles / n_min back

@@ -115,6 +115,7 @@ extern "C" int mt_autotune(const mt_index *index, const mt_query_params *params,
         fa.read_lohi = rb.planes.lohi.p;
         fa.read_nb = rb.planes.nb.p;
         fa.read_has_n = rb.has_n.p;
+        fa.max_len = rb.planes.max_len;
         fa.n_genomes = index->n_genomes;
         fa.meta = index->meta.p;
         fa.ref_lohi = index->ref.lohi.p;

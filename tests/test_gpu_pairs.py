@@ -199,3 +199,80 @@ def test_diagonals_to_the_ends_of_64_bits(mt, kind):
         bad = np.flatnonzero(ap != want[0][sel])
         assert len(bad) == 0, [rows[sel[i]] for i in bad[:5]]
         assert np.array_equal(ac, want[1][sel])
+
+
+# ------------------------------------------------ short E and longer reads --
+
+@pytest.fixture(scope="module")
+def far_case(mt):
+    """Reads on both sides of the lengths that go to groups of lanes at a short E (past
+    256 bases of few pairs to 1,024 of many), exact, with errors, with an N, with an indel."""
+    rng = np.random.default_rng(29)
+    clean = synth.ACGT[synth.random_codes(rng, 40_000)]
+    dirty = clean.copy()
+    dirty[rng.integers(0, 40_000, 40)] = ord("N")
+    ga = synth.SeqSet.from_list([clean.tobytes(), dirty.tobytes(), clean[:900].tobytes()])
+    reads, rows = [], []
+    for m in (150, 255, 256, 257, 258, 259, 1000, 1023, 1024, 1025, 1088, 2500, 21_000):
+        for what in ("exact", "errors", "n", "indel"):
+            start = int(rng.integers(100, 40_000 - m - 100))
+            body = clean[start:start + m].copy()
+            if what == "errors":
+                hit = rng.random(m) < 0.01
+                body[hit] = synth.ACGT[rng.integers(0, 4, int(hit.sum()))]
+            elif what == "n":
+                body[m - 3] = ord("N")
+            elif what == "indel":
+                body = np.concatenate([body[:m // 3], body[m // 3 + 2:], body[:2]])
+            reads.append(body.tobytes())
+            for E in (0, 3, 7, 8, 15, 16, 31):
+                rows += [(len(reads) - 1, g, d, E) for g, d in ((0, start), (1, start - 2), (0, 200), (2, -5), (0, 39_900))]
+    rs = synth.SeqSet.from_list(reads)
+    r = np.array(rows, np.int64)
+    arr = (r[:, 0].astype(np.uint32), r[:, 1].astype(np.uint32), r[:, 2].copy(), r[:, 3].astype(np.uint16))
+    oix = oracle.Index(ga, 15, 10)
+    return dict(ga=ga, ix=mt.Index(ga, 15, 10), oix=oix, rs=rs, dr=mt.to_device(rs), pairs=arr,
+                want=[oix.filter_pairs(rs, *arr)])
+
+
+@pytest.mark.parametrize("variant", range(3))
+@pytest.mark.parametrize("n", [0, 16_384, 16_512, 65_536, 80_000])
+def test_short_E_of_longer_reads(mt, far_case, n, variant):
+    total = len(far_case["pairs"][0])
+    sel = np.random.default_rng(n).integers(0, total, n) if n else np.arange(total)
+    mt.tune_reset()
+    try:
+        for bucket in range(3):
+            try:
+                mt.tune_set(bucket, variant)
+            except mt.MTError:
+                pass  # past the bucket's variants: the default runs
+        ap, ac = _run(mt, far_case, sel)
+        one = sel[far_case["pairs"][3][sel] == 31]  # one bucket: no pair is placed
+        ap1, _ = _run(mt, far_case, one)
+    finally:
+        mt.tune_reset()
+    bad = np.flatnonzero(ap != far_case["want"][0][0][sel])
+    assert len(bad) == 0, [tuple(int(a[sel[i]]) for a in far_case["pairs"]) + (int(ap[i]),) for i in bad[:5]]
+    assert np.array_equal(ac, far_case["want"][0][1][sel])
+    assert np.array_equal(ap1, far_case["want"][0][0][one])
+
+
+@pytest.mark.parametrize("E", [7, 15, 31])
+@pytest.mark.parametrize("n", [200, 12_000])
+def test_classify_longer_reads_at_a_fixed_short_E(mt, far_case, n, E):
+    rng = np.random.default_rng(n + E)
+    genome = far_case["ga"].get(0)
+    own = []
+    for m in rng.choice([150, 256, 257, 1000, 1024, 1025, 1500, 3000], n):
+        s = int(rng.integers(0, 40_000 - m))
+        body = np.frombuffer(genome[s:s + m], np.uint8).copy()
+        hit = rng.random(m) < 0.01
+        body[hit] = synth.ACGT[rng.integers(0, 4, int(hit.sum()))]
+        own.append(body.tobytes())
+    reads = synth.SeqSet.from_list(own)
+    ref = far_case["oix"].classify(reads, 3, 3, 0, E)
+    for mode in (0, 1):
+        got = far_case["ix"].classify(mt.to_device(reads), mode=mode, e_value=E).to_host()
+        for f in ("cand_offsets", "genome", "diag", "hits", "approx", "accept", "unique", "multi"):
+            assert np.array_equal(got[f], ref[f]), (f, mode)
