@@ -576,18 +576,18 @@ struct WalkFilter {
     }
 };
 
-// kAscii: the fused form's pairs, reads of at most 320 bases as ASCII.  A pair that
-// does not fit in LDS (F::ALL_FIT: there is none, by its class) takes the whole
-// wavefront.
+// kAscii: the fused form's pairs, reads of at most 320 bases as ASCII.  F::ALL_FIT: by
+// their class, all pairs fit in LDS.  per_wave: pairs a wavefront takes, 64 where all fit.
 template <class F, bool kAscii>
-__global__ __launch_bounds__(LANE_TPB) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_filter_lane(FilterArgs a, const u32 *__restrict__ idx, u64 n) {
+__global__ __launch_bounds__(LANE_TPB) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_filter_lane(FilterArgs a, const u32 *__restrict__ idx, u64 n, u32 per_wave) {
     __shared__ __align__(16) u32 lds[LANE_TPB / 64][LANE_DW + LANE_PAD];
     const int lane = threadIdx.x & 63;
     u32 *S = lds[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)];
-    const u64 t = wide_block() * LANE_TPB + threadIdx.x;
+    const u32 P = kAscii || F::ALL_FIT ? 64u : per_wave;
+    const u64 t0 = (wide_block() * (LANE_TPB / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * P, t = t0 + lane;
     // the pair's fields are requested along with the number of pairs (n bounds
     // their arrays) and looked at after it
-    const bool inside = t < n;
+    const bool inside = (u32)lane < P && t < n;
     const u64 p = !inside ? 0 : idx ? idx[t] : t;
     const u32 gate = kAscii ? *a.gate : 0u;
     const u64 np = idx ? n : pair_count(a, n);
@@ -598,8 +598,8 @@ __global__ __launch_bounds__(LANE_TPB) __attribute__((amdgpu_waves_per_eu(4, 8))
         g = a.pair_genome[p];
         diag = pair_diag(a, p);
     }
-    if (gate || t - lane >= np) return;  // malformed offsets; the whole wavefront is past the end
-    const bool in = t < np;
+    if (gate || t0 >= np) return;  // malformed offsets; the whole wavefront is past the end
+    const bool in = inside && t < np;
     u32 err = 0;
     int E = 0, m = 0, nbr = 0, nbw = 0, wofs = 0;
     bool ok = false, with_n = false;
@@ -657,23 +657,51 @@ __global__ __launch_bounds__(LANE_TPB) __attribute__((amdgpu_waves_per_eu(4, 8))
             err = ERR_INTERNAL;
         }
     } else {
+        // The pairs that do not fit, a lane per 64-base word of the read: as many pairs at
+        // once as have words for the lanes.  One pair at a time left most lanes without a
+        // word (100,000 pairs of 400 bases at E = 7: 1.12 ms, 0.21 so; 40,000 of 1 kbp
+        // at E = 50: 4.9 ms, 1.39).
         u64 big = __ballot(ok && !fits);
+        u32 *owner = S, *count = S + 64;
         while (big) {
-            const int l = __builtin_ctzll(big);
-            big &= big - 1;
+            int end = ((big >> lane) & 1) ? max(1, min((m + 63) / 64, 64)) : 0;
+            const int mine = end;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int y = __shfl_up(end, o, 64);
+                if (lane >= o) end += y;
+            }
+            const u64 now = __ballot(mine && end <= 64);  // the first of those left at least
+            const bool me = (now >> lane) & 1;
+            if (me)
+                for (int i = end - mine; i < end; i++) owner[i] = (u32)lane;
+            count[lane] = 0;
+            const int used = __shfl(end, 63 - __builtin_clzll(now), 64);
+            lds_wave_sync();
+            const int l = lane < used ? (int)owner[lane] : __builtin_ctzll(now);
             const u32 wr = __shfl(r, l, 64), wg = __shfl(g, l, 64);
+            const i64 wdiag = __shfl(diag, l, 64);
+            const int wE = __shfl(E, l, 64), first = __shfl(end - mine, l, 64);
             const GenomeMeta wm = a.meta[wg];
-            PairView v;
-            v.qlohi = a.read_lohi + a.read_blk[wr];
-            v.qnb = a.read_nb + a.read_blk[wr];
-            v.m = read_len(a, wr);
-            v.rlohi = a.ref_lohi + wm.blk;
-            v.rnb = a.ref_nb + wm.blk;
-            v.L = (i64)wm.len;
-            v.has_n = meta_has_n(wm);
-            v.diag = __shfl(diag, l, 64);
-            const int wc = F::by_wave(v, __shfl(E, l, 64), lane);
-            if (lane == l) c = wc;
+            const PairView v{a.read_lohi + a.read_blk[wr], a.read_nb + a.read_blk[wr], read_len(a, wr),
+                             a.ref_lohi + wm.blk, a.ref_nb + wm.blk, (i64)wm.len, meta_has_n(wm), wdiag};
+            // a pair of more words than lanes is alone and takes turns
+            const int turns = __popcll(now) == 1 ? max(1, (v.m + 4095) / 4096) : 1;
+            int wc = 0;
+            for (int t = 0; t < turns; t++) {
+                if (lane < used) wc += F::word(v, wE, lane - first + 64 * t);
+                if (t + 1 < turns) {
+                    int all = wc;
+#pragma unroll
+                    for (int o = 32; o; o >>= 1) all += __shfl_xor(all, o, 64);
+                    if (all > wE) break;
+                }
+            }
+            if (lane < used) atomicAdd(&count[l], (u32)wc);
+            lds_wave_sync();
+            if (me) c = (int)count[lane];
+            big &= ~now;
+            lds_wave_sync();
         }
     }
     if (!in) return;
@@ -910,8 +938,8 @@ static void launch_short(const FilterArgs &a, const u32 *idx, u64 cnt, int bucke
         k_filter<16><<<wide_grid(cnt, 16, 256), 256, 0, s>>>(a, idx, cnt);
     } else if (bucket < CLS_LONG && v == 0 && !far) {
         const dim3 blocks = wide_grid(cnt, LANE_TPB, LANE_TPB);
-        if (bucket < 2) k_filter_lane<WalkFilter<1, 6>, false><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
-        else k_filter_lane<WalkFilter<2, 7>, false><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt);
+        if (bucket < 2) k_filter_lane<WalkFilter<1, 6>, false><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt, 64);
+        else k_filter_lane<WalkFilter<2, 7>, false><<<blocks, LANE_TPB, 0, s>>>(a, idx, cnt, 64);
     } else if ((bucket == 0 && v == 1) || (bucket == 1 && v == 0)) {
         k_filter<32><<<wide_grid(cnt, 8, 256), 256, 0, s>>>(a, idx, cnt);
     } else {
@@ -1179,7 +1207,7 @@ struct ShdFilter {
         const u32 mid = d[k + 1];
         return (u64)__builtin_amdgcn_alignbit(d[k + 2], mid, sh) << 32 | __builtin_amdgcn_alignbit(mid, d[k], sh);
     }
-    // longer reads: a lane per word, each row word with its neighbours
+    // a word of a longer read, each row word with its neighbours
     __device__ static u64 row_word(const PairView &v, int d, int w) {
         const int left = v.m - 64 * w;
         if (w < 0 || left <= 0) return 0;
@@ -1188,21 +1216,24 @@ struct ShdFilter {
         const u64 x = (q.lo ^ r.lo) | (q.hi ^ r.hi) | v.qnb[w] | r.nb;
         return left >= 64 ? x : x & ((1ull << left) - 1);
     }
-    __device__ static int by_wave(const PairView &v, int E, int lane) {
-        int c = 0;
-        for (int w0 = 0; 64 * w0 < v.m && c <= E; w0 += 64) {
-            const int w = w0 + lane, left = v.m - 64 * w;
-            u64 acc = left >= 64 ? ~0ull : left > 0 ? (1ull << left) - 1 : 0ull;
-            for (int d = -E; d <= E && acc; d++)
-                acc &= shd_amend(row_word(v, d, w - 1), row_word(v, d, w), row_word(v, d, w + 1));
-            int t = __popcll(acc);
-#pragma unroll
-            for (int o = 32; o; o >>= 1) t += __shfl_xor(t, o, 64);
-            c += t;
-        }
-        return c;
+    __device__ static int word(const PairView &v, int E, int w) {
+        const int left = v.m - 64 * w;
+        u64 acc = left >= 64 ? ~0ull : left > 0 ? (1ull << left) - 1 : 0ull;
+        for (int d = -E; d <= E && acc; d++)
+            acc &= shd_amend(row_word(v, d, w - 1), row_word(v, d, w), row_word(v, d, w + 1));
+        return __popcll(acc);
     }
 };
+
+// Pairs of long reads keep a wavefront for several rounds of words, so a few of them
+// are spread over wavefronts for the whole chip (at least 4 each; 40,000 pairs of 1 kbp
+// at E = 50: 1.39 ms with 64 a wavefront, 0.74 so).
+static void launch_shd(const FilterArgs &a, u64 n, hipStream_t s) {
+    constexpr u64 CHIP_WAVES = 4096;
+    const u32 per = a.max_len <= (u32)ShdFilter::MAX_M ? 64u : (u32)std::min<u64>(std::max<u64>(n / CHIP_WAVES, 4), 64);
+    k_filter_lane<ShdFilter, false><<<wide_grid(n, (u64)per * (LANE_TPB / 64), LANE_TPB), LANE_TPB, 0, s>>>(a, nullptr, n,
+                                                                                                           per);
+}
 
 void launch_filter_simple(const FilterArgs &a, u64 n, u32 kind, hipStream_t s) {
     if (n == 0) return;  // n: the capacity; the kernels read the count itself
@@ -1211,7 +1242,7 @@ void launch_filter_simple(const FilterArgs &a, u64 n, u32 kind, hipStream_t s) {
     else if (kind == MT_FILTER_BASE_COUNT)
         k_filter_simple<2, false><<<wide_grid(n, 256, 256), 256, 0, s>>>(a, n);
     else if (kind == MT_FILTER_SHD)
-        k_filter_lane<ShdFilter, false><<<wide_grid(n, LANE_TPB, LANE_TPB), LANE_TPB, 0, s>>>(a, nullptr, n);
+        launch_shd(a, n, s);
     else if (kind == MT_FILTER_QGRAM)
         k_filter_qgram<false><<<(unsigned)std::min<u64>(grid_for(n, QG_WPB), 65536), 64 * QG_WPB, 0, s>>>(a, n);
     else
@@ -1262,8 +1293,8 @@ void launch_filter_fused(const FilterArgs &a, u64 cap, int max_E, u32 kind, hipS
     static_assert(LANE_TPB == 256, "the simple filters share the grid");
     switch (kind) {
     case MT_FILTER_OBSTACLE:
-        if (max_E <= 15) k_filter_lane<WalkFilter<1, 6>, true><<<blocks, LANE_TPB, 0, s>>>(a, nullptr, cap);
-        else k_filter_lane<WalkFilter<2, 7>, true><<<blocks, LANE_TPB, 0, s>>>(a, nullptr, cap);
+        if (max_E <= 15) k_filter_lane<WalkFilter<1, 6>, true><<<blocks, LANE_TPB, 0, s>>>(a, nullptr, cap, 64);
+        else k_filter_lane<WalkFilter<2, 7>, true><<<blocks, LANE_TPB, 0, s>>>(a, nullptr, cap, 64);
         break;
     case MT_FILTER_HAMMING:
         k_filter_simple<1, true><<<blocks, LANE_TPB, 0, s>>>(a, cap);
@@ -1272,7 +1303,7 @@ void launch_filter_fused(const FilterArgs &a, u64 cap, int max_E, u32 kind, hipS
         k_filter_simple<2, true><<<blocks, LANE_TPB, 0, s>>>(a, cap);
         break;
     case MT_FILTER_SHD:
-        k_filter_lane<ShdFilter, true><<<blocks, LANE_TPB, 0, s>>>(a, nullptr, cap);
+        k_filter_lane<ShdFilter, true><<<blocks, LANE_TPB, 0, s>>>(a, nullptr, cap, 64);
         break;
     case MT_FILTER_QGRAM:
         k_filter_qgram<true><<<(unsigned)std::min<u64>(grid_for(cap, QG_WPB), 65536), 64 * QG_WPB, 0, s>>>(a, cap);

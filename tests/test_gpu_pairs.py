@@ -276,3 +276,39 @@ def test_classify_longer_reads_at_a_fixed_short_E(mt, far_case, n, E):
         got = far_case["ix"].classify(mt.to_device(reads), mode=mode, e_value=E).to_host()
         for f in ("cand_offsets", "genome", "diag", "hits", "approx", "accept", "unique", "multi"):
             assert np.array_equal(got[f], ref[f]), (f, mode)
+
+
+# ----------------------------------------------------- SHD of longer reads --
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 700, 5000])
+def test_shd_of_reads_past_the_staged_words(mt, n):
+    """A lane for each 64-base word of the reads past 320 bases, several pairs to a
+    wavefront: lengths around the words, more words than lanes, empty reads, bands too
+    wide for LDS, short reads among them."""
+    rng = np.random.default_rng(37)
+    clean = synth.ACGT[synth.random_codes(rng, 20_000)]
+    dirty = clean.copy()
+    dirty[rng.integers(0, 20_000, 60)] = ord("N")
+    ga = synth.SeqSet.from_list([clean.tobytes(), dirty.tobytes(), clean[:900].tobytes()])
+    lens = [0, 1, 64, 150, 319, 320, 321, 383, 384, 385, 575, 640, 1000, 2047, 2048, 2049, 4095, 4096, 4097, 4160, 9000]
+    reads, rows = [], []
+    for m in lens:
+        for _ in range(2):
+            start = int(rng.integers(100, 20_000 - m - 50))
+            body = clean[start:start + m].copy()
+            hit = rng.random(m) < 0.02
+            body[hit] = synth.ACGT[rng.integers(0, 4, int(hit.sum()))]
+            if m and rng.random() < 0.4:
+                body[rng.integers(0, m)] = ord("N")
+            reads.append(body.tobytes())
+            for E in (0, 5, 31, 60) + ((15_000,) if m <= 400 else ()):
+                rows += [(len(reads) - 1, g, d, E) for g, d in ((0, start), (1, start + 1), (0, 3), (2, -20), (0, 19_700))]
+    r = np.array(rows, np.int64)
+    sel = rng.permutation(len(r)) if n == 5000 else rng.integers(0, len(r), n)
+    rs = synth.SeqSet.from_list(reads)
+    arr = (r[:, 0].astype(np.uint32), r[:, 1].astype(np.uint32), r[:, 2].copy(), r[:, 3].astype(np.uint16))
+    want = oracle.Index(ga, 15, 10).filter_pairs(rs, *(a[sel] for a in arr), kind=4)
+    ap, ac = _run(mt, dict(ix=mt.Index(ga, 15, 10), dr=mt.to_device(rs), pairs=arr), sel, 4)
+    bad = np.flatnonzero(ap != want[0])
+    assert len(bad) == 0, [rows[sel[i]] + (int(ap[i]), int(want[0][i])) for i in bad[:5]]
+    assert np.array_equal(ac, want[1])
