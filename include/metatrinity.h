@@ -103,7 +103,8 @@ typedef struct mt_query_params {
     uint32_t e_value;    /* E, or permille of the read length */
     uint32_t mode;       /* MT_MODE_* */
     uint32_t filter;     /* MT_FILTER_* (0: the obstacle walk).  The other filters
-                            run in the fused form whatever the mode. */
+                            run in the fused form whatever the mode when a read of
+                            the mean length fits it, else per stage. */
     uint32_t strands;    /* 0 or 1: the forward strand of each genome; 2: both
                             strands (see mt_result_strands). */
     uint32_t reserved;   /* must be 0 */

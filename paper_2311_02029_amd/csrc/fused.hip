@@ -27,10 +27,11 @@ namespace mt {
 
 constexpr int F_WPB = 4;         // wavefronts per block
 constexpr int F_MAX_M = LN_MAX_M;  // longest read of k_seed_wave
+static_assert(F_MAX_M == FUSED_MAX_M, "the forms are told apart by it");
 constexpr int F_ROUNDS = F_MAX_M / 64;  // of 64 positions; a read takes those it reaches
 constexpr int F_HIT_CAP = 256;   // seed hits per read (distinct locations fit the table)
 constexpr int F_TSLOTS = 256;    // per-read LDS hash table of locations
-constexpr int F_MAX_E = 31;      // 2E + 1 rows fit two words of the filter
+constexpr int F_MAX_E = FUSED_MAX_E;  // 2E + 1 rows fit two words of the filter
 constexpr int F_MAX_TOPN = 8;    // staged candidates per read (top_n = 0 keeps up to this many)
 constexpr int F_WORDS = F_MAX_M / 16 + 2;  // 2-bit stream words (16 bases per word) + padding
 
@@ -1070,7 +1071,8 @@ static void launch_fused_graph(const FusedLaunch &L, hipStream_t s) {
 
 void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs &reads, ReadBatch &rb,
                     mt_result &res, Timer &tm, hipStream_t s, bool graph) {
-    if (q.strands == 2) {  // the two-strand read set comes back here
+    // the two-strand read set comes back here; a served batch may not be for the fused form
+    if (q.strands == 2 || (q.filter != MT_FILTER_OBSTACLE && !takes_fused(q, reads))) {
         classify_staged(ix, q, reads, rb, res, tm, s);
         return;
     }

@@ -116,3 +116,39 @@ def test_other_filters_in_every_mode(mt, db, kind, mode):
         ref = oix.classify(reads, 3, 3, q.get("e_mode", 0), q["e_value"], filter_kind=kind, strands=strands)
         for f in FIELDS:
             assert np.array_equal(got[f], ref[f]), (f, n, strands)
+
+
+@pytest.mark.parametrize("strands", [1, 2])
+@pytest.mark.parametrize("lo,hi,q,fused", [(100, 540, dict(e_value=7), True), (100, 560, dict(e_value=7), False),
+                                           (60, 140, dict(e_value=31), True), (60, 140, dict(e_value=32), False),
+                                           (300, 300, dict(e_mode=1, e_value=100), True),
+                                           (310, 330, dict(e_mode=2, e_value=101), False)])
+def test_other_filters_go_per_stage_where_most_reads_are_left_over(mt, db, lo, hi, q, fused, strands):
+    """By the mean length and its E; both routes with short and long reads among them."""
+    rng = np.random.default_rng(lo + hi)
+    n = 1501
+    reads = _cut(rng, db, n, np.linspace(lo, hi, n).astype(np.int64), 0.01, 0.001)
+    reads = synth.SeqSet.from_list([reads.get(i) for i in rng.permutation(n)])
+    ix, oix = mt.Index(db, 21, 11, 200), oracle.Index(db, 21, 11, 200)
+    for kind in range(1, 5):
+        ref = oix.classify(reads, 3, 3, q.get("e_mode", 0), q["e_value"], filter_kind=kind, strands=strands)
+        for mode in range(3):
+            got = ix.classify(mt.to_device(reads), mode=mode, filter_kind=kind, strands=strands, **q).to_host()
+            assert (mt.last_stats()["fused_reads"] > 0) == fused, (kind, mode)
+            for f in FIELDS:
+                assert np.array_equal(got[f], ref[f]), (f, kind, mode)
+
+
+@pytest.mark.parametrize("strands", [1, 2])
+@pytest.mark.parametrize("hi", [400, 1200])
+def test_other_filters_served_short_and_long(mt, db, hi, strands):
+    rng = np.random.default_rng(hi)
+    ix, oix = mt.Index(db, 21, 11, 200), oracle.Index(db, 21, 11, 200)
+    sets = [_cut(rng, db, 500, rng.integers(80, hi, 500), 0.01, 0.001) for _ in range(4)]
+    with mt.Server(ix) as server:
+        ids = [server.submit(s, filter_kind=1 + i, strands=strands) for i, s in enumerate(sets)]
+        for i, (s, rid) in enumerate(zip(sets, ids)):
+            got = server.wait(rid).to_host()
+            ref = oix.classify(s, 3, 3, 0, 7, filter_kind=1 + i, strands=strands)
+            for f in FIELDS:
+                assert np.array_equal(got[f], ref[f]), (f, i)
