@@ -41,7 +41,7 @@ constexpr int F_WORDS = F_MAX_M / 16 + 2;  // 2-bit stream words (16 bases per w
 // against 119.
 constexpr u64 LANE_MIN_READS = 48 * 1024;
 
-enum : u32 { ST_READS, ST_BASES, ST_MINS, ST_WBLOCKS, ST_CANDS, ST_OCC, ST_COUNT };
+enum : u32 { ST_READS, ST_BASES, ST_MINS, ST_WBLOCKS, ST_CANDS, ST_OCC, ST_HITS, ST_COUNT };
 
 struct SeedArgs {
     const u8 *seq;
@@ -271,7 +271,8 @@ __global__ __launch_bounds__(LN_TPB) void k_seed_lane(SeedArgs a) {
     // work counts: one record per block, summed by k_fused_summary
     const bool done = take && !slow && !fall;
     const u32 st[ST_COUNT] = {done, done ? (u32)m : 0u, done ? (u32)nmin : 0u,
-                              (u32)nc * (u32)((m + 2 * E + 63) / 64), (u32)nc, done ? (u32)nocc : 0u};
+                              (u32)nc * (u32)((m + 2 * E + 63) / 64), (u32)nc, done ? (u32)nocc : 0u,
+                              done ? (u32)H : 0u};
 #pragma unroll
     for (u32 i = 0; i < ST_COUNT; i++) {
         const u32 t = wave_sum(st[i]);
@@ -759,6 +760,7 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
             wst[ST_CANDS] += (u64)nc;
             wst[ST_WBLOCKS] += (u64)nc * (u64)((m + 2 * E + 63) / 64);
             wst[ST_OCC] += (u64)nocc;
+            wst[ST_HITS] += (u64)H;
         }
         cur = nxt;
         wave_sync();
@@ -1173,6 +1175,7 @@ void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs 
     ls.fused_cands += h.stats[ST_CANDS];
     ls.fused_occ += h.stats[ST_OCC];
     ls.n_minimizers += h.stats[ST_MINS];
+    ls.n_hits += h.stats[ST_HITS];
     // Every read's count is at most N (the seed kernels write one per read), so
     // the total fits the staged capacity; a result never claims more
     // candidates than its arrays hold.

@@ -152,3 +152,22 @@ def test_other_filters_served_short_and_long(mt, db, hi, strands):
             ref = oix.classify(s, 3, 3, 0, 7, filter_kind=1 + i, strands=strands)
             for f in FIELDS:
                 assert np.array_equal(got[f], ref[f]), (f, i)
+
+
+@pytest.mark.parametrize("n", [400, N_READS])
+def test_seed_hits_counted_in_every_form(mt, db, n):
+    """Work counts: the hits of a classification are those of the containment search over
+    the same reads, whatever the form, the filter or the reads left over."""
+    rng = np.random.default_rng(n)
+    reads = _cut(rng, db, n, rng.integers(0, 341, n), 0.01, 0.001)
+    ix = mt.Index(db, 21, 11, 20)
+    want = int(oracle.Index(db, 21, 11, 20).containment(reads).sum())
+    dr = mt.to_device(reads)
+    minimizers = set()
+    for q in (dict(), dict(top_n=0), dict(min_hits=1, top_n=8), dict(top_n=9), dict(filter_kind=1), dict(filter_kind=4, e_value=40)):
+        for mode in range(3):
+            ix.classify(dr, mode=mode, **q).free()
+            st = mt.last_stats()
+            assert st["n_hits"] == want, (q, mode)
+            minimizers.add(st["n_minimizers"])
+    assert len(minimizers) == 1
