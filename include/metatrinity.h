@@ -422,10 +422,15 @@ int mt_result_times(const mt_result *res, uint64_t *submit_ns, uint64_t *done_ns
  * rows of Table 1's pigeonhole filters).  Filter pairs are bucketed by E
  * (<= 7, <= 15, <= 31) and, for larger E, by the 64-base blocks of read and
  * reference window they stage in LDS (<= 96, 192, 384, 768); each bucket has
- * variants: for small E one lane per pair (the first variant, under the name
- * of the narrowest group of lanes) or a wider group; for large E the LDS tile
- * with 1/2/4/8 wavefronts per block or a rows-in-lanes layout reading global
- * memory for large E.  Every variant gives bit-identical results; the choice
+ * variants.  The names are kept for saved selections and stand for:
+ *   E <= 7, 15, 31  the first ("g16", "g32", "g64"): one lane per pair, and
+ *                   groups of that many lanes for longer reads; the others:
+ *                   groups of 32 or 64 lanes for all pairs;
+ *   long            the last "lds_w*" that a bucket takes: read and window in
+ *                   LDS, 8 lanes per pair, more for few pairs; each "lds_w*"
+ *                   below it: twice the lanes, up to 64; "global": 64 lanes,
+ *                   from global memory.
+ * Every variant gives bit-identical results; the choice
  * is process-wide and applies to mt_classify (per-stage form and the fused
  * form's per-stage finish) and mt_filter_pairs.
  */
@@ -451,9 +456,10 @@ int mt_tune_set(uint32_t bucket, uint32_t variant);
 int mt_tune_reset(void);
 /*
  * Classifies `reads` (host struct with device arrays) in the per-stage form to
- * obtain their filter pairs, then times every variant of every bucket that
+ * obtain their filter pairs, then times the variants of every bucket that
  * holds pairs on those pairs (best of `reps` launches, HIP events on
- * `stream`) and selects the fastest.  Results: mt_tune_info.
+ * `stream`; a variant whose launch for so many pairs is another's is not timed)
+ * and selects the fastest.  Results: mt_tune_info.
  */
 int mt_autotune(const mt_index *index, const mt_query_params *params, const mt_seqs *reads, uint32_t reps,
                 void *stream);

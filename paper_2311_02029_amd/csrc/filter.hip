@@ -870,8 +870,8 @@ struct BucketDesc {
 // Variant 0 of a short bucket is one lane per pair; it keeps the name of the
 // narrowest group, which it replaces, so that saved selections go on loading.
 // Variant v of a long bin: v < 4 -> pairs in LDS, up to 8 per wavefront for the
-// default variant and half as many with each below it; v == 4 -> rows in lanes from global
-// memory.  (The names count the wavefronts that shared a block when a pair took a
+// default variant and half as many with each below it (long_lanes); v == 4 -> rows in
+// lanes from global memory.  (The names count the wavefronts that shared a block when a pair took a
 // whole wavefront and its whole planes; their limits stay, so that the same
 // selections are taken and refused as ever.)
 const BucketDesc BUCKETS[N_BUCKETS] = {
@@ -906,6 +906,19 @@ int current_variant(int bucket) {
 }
 
 }  // namespace
+
+// Lanes for each of so many pairs of a long bin, by one of its variants in LDS.  A few
+// pairs leave the chip idle whatever their layout: more lanes each make a step shorter
+// (1,024 pairs of 4-5 kbp: 0.29 ms with 64 lanes, 0.35 with 32, 0.36 with 8; 1,024 of
+// 8-10 kbp: 0.58 ms with 32 lanes, 0.75 with 8; 4,096: 0.71 with 16, 0.81 with 32, 0.86
+// with 8; 16,384: 1.16 and 1.19 with 16 and 8; 40,000: 2.54 and 2.30).  A variant below
+// the default, which is the last that fits, doubles them: a selection tuned on a few
+// pairs and used for many is then a step from the default at most, as the tuner times
+// no second variant with the same lanes.
+static int long_lanes(int bucket, int v, u64 pairs) {
+    const int few = pairs <= 1024 ? 3 : pairs <= 2048 ? 2 : pairs <= 8192 ? 1 : 0;
+    return 8 << std::min(few + std::max(DEFAULT_VARIANT[bucket] - v, 0), 3);
+}
 
 // Blocks for cnt pairs of the long kernel: up to four pairs to a group once there
 // are blocks for every CU, so that groups with short pairs go on while others finish.
@@ -954,24 +967,17 @@ static void launch_bucket(const FilterArgs &a, const Buckets &B, int bucket, int
     const u32 *idx = B.of(bucket);
     if (bucket >= CLS_LONG && bucket < CLS_LONG + LONG_BINS) {
         const int b = bucket - CLS_LONG, cn = CLS_LONG_N + b, cw = CLS_LONG_WIDE + b;
-        int below = DEFAULT_VARIANT[bucket] - v;  // the default is the last that fits
-        // A few pairs leave the chip idle whatever their layout: more lanes each make
-        // a step shorter (1,024 pairs of 4-5 kbp: 0.29 ms with 64 lanes, 0.35 with 32,
-        // 0.36 with 8; 1,024 of 8-10 kbp: 0.58 ms with 32 lanes, 0.75 with 8; 4,096: 0.71
-        // with 16, 0.81 with 32, 0.86 with 8; 16,384: 1.16 and 1.19 with 16 and 8;
-        // 40,000: 2.54 and 2.30).
-        const u64 pairs = cnt + B.count[cn];
-        if (below <= 0) below = pairs <= 1024 ? 3 : pairs <= 2048 ? 2 : pairs <= 8192 ? 1 : 0;
+        const int lanes = long_lanes(bucket, v, cnt + B.count[cn]);
         if (v == 4) {
             for (int c : {bucket, cn, cw})
                 if (B.count[c])
                     k_filter<64><<<wide_grid(B.count[c], 4, 256), 256, 0, s>>>(a, B.of(c), B.count[c]);
         } else {
-            if (below <= 0)
+            if (lanes == 8)
                 launch_long<8>(a, idx, cnt, LONG_TILE, B.of(cn), B.count[cn], LONG_TILE_N, s);
-            else if (below == 1)
+            else if (lanes == 16)
                 launch_long<16>(a, idx, cnt, LONG_TILE, B.of(cn), B.count[cn], LONG_TILE_N, s);
-            else if (below == 2)
+            else if (lanes == 32)
                 launch_long<32>(a, idx, cnt, LONG_TILE, B.of(cn), B.count[cn], LONG_TILE_N, s);
             else
                 launch_long<64>(a, idx, cnt, LONG_TILE, B.of(cn), B.count[cn], LONG_TILE_N, s);
@@ -1314,8 +1320,18 @@ void launch_filter_fused(const FilterArgs &a, u64 cap, int max_E, u32 kind, hipS
     MT_HIP(hipGetLastError());
 }
 
-// Times every variant of every bucket that holds pairs (best of `reps`
-// launches each, after one untimed launch) and keeps the fastest.
+// Whether a variant's launch is that of a variant nearer the default, for the pairs
+// of the bucket.
+static bool same_launch(const u32 *count, int bucket, int v) {
+    if (bucket < CLS_LONG || bucket >= CLS_LONG + LONG_BINS || v >= DEFAULT_VARIANT[bucket]) return false;
+    const int b = bucket - CLS_LONG;
+    const u64 pairs = (u64)count[bucket] + count[CLS_LONG_N + b];
+    return long_lanes(bucket, v, pairs) == long_lanes(bucket, v + 1, pairs);
+}
+
+// Times the variants of every bucket that holds pairs (best of `reps`
+// launches each, after one untimed launch) and keeps the fastest.  A variant whose
+// launch is another's is not timed: noise would choose between them.
 void autotune_filter(const FilterArgs &args, u64 n_pairs, u32 reps, hipStream_t s) {
     if (n_pairs == 0) return;
     FilterArgs a = args;
@@ -1335,7 +1351,7 @@ void autotune_filter(const FilterArgs &args, u64 n_pairs, u32 reps, hipStream_t 
             int best = -1;
             float ms_v[6] = {0, 0, 0, 0, 0, 0};
             for (int v = 0; v < BUCKETS[c].n_variants; v++) {
-                if (!variant_ok(c, v)) continue;
+                if (!variant_ok(c, v) || same_launch(hc, c, v)) continue;
                 launch(v);
                 float mn = 0;
                 for (u32 r = 0; r < (reps ? reps : 1); r++) {

@@ -119,3 +119,27 @@ def test_autotune_selects_fastest_and_round_trips(mt, pairs, tmp_path):
         mt.tune_load(str(bad))
     assert e.value.status == mt._abi.MT_EINVAL
     mt.tune_reset()
+
+
+@pytest.mark.parametrize("n,lanes_differ", [(60, False), (700, False), (9000, True)])
+def test_autotune_times_no_launch_twice(mt, n, lanes_differ):
+    """A few long pairs take 64 lanes each under every LDS variant: only the default is
+    timed (and the layout from global memory), so that a larger batch later runs with its
+    own layout.  Many pairs tell the variants apart."""
+    rnd = np.random.default_rng(n)
+    gen = synth.make_genomes(rnd, 2, 200_000, 0.5)
+    reads, _ = synth.make_reads(rnd, gen, np.full(n, 1500), 0.01, 0.01)
+    ix = mt.Index(gen.ascii(), 15, 10)
+    mt.tune_reset()
+    try:
+        for _ in range(5):
+            info = ix.autotune(mt.to_device(reads), reps=1, top_n=1, e_mode=mt.MT_E_CEIL_PERMILLE, e_value=50)
+            long = [b for b in info if b["name"].startswith("long") and b["pairs"] > 0]
+            assert long
+            for b in long:
+                default = {"long<=96": "lds_w8", "long<=192": "lds_w8", "long<=384": "lds_w4", "long<=768": "lds_w2"}[b["name"]]
+                lds = {v for v in b["ms"] if v.startswith("lds")}
+                assert default in lds and (len(lds) > 1) == lanes_differ, b
+                assert b["current"] == min(b["ms"], key=b["ms"].get), b
+    finally:
+        mt.tune_reset()
