@@ -547,12 +547,17 @@ void build_index(mt_index &ix, const mt_index_params &p, const mt_seqs &g, const
     ix.nbuckets = nbuckets;
     u64 nslots = nbuckets * 4;
     ix.table.alloc(nslots);
+    // Two pairs of arrays for the minimizers: the duplicates end up in one, and the
+    // other's memory then serves the occurrence lists (nd < n_min, so rank and size fit
+    // x's and the nd + 1 starts occ's).
     DBuf<u64> tx(n_min), tocc(n_min);
-    u64 *dup_slot = tx.p, *dup_occ = tocc.p, nd = 0;
+    u64 *dup_slot = tx.p, *dup_occ = tocc.p, *free_x = ex.p, *free_occ = eocc.p, nd = 0;
     if (by_regions(n_min, nbuckets)) {
         nd = insert_by_regions(ix, n_min, ex.p, eocc.p, tx.p, tocc.p, s);
         dup_slot = ex.p;
         dup_occ = eocc.p;
+        free_x = tx.p;
+        free_occ = tocc.p;
     } else {
         MT_HIP(hipMemsetAsync(ix.table.p, 0xFF, nslots * sizeof(u64x2), s));
         DBuf<unsigned long long> ndups(1);
@@ -570,23 +575,24 @@ void build_index(mt_index &ix, const mt_index_params &p, const mt_seqs &g, const
     // work is that of the duplicates, not of the table
     u64 n_multi = 0;
     if (nd) {
-        DBuf<u32> cnt(nslots), rank(nd), size(nd);
-        DBuf<u64> start(nd + 1);
+        DBuf<u32> cnt(nslots);
+        u32 *rank = (u32 *)free_x, *size = rank + nd;
+        u64 *start = free_occ;
         MT_HIP(hipMemsetAsync(cnt.p, 0, nslots * sizeof(u32), s));
-        k_dup_rank<<<grid_for(nd, 256), 256, 0, s>>>(dup_slot, nd, cnt.p, rank.p);
+        k_dup_rank<<<grid_for(nd, 256), 256, 0, s>>>(dup_slot, nd, cnt.p, rank);
         MT_HIP(hipGetLastError());
-        k_dup_sizes<<<grid_for(nd, 256), 256, 0, s>>>(dup_slot, rank.p, nd, cnt.p, p.max_occ, size.p, flags.p);
+        k_dup_sizes<<<grid_for(nd, 256), 256, 0, s>>>(dup_slot, rank, nd, cnt.p, p.max_occ, size, flags.p);
         MT_HIP(hipGetLastError());
-        scan_u32(size.p, start.p, nd, s);
+        scan_u32(size, start, nd, s);
         u32 f1 = 0;
         MT_HIP(hipMemcpyAsync(&f1, flags.p, sizeof(u32), hipMemcpyDeviceToHost, s));
-        read_back(s, start.p + nd, &n_multi, sizeof(u64));
+        read_back(s, start + nd, &n_multi, sizeof(u64));
         check_flags(f1);
         tm.mark("index_sizes");
         ix.occ.alloc(n_multi);
-        k_dup_heads<<<grid_for(nd, 256), 256, 0, s>>>(dup_slot, rank.p, start.p, nd, ix.table.p, ix.occ.p);
+        k_dup_heads<<<grid_for(nd, 256), 256, 0, s>>>(dup_slot, rank, start, nd, ix.table.p, ix.occ.p);
         MT_HIP(hipGetLastError());
-        k_dup_place<<<grid_for(nd, 256), 256, 0, s>>>(dup_slot, dup_occ, rank.p, nd, ix.table.p, ix.occ.p);
+        k_dup_place<<<grid_for(nd, 256), 256, 0, s>>>(dup_slot, dup_occ, rank, nd, ix.table.p, ix.occ.p);
         MT_HIP(hipGetLastError());
     } else {
         ix.occ.alloc(0);

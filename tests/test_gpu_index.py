@@ -121,3 +121,22 @@ def test_minimizers_around_tiles(mt, w):
         reads = synth.SeqSet.from_list([ga.get(i) for i in keep])
         hits = ix.containment(mt.to_device(reads)).cpu().numpy().view(np.uint64)
         assert np.array_equal(hits, oix.containment(reads))
+
+
+@pytest.mark.parametrize("w", [8, 1])  # inserted directly, and by regions
+@pytest.mark.parametrize("copies", [1, 40])
+def test_index_build_memory(mt, copies, w):
+    """The build holds at most 48 bytes a minimizer beside the index, and less than half a
+    byte a base, whether its k-mers are distinct or nearly all duplicates."""
+    import torch
+    rng = np.random.default_rng(80)
+    g = synth.ACGT[synth.random_codes(rng, 6_000_000 // copies)].tobytes()
+    ga = mt.to_device(synth.SeqSet.from_list([g] * copies))
+    mt.Index(ga, 17, w).free()
+    torch.cuda.synchronize()
+    torch.cuda.reset_peak_memory_stats()
+    before = torch.cuda.memory_allocated()
+    info = mt.Index(ga, 17, w).info()
+    peak = torch.cuda.max_memory_allocated() - before
+    assert info["n_keys"] * copies <= info["n_minimizers"] + 1000 * copies
+    assert peak <= info["device_bytes"] + 48 * info["n_minimizers"] + ga.total // 2 + (4 << 20)
