@@ -171,3 +171,18 @@ def test_seed_hits_counted_in_every_form(mt, db, n):
             assert st["n_hits"] == want, (q, mode)
             minimizers.add(st["n_minimizers"])
     assert len(minimizers) == 1
+
+
+@pytest.mark.parametrize("family", [1, 5])
+@pytest.mark.parametrize("genomes", [2045, 2050])
+def test_containment_around_the_counters_in_lds(mt, genomes, family):
+    """On both sides of the genomes whose counters fit LDS, distinct and repetitive."""
+    rng = np.random.default_rng(genomes + family)
+    gen = []
+    for _ in range(genomes // family):
+        root = synth.random_codes(rng, 300)
+        gen += [synth.ACGT[synth.substitute(rng, root, 0.02)].tobytes() for _ in range(family)]
+    ga = synth.SeqSet.from_list(gen)
+    reads = _cut(rng, ga, N_READS, rng.integers(0, 200, N_READS), 0.01, 0.001)
+    hits = mt.Index(ga, 15, 8).containment(mt.to_device(reads)).cpu().numpy().view(np.uint64)
+    assert np.array_equal(hits, oracle.Index(ga, 15, 8).containment(reads))
