@@ -568,7 +568,7 @@ __device__ inline LdsPair stage_pair(const FilterArgs &a, u32 *S, u64 rb, int nb
 // rows in R words, surviving NC columns ...
 template <int R, int NC>
 struct WalkFilter {
-    static constexpr int MAX_M = FAR_MOST;
+    static constexpr int MAX_M = FAR_MOST, MAX_DW = LANE_DW;
     static constexpr bool AHEAD = true, ALL_FIT = true;
     template <bool kN>
     __device__ static int value(const LdsPair &P, int wofs, int m, int E) {
@@ -628,7 +628,7 @@ __global__ __launch_bounds__(LANE_TPB) __attribute__((amdgpu_waves_per_eu(4, 8))
     int c = 0;
     const u64 any_n = __ballot(with_n);
     const int need = (any_n ? 6 : 4) * (nbr + nbw);
-    const bool fits = need <= LANE_DW && m <= F::MAX_M;
+    const bool fits = need <= F::MAX_DW && m <= F::MAX_M;
     u64 todo = __ballot(ok && m > 0 && fits);
     while (todo) {
         int end = ((todo >> lane) & 1) ? need : 0;  // inclusive prefix sum of the lanes left
@@ -1170,7 +1170,9 @@ __device__ inline u64 shd_amend(u64 xp, u64 x, u64 xn) {
 // by VALU issue (about 25 operations a row and word); 250k pairs of 100 bases at
 // E = 5: 74 us with each row word fetched from global memory, SHD_US us staged.
 struct ShdFilter {
-    static constexpr int WORDS = 5, MAX_M = 64 * WORDS;
+    // MAX_DW: with fewer than 16 pairs at once in LDS, a lane for each word does more
+    // (40,000 pairs of 150 bases at E = 3,000, three at once: 9.5 ms and 3.1)
+    static constexpr int WORDS = 5, MAX_M = 64 * WORDS, MAX_DW = LANE_DW / 16;
     static constexpr bool AHEAD = false, ALL_FIT = false;
     template <bool kN>
     __device__ static int value(const LdsPair &P, int wofs, int m, int E) {
