@@ -41,7 +41,7 @@ constexpr int F_WORDS = F_MAX_M / 16 + 2;  // 2-bit stream words (16 bases per w
 // against 119.
 constexpr u64 LANE_MIN_READS = 48 * 1024;
 
-enum : u32 { ST_READS, ST_BASES, ST_MINS, ST_WBLOCKS, ST_CANDS, ST_OCC, ST_HITS, ST_COUNT };
+enum : u32 { ST_READS, ST_BASES, ST_MINS, ST_WBLOCKS, ST_CANDS, ST_OCC, ST_HITS, ST_FB_BASES, ST_COUNT };
 
 struct SeedArgs {
     const u8 *seq;
@@ -60,7 +60,6 @@ struct SeedArgs {
     u8 *read_n;  // 1 if the read has an N
     u32 *slow_list, *slow_count;  // reads for k_seed_wave
     u32 *fb_list, *fb_count;      // reads for the per-stage kernels
-    unsigned long long *fb_bases; // ... and their bases
     u32 *flags;
     const u32 *gate;  // offsets check result: nonzero skips the whole launch
     u64 *stats_part;  // ST_COUNT work counts per block
@@ -266,13 +265,13 @@ __global__ __launch_bounds__(LN_TPB) void k_seed_lane(SeedArgs a) {
         a.read_n[r] = rd.has_n;
     }
     list_append(in && slow && !fall, r, lane, a.slow_list, a.slow_count);
-    list_append(in && fall, r, length, lane, a.fb_list, a.fb_count, a.fb_bases);
+    list_append(in && fall, r, lane, a.fb_list, a.fb_count);
     if (wflags) atomicOr(a.flags, wflags);
     // work counts: one record per block, summed by k_fused_summary
     const bool done = take && !slow && !fall;
     const u32 st[ST_COUNT] = {done, done ? (u32)m : 0u, done ? (u32)nmin : 0u,
                               (u32)nc * (u32)((m + 2 * E + 63) / 64), (u32)nc, done ? (u32)nocc : 0u,
-                              done ? (u32)H : 0u};
+                              done ? (u32)H : 0u, in && fall ? (u32)length : 0u};
 #pragma unroll
     for (u32 i = 0; i < ST_COUNT; i++) {
         const u32 t = wave_sum(st[i]);
@@ -411,6 +410,9 @@ static void launch_seed_lane(const SeedArgs &a, bool rep, unsigned blocks, hipSt
 //      registers, one ballot per distinct location, when they fit one lane each,
 //      and in a per-read LDS hash table otherwise;
 //   5. the locations with >= min_hits hits are ranked and staged.
+// A read left to the per-stage kernels costs one atomic, for its place in the list; its
+// bases are summed with the work counts (a second atomic on that line took as long as
+// the rest: 300,000 reads on families of 50 strains, 126,000 left, 3.04 ms, 1.55 so).
 // blk0: first record of stats_part.
 __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_seed_wave(
     SeedArgs a, const u32 *__restrict__ list, const u32 *__restrict__ list_n, u32 blk0) {
@@ -469,7 +471,7 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
         if (m > F_MAX_M || E > F_MAX_E) {
             if (lane == 0) {
                 a.fb_list[atomicAdd(a.fb_count, 1u)] = (u32)r;
-                atomicAdd(a.fb_bases, (unsigned long long)m);
+                wst[ST_FB_BASES] += (u64)m;
                 a.ncand[r] = 0;  // until the per-stage kernels fill it in
                 a.read_n[r] = 0;
             }
@@ -685,7 +687,7 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
             if (lane == 0) {
                 *tn = 0;
                 a.fb_list[atomicAdd(a.fb_count, 1u)] = (u32)r;
-                atomicAdd(a.fb_bases, (unsigned long long)m);
+                wst[ST_FB_BASES] += (u64)m;
                 a.ncand[r] = 0;
                 a.read_n[r] = has_n;
             }
@@ -723,7 +725,7 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
             // keep-all with more candidates than staging slots: per-stage finish
             if (lane == 0) {
                 a.fb_list[atomicAdd(a.fb_count, 1u)] = (u32)r;
-                atomicAdd(a.fb_bases, (unsigned long long)m);
+                wst[ST_FB_BASES] += (u64)m;
                 a.ncand[r] = 0;
                 a.read_n[r] = has_n;
             }
@@ -777,13 +779,13 @@ __global__ __launch_bounds__(64 * F_WPB) __attribute__((amdgpu_waves_per_eu(5, 8
 
 // Control words of one fused call: [0] offsets check, [1] run flags,
 // [2] reads for the per-stage kernels, [3] reads for k_seed_wave, [4..5] bases of
-// the former.
+// the former (containment; the classification sums them with its work counts).
 constexpr int CTL_GATE = 0, CTL_FLAGS = 1, CTL_FB = 2, CTL_SLOW = 3, CTL_FB_BASES = 4, CTL_WORDS = 6;
 
 // Host-visible summary of one fused call, read back with a single copy.
 struct FusedSummary {
     u32 gate, flags, nfb, pad;
-    u64 fb_bases, n_cands;
+    u64 n_cands;
     u64 stats[ST_COUNT];
 };
 
@@ -818,7 +820,6 @@ __global__ __launch_bounds__(SUM_TPB) void k_fused_summary(const u32 *__restrict
             out->flags = ctl[CTL_FLAGS];
             out->nfb = ctl[CTL_FB];
             out->pad = 0;
-            out->fb_bases = ctl[CTL_FB_BASES] | (u64)ctl[CTL_FB_BASES + 1] << 32;
             out->n_cands = ctl[CTL_GATE] ? 0 : *cand_end;
         }
     }
@@ -1145,7 +1146,6 @@ void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs 
     a.slow_count = ctl.p + CTL_SLOW;
     a.fb_list = fb_list.p;
     a.fb_count = ctl.p + CTL_FB;
-    a.fb_bases = (unsigned long long *)(ctl.p + CTL_FB_BASES);
     a.flags = ctl.p + CTL_FLAGS;
     a.gate = ctl.p + CTL_GATE;
     a.stats_part = stats_part.p;
@@ -1187,7 +1187,7 @@ void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs 
 
     // Reads past the fused kernels' limits: finish them per stage, as a subset
     // that shares the bytes, and make room for their candidates among the others'.
-    const Subset sub(reads, fb_list.p, nfb, h.fb_bases, s);
+    const Subset sub(reads, fb_list.p, nfb, h.stats[ST_FB_BASES], s);
     mt_result tmp;
     mt_result_init(tmp, nfb, ix.n_taxa, s);
     ReadBatch srb;
@@ -1356,6 +1356,7 @@ __global__ __launch_bounds__(64 * F_WPB) void k_contain_wave(ContainArgs a, cons
     const u32 k = a.k;
     const u64 kmask = (1ull << k) - 1;
     u32 wflags = 0;
+    u64 fb_bases = 0;
     const u64 stride = (u64)gridDim.x * F_WPB;
     const u64 n = list ? *list_n : a.n;
     u64 i = (u64)blockIdx.x * F_WPB + wid;
@@ -1382,10 +1383,8 @@ __global__ __launch_bounds__(64 * F_WPB) void k_contain_wave(ContainArgs a, cons
         u64 noff = 0;
         if (more) noff = a.off[rn + (u64)(lane & 1)];
         if (m > F_MAX_M) {
-            if (lane == 0) {
-                a.fb_list[atomicAdd(a.fb_count, 1u)] = (u32)r;
-                atomicAdd(a.fb_bases, (unsigned long long)m);
-            }
+            if (lane == 0) a.fb_list[atomicAdd(a.fb_count, 1u)] = (u32)r;
+            fb_bases += (u64)m;
             const u64 nbeg = readlane64(noff, 0);
             m = (int)(readlane64(noff, 1) - nbeg);
 #pragma unroll
@@ -1478,6 +1477,7 @@ __global__ __launch_bounds__(64 * F_WPB) void k_contain_wave(ContainArgs a, cons
         wave_sync();  // the next read reuses the wavefront's LDS
     }
     if (lane == 0 && wflags) atomicOr(a.flags, wflags);
+    if (lane == 0 && fb_bases) atomicAdd(a.fb_bases, (unsigned long long)fb_bases);
     if (in_lds) {
         __syncthreads();
         for (u64 g = threadIdx.x; g < a.n_genomes; g += blockDim.x)
