@@ -35,7 +35,7 @@ constexpr int F_MAX_E = FUSED_MAX_E;  // 2E + 1 rows fit two words of the filter
 constexpr int F_MAX_TOPN = 8;    // staged candidates per read (top_n = 0 keeps up to this many)
 constexpr int F_WORDS = F_MAX_M / 16 + 2;  // 2-bit stream words (16 bases per word) + padding
 
-// Fewest reads for k_seed_lane: 64 reads a wavefront fill the chip late, and a
+// Fewest reads for the lane kernels (see lane_least): 64 reads a wavefront fill the chip late, and a
 // lane's chain of k-mers and probes has a latency of its own of about 80 us.
 // 32k reads of 150 bases: 88 us in lanes, 63 with a wavefront each; 64k: 101
 // against 119.
@@ -1072,8 +1072,27 @@ static void launch_fused_graph(const FusedLaunch &L, hipStream_t s) {
     MT_HIP(e);
 }
 
-// At least one occurrence in eight belongs to a k-mer found in several places.
-static bool repetitive(const mt_index &ix) { return ix.n_multi_occ * 8 >= ix.n_minimizers && ix.n_multi_occ > 0; }
+// Hits of a read of the mean length beyond one for each of its minimizers.
+static double extra_hits(const mt_index &ix, const mt_seqs &reads) {
+    const double starts = (double)reads.total / (double)reads.n - ix.k + 1;
+    return starts > 0 ? 2 * starts / (ix.w + 1) * (ix.hits - 1) : 0;
+}
+
+// Fewest reads for k_seed_lane: LANE_MIN_READS, more on repetitive databases, where a
+// lane goes through a read's extra hits one after the other, and none at all where the
+// locations of a read pass its list.  Lanes and a wavefront each, 150 bases, k = 21:
+//   families of 5 (20 extra hits)   60k 0.28, 0.21 ms; 120k 0.33, 0.34; 1M 1.47, 2.10
+//   of 8 (36)                       120k 0.42, 0.38; 300k 0.76, 0.79; 1M 1.99, 2.33
+//   of 10 (44)                      300k 0.90, 0.84; 1M 2.40, 2.50
+//   of 12 (50; 12 locations)        1M 2.86, 2.63
+//   of 20 (89)                      300k 2.47, 1.49
+//   k = 13, unrelated (12; 13 locations)   300k 1.16, 0.68
+static u64 lane_least(const mt_index &ix, const mt_seqs &reads) {
+    if (!ix.repetitive()) return LANE_MIN_READS;
+    const double extra = extra_hits(ix, reads), x = extra / 16;
+    if ((ix.scattered() ? 1 + extra : ix.locations) > 10) return ~0ull;
+    return (u64)((double)LANE_MIN_READS * (1 + x * x));
+}
 
 void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs &reads, ReadBatch &rb,
                     mt_result &res, Timer &tm, hipStream_t s, bool graph) {
@@ -1108,7 +1127,7 @@ void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs 
     int dev = 0, cus = 0;
     MT_HIP(hipGetDevice(&dev));
     MT_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    const bool lanes = n >= LANE_MIN_READS && ix.w >= (u32)LN_MIN_W && ix.w <= (u32)LN_MAX_W;
+    const bool lanes = ix.w >= (u32)LN_MIN_W && ix.w <= (u32)LN_MAX_W && n >= lane_least(ix, reads);
     const u64 lane_blocks = lanes ? grid_for(n, LN_TPB) : 0;
     // k_seed_wave: many short blocks, so that resident blocks finish together; a
     // list of slow reads, whose length only the device knows, takes fewer
@@ -1157,7 +1176,7 @@ void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs 
     L.wave_blocks = (unsigned)wave_blocks;
     L.res = &res;
     L.sum = sum.p;
-    L.rep = repetitive(ix);
+    L.rep = ix.repetitive();
 
     if (graph) {
         launch_fused_graph(L, s);
@@ -1495,8 +1514,14 @@ void containment(const mt_index &ix, const mt_seqs &reads, u64 *hits, hipStream_
     // A lane adds the occurrences of a k-mer one after the other; where they are many and
     // go to global counters, a wavefront per read has more of them on their way (300,000
     // reads, 3,000 genomes: strains 0.87 ms in lanes and 0.66, random ones 0.42 and 0.48).
-    const bool lanes = n >= LANE_MIN_READS && ix.w >= (u32)LN_MIN_W && ix.w <= (u32)LN_MAX_W &&
-                       (ix.n_genomes <= CF_LDS_GENOMES || !repetitive(ix));
+    // In LDS they matter less than to the classification (60,000, 120,000 and 300,000
+    // reads, lanes and a wavefront each: families of 10 0.15, 0.18; 0.19, 0.26 and 0.34,
+    // 0.50 ms; of 50 0.31, 0.26; 0.37, 0.42 and 0.66, 0.90; k = 13, unrelated, 0.29, 0.24;
+    // 0.37, 0.31 and 0.65, 0.65).
+    const double x = ix.repetitive() ? extra_hits(ix, reads) / (ix.scattered() ? 10 : 200) : 0;
+    const bool lanes = ix.w >= (u32)LN_MIN_W && ix.w <= (u32)LN_MAX_W &&
+                       n >= (u64)((double)LANE_MIN_READS * (1 + x)) &&
+                       (ix.n_genomes <= CF_LDS_GENOMES || !ix.repetitive());
     DBuf<u32> ctl(CTL_WORDS), fb_list(n), slow_list(lanes ? n : 0);
     enqueue_begin(reads.offsets, n, reads.total, ctl.p, hits, ix.n_genomes, s);
     int dev = 0, cus = 0;

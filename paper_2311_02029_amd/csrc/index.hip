@@ -488,6 +488,67 @@ __global__ void k_dup_place(const u64 *__restrict__ dup_slot, const u64 *__restr
     if (slot_count(v)) occ[slot_start(v) + 1 + rank[d]] = dup_occ[d];
 }
 
+// How repetitive the database is, as a read of it meets it: SAMPLES runs of SAMPLE_RUN
+// minimizers in a row, from tiles spread over the genomes; out receives the sums of
+// their locations (genome, diagonal), of their hits, and of the minimizers.  A
+// wavefront per run, which stops at SAMPLE_MOST locations and occurrences of one k-mer.
+constexpr int SAMPLES = 512, SAMPLE_RUN = mt_index::SAMPLE_RUN, SAMPLE_MOST = 32, SAMPLE_SLOTS = 128, SAMPLE_WPB = 4;
+
+__global__ __launch_bounds__(64 * SAMPLE_WPB) void k_sample_locations(
+    const u64x2 *__restrict__ lohi, const u64 *__restrict__ nbp, const u64 *__restrict__ blk_off,
+    const u64 *__restrict__ tile_off, const u32 *__restrict__ tile_map, u64 n, u32 k,
+    const u64 *__restrict__ tile_bits, const u64x2 *__restrict__ table, u64 nbuckets, const u64 *__restrict__ occ,
+    unsigned long long *__restrict__ out) {
+    __shared__ u64 key_all[SAMPLE_WPB][SAMPLE_SLOTS];
+    __shared__ u16 list_all[SAMPLE_WPB][SAMPLE_RUN];
+    __shared__ u32 found_all[SAMPLE_WPB];
+    const u32 lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    u64 *key = key_all[wid];
+    for (int i = (int)lane; i < SAMPLE_SLOTS; i += 64) key[i] = ~0ull;
+    if (lane == 0) found_all[wid] = 0;
+    const u64 tiles = tile_off[n];
+    const u64 t = tiles * ((u64)blockIdx.x * SAMPLE_WPB + wid) / SAMPLES;
+    u32 nl = 0, s = 0;
+    if (tiles) {
+        s = tile_map[t];
+        constexpr int WORDS = MIN_TILE / 64;
+        for (int q = 0; q < WORDS && nl < (u32)SAMPLE_RUN; q++) {
+            const u64 m = tile_bits[t * WORDS + q];
+            const u32 at = nl + (u32)__popcll(m & ((1ull << lane) - 1));
+            if (((m >> lane) & 1) && at < (u32)SAMPLE_RUN) list_all[wid][at] = (u16)(64 * q + lane);
+            nl += (u32)__popcll(m);
+        }
+    }
+    if (nl > (u32)SAMPLE_RUN) nl = SAMPLE_RUN;
+    __syncthreads();
+    u32 hits = 0;
+    if (lane < nl) {
+        const i64 p = (i64)(t - tile_off[s]) * MIN_TILE + list_all[wid][lane];
+        const Bits64 bits = fetch_planes(lohi + blk_off[s], nbp + blk_off[s], p);
+        const u64 v = table_lookup(table, nbuckets, kmer_value(bits.lo, bits.hi, k));
+        if (v != SLOT_NONE) hits = slot_count(v) < (u32)SAMPLE_MOST ? slot_count(v) : (u32)SAMPLE_MOST;
+        for (u32 u = 0; u < hits; u++) {
+            // (the lanes pass the bound by one each at most, far from filling the slots)
+            if (__hip_atomic_load(&found_all[wid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >= (u32)SAMPLE_MOST) break;
+            const u64 gp = (v & SLOT_MULTI) ? occ[slot_start(v) + u] : v;
+            const u64 x = cand_key((u32)(gp >> 32), (i64)(u32)gp - p);
+            for (u32 sl = (u32)(mix64(x) % SAMPLE_SLOTS);; sl = (sl + 1) % SAMPLE_SLOTS) {
+                const u64 cur = atomicCAS((unsigned long long *)&key[sl], ~0ull, (unsigned long long)x);
+                if (cur == ~0ull) atomicAdd(&found_all[wid], 1u);
+                if (cur == ~0ull || cur == x) break;
+            }
+        }
+    }
+#pragma unroll
+    for (int o = 32; o; o >>= 1) hits += __shfl_xor(hits, o, 64);
+    __syncthreads();
+    if (lane == 0 && nl) {
+        atomicAdd(&out[0], (unsigned long long)found_all[wid]);
+        atomicAdd(&out[1], (unsigned long long)hits);
+        atomicAdd(&out[2], (unsigned long long)nl);
+    }
+}
+
 void build_index(mt_index &ix, const mt_index_params &p, const mt_seqs &g, const uint32_t *taxon, uint32_t n_taxa,
                  hipStream_t s) {
     Timer tm;
@@ -510,8 +571,8 @@ void build_index(mt_index &ix, const mt_index_params &p, const mt_seqs &g, const
     ix.n_genomes = g.n;
     ix.total_bases = g.total;
 
-    DBuf<u32> flags(2);
-    MT_HIP(hipMemsetAsync(flags.p, 0, 2 * sizeof(u32), s));
+    DBuf<u32> flags(8);  // the flags, the longest length, three 64-bit sums of k_sample_locations
+    MT_HIP(hipMemsetAsync(flags.p, 0, 8 * sizeof(u32), s));
     ix.has_n.alloc(g.n);
     MT_HIP(hipMemsetAsync(ix.has_n.p, 0, g.n ? g.n : 1, s));
     pack_sequences(g, 4294901759ull, ERR_READ_TOO_LONG, "genome length must be below 2^32 - 2^16", ix.ref,
@@ -598,6 +659,19 @@ void build_index(mt_index &ix, const mt_index_params &p, const mt_seqs &g, const
         ix.occ.alloc(0);
     }
     ix.n_multi_occ = n_multi;
+    if (ix.repetitive()) {
+        auto *sums = (unsigned long long *)(flags.p + 2);
+        k_sample_locations<<<SAMPLES / SAMPLE_WPB, 64 * SAMPLE_WPB, 0, s>>>(
+            ix.ref.lohi.p, ix.ref.nb.p, ix.ref.blk_off.p, mp.tile_off.p, mp.tile_map.p, g.n, p.k, mp.tile_bits.p,
+            ix.table.p, nbuckets, ix.occ.p, sums);
+        MT_HIP(hipGetLastError());
+        u64 h[3];
+        read_back(s, sums, h, sizeof h);
+        if (h[2]) {
+            ix.locations = (double)h[0] / SAMPLES;
+            ix.hits = (double)h[1] / (double)h[2];
+        }
+    }
     tm.mark("index_fill");
     MT_HIP(hipStreamSynchronize(s));
     tm.finish();

@@ -8,6 +8,15 @@ struct mt_index {
     uint32_t k = 0, w = 0, max_occ = 0, n_taxa = 0;
     uint64_t n_genomes = 0, total_bases = 0;
     uint64_t n_minimizers = 0, n_keys = 0, n_multi_occ = 0;
+    // At least one occurrence in eight belongs to a k-mer found in several places.
+    bool repetitive() const { return n_multi_occ * 8 >= n_minimizers && n_multi_occ > 0; }
+    // Of a repetitive database, from a sample of itself: locations of a run of SAMPLE_RUN
+    // minimizers (about a read of 150 bases), hits of a minimizer.
+    static constexpr int SAMPLE_RUN = 24;
+    double locations = 1, hits = 1;
+    // The hits of a read scatter (k-mers that recur by chance), instead of lying along the
+    // genomes of a family.
+    bool scattered() const { return locations > (1 + SAMPLE_RUN * (hits - 1)) / 2; }
     mt::PackedSeqs ref;          // reference bit planes, genome g at block ref.blk_off[g]
     mt::DBuf<mt::u64> glen;      // genome lengths
     mt::DBuf<mt::u8> has_n;      // 1 if the genome contains N
