@@ -835,12 +835,13 @@ __global__ void k_strand_merge_done(const u64 *__restrict__ cand_off2, u64 n, co
 // walk in every mode, as long as a read of the mean length is within its limits: a set
 // of which most reads are left over pays for its launches as well as for the per-stage
 // ones (10,000 reads of 2 kbp through the Hamming filter: 0.75 ms, 0.42 per stage; 1M of
-// 100 bases: 0.18 and 0.81).  A graph holds the obstacle walk only.
-bool takes_fused(const mt_query_params &q, const mt_seqs &reads) {
+// 100 bases: 0.18 and 0.81).  So for its seed hits, as the database gives them to such
+// reads (a few of which have more than the mean).  A graph holds the obstacle walk only.
+bool takes_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs &reads) {
     if (q.filter == MT_FILTER_OBSTACLE) return q.mode != MT_MODE_PER_STAGE;
     const u64 m = reads.n ? reads.total / reads.n : 0;
     const u64 E = q.e_mode == MT_E_FIXED ? q.e_value : m * q.e_value / 1000;
-    return m <= (u64)FUSED_MAX_M && E <= (u64)FUSED_MAX_E;
+    return m <= (u64)FUSED_MAX_M && E <= (u64)FUSED_MAX_E && ix.hits_of(m) <= 0.75 * FUSED_MAX_HITS;
 }
 static bool takes_graph(const mt_query_params &q) {
     return q.mode == MT_MODE_FUSED_GRAPH && q.filter == MT_FILTER_OBSTACLE;
@@ -905,7 +906,7 @@ static void classify_both_strands(const mt_index &ix, const mt_query_params &q, 
         MT_HIP(hipGetLastError());
     }
     const mt_seqs two{(const char *)seq2.p, off2.p, 2 * n, 2 * reads.total};
-    if (takes_fused(q, reads)) {
+    if (takes_fused(ix, q, reads)) {
         tm.mark("pack");
         both_strands_fused(ix, q, two, rb, res, tm, s);
         return;
@@ -1038,7 +1039,7 @@ extern "C" int mt_classify(const mt_index *index, const mt_query_params *params,
             tm.begin(s);
             mt::mt_result_init(*res, reads->n, index->n_taxa, s);
             mt::ReadBatch rb;
-            if (mt::takes_fused(*params, *reads))
+            if (mt::takes_fused(*index, *params, *reads))
                 mt::classify_fused(*index, *params, *reads, rb, *res, tm, s, mt::takes_graph(*params));
             else
                 mt::classify_staged(*index, *params, *reads, rb, *res, tm, s);

@@ -114,10 +114,10 @@ void tune_info(int bucket, mt_tune_bucket &out);
 void tune_set(int bucket, int variant);
 void tune_reset();
 
-// Limits of the fused form: longest read, largest E.
-constexpr int FUSED_MAX_M = 320, FUSED_MAX_E = 31;
+// Limits of the fused form: longest read, largest E, most seed hits of a read.
+constexpr int FUSED_MAX_M = 320, FUSED_MAX_E = 31, FUSED_MAX_HITS = 256;
 // Whether a query over these reads takes the fused form (classify.hip).
-bool takes_fused(const mt_query_params &q, const mt_seqs &reads);
+bool takes_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs &reads);
 
 void validate_query(const mt_query_params &q);
 // Allocates the per-read and per-taxon arrays; the forms below clear the counters.

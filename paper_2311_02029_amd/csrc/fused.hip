@@ -29,7 +29,7 @@ constexpr int F_WPB = 4;         // wavefronts per block
 constexpr int F_MAX_M = LN_MAX_M;  // longest read of k_seed_wave
 static_assert(F_MAX_M == FUSED_MAX_M, "the forms are told apart by it");
 constexpr int F_ROUNDS = F_MAX_M / 64;  // of 64 positions; a read takes those it reaches
-constexpr int F_HIT_CAP = 256;   // seed hits per read (distinct locations fit the table)
+constexpr int F_HIT_CAP = FUSED_MAX_HITS;  // seed hits per read (distinct locations fit the table)
 constexpr int F_TSLOTS = 256;    // per-read LDS hash table of locations
 constexpr int F_MAX_E = FUSED_MAX_E;  // 2E + 1 rows fit two words of the filter
 constexpr int F_MAX_TOPN = 8;    // staged candidates per read (top_n = 0 keeps up to this many)
@@ -1074,8 +1074,7 @@ static void launch_fused_graph(const FusedLaunch &L, hipStream_t s) {
 
 // Hits of a read of the mean length beyond one for each of its minimizers.
 static double extra_hits(const mt_index &ix, const mt_seqs &reads) {
-    const double starts = (double)reads.total / (double)reads.n - ix.k + 1;
-    return starts > 0 ? 2 * starts / (ix.w + 1) * (ix.hits - 1) : 0;
+    return ix.hits_of(reads.total / reads.n) * (1 - 1 / ix.hits);
 }
 
 // Fewest reads for k_seed_lane: LANE_MIN_READS, more on repetitive databases, where a
@@ -1097,7 +1096,7 @@ static u64 lane_least(const mt_index &ix, const mt_seqs &reads) {
 void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs &reads, ReadBatch &rb,
                     mt_result &res, Timer &tm, hipStream_t s, bool graph) {
     // the two-strand read set comes back here; a served batch may not be for the fused form
-    if (q.strands == 2 || (q.filter != MT_FILTER_OBSTACLE && !takes_fused(q, reads))) {
+    if (q.strands == 2 || (q.filter != MT_FILTER_OBSTACLE && !takes_fused(ix, q, reads))) {
         classify_staged(ix, q, reads, rb, res, tm, s);
         return;
     }

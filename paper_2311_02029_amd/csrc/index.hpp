@@ -14,6 +14,8 @@ struct mt_index {
     // minimizers (about a read of 150 bases), hits of a minimizer.
     static constexpr int SAMPLE_RUN = 24;
     double locations = 1, hits = 1;
+    // Hits of a read of m bases, about.
+    double hits_of(uint64_t m) const { return m < k ? 0 : 2.0 * (double)(m - k + 1) / (w + 1) * hits; }
     // The hits of a read scatter (k-mers that recur by chance), instead of lying along the
     // genomes of a family.
     bool scattered() const { return locations > (1 + SAMPLE_RUN * (hits - 1)) / 2; }

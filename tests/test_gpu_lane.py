@@ -124,9 +124,12 @@ def test_other_filters_in_every_mode(mt, db, kind, mode):
                                            (300, 300, dict(e_mode=1, e_value=100), True),
                                            (310, 330, dict(e_mode=2, e_value=101), False)])
 def test_other_filters_go_per_stage_where_most_reads_are_left_over(mt, db, lo, hi, q, fused, strands):
-    """By the mean length and its E; both routes with short and long reads among them."""
+    """By the mean length and its E; both routes with short and long reads among them.
+    A database of many strains, whose reads have more hits than the fused form counts,
+    goes per stage as well."""
     rng = np.random.default_rng(lo + hi)
     n = 1501
+    db = synth.SeqSet.from_list([db.get(i) for i in range(3)])
     reads = _cut(rng, db, n, np.linspace(lo, hi, n).astype(np.int64), 0.01, 0.001)
     reads = synth.SeqSet.from_list([reads.get(i) for i in rng.permutation(n)])
     ix, oix = mt.Index(db, 21, 11, 200), oracle.Index(db, 21, 11, 200)
@@ -137,6 +140,15 @@ def test_other_filters_go_per_stage_where_most_reads_are_left_over(mt, db, lo, h
             assert (mt.last_stats()["fused_reads"] > 0) == fused, (kind, mode)
             for f in FIELDS:
                 assert np.array_equal(got[f], ref[f]), (f, kind, mode)
+    if strands == 1 and fused:
+        many = synth.SeqSet.from_list([synth.ACGT[synth.substitute(rng, synth.random_codes(np.random.default_rng(1), 6000),
+                                                                   0.002)].tobytes() for _ in range(60)])
+        reads = _cut(rng, many, n, np.full(n, 300), 0.01, 0.001)
+        got = mt.Index(many, 21, 11).classify(mt.to_device(reads), filter_kind=4).to_host()
+        assert mt.last_stats()["fused_reads"] == 0
+        ref = oracle.Index(many, 21, 11).classify(reads, 3, 3, 0, 7, filter_kind=4)
+        for f in FIELDS:
+            assert np.array_equal(got[f], ref[f]), f
 
 
 @pytest.mark.parametrize("strands", [1, 2])
