@@ -77,7 +77,7 @@ struct FilterArgs {
     const u64x2 *read_lohi;
     const u64 *read_nb;
     const u8 *read_has_n;
-    u32 max_len;      // of the reads (at most)
+    u32 max_len;      // of the reads, as PackedSeqs has it
     int far_len;      // short E: reads past it take groups of lanes (set by launch_filter)
     u64 n_genomes;
     const GenomeMeta *meta;
@@ -125,11 +125,9 @@ void mt_result_init(mt_result &res, u64 n, u32 n_taxa, hipStream_t s);
 void zero_counters(mt_result &res, hipStream_t s);
 void classify_per_stage(const mt_index &ix, const mt_query_params &q, const mt_seqs &reads, ReadBatch &rb,
                         mt_result &res, Timer &tm, hipStream_t s);
-// Fused form.  Checks the call's flags and sets res.n_cands before it
-// returns; graph = launch the sequence as one captured HIP graph.
 // Containment search: every genome's seed hits over `reads` (device, n_genomes;
-// containment_per_stage adds to hits).  containment runs reads of up to 256 bases in one
-// fused kernel and the rest through containment_per_stage.
+// containment_per_stage adds to hits).  containment runs reads of up to 320 bases in the
+// fused kernels and the rest through containment_per_stage.
 void containment(const mt_index &ix, const mt_seqs &reads, u64 *hits, hipStream_t s);
 void containment_per_stage(const mt_index &ix, const mt_seqs &reads, const u64 *src, u64 src_total, u64 *hits,
                            hipStream_t s);
@@ -138,6 +136,8 @@ void containment_per_stage(const mt_index &ix, const mt_seqs &reads, const u64 *
 // flags, candidate count.
 void classify_staged(const mt_index &ix, const mt_query_params &q, const mt_seqs &reads, ReadBatch &rb,
                      mt_result &res, Timer &tm, hipStream_t s);
+// Fused form.  Checks the call's flags and sets res.n_cands before it
+// returns; graph = launch the sequence as one captured HIP graph.
 void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs &reads, ReadBatch &rb,
                     mt_result &res, Timer &tm, hipStream_t s, bool graph);
 // The taxon step: read_accepted and the taxon counts of res from its filtered

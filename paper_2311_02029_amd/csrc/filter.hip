@@ -305,6 +305,7 @@ __device__ inline void lds_wave_sync() {
 // 0.21 (0.73, 0.45); 10 kbp, 12,000 3.3 and 0.16.  Reads up to 256 bases keep to lanes;
 // past 1 kbp too few pairs fit a wavefront's LDS at once.
 constexpr int FAR_LEAST = 256, FAR_MOST = 1024;
+static_assert(FAR_LEAST >= (int)NOTED_LEN, "the longest length is known from there on");
 constexpr u64 FAR_PAIRS = 64;  // pairs a base
 static int far_len(u64 n) {
     return (int)std::min<u64>(std::max<u64>(n / FAR_PAIRS, FAR_LEAST), FAR_MOST);
@@ -1168,7 +1169,7 @@ __device__ inline u64 shd_amend(u64 xp, u64 x, u64 xn) {
 
 // ... and SHD, for k_filter_lane: rows outer, the read's words in registers.  Bound
 // by VALU issue (about 25 operations a row and word); 250k pairs of 100 bases at
-// E = 5: 74 us with each row word fetched from global memory, SHD_US us staged.
+// E = 5: 74 us with each row word fetched from global memory, 32 us staged.
 struct ShdFilter {
     // MAX_DW: with fewer than 16 pairs at once in LDS, a lane for each word does more
     // (40,000 pairs of 150 bases at E = 3,000, three at once: 9.5 ms and 3.1)

@@ -12,7 +12,7 @@ namespace mt {
 // Small results (counts, flags, a call's summary) are written by a kernel into
 // pinned memory and read after the wait: a copy to pageable
 // memory goes through the runtime's staging and is waited for there as well (16 reads
-// classified and taken to the host 131 us, 116 us so; 1M explicit pairs, with two
+// classified and taken to the host 131 us, 116 us so; 1M explicit pairs, with three
 // such waits, 243 and 208 us).  Bound by latency.
 // The library has one block of WORD_SLOTS places, for as many calls waiting at once;
 // the next one copies.  (A place per host thread cost a program that starts a thread
@@ -78,8 +78,8 @@ void read_back(hipStream_t s, const void *dev, void *host, size_t bytes) {
 
 // Blocks per sequence: ceil(len / 64) + 1 (the last one is padding).  Also
 // checks the offsets: 0 first, never decreasing, `total` last; and leaves the longest
-// length in flags[1], an atomic a block (an atomic a wavefront on that one word took
-// 35 us for 300k reads).
+// length above NOTED_LEN in flags[1], an atomic a block (an atomic a wavefront on that
+// one word took 35 us for 300k reads; one a block, for short reads too, 5).
 constexpr int SB_TPB = 1024, SB_BLOCKS = 512;
 
 __global__ __launch_bounds__(SB_TPB) void k_seq_blocks(const u64 *__restrict__ off, u64 n, u64 total, u64 len_limit,
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(SB_TPB) void k_seq_blocks(const u64 *__restrict__ o
     for (int o = 32; o; o >>= 1) mine = max(mine, (u32)__shfl_xor((int)mine, o, 64));
     if ((threadIdx.x & 63) == 0) atomicMax(&longest, mine);
     __syncthreads();
-    if (threadIdx.x == 0 && longest) atomicMax(flags + 1, longest);
+    if (threadIdx.x == 0 && longest > NOTED_LEN) atomicMax(flags + 1, longest);
 }
 
 // Four lanes per 64-base block, 16 bytes each in one load (a byte at a time

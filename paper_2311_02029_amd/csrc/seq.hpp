@@ -6,6 +6,8 @@
 
 namespace mt {
 
+constexpr u32 NOTED_LEN = 256;
+
 // Bit planes of a sequence set (layout described in device.hpp).
 struct PackedSeqs {
     DBuf<u64x2> lohi;
@@ -13,7 +15,7 @@ struct PackedSeqs {
     DBuf<u64> blk_off;  // n + 1: first block of each sequence
     u64 n = 0;
     u64 blocks_cap = 0;
-    u32 max_len = 0;    // longest sequence (of a subset: all ones)
+    u32 max_len = 0;    // longest sequence; 0: none is longer than NOTED_LEN; of a subset: all ones
 };
 
 // Packs `in` (device ASCII) into planes.  The offsets are checked first (a
