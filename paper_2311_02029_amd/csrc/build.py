@@ -1,4 +1,5 @@
-"""Builds libmetatrinity.so for gfx950 with hipcc (one object per source)."""
+"""Builds libmetatrinity.so for gfx950 with hipcc (one object per source, and one for
+each minimizer window of the lane kernels)."""
 from __future__ import annotations
 
 import os
@@ -12,6 +13,7 @@ ROOT = os.path.dirname(PKG)
 OUT = os.path.join(PKG, "libmetatrinity.so")
 SOURCES = ["runtime.hip", "seq.hip", "index.hip", "classify.hip", "filter.hip", "fused.hip", "server.hip", "tune.hip", "contain.hip",
            "abundance.hip"]
+LANE_SOURCE, LANE_WINDOWS = "lane.hip", range(4, 21)  # an object for each minimizer window
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include")]
@@ -42,9 +44,12 @@ def build(out: str = OUT, verbose: bool = False) -> str:
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
 
-    def compile_one(src):
-        obj = os.path.join(objdir, os.path.splitext(src)[0] + ".o")
-        cmd = ["hipcc", *FLAGS, "-c", os.path.join(HERE, src), "-o", obj]
+    def compile_one(job):
+        src, window = job
+        name = os.path.splitext(src)[0]
+        obj = os.path.join(objdir, f"{name}.o" if window is None else f"{name}_{window}.o")
+        defs = [] if window is None else [f"-DMT_WINDOW={window}"]
+        cmd = ["hipcc", *FLAGS, *defs, "-c", os.path.join(HERE, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         r = subprocess.run(cmd, capture_output=True, text=True)
@@ -52,8 +57,9 @@ def build(out: str = OUT, verbose: bool = False) -> str:
             raise RuntimeError(f"hipcc failed for {src}:\n{r.stdout}\n{r.stderr}")
         return obj
 
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
-        objs = list(ex.map(compile_one, SOURCES))
+    jobs = [(src, None) for src in SOURCES] + [(LANE_SOURCE, w) for w in LANE_WINDOWS]
+    with ThreadPoolExecutor(max_workers=min(8, len(jobs))) as ex:
+        objs = list(ex.map(compile_one, jobs))
     tmp = out + ".tmp"
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -1,6 +1,6 @@
 // Fused seeding for short reads (Fig. 1 steps 2b-2c in one kernel), then the
 // filter and the taxon step over its candidates (2d, 3a).
-//   k_seed_lane   one lane per read (lane.hpp): 2-bit stream, k-mers and window
+//   k_seed_lane   one lane per read (lane.hip): 2-bit stream, k-mers and window
 //                 minima base by base, then one table probe per minimizer; the
 //                 read's locations are counted in a short per-lane list, and the
 //                 ones with >= min_hits hits ranked in (hits desc, genome,
@@ -20,8 +20,7 @@
 // in per-stage mode; top_n above 8 runs per stage throughout.
 #include <algorithm>
 
-#include "classify.hpp"
-#include "lane.hpp"
+#include "fused.hpp"
 
 namespace mt {
 
@@ -29,9 +28,7 @@ constexpr int F_WPB = 4;         // wavefronts per block
 constexpr int F_MAX_M = LN_MAX_M;  // longest read of k_seed_wave
 static_assert(F_MAX_M == FUSED_MAX_M, "the forms are told apart by it");
 constexpr int F_ROUNDS = F_MAX_M / 64;  // of 64 positions; a read takes those it reaches
-constexpr int F_HIT_CAP = FUSED_MAX_HITS;  // seed hits per read (distinct locations fit the table)
 constexpr int F_TSLOTS = 256;    // per-read LDS hash table of locations
-constexpr int F_MAX_E = FUSED_MAX_E;  // 2E + 1 rows fit two words of the filter
 constexpr int F_MAX_TOPN = 8;    // staged candidates per read (top_n = 0 keeps up to this many)
 constexpr int F_WORDS = F_MAX_M / 16 + 2;  // 2-bit stream words (16 bases per word) + padding
 
@@ -40,246 +37,6 @@ constexpr int F_WORDS = F_MAX_M / 16 + 2;  // 2-bit stream words (16 bases per w
 // 32k reads of 150 bases: 88 us in lanes, 63 with a wavefront each; 64k: 101
 // against 119.
 constexpr u64 LANE_MIN_READS = 48 * 1024;
-
-enum : u32 { ST_READS, ST_BASES, ST_MINS, ST_WBLOCKS, ST_CANDS, ST_OCC, ST_HITS, ST_FB_BASES, ST_COUNT };
-
-struct SeedArgs {
-    const u8 *seq;
-    const u64 *off;
-    u64 n, total;
-    u32 k, w, min_hits, top_n, e_mode, e_value;
-    u32 ncap;  // staging slots per read: top_n, or F_MAX_TOPN when top_n = 0 (keep all)
-    const u64x2 *table;
-    u64 nbuckets;
-    const u64 *occ;
-    // staging: rank-major, slot (rank, read) at rank * n + read
-    u64 *st_key;
-    u32 *st_hits;
-    u32 *ncand;
-    u16 *read_E;
-    u8 *read_n;  // 1 if the read has an N
-    u32 *slow_list, *slow_count;  // reads for k_seed_wave
-    u32 *fb_list, *fb_count;      // reads for the per-stage kernels
-    u32 *flags;
-    const u32 *gate;  // offsets check result: nonzero skips the whole launch
-    u64 *stats_part;  // ST_COUNT work counts per block
-};
-
-// E of a read of m bases; ERR_E_TOO_LARGE in *flags when it passes the limit.
-__device__ inline int read_threshold(const SeedArgs &a, int m, u32 *flags) {
-    const u64 E = a.e_mode == MT_E_FIXED           ? a.e_value
-                  : a.e_mode == MT_E_CEIL_PERMILLE ? ((u64)m * a.e_value + 999) / 1000
-                                                   : ((u64)m * a.e_value) / 1000;
-    if (E > 65534) *flags |= ERR_E_TOO_LARGE;
-    return E > 65535 ? 65535 : (int)E;
-}
-
-__device__ inline void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-__device__ inline u64 ballot64(bool p) { return __ballot(p); }
-
-// Value of v in lane l (l wave-uniform).
-__device__ inline u64 readlane64(u64 v, int l) {
-    const u32 lo = __builtin_amdgcn_readlane((u32)v, l), hi = __builtin_amdgcn_readlane((u32)(v >> 32), l);
-    return ((u64)hi << 32) | lo;
-}
-
-// Number of set bits of m below this lane.
-__device__ inline u32 lanes_below(u64 m, int lane) {
-    return (u32)__popcll(lane ? m & ((~0ull) >> (64 - lane)) : 0ull);
-}
-
-// Appends r to a list for the lanes with `add` set, one atomic per wavefront.
-__device__ inline void list_append(bool add, u64 r, int lane, u32 *list, u32 *count) {
-    const u64 m = ballot64(add);
-    if (!m) return;
-    const int leader = __builtin_ctzll(m);
-    u32 first = 0;
-    if (lane == leader) first = atomicAdd(count, (u32)__popcll(m));
-    first = __shfl(first, leader, 64);
-    if (add) list[first + lanes_below(m, lane)] = (u32)r;
-}
-
-__device__ inline u32 wave_sum(u32 v) {
-#pragma unroll
-    for (int o = 32; o; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// ... and their bases to *bases.
-__device__ inline void list_append(bool add, u64 r, int m, int lane, u32 *list, u32 *count,
-                                   unsigned long long *bases) {
-    if (!ballot64(add)) return;
-    list_append(add, r, lane, list, count);
-    const u32 t = wave_sum(add ? (u32)m : 0u);
-    if (lane == 0) atomicAdd(bases, (unsigned long long)t);
-}
-
-// One lane per read.  MAXD: locations a lane's list holds; MAXM: longest read.  The list is searched
-// from its front for every hit; the first location, usually the only one, stays
-// in registers.
-// Bound by the random table lines of the probes: 1M reads of 150 bases on 500 Mbp
-// take 0.65 ms (20.8M probes, 32 G/s; the per-stage lookup, which does nothing
-// else, reaches 36 G/s), 10M on 4 Gbp of strains 13.4 ms with 52M occurrence
-// lists (208M probes, 16 G/s; the lookup alone reaches 19 G/s on that table of
-// 24 GB).  k_seed_wave takes 1.57 and 18.6 ms on the same reads.
-template <int W, int MAXD, int MAXM>
-__global__ __launch_bounds__(LN_TPB) void k_seed_lane(SeedArgs a) {
-    __shared__ LaneReads<MAXM> sh_reads[LN_TPB / 64];
-    __shared__ u64 sh_key[LN_TPB / 64][MAXD][64];
-    __shared__ u16 sh_cnt[LN_TPB / 64][MAXD][64];
-    __shared__ u32 sh_stats[ST_COUNT];
-    if (*a.gate) return;  // malformed offsets: nothing may be read through them
-    if (threadIdx.x < ST_COUNT) sh_stats[threadIdx.x] = 0;
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    LaneReads<MAXM> &L = sh_reads[wid];
-    u64 *keys = &sh_key[wid][0][lane];
-    u16 *cnts = &sh_cnt[wid][0][lane];
-    const u32 k = a.k, T = a.min_hits ? a.min_hits : 1u, N = a.ncap;
-    const u64 r = (u64)blockIdx.x * LN_TPB + threadIdx.x;
-    const bool in = r < a.n;
-    u64 beg = 0;
-    int m = 0, E = 0;
-    u32 wflags = 0;
-    bool fall = false, slow = false;
-    if (in) {
-        beg = a.off[r];
-        m = (int)(a.off[r + 1] - beg);
-        E = read_threshold(a, m, &wflags);
-        a.read_E[r] = (u16)E;
-        fall = m > LN_MAX_M || E > F_MAX_E;
-        slow = !fall && m > MAXM;
-    }
-    const bool take = in && !fall && !slow;
-    const int length = m;
-    if (!take) m = 0;
-    const int max_m = wave_max(m);
-    const LaneRead rd = lane_decode(a.seq, beg, m, a.total, lane, max_m, L);
-    if (rd.bad) wflags |= ERR_BAD_BYTE;  // the call fails; its codes are in range all the same
-    const bool mixed = ballot64(rd.has_n || m != max_m) != 0;
-    const bool sure = mixed ? lane_minimizers<W, true>(L, lane, m, max_m, k)
-                            : lane_minimizers<W, false>(L, lane, m, max_m, k);
-    slow |= take && !sure;
-
-    // one probe per minimizer; every occurrence is a hit on its location
-    int H = 0, nd = 0, nmin = 0, nocc = 0;
-    bool many = false;
-    u64 key0 = ~0ull;
-    u32 cnt0 = 0;
-    auto hit = [&](u64 key) {
-        if (key == key0) {
-            cnt0++;
-            return;
-        }
-        if (nd == 0) {
-            key0 = key;
-            cnt0 = 1;
-            nd = 1;
-            return;
-        }
-        int e = 1;
-        while (e < nd && keys[e * 64] != key) e++;
-        if (e < nd) {
-            cnts[e * 64] += 1;
-        } else if (nd < MAXD) {
-            keys[e * 64] = key;
-            cnts[e * 64] = 1;
-            nd++;
-        } else {
-            many = true;
-        }
-    };
-    if (take && !slow) {
-        PickIter<MAXM> it(L, lane, max_m - (int)k + 1);
-        // the next minimizer's bucket is requested before this one's is looked at
-        Probe cur, nxt;
-        int pn = it.next(L, lane);
-        if (pn >= 0) nxt.request(a.table, a.nbuckets, lane_kmer(L, lane, pn, k));
-        while (pn >= 0) {
-            const int p = pn;
-            cur = nxt;
-            pn = it.next(L, lane);
-            if (pn >= 0) nxt.request(a.table, a.nbuckets, lane_kmer(L, lane, pn, k));
-            const u64 v = cur.find(a.table, a.nbuckets);
-            nmin++;
-            if (v == SLOT_NONE) continue;
-            const u32 c = slot_count(v);  // 0 for a k-mer above max_occ
-            H += (int)min(c, (u32)F_HIT_CAP + 1u);
-            if (H > F_HIT_CAP) {
-                fall = true;
-                break;
-            }
-            if (!(v & SLOT_MULTI)) {
-                hit(cand_key((u32)(v >> 32), (i64)(u32)v - p));
-            } else {  // four occurrences in flight at a time
-                const u64 st = slot_start(v);
-                nocc += (int)c;
-                for (u32 u0 = 0; u0 < c; u0 += 4) {
-                    u64 gp[4];
-#pragma unroll
-                    for (int t = 0; t < 4; t++) gp[t] = u0 + t < c ? a.occ[st + u0 + t] : 0ull;
-#pragma unroll
-                    for (int t = 0; t < 4; t++)
-                        if (u0 + t < c) hit(cand_key((u32)(gp[t] >> 32), (i64)(u32)gp[t] - p));
-                }
-            }
-            if (many) break;
-        }
-    }
-    if (many) slow = true;
-
-    // the locations with >= min_hits hits, each to its rank
-    int nc = 0;
-    if (take && !slow && !fall && nd) {
-        keys[0] = key0;
-        cnts[0] = (u16)cnt0;
-        u32 C = 0;
-        for (int e = 0; e < nd; e++) C += cnts[e * 64] >= T;
-        if (a.top_n == 0 && C > N) {
-            fall = true;  // keep-all with more candidates than staging slots
-        } else {
-            nc = (int)min(C, N);
-            for (int e = 0; e < nd; e++) {
-                const u32 he = cnts[e * 64];
-                if (he < T) continue;
-                const u64 ke = keys[e * 64];
-                u32 rank = 0;
-                for (int b = 0; b < nd; b++) {
-                    const u32 hb = cnts[b * 64];
-                    rank += hb > he || (hb == he && keys[b * 64] < ke);
-                }
-                if (rank < N) {
-                    a.st_key[(u64)rank * a.n + r] = ke;
-                    a.st_hits[(u64)rank * a.n + r] = he;
-                }
-            }
-        }
-    }
-    if (in) {
-        a.ncand[r] = (u32)nc;
-        a.read_n[r] = rd.has_n;
-    }
-    list_append(in && slow && !fall, r, lane, a.slow_list, a.slow_count);
-    list_append(in && fall, r, lane, a.fb_list, a.fb_count);
-    if (wflags) atomicOr(a.flags, wflags);
-    // work counts: one record per block, summed by k_fused_summary
-    const bool done = take && !slow && !fall;
-    const u32 st[ST_COUNT] = {done, done ? (u32)m : 0u, done ? (u32)nmin : 0u,
-                              (u32)nc * (u32)((m + 2 * E + 63) / 64), (u32)nc, done ? (u32)nocc : 0u,
-                              done ? (u32)H : 0u, in && fall ? (u32)length : 0u};
-#pragma unroll
-    for (u32 i = 0; i < ST_COUNT; i++) {
-        const u32 t = wave_sum(st[i]);
-        if (lane == 0) atomicAdd(&sh_stats[i], t);
-    }
-    __syncthreads();
-    if (threadIdx.x < ST_COUNT) a.stats_part[(u64)blockIdx.x * ST_COUNT + threadIdx.x] = sh_stats[threadIdx.x];
-}
 
 // Slot of a location key in the per-read LDS table.
 __device__ inline u32 tslot(u64 key) {
@@ -379,25 +136,6 @@ __device__ inline void issue_read_bytes(const SeedArgs &a, u64 r, int lane, Read
         rb.b[q] = 'N';
         if (64 * q < rb.m && rb.m <= F_MAX_M && i < rb.m) rb.b[q] = (u32)a.seq[rb.beg + i];
     }
-}
-
-static void launch_seed_lane(const SeedArgs &a, bool rep, unsigned blocks, hipStream_t s) {
-    const bool ok = with_window(a.w, [&](auto w) {
-        constexpr int W = decltype(w)::value;
-        // Reads that are short on average take the instance whose LDS holds half
-        // as many wavefronts again (1M reads of 150 bases: 0.67 against 0.75 ms); its
-        // longer reads go to k_seed_wave.
-        const bool brief = a.total / a.n <= 160;
-        if (rep) {
-            if (brief) k_seed_lane<W, 12, LN_SHORT_M><<<blocks, LN_TPB, 0, s>>>(a);
-            else k_seed_lane<W, 12, LN_MAX_M><<<blocks, LN_TPB, 0, s>>>(a);
-        } else {
-            if (brief) k_seed_lane<W, 6, LN_SHORT_M><<<blocks, LN_TPB, 0, s>>>(a);
-            else k_seed_lane<W, 6, LN_MAX_M><<<blocks, LN_TPB, 0, s>>>(a);
-        }
-    });
-    if (!ok) throw Error(MT_EINTERNAL, "no lane kernel for this minimizer window");
-    MT_HIP(hipGetLastError());
 }
 
 // One wavefront per read: reads list[0, *list_n), or all of them when list is null.
@@ -986,7 +724,7 @@ static void enqueue_fused(const FusedLaunch &L, Timer *tm, hipStream_t s) {
     enqueue_begin(a.off, a.n, a.total, L.ctl, res.uniq.p, res.n_counters(), s);
     if (tm) tm->mark("check");
     if (L.lane_blocks) {
-        launch_seed_lane(a, L.rep, L.lane_blocks, s);
+        with_window(a.w, [&](auto w) { launch_seed_lane<decltype(w)::value>(a, L.rep, L.lane_blocks, s); });
         k_seed_wave<<<L.wave_blocks, 64 * F_WPB, 0, s>>>(a, a.slow_list, a.slow_count, L.lane_blocks);
     } else {
         k_seed_wave<<<L.wave_blocks, 64 * F_WPB, 0, s>>>(a, nullptr, nullptr, 0);
@@ -1258,97 +996,6 @@ void classify_fused(const mt_index &ix, const mt_query_params &q, const mt_seqs 
 // the global counters directly.  k_contain_lane takes a lane per read,
 // k_contain_wave a wavefront (k_seed_lane and k_seed_wave divide the reads the
 // same way); reads beyond both are listed for the per-stage chain.
-struct ContainArgs {
-    const u8 *seq;
-    const u64 *off;
-    u64 n, total;
-    u32 k, w;
-    const u64x2 *table;
-    u64 nbuckets;
-    const u64 *occ;
-    u64 n_genomes;
-    unsigned long long *hits;
-    u32 *slow_list, *slow_count;  // reads for k_contain_wave
-    u32 *fb_list, *fb_count;
-    unsigned long long *fb_bases;
-    u32 *flags;
-    const u32 *gate;  // offsets check result: nonzero skips the whole launch
-};
-
-constexpr u64 CF_LDS_GENOMES = 2048;  // 64-bit counters, at most 16 KB per block
-
-// One hit per occurrence of a probed k-mer (v: its slot value).
-__device__ inline void count_genomes(const u64 *__restrict__ occ, u64 v, unsigned long long *dst) {
-    if (v == SLOT_NONE) return;
-    if (!(v & SLOT_MULTI)) {
-        atomicAdd(&dst[v >> 32], 1ull);
-        return;
-    }
-    const u32 c = slot_count(v);  // 0 for a k-mer above max_occ
-    const u64 st = slot_start(v);
-    for (u32 u = 0; u < c; u++) atomicAdd(&dst[occ[st + u] >> 32], 1ull);
-}
-
-// One lane per read, grid-stride so that a block's counters are flushed once.
-// Bound by the probes' random table lines: 1M reads of 150 bases on 500 Mbp,
-// 0.60 ms (k_contain_wave on the same reads 1.09 ms).
-template <int W, int MAXM>
-__global__ __launch_bounds__(LN_TPB) void k_contain_lane(ContainArgs a) {
-    __shared__ LaneReads<MAXM> sh_reads[LN_TPB / 64];
-    extern __shared__ unsigned long long cnt[];  // one counter per genome when they fit (sized at launch)
-    if (*a.gate) return;  // malformed offsets: the whole grid leaves
-    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    LaneReads<MAXM> &L = sh_reads[wid];
-    const bool in_lds = a.n_genomes <= CF_LDS_GENOMES;  // uniform over the grid
-    unsigned long long *dst = in_lds ? cnt : a.hits;
-    if (in_lds)
-        for (u64 g = threadIdx.x; g < a.n_genomes; g += LN_TPB) cnt[g] = 0;
-    __syncthreads();
-    const u32 k = a.k;
-    u32 wflags = 0;
-    for (u64 r0 = (u64)blockIdx.x * LN_TPB + 64 * wid; r0 < a.n; r0 += (u64)gridDim.x * LN_TPB) {
-        const u64 r = r0 + lane;
-        const bool in = r < a.n;
-        u64 beg = 0;
-        int m = 0;
-        if (in) {
-            beg = a.off[r];
-            m = (int)(a.off[r + 1] - beg);
-        }
-        const bool fall = m > LN_MAX_M;
-        bool slow = !fall && m > MAXM;
-        const bool take = in && !fall && !slow;
-        const int length = m;
-        if (!take) m = 0;
-        const int max_m = wave_max(m);
-        const LaneRead rd = lane_decode(a.seq, beg, m, a.total, lane, max_m, L);
-        if (rd.bad) wflags |= ERR_BAD_BYTE;  // the call fails; its codes are in range all the same
-        const bool mixed = ballot64(rd.has_n || m != max_m) != 0;
-        const bool sure = mixed ? lane_minimizers<W, true>(L, lane, m, max_m, k)
-                                : lane_minimizers<W, false>(L, lane, m, max_m, k);
-        slow |= take && !sure;
-        if (take && !slow) {
-            PickIter<MAXM> it(L, lane, max_m - (int)k + 1);
-            Probe cur, nxt;
-            int pn = it.next(L, lane);
-            if (pn >= 0) nxt.request(a.table, a.nbuckets, lane_kmer(L, lane, pn, k));
-            while (pn >= 0) {
-                cur = nxt;
-                pn = it.next(L, lane);
-                if (pn >= 0) nxt.request(a.table, a.nbuckets, lane_kmer(L, lane, pn, k));
-                count_genomes(a.occ, cur.find(a.table, a.nbuckets), dst);
-            }
-        }
-        list_append(in && slow, r, lane, a.slow_list, a.slow_count);
-        list_append(in && fall, r, length, lane, a.fb_list, a.fb_count, a.fb_bases);
-    }
-    if (wflags) atomicOr(a.flags, wflags);
-    if (in_lds) {
-        __syncthreads();
-        for (u64 g = threadIdx.x; g < a.n_genomes; g += LN_TPB)
-            if (cnt[g]) atomicAdd(&a.hits[g], cnt[g]);
-    }
-}
 
 // One wavefront per read: reads list[0, *list_n), or all of them when list is null.
 __global__ __launch_bounds__(64 * F_WPB) void k_contain_wave(ContainArgs a, const u32 *__restrict__ list,
@@ -1537,12 +1184,7 @@ void containment(const mt_index &ix, const mt_seqs &reads, u64 *hits, hipStream_
     const u64 wave_blocks = std::min<u64>(grid_for(n, F_WPB), (u64)std::max(cus, 1) * (lanes ? 8 : 32));
     if (lanes) {
         const unsigned blocks = (unsigned)std::min<u64>(grid_for(n, LN_TPB), (u64)std::max(cus, 1) * 16);
-        with_window(ix.w, [&](auto w) {
-            constexpr int W = decltype(w)::value;
-            if (reads.total / n <= 160) k_contain_lane<W, LN_SHORT_M><<<blocks, LN_TPB, lds, s>>>(a);
-            else k_contain_lane<W, LN_MAX_M><<<blocks, LN_TPB, lds, s>>>(a);
-        });
-        MT_HIP(hipGetLastError());
+        with_window(ix.w, [&](auto w) { launch_contain_lane<decltype(w)::value>(a, blocks, lds, s); });
         k_contain_wave<<<(unsigned)wave_blocks, 64 * F_WPB, lds, s>>>(a, a.slow_list, a.slow_count);
     } else {
         k_contain_wave<<<(unsigned)wave_blocks, 64 * F_WPB, lds, s>>>(a, nullptr, nullptr);
